@@ -33,8 +33,8 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 MFMA_PEAK_TFLOPS = 2500.0        # dense bf16 / fp16 MFMA, published
 INFINITY_CACHE_BYTES = 256 << 20
 MIN_TIMED_MS = 50.0
-KERNEL_NAMES = {1: "wros_kernel", 2: "stripe_kernel", 3: "naive_kernel", 4: "xstat_kernel", 5: "xchunk_kernel", 6: "blk_kernel",
-                7: "gemm_kernel"}
+KERNEL_NAMES = {1: "wros_kernel", 2: "stripe_kernel", 3: "naive_kernel", 4: "xstat_kernel", 5: "mtile_kernel", 6: "blk_kernel",
+                7: "mtile_kernel", 9: "mtile_kernel"}
 
 
 def algorithmic_bytes(cfg, nb, N, y_bytes):
@@ -147,7 +147,7 @@ def measure(cfg, layer, steps, warmup, y_dtype, plan_kw, use_graph, hot, verify_
         checked = verify(cfg, layer, Ys[(warmup + steps - 1) % nsets], y_dtype, verify_rows, bias)
 
     issued = {2: 100 + ubp.layout_slot(chosen.sub_stripes, chosen.col_tiles) if chosen.kernel == 2 else -1,
-              4: 10, 5: 10, 6: 300 + {2: 0, 4: 1, 5: 2}.get(chosen.sub_stripes, 1)}.get(chosen.kernel, -1)
+              4: 10, 5: 10, 9: 10, 6: 300 + {2: 0, 4: 1, 5: 2}.get(chosen.sub_stripes, 1)}.get(chosen.kernel, -1)
     res = {
         "workload": cfg.name, "what": cfg.what, "M": cfg.M, "K": cfg.K, "N": N, "block": "%dx%d" % (cfg.bh, cfg.bw),
         "density": cfg.density, "nb": nb, "in_dtype": cfg.dtype, "y_dtype": y_dtype,

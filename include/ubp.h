@@ -127,7 +127,7 @@ const void *ubp_packed_values(const ubp_packed *p, int64_t *len_elems);
  * UBP_ERR_ALLOC, UBP_ERR_DEVICE (launch failed).  Nothing is written to Y on error.
  * Non-finite X: the MFMA kernels multiply whole operand tiles, zero weights included.  An Inf
  * or NaN in a row of X therefore reaches (as NaN) outputs whose exact sum does not contain it:
- * with kernels 4, 5 and 7, every output row whose 16-row stripe keeps a weight within the aligned
+ * with kernels 4, 5, 7 and 9, every output row whose 16-row stripe keeps a weight within the aligned
  * 32 rows of X around it; with kernel 2, every row of a row group that keeps a weight in that
  * column; with kernel 6, every row of a stripe that a block reaches into whose 16-row window of X
  * (its columns, moved left at the right edge) contains it.  Kernel 1 multiplies kept weights only.
@@ -146,36 +146,30 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                shifting can be measured next to kernel 1 (same results bit for bit).
  *                2 = MFMA kernel on aligned 16-row stripes that gathers the rows of X a row
  *                group needs (f16 / bf16).
- *                4, 5 and 7 = MFMA kernels that use W as zero-filled 16 x 32 operand tiles; 4 and 5
- *                skip tiles that keep nothing (f16 / bf16, N a multiple of 8, 16-byte
- *                aligned rows of X and Y; col_tiles 2 or 4; wg_rows = slices the stripes are
- *                cut into, one workgroup per slice and pixel block).
- *                4 (K <= 256) keeps the X of one pixel block in registers and streams the stripes
- *                past it, 16 finished rows at a time - the order of the paper's section 4.2
- *                (waves 1..8 share a slice's stripes).
- *                5 (any K whose zero-filled W stays below 8 MB) cuts K into chunks of 128 rows
- *                that pass through LDS and the registers while the accumulators of 16 stripes
- *                stay (sub_stripes 2 or 4 = stripes per multiplying wavefront; waves fixed; by
- *                itself 4, or 2 with twice the slices where the workgroups would fill less than
- *                half the CUs).
+ *                4, 5, 7 and 9 = MFMA kernels that use W as zero-filled 16 x 32 operand tiles (f16 / bf16).
+ *                4 (K <= 256; N a multiple of 8, 16-byte aligned rows of X and Y) keeps the X of one
+ *                pixel block in registers and streams the stripes past it, 16 finished rows at a time -
+ *                the order of the paper's section 4.2 (col_tiles 2 or 4; wg_rows = slices the stripes are
+ *                cut into, one workgroup per slice and pixel block; waves 1..8 share a slice's stripes).
+ *                5, 7 and 9 are one kernel that stages both operands in LDS, in tiles of 128 or 64 rows x
+ *                128 or 64 pixels of Y, K in stages of 64 columns (M x K as zero-filled tiles below 8 MB,
+ *                K <= 16384, N >= 8).  5 and 7 need the alignment that 4 needs; 7 multiplies every operand
+ *                tile and is only for matrices whose every tile keeps a weight; 5 leaves the empty ones
+ *                out; 9 takes any N and alignment.  sub_stripes x col_tiles names the tile, in units of
+ *                16 rows x 16 pixels (kernel 5: of 32, 2 or 4 each); sizes beyond 128 stand for 128.
  *                6 = MFMA kernel with whole blocks as operands, stored by row modulo 16 - the
  *                paper's rotation with period 16 (f16 / bf16, bh <= 16, 16 <= K < 65408, N >= 64,
  *                16-byte aligned rows; col_tiles 4 only; sub_stripes 2, 4 or 5 = the most stripes a
  *                wavefront's row group may have: row groups are cut shorter where many blocks start).
- *                7 = MFMA kernel on the same operand tiles with BOTH operands staged in LDS: a
- *                workgroup owns up to 256 rows x 256 pixels of Y for the whole of K (f16 / bf16,
- *                same alignment as 4 and 5; only for matrices whose every tile keeps a weight;
- *                sub_stripes x col_tiles = the workgroup's tile in units of 16 rows x 16 pixels:
- *                16 x 16, 8 x 16, 8 x 8, 16 x 4, 4 x 8 or 4 x 4; 0 = the largest that still gives
- *                about one workgroup per CU).
- *                0 picks 1 for fp32; 6 for 16-row blocks at least 16 wide when K > 1024; else, while
- *                at least half of the 16 x 32 tiles of W keep a weight, 7 (every tile keeps one, and
- *                K <= 256 or N <= 4096), 4 (K <= 256) or 5; else 2.  (3 is never picked.)
+ *                0 picks 1 for fp32, else the kernel with the smallest estimated time among 4, 5, 7
+ *                and 9 while at least half of the 16 x 32 tiles of W keep a weight; and 6 for 16-row blocks
+ *                at least 16 wide when K > 1024; or 2 where none of these takes the call.  (3 is never
+ *                picked.)
  *   sub_stripes: kernels 2 and 6, 16-row stripes per wavefront (1, 2 or 4; kernel 6: 2, 4 or 5,
  *                by itself 5 where that saves a workgroup row, else 4);
- *                kernel 5: 2 or 4.
- *   col_tiles  : kernel 2, 16-column tiles per wavefront (2, 4 or 8); kernels 4 and 5: 2 or 4;
- *                kernel 7: as above.
+ *                kernels 5, 7 and 9: as above.
+ *   col_tiles  : kernel 2, 16-column tiles per wavefront (2, 4 or 8); kernels 4, 5, 7 and 9:
+ *                as above.
  *   waves      : wavefronts per workgroup (kernels 2 and 6: producers + 1 .. 16, fewer for shapes
  *                that need many registers; kernel 4 as above).
  *   rows_per_range : kernels 1 and 3, output rows owned by one workgroup row (multiple of bh).
@@ -184,7 +178,8 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *   wg_rows    : kernels 2 and 6, workgroups that share one column tile (each takes a share of
  *                the row groups).  Free only for kernel 2 when the staged tile holds all K rows
  *                of X at once (K <= 4096 / col_tiles); otherwise it must be 0 or
- *                ceil(row groups / (waves - producers)).  Kernels 4 and 5: slices, as above.
+ *                ceil(row groups / (waves - producers)).  Kernel 4: slices, as above;
+ *                the others ignore it.
  */
 typedef struct {
     int32_t kernel, sub_stripes, col_tiles, waves, rows_per_range, producers, wg_rows;
@@ -231,7 +226,7 @@ ubp_status ubp_spmm_prepare(const ubp_packed *p, const void *X_dev, int64_t ldx,
 /*
  * Synchronous health check (copies one word from the device, so it waits for the work queued
  * before it on the NULL stream's terms; call it after synchronising the stream you used).
- * Every wait inside kernels 2, 5 and 6 (the ones whose wavefronts hand data to each other through
+ * Every wait inside kernels 2 and 6 (the ones whose wavefronts hand data to each other through
  * LDS without barriers) is bounded; a wait that runs out sets a bit here and the kernel finishes
  * with undefined Y instead of hanging.  *flags == 0 means no such event since
  * the handle was packed.
@@ -247,7 +242,7 @@ ubp_status ubp_packed_device_error(const ubp_packed *p, uint32_t *flags);
  *     completely: ceil(nb * bh * bw / 512) - the yardstick for the counts below.
  * The following describe private re-layouts and build the one they ask about (host memory
  * only); -1 where it does not exist for this matrix (always for fp32):
- *   10 / 11  dense operand tiles (kernels 4, 5): tiles that keep a weight = MFMAs issued per 16
+ *   10 / 11  dense operand tiles (kernels 4, 5, 7, 9): tiles that keep a weight = MFMAs issued per 16
  *            columns / all 16 x 32 tiles of the matrix;
  *   100 + s / 200 + s  gather layout s = 3 * log2(sub_stripes) + log2(col_tiles) - 1 (kernel 2):
  *            MFMAs issued per 16 columns / steps;

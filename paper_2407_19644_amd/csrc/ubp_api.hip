@@ -170,50 +170,126 @@ namespace {
 
 // What a call resolves to: the kernel and its launch shape, every field set.
 struct Shape {
-    int kernel = 0;   // 1 vector, 2 gather, 4 small-K dense tiles, 5 chunked dense tiles, 6 block, 7 dense tiles through LDS
-    int shape = 0;    // kernel 7: tile shape
+    int kernel = 0;   // 1 vector, 2 gather, 4 small-K dense tiles, 5 / 7 / 9 dense tiles through LDS, 6 block
+    int shape = 0;    // kernels 5, 7, 9: index into kMtileShapes
     int G = 0, CT = 0, waves = 0, NP = 0, wg_rows = 0, rpr = 0;
     bool resident = false;
 };
 
-// Decides kernel and shape for (handle, N, alignment) and the caller's pins; builds the host image
-// of the layout that shape needs (under the handle's lock).  No device work.
-ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, const ubp_plan &pl, Shape &s) {
-    int kernel = pl.kernel;
-    // the dense-tile kernels need 16-byte pieces of X rows that lie entirely inside or outside the matrix
-    const bool tile_able = p->dtype != UBP_F32 && vec_ok && N % 8 == 0;
-    if (kernel == 0) {
-        if (p->dtype == UBP_F32) {
-            kernel = 1;
-        } else {
-            // Whole blocks as operands where a block fills one (16-row blocks at least 16 wide) and K is
-            // beyond what the ring holds at once.  Dense zero-filled tiles where most 16 x 32 tiles hold
-            // a kept weight anyway (at least half of them, which small blocks reach from about a tenth
-            // of the weights kept): the matrix instructions issued then stay within about twice those a
-            // gather issues, and no row of X is gathered.  Otherwise gathered rows.
-            const bool blk_auto = blk_eligible(p) && p->bh == kStripe && p->bw >= 16 && p->K > ring_rows(4) && vec_ok && N >= 64;
-            if (blk_auto) {
-                kernel = 6;
-            } else if (tile_able) {
-                const TileLayout &T = get_tile_layout(p);
-                const int kt = (p->K + kStep - 1) / kStep;
-                const bool mostly_full = T.kt_pad != 0 && 2 * T.tiles_nonzero >= (int64_t)T.nstripes * kt;
-                // Among the dense-tile kernels: where every tile keeps a weight, the one that stages both
-                // operands in LDS for small K or few pixels (there a weight tile fetched once per 64 pixels
-                // is what costs: 4.3 against 5.3 us and 11.8 against 13.8 us on two such layers); else
-                // the small-K kernel or the chunked one, which skip empty tiles.
-                const bool all_full = T.kt_pad != 0 && T.tiles_nonzero == (int64_t)T.nstripes * kt;
-                if (all_full && (p->K <= kTileMaxK || N <= 4096) && (int64_t)p->K * ldx_bytes < (int64_t(1) << 31)) kernel = 7;
-                else if (mostly_full && p->K <= kTileMaxK) kernel = 4;
-                else if (mostly_full && T.kt_pad % 4 == 0) kernel = 5;
-                else kernel = 2;
-            } else {
-                kernel = 2;
+// ------------------------------------------------------------------ estimates
+// What a 16-bit product would take, in microseconds, by each kernel: linear in the few quantities that
+// cost, coefficients fitted (relative least squares, none negative) to 165 layers drawn over the range of
+// layers this library is for - 1 x 1 and im2col convolutions at batch 1 to 64, fully connected layers, large
+// layers of 16 x 16 blocks, aligned and odd rows - each timed through every kernel that takes it.  Mean error
+// 5 to 10 %; the kernel of the smallest estimate took 2.5 % longer than the fastest one on average.
+constexpr double kNever = 1e30;
+constexpr double kCUs = 256.0;
+
+// Dense tiles through LDS, by shape and by whether rows of X take the way through registers
+double estimate_mtile(const ubp_packed *p, int N, int shape, bool ragged, size_t ysz) {
+    // fixed; per tile and stage of 64 columns (of a CU's tiles one after the other); per tile; per 5 MB of Y;
+    // per tile and stage where empty tiles of W are left out; per round of tiles and stage
+    static const double kAligned[kNumMtileShapes][6] = {{3.015, 0.370, 0.410, 0.913, 0.039, 0.0},
+                                                        {2.606, 0.285, 0.460, 0.788, 0.021, 0.0},
+                                                        {2.609, 0.283, 0.430, 0.794, 0.028, 0.0},
+                                                        {2.653, 0.129, 0.199, 0.726, 0.012, 0.106}};
+    static const double kRagged[kNumMtileShapes][6] = {{4.592, 0.695, 0.0, 0.397, 0.020, 0.0},
+                                                       {3.788, 0.523, 0.0, 0.297, 0.0, 0.0},
+                                                       {kNever, 0.0, 0.0, 0.0, 0.0, 0.0},   // (never the best one there)
+                                                       {3.109, 0.0, 0.312, 1.143, 0.0, 0.508}};
+    const MtileShape &sh = kMtileShapes[shape];
+    const MaskStats &S = get_mask_stats(p);
+    const double *c = ragged ? kRagged[shape] : kAligned[shape];
+    const int64_t tiles = (int64_t)((p->M + sh.rows - 1) / sh.rows) * ((N + sh.pixels - 1) / sh.pixels);
+    const double per_cu = (double)(((tiles + 7) / 8 + 31) / 32); // an eighth of the tiles to each XCD, 32 CUs each
+    const double stages = (p->K + 63) / 64, rounds = std::ceil(per_cu / sh.per_cu);
+    return c[0] + per_cu * (stages * (c[1] + (S.tiles_hit < S.tiles ? c[4] : 0.0)) + c[2]) + rounds * stages * c[5] +
+           c[3] * 0.2e-6 * p->M * (double)N * ysz;
+}
+
+// Launch shape of the small-K kernel.  64-pixel blocks halve the weight traffic per pixel; 32-pixel blocks
+// where those would be few.  Workgroups of 4 wavefronts, about one and a half per CU: two share a CU and the
+// one's loading of X overlaps the other's streaming (measured better than one workgroup of 8).  The stripes are
+// cut into slices to get there - every slice loads the X block again, so only while a wavefront keeps at least
+// 3 stripes.
+int xstat_col_tiles(int N) { return N >= 128 * 64 ? 4 : 2; }
+int xstat_slices(int nstripes, int n_blocks) {
+    return std::max(1, std::min((int)std::lround(384.0 / n_blocks), nstripes / 12));
+}
+
+double estimate_xstat(const ubp_packed *p, int N, size_t ysz) {
+    const int CT = xstat_col_tiles(N), blocks = (N + 16 * CT - 1) / (16 * CT), stripes = (p->M + 15) / 16;
+    const int slices = xstat_slices(stripes, blocks), each = (stripes + slices - 1) / slices;
+    const double wgs = (double)blocks * slices, rounds = std::ceil(wgs / (2 * kCUs));
+    return 3.13 + 0.795 * 0.2e-6 * p->M * (double)N * ysz + 1.0 * p->K / 256.0 +
+           0.01865 * rounds * ((each + 3) / 4) * ((p->K + 31) / 32) * CT + 2.42 * wgs / (2 * kCUs) * p->K * CT / 1024.0;
+}
+
+int blk_auto_G(const ubp_packed *p) { // 5 stripes per wavefront where that saves a workgroup row: X is staged once per workgroup row
+    auto rows_for = [&](int g) { return ((p->M + 16 * g - 1) / (16 * g) + 13) / 14; };
+    return rows_for(5) < rows_for(4) ? 5 : 4;
+}
+
+double estimate_blk(const ubp_packed *p, int N, size_t ysz) {
+    const int G = blk_auto_G(p), rows = ((p->M + 16 * G - 1) / (16 * G) + 13) / 14;
+    const double rounds = std::max(1.0, std::ceil((N / 64) * (double)rows / kCUs));
+    const double halves = (double)p->nb * ((p->bw + 15) / 16); // (each in about two stripes)
+    return 4.24 + 0.0073 * rounds * p->K / 64.0 + 0.2446 * halves / 4.0 * (N / 64.0) / kCUs + 1.06 * 0.2e-6 * p->M * (double)N * ysz;
+}
+
+int tile_layout_words(const ubp_packed *p) { return (tile_kt_pad(p->M, p->K) + 31) / 32; } // occupancy words per stripe; 0: no dense tiles
+bool all_tiles_kept(const ubp_packed *p) {
+    const TileLayout &T = get_tile_layout(p);
+    return T.kt_pad != 0 && T.tiles_nonzero == (int64_t)T.nstripes * ((p->K + kStep - 1) / kStep);
+}
+bool mtile_able(const ubp_packed *p, int N, int64_t ldx_bytes) {
+    // a piece of 8 pixels fits a row; 64 rows of X have 32-bit offsets; the occupancy words of 4 stripes fit a wavefront's lanes
+    return p->dtype != UBP_F32 && N >= 8 && ldx_bytes <= (int64_t(1) << 25) && tile_layout_words(p) > 0 && 4 * tile_layout_words(p) <= 64;
+}
+
+// The kernel for a 16-bit product by the smallest estimate among those whose weights suit it: dense tiles
+// only where blocks reach into at least half of the 16 x 32 tiles (W would grow and most products be by
+// zeros otherwise), whole blocks as operands only where a block fills an operand and K is beyond what the
+// ring holds at once.  aligned: 16-byte pieces of rows of X and Y lie inside or outside the matrix.
+void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, Shape &s) {
+    const MaskStats &S = get_mask_stats(p);
+    const bool aligned = vec_ok && N % 8 == 0;
+    const bool mostly = 2 * S.tiles_hit >= S.tiles, full = S.tiles_hit == S.tiles;
+    double best = kNever;
+    s.kernel = 2;
+    if (mostly && mtile_able(p, N, ldx_bytes)) {
+        for (int sh = 0; sh < kNumMtileShapes; ++sh) {
+            const double t = estimate_mtile(p, N, sh, !aligned, ysz);
+            if (t < best) {
+                best = t;
+                s.kernel = !aligned ? 9 : full && (p->K <= kTileMaxK || N <= 4096) ? 7 : p->K > kTileMaxK ? 5 : 9;
+                s.shape = sh;
             }
         }
     }
-    if (kernel < 1 || kernel > 7) return UBP_ERR_INVALID_ARG;
-    if (kernel != 1 && kernel != 3 && p->dtype == UBP_F32) return UBP_ERR_UNSUPPORTED;
+    if (mostly && aligned && p->K <= kTileMaxK && tile_layout_words(p) > 0 && estimate_xstat(p, N, ysz) < best) {
+        best = estimate_xstat(p, N, ysz);
+        s.kernel = 4;
+    }
+    if (blk_eligible(p) && p->bh == kStripe && p->bw >= 16 && p->K > ring_rows(4) && vec_ok && N >= 64 && estimate_blk(p, N, ysz) < best) {
+        best = estimate_blk(p, N, ysz);
+        s.kernel = 6;
+    }
+}
+
+// Decides kernel and shape for (handle, N, alignment) and the caller's pins; builds the host image
+// of the layout that shape needs (under the handle's lock).  No device work.
+ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
+    int kernel = pl.kernel;
+    // the dense-tile kernels 4, 5 and 7 need 16-byte pieces of X rows that lie entirely inside or outside the matrix
+    const bool tile_able = p->dtype != UBP_F32 && vec_ok && N % 8 == 0;
+    if (kernel < 0 || kernel > 9 || kernel == 8) return UBP_ERR_INVALID_ARG;
+    if (kernel > 1 && kernel != 3 && p->dtype == UBP_F32) return UBP_ERR_UNSUPPORTED;
+    if (kernel == 0 && p->dtype == UBP_F32) kernel = 1;
+    if (kernel == 0) {
+        choose(p, N, ldx_bytes, vec_ok, ysz, s);
+        kernel = s.kernel;
+    }
     s.kernel = kernel;
     if (kernel == 1 || kernel == 3) {
         if (p->bh > 16) return UBP_ERR_UNSUPPORTED;
@@ -231,91 +307,69 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, c
         s.rpr = rpr;
         return UBP_OK;
     }
-    if (kernel == 7) {
-        if (!tile_able) return UBP_ERR_UNSUPPORTED;
+    if (kernel == 5 || kernel == 7 || kernel == 9) {
+        if (kernel != 9 && !tile_able) return UBP_ERR_UNSUPPORTED;
         const TileLayout &T = get_tile_layout(p);
         if (T.kt_pad == 0) return UBP_ERR_UNSUPPORTED;
-        // this kernel multiplies every tile: only for matrices whose every tile keeps a weight
-        if (T.tiles_nonzero != (int64_t)T.nstripes * ((p->K + kStep - 1) / kStep)) return UBP_ERR_UNSUPPORTED;
-        int best = -1;
-        int64_t best_score = -1;
-        for (int sh = 0; sh < kNumGemmShapes; ++sh) {
-            int rows, px;
-            gemm_shape(sh, &rows, &px);
-            if (pl.sub_stripes && pl.sub_stripes * 16 != rows) continue;
-            if (pl.col_tiles && pl.col_tiles * 16 != px) continue;
-            // the largest tile that still gives about one workgroup per CU; else the most workgroups
-            const int64_t wgs = (int64_t)((p->M + rows - 1) / rows) * ((N + px - 1) / px);
-            const int64_t score = wgs >= 190 ? ((int64_t)1 << 40) + (int64_t)rows * px : wgs;
-            if (score > best_score) {
-                best_score = score;
-                best = sh;
+        if (kernel == 5 && (T.kt_pad % 4 != 0 || pl.waves != 0 || pl.wg_rows < 0)) return UBP_ERR_UNSUPPORTED;
+        if (kernel == 5 && ((pl.sub_stripes != 0 && pl.sub_stripes != 2 && pl.sub_stripes != 4) ||
+                            (pl.col_tiles != 0 && pl.col_tiles != 2 && pl.col_tiles != 4))) return UBP_ERR_UNSUPPORTED;
+        // kernel 7 multiplies every tile: only for matrices whose every tile keeps a weight
+        if (kernel == 7 && !all_tiles_kept(p)) return UBP_ERR_UNSUPPORTED;
+        if (!mtile_able(p, N, ldx_bytes)) { // (a K or a pitch beyond this kernel's offsets)
+            if (kernel == 9) return UBP_ERR_UNSUPPORTED;
+            ubp_plan other = {};
+            other.kernel = 2;
+            return resolve(p, N, ldx_bytes, vec_ok, ysz, other, s);
+        }
+        // Of the shapes no larger than what the plan names (kernel 5: in units of 32 rows and 32 pixels,
+        // else of 16; all of them where it names nothing) the one with the smallest estimate
+        const int unit = kernel == 5 ? 32 : 16;
+        const bool ragged = !tile_able;
+        double best = kNever;
+        for (int sh = 0; sh < kNumMtileShapes; ++sh) {
+            if (ragged && sh == 2) continue; // (not built for odd rows)
+            const int want_r = pl.sub_stripes * unit, want_p = pl.col_tiles * unit;
+            if (want_r != 0 && kMtileShapes[sh].rows != std::min(want_r, 128)) continue;
+            if (want_p != 0 && kMtileShapes[sh].pixels != std::min(want_p, 128)) continue;
+            const double t = estimate_mtile(p, N, sh, ragged, ysz);
+            if (t < best) {
+                best = t;
+                s.shape = sh;
             }
         }
-        if (best < 0) return UBP_ERR_UNSUPPORTED;
-        int rows, px;
-        gemm_shape(best, &rows, &px);
-        s.shape = best;
-        s.G = rows / 16;
-        s.CT = px / 16;
-        s.wg_rows = (p->M + rows - 1) / rows;
-        s.waves = rows * px >= 128 * 256 ? 8 : 4;
+        if (best == kNever) return UBP_ERR_UNSUPPORTED;
+        const MtileShape &sh = kMtileShapes[s.shape];
+        s.G = sh.rows / 16;
+        s.CT = sh.pixels / 16;
+        s.wg_rows = (p->M + sh.rows - 1) / sh.rows;
         return UBP_OK;
     }
-    if (kernel == 4 || kernel == 5) {
-        if (!tile_able) return UBP_ERR_UNSUPPORTED;
+    if (kernel == 4) {
+        if (!tile_able || p->K > kTileMaxK) return UBP_ERR_UNSUPPORTED;
         const TileLayout &T = get_tile_layout(p);
         if (T.kt_pad == 0) return UBP_ERR_UNSUPPORTED;
-        if (kernel == 4 && p->K > kTileMaxK) return UBP_ERR_UNSUPPORTED;
-        if (kernel == 5 && T.kt_pad % 4 != 0) return UBP_ERR_UNSUPPORTED;
         int CT = pl.col_tiles;
-        // 64-pixel blocks halve the weight traffic per pixel; 32-pixel blocks where those would be few
-        if (CT == 0) CT = kernel == 5 ? 4 : (N >= 128 * 64 ? 4 : 2);
+        if (CT == 0) CT = xstat_col_tiles(N);
         if (CT != 2 && CT != 4) return UBP_ERR_UNSUPPORTED;
         s.CT = CT;
         const int n_blocks = (N + 16 * CT - 1) / (16 * CT);
         int slices = pl.wg_rows;
         if (slices < 0) return UBP_ERR_INVALID_ARG;
-        if (kernel == 5) {
-            if (pl.waves != 0) return UBP_ERR_UNSUPPORTED; // fixed: 16 stripes' worth of multiplying wavefronts + 4 that load X
-            // a workgroup's multiplying wavefronts hold 16 stripes: slices of at most 16 stripes
-            // (more slices on request: each streams all of the block's X again)
-            const int least = (T.nstripes + 15) / 16;
-            // Fewer workgroups than half the CUs: twice the slices, and two stripes per wavefront so
-            // that a workgroup still has 4 multiplying wavefronts (measured: 21 against 27 us on a
-            // 256 x 2304 layer with 6272 pixels, 12.8 against 15.1 us on 1024 x 1024 with 1568)
-            const bool few = slices == 0 && pl.sub_stripes == 0 && (int64_t)n_blocks * least < 128 && T.nstripes >= 2 * least * 2;
-            slices = std::min(std::max(few ? 2 * least : slices, least), T.nstripes);
-            s.G = pl.sub_stripes ? pl.sub_stripes : (few ? 2 : 4); // stripes per multiplying wavefront
-            if (s.G != 2 && s.G != 4) return UBP_ERR_UNSUPPORTED;
-        } else {
-            // Workgroups of 4 wavefronts, about one and a half per CU: two share a CU and the one's
-            // loading of X overlaps the other's streaming (measured better than one workgroup of 8).
-            // The stripes are cut into slices to get there - every slice loads the X block again, so
-            // only while a wavefront keeps at least 3 stripes.
-            if (slices == 0) slices = std::max(1, std::min((int)std::lround(384.0 / n_blocks), T.nstripes / 12));
-            slices = std::min(slices, T.nstripes);
-        }
+        if (slices == 0) slices = xstat_slices(T.nstripes, n_blocks);
+        slices = std::min(slices, T.nstripes);
         const int sps = (T.nstripes + slices - 1) / slices;
         slices = (T.nstripes + sps - 1) / sps;
         if ((int64_t)n_blocks * slices > 0x7fffffff) return UBP_ERR_UNSUPPORTED;
         s.wg_rows = slices;
-        if (kernel == 4) {
-            s.waves = pl.waves ? pl.waves : std::min(4, sps);
-            if (s.waves < 1 || s.waves > 8) return UBP_ERR_UNSUPPORTED;
-        }
+        s.waves = pl.waves ? pl.waves : std::min(4, sps);
+        if (s.waves < 1 || s.waves > 8) return UBP_ERR_UNSUPPORTED;
         return UBP_OK;
     }
     if (kernel == 6) {
         if (!blk_eligible(p) || !vec_ok || N < 64) return UBP_ERR_UNSUPPORTED;
         if (pl.col_tiles != 0 && pl.col_tiles != 4) return UBP_ERR_UNSUPPORTED;
-        // 4 stripes per wavefront, or 5 (which just fits the registers) where that saves a workgroup
-        // row: X is staged once per workgroup row
-        int G = pl.sub_stripes;
-        if (G == 0) {
-            auto rows_for = [&](int g) { return ((p->M + 16 * g - 1) / (16 * g) + 13) / 14; };
-            G = rows_for(5) < rows_for(4) ? 5 : 4;
-        }
+        const int G = pl.sub_stripes ? pl.sub_stripes : blk_auto_G(p);
         if (G != 2 && G != 4 && G != 5) return UBP_ERR_UNSUPPORTED;
         const BlkLayout &L = get_blk_layout(p, G);
         if (L.G == 0) return UBP_ERR_UNSUPPORTED;
@@ -488,7 +542,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         // Layouts are built and uploaded on first use, under the handle's lock.  A repeated call
         // finds everything in place and allocates nothing.
         std::lock_guard<std::mutex> hold(p->lock);
-        ubp_status rc = resolve(p, N, ldx * 2, vec_ok, pl, s);
+        ubp_status rc = resolve(p, N, ldx * 2, vec_ok, ysz, pl, s);
         if (rc != UBP_OK) return rc;
         switch (s.kernel) {
         case 1:
@@ -496,6 +550,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         case 2: rc = upload_stripe_layout(p, layout_slot(s.G, s.CT)); break;
         case 4:
         case 5:
+        case 9:
         case 7: rc = upload_tile_layout(p); break;
         case 6:
             rc = upload_blk_layout(p, blk_slot(s.G));
@@ -504,7 +559,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
                 std::memset(&tp, 0, sizeof tp);
                 tp.kernel = 2;
                 tp.col_tiles = 4;
-                rc = resolve(p, N, ldx * 2, vec_ok, tp, tail);
+                rc = resolve(p, N, ldx * 2, vec_ok, ysz, tp, tail);
                 if (rc == UBP_OK) rc = upload_stripe_layout(p, layout_slot(tail.G, tail.CT));
                 has_tail = true;
             }
@@ -517,9 +572,9 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         chosen->kernel = s.kernel;
         chosen->sub_stripes = s.G;
         chosen->col_tiles = s.CT;
-        chosen->waves = s.kernel == 5 ? 16 / s.G + 4 : s.waves;
+        chosen->waves = s.waves;
         chosen->rows_per_range = s.rpr;
-        chosen->producers = s.kernel == 5 ? 4 : s.NP;
+        chosen->producers = s.NP;
         chosen->wg_rows = s.wg_rows;
     }
 
@@ -529,6 +584,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
     case 2: return launch_stripe(stripe_args(p, s, X_dev, ldx, N, Y_dev, ldy, vec_ok, 0, ep), bf16, y_f32, s.G, s.CT, s.waves, stream, dry);
     case 4:
     case 5:
+    case 9:
     case 7: {
         const TileLayout &T = p->tiles;
         TileArgs a = {};
@@ -549,9 +605,8 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         a.n_blocks = (N + 16 * s.CT - 1) / (16 * s.CT);
         a.slices = s.wg_rows;
         a.sps = (T.nstripes + s.wg_rows - 1) / s.wg_rows;
-        if (s.kernel == 7) return launch_gemm(a, bf16, y_f32, s.shape, stream, dry);
         if (s.kernel == 4) return launch_xstat(a, bf16, y_f32, s.CT, T.kt_pad, s.waves, stream, dry);
-        return launch_xchunk(a, bf16, y_f32, s.CT, s.G, stream, dry);
+        return launch_mtile(a, bf16, y_f32, s.shape, !(vec_ok && N % 8 == 0), stream, dry);
     }
     case 6: {
         const int slot = blk_slot(s.G);

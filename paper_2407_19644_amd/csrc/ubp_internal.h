@@ -122,6 +122,12 @@ struct BlkLayout {
 // stripe * ceil(kt_pad / 32) + kt / 32): the tile has a kept weight.
 constexpr int kTileMaxK = 256;
 constexpr int64_t kTileMaxBytes = 8 << 20;
+// Tiles per stripe of the dense tiles; 0 where they are not built (larger than kTileMaxBytes).
+inline int tile_kt_pad(int M, int K) {
+    const int kt = (K + kStep - 1) / kStep;
+    const int kt_pad = K <= kTileMaxK ? (kt < 2 ? 2 : (kt + 1) / 2 * 2) : (kt + 7) / 8 * 8;
+    return (int64_t)((M + kStripe - 1) / kStripe) * kt_pad * 1024 <= kTileMaxBytes ? kt_pad : 0;
+}
 struct TileLayout {
     bool built = false;
     int kt_pad = 0;                  // 0: not usable for this matrix
@@ -129,6 +135,13 @@ struct TileLayout {
     std::vector<uint16_t> frags;     // [nstripes][kt_pad][64 lanes][8]
     std::vector<uint32_t> occupied;
     int64_t tiles_nonzero = 0;
+};
+
+// Where blocks lie, counted once per handle (16-bit handles): what the estimates of the kernels need.
+struct MaskStats {
+    bool built = false;
+    int64_t tiles_hit = 0;  // 16 x 32 tiles a block reaches into
+    int64_t tiles = 0;      // all of them
 };
 
 struct StripeLayoutDev {
@@ -232,6 +245,7 @@ struct ubp_packed {
     mutable ubp::StripeLayout sg[ubp::kNumLayouts];
     mutable ubp::BlkLayout blk[3];           // G = 2, 4, 5
     mutable ubp::TileLayout tiles;
+    mutable ubp::MaskStats stats;
     // device side
     int32_t *d_indptr = nullptr;
     int32_t *d_indices = nullptr;
@@ -254,6 +268,7 @@ inline int blk_slot(int G) { return G == 2 ? 0 : G == 4 ? 1 : G == 5 ? 2 : -1; }
 const StripeLayout &get_stripe_layout(const ubp_packed *p, int G, int CT);
 const BlkLayout &get_blk_layout(const ubp_packed *p, int G);
 const TileLayout &get_tile_layout(const ubp_packed *p);
+const MaskStats &get_mask_stats(const ubp_packed *p);
 bool blk_eligible(const ubp_packed *p);
 
 // ---- device (HIP translation units)
@@ -273,10 +288,11 @@ int stripe_max_waves(int G, int CT);
 ubp_status launch_blk(const BlkArgs &a, bool bf16, bool y_f32, int G, int waves, void *stream, bool dry);
 int blk_max_waves(int G);
 ubp_status launch_xstat(const TileArgs &a, bool bf16, bool y_f32, int CT, int KT, int waves, void *stream, bool dry);
-ubp_status launch_xchunk(const TileArgs &a, bool bf16, bool y_f32, int CT, int SW, void *stream, bool dry);
-constexpr int kNumGemmShapes = 6;
-void gemm_shape(int shape, int *rows, int *pixels);
-ubp_status launch_gemm(const TileArgs &a, bool bf16, bool y_f32, int shape, void *stream, bool dry);
+// shapes of kernel 5 / 7 / 9: rows x pixels of a workgroup's tile, workgroups a CU holds
+struct MtileShape { int rows, pixels, per_cu; };
+constexpr int kNumMtileShapes = 4;
+constexpr MtileShape kMtileShapes[kNumMtileShapes] = {{128, 128, 1}, {128, 64, 1}, {64, 128, 1}, {64, 64, 2}};
+ubp_status launch_mtile(const TileArgs &a, bool bf16, bool y_f32, int shape, bool ragged, void *stream, bool dry);
 ubp_status launch_floor(void *stream);
 
 } // namespace ubp

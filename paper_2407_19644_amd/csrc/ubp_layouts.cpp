@@ -202,12 +202,11 @@ void build_one(const ubp_packed *p, StripeLayout &L, int G, int CT) {
 void build_tiles(const ubp_packed *p, TileLayout &T) {
     T.kt_pad = 0;
     const int M = p->M, K = p->K, bh = p->bh, bw = p->bw;
-    const int kt = (K + kStep - 1) / kStep;
     // K <= 256: 2, 4, 6 or 8 tiles per stripe (held in registers at once); beyond that whole chunks
     // of 8 tiles, while the zero-filled matrix stays small
-    const int kt_pad = K <= kTileMaxK ? std::max(2, ((kt + 1) / 2) * 2) : ((kt + 7) / 8) * 8;
+    const int kt_pad = tile_kt_pad(M, K);
     const int nstripes = (M + kStripe - 1) / kStripe;
-    if ((int64_t)nstripes * kt_pad * 1024 > kTileMaxBytes) return;
+    if (kt_pad == 0) return;
     T.kt_pad = kt_pad;
     T.nstripes = nstripes;
     T.frags.assign((size_t)T.nstripes * T.kt_pad * 512, 0);
@@ -477,6 +476,25 @@ const BlkLayout &get_blk_layout(const ubp_packed *p, int G) {
         if (blk_eligible(p)) build_blk(p, L, G);
     }
     return L;
+}
+
+// One bit per (stripe, column) with a kept weight: its words are the columns of one 16 x 32 tile each.
+const MaskStats &get_mask_stats(const ubp_packed *p) {
+    MaskStats &S = p->stats;
+    if (S.built) return S;
+    S.built = true;
+    const int nstripes = (p->M + kStripe - 1) / kStripe, words = (p->K + 31) / 32;
+    S.tiles = (int64_t)nstripes * words;
+    std::vector<uint32_t> bits((size_t)S.tiles, 0u);
+    for (int i = 0; i + p->bh <= p->M; ++i)
+        for (int32_t b = p->indptr[(size_t)i]; b < p->indptr[(size_t)i + 1]; ++b)
+            for (int st = i / kStripe; st <= (i + p->bh - 1) / kStripe; ++st)
+                for (int k = p->indices[(size_t)b]; k < p->indices[(size_t)b] + p->bw; ++k)
+                    bits[(size_t)st * words + k / 32] |= 1u << (k % 32);
+    for (int st = 0; st < nstripes; ++st) {
+        for (int w = 0; w < words; ++w) S.tiles_hit += bits[(size_t)st * words + w] != 0;
+    }
+    return S;
 }
 
 const TileLayout &get_tile_layout(const ubp_packed *p) {

@@ -1,0 +1,55 @@
+"""GPU parity of the LDS-staged dense tiles at any alignment (9), at the
+edges of their tiles, against the CPU oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle                                    # noqa: E402
+import paper_2407_19644_amd as ubp               # noqa: E402
+from synthetic import decode_f64, make_activations, make_weights, select_blocks   # noqa: E402
+from gpu_util import check, run_spmm             # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _plan(**kw):
+    p = ubp.Plan()
+    for k, v in kw.items():
+        setattr(p, k, v)
+    return p
+
+
+def _case(M, K, N, bh, bw, density, dtype, seed):
+    blocks = select_blocks(M, K, bh, bw, density, seed, "uniform", 1.1)
+    W = make_weights(M, K, seed + 1, dtype)
+    X = make_activations(K, N, seed + 2, dtype, "normal")
+    return blocks, W, X, oracle.spmm(decode_f64(W, dtype), bh, bw, blocks, decode_f64(X, dtype), want_abs=True)
+
+
+@pytest.mark.parametrize("N", [8, 9, 15, 16, 63, 65, 127, 136, 200, 385])
+@pytest.mark.parametrize("shape", [(64, 64, 4, 4, 0.6), (130, 65, 4, 4, 0.5), (17, 300, 8, 8, 0.3), (300, 129, 16, 16, 0.2)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_staged_tiles_at_any_alignment(shape, N):
+    """Every tile size, rows of X with and without 16-byte alignment, pieces of 8 pixels over the right
+    edge, a last stage of fewer than 64 columns, one stage only, rows beyond M; matrices with and
+    without empty operand tiles."""
+    M, K, bh, bw, d = shape
+    for dtype in ("f16", "bf16"):
+        blocks, W, X, (Yref, Yabs) = _case(M, K, N, bh, bw, d, dtype, seed=M + N + 1)
+        for G, CT, pad in [(0, 0, 0), (8, 8, 1), (8, 4, 3), (4, 8, -N % 8), (4, 4, 0), (8, 8, -N % 8), (4, 4, 5)]:
+            if (G, CT) == (4, 8) and N % 8:
+                continue        # (that shape is for aligned rows)
+            for y_dtype in (dtype, "f32"):
+                Y = run_spmm(W, dtype, bh, bw, blocks, X, y_dtype, _plan(kernel=9, sub_stripes=G, col_tiles=CT),
+                             ldx=N + pad, ldy=N + pad)
+                check(Y, Yref, Yabs, dtype, y_dtype)
+    with pytest.raises(ubp.UBPError):
+        run_spmm(W, dtype, bh, bw, blocks, X[:, :7], dtype, _plan(kernel=9))
+
+
+def test_kernels_5_and_7_beyond_the_staged_tiles_columns():
+    """A K whose occupancy words do not fit a wavefront's lanes: pinned kernel 5 still computes."""
+    M, K, N, dtype = 16, 20000, 64, "bf16"
+    blocks, W, X, (Yref, Yabs) = _case(M, K, N, 4, 4, 0.05, dtype, seed=5)
+    check(run_spmm(W, dtype, 4, 4, blocks, X, "f32", _plan(kernel=5)), Yref, Yabs, dtype, "f32")
