@@ -34,7 +34,7 @@ MFMA_PEAK_TFLOPS = 2500.0        # dense bf16 / fp16 MFMA, published
 INFINITY_CACHE_BYTES = 256 << 20
 MIN_TIMED_MS = 50.0
 KERNEL_NAMES = {1: "wros_kernel", 2: "stripe_kernel", 3: "naive_kernel", 4: "xstat_kernel", 5: "mtile_kernel", 6: "blk_kernel",
-                7: "mtile_kernel", 9: "mtile_kernel"}
+                7: "mtile_kernel", 8: "direct_kernel", 9: "mtile_kernel"}
 
 
 def algorithmic_bytes(cfg, nb, N, y_bytes):

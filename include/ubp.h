@@ -130,7 +130,8 @@ const void *ubp_packed_values(const ubp_packed *p, int64_t *len_elems);
  * with kernels 4, 5, 7 and 9, every output row whose 16-row stripe keeps a weight within the aligned
  * 32 rows of X around it; with kernel 2, every row of a row group that keeps a weight in that
  * column; with kernel 6, every row of a stripe that a block reaches into whose 16-row window of X
- * (its columns, moved left at the right edge) contains it.  Kernel 1 multiplies kept weights only.
+ * (its columns, moved left at the right edge) contains it; with kernel 8, every row of a 16-row stripe
+ * that keeps a weight in that column.  Kernel 1 multiplies kept weights only.
  */
 ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t N,
                     void *Y_dev, int64_t ldy, ubp_dtype y_dtype, void *hip_stream);
@@ -161,17 +162,20 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                paper's rotation with period 16 (f16 / bf16, bh <= 16, 16 <= K < 65408, N >= 64,
  *                16-byte aligned rows; col_tiles 4 only; sub_stripes 2, 4 or 5 = the most stripes a
  *                wavefront's row group may have: row groups are cut shorter where many blocks start).
- *                0 picks 1 for fp32, else the kernel with the smallest estimated time among 4, 5, 7
+ *                8 = MFMA kernel without LDS staging: the wavefronts of a workgroup split the nonempty
+ *                columns of one 16-row stripe and read X straight into registers (f16 / bf16, K <= 65536,
+ *                any N >= col_tiles, any alignment; col_tiles 1, 2 or 4; waves 1 .. 16).
+ *                0 picks 1 for fp32, else the kernel with the smallest estimated time among 8; 4, 5, 7
  *                and 9 while at least half of the 16 x 32 tiles of W keep a weight; and 6 for 16-row blocks
  *                at least 16 wide when K > 1024; or 2 where none of these takes the call.  (3 is never
- *                picked.)
+ *                picked.)  Kernels 2, 6 and 7 asked for without any other field resolve to 8 where 0 does.
  *   sub_stripes: kernels 2 and 6, 16-row stripes per wavefront (1, 2 or 4; kernel 6: 2, 4 or 5,
  *                by itself 5 where that saves a workgroup row, else 4);
  *                kernels 5, 7 and 9: as above.
- *   col_tiles  : kernel 2, 16-column tiles per wavefront (2, 4 or 8); kernels 4, 5, 7 and 9:
+ *   col_tiles  : kernel 2, 16-column tiles per wavefront (2, 4 or 8); kernels 4, 5, 7, 8 and 9:
  *                as above.
  *   waves      : wavefronts per workgroup (kernels 2 and 6: producers + 1 .. 16, fewer for shapes
- *                that need many registers; kernel 4 as above).
+ *                that need many registers; kernels 4 and 8 as above).
  *   rows_per_range : kernels 1 and 3, output rows owned by one workgroup row (multiple of bh).
  *   producers  : kernels 2 and 6, wavefronts of a workgroup that stage X into LDS (1, 2 or 4);
  *                the others each own a row group.

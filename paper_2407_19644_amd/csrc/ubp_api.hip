@@ -138,6 +138,20 @@ ubp_status upload_tile_layout(const ubp_packed *p) {
     return UBP_OK;
 }
 
+ubp_status upload_direct_layout(const ubp_packed *p) {
+    DirectLayoutDev &D = p->d_direct;
+    if (D.uploaded) return UBP_OK;
+    const DirectLayout &L = p->direct;
+    bool ok = dev_copy_vec(&D.first, L.first, &p->device_bytes) && dev_copy_vec(&D.order, L.order, &p->device_bytes) &&
+              dev_copy_vec(&D.ids, L.ids, &p->device_bytes) && dev_copy_vec(&D.frags, L.frags, &p->device_bytes);
+    if (!ok) {
+        (void)hipGetLastError();
+        return UBP_ERR_ALLOC;
+    }
+    D.uploaded = true;
+    return UBP_OK;
+}
+
 void release_device(ubp_packed *p) {
     if (!p || p->device == UBP_HOST_ONLY) return;
     DeviceGuard guard(p->device);
@@ -152,6 +166,10 @@ void release_device(ubp_packed *p) {
     rel(p->d_error);
     rel(p->d_tiles.frags);
     rel(p->d_tiles.occupied);
+    rel(p->d_direct.first);
+    rel(p->d_direct.order);
+    rel(p->d_direct.ids);
+    rel(p->d_direct.frags);
     for (int s = 0; s < kNumLayouts; ++s) {
         rel(p->d_sg[s].rg_ptr);
         rel(p->d_sg[s].rg_order);
@@ -170,7 +188,7 @@ namespace {
 
 // What a call resolves to: the kernel and its launch shape, every field set.
 struct Shape {
-    int kernel = 0;   // 1 vector, 2 gather, 4 small-K dense tiles, 5 / 7 / 9 dense tiles through LDS, 6 block
+    int kernel = 0;   // 1 vector, 2 gather, 4 small-K dense tiles, 5 / 7 / 9 dense tiles through LDS, 6 block, 8 direct
     int shape = 0;    // kernels 5, 7, 9: index into kMtileShapes
     int G = 0, CT = 0, waves = 0, NP = 0, wg_rows = 0, rpr = 0;
     bool resident = false;
@@ -184,6 +202,37 @@ struct Shape {
 // 5 to 10 %; the kernel of the smallest estimate took 2.5 % longer than the fastest one on average.
 constexpr double kNever = 1e30;
 constexpr double kCUs = 256.0;
+
+bool direct_able(const ubp_packed *p, int N, int64_t ldx_bytes) { // 16-bit row numbers, 32-bit byte offsets into X
+    return p->dtype != UBP_F32 && p->K <= 0x10000 && N >= 1 && ldx_bytes < (int64_t(1) << 24) &&
+           (int64_t)p->K * ldx_bytes < (int64_t(1) << 32) &&
+           (int64_t)((p->M + 15) / 16) * ((N + 15) / 16) <= 0x7fffffff;
+}
+int direct_tiles(int N) { return N <= 16 ? 1 : N <= 32 ? 2 : 4; }
+
+// Wavefronts per workgroup: enough that a wavefront has one or two steps, as long as the chip is not full.
+// waves: in: 0 or pinned; out: what the estimate is for.
+double estimate_direct(const ubp_packed *p, int N, int CT, size_t ysz, int &waves) {
+    const MaskStats &S = get_mask_stats(p);
+    const double stripes = (p->M + 15) / 16, px_tiles = (N + 16 * CT - 1) / (16 * CT), wgs = stripes * px_tiles;
+    const double load = S.steps * px_tiles * (1024 + 64 + 1024 * CT) / kCUs * 1e-5; // weights, row numbers, rows of X
+    const double fixed = 2.77 + (N % 8 != 0 ? 2.023 : 1.427) * load + 0.594 * 0.2e-6 * p->M * (double)N * ysz +
+                         0.352 * 0.4e-6 * p->K * (double)N;
+    double best = kNever;
+    int best_w = 4;
+    for (int w = 1; w <= 16; w *= 2) {
+        if (waves != 0 && w != 16) continue;
+        const int ww = waves ? waves : w;
+        if (w == 16 && CT > 1 && !waves) continue; // (its exchange of partial sums costs more than the steps it saves)
+        const double t = fixed + 0.156 * std::ceil((double)S.steps / stripes / ww) + 0.01404 * wgs * ww * CT / kCUs;
+        if (t < best * (ww == 4 ? 1.03 : 1.0)) { // (four where it hardly matters)
+            best = t;
+            best_w = ww;
+        }
+    }
+    waves = best_w;
+    return best;
+}
 
 // Dense tiles through LDS, by shape and by whether rows of X take the way through registers
 double estimate_mtile(const ubp_packed *p, int N, int shape, bool ragged, size_t ysz) {
@@ -257,6 +306,14 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
     const bool mostly = 2 * S.tiles_hit >= S.tiles, full = S.tiles_hit == S.tiles;
     double best = kNever;
     s.kernel = 2;
+    // (layers that some tile of keeps nothing and whose K fits the registers stay with the kernels that
+    // add up in column order, whatever the number of pixels)
+    if (direct_able(p, N, ldx_bytes) && !(aligned && mostly && !full && p->K <= kTileMaxK)) {
+        int waves = 0;
+        best = estimate_direct(p, N, direct_tiles(N), ysz, waves);
+        s.kernel = 8;
+        s.waves = waves;
+    }
     if (mostly && mtile_able(p, N, ldx_bytes)) {
         for (int sh = 0; sh < kNumMtileShapes; ++sh) {
             const double t = estimate_mtile(p, N, sh, !aligned, ysz);
@@ -281,14 +338,23 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
 // of the layout that shape needs (under the handle's lock).  No device work.
 ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
     int kernel = pl.kernel;
+    const bool no_shape = !(pl.sub_stripes || pl.col_tiles || pl.waves || pl.rows_per_range || pl.producers || pl.wg_rows);
     // the dense-tile kernels 4, 5 and 7 need 16-byte pieces of X rows that lie entirely inside or outside the matrix
     const bool tile_able = p->dtype != UBP_F32 && vec_ok && N % 8 == 0;
-    if (kernel < 0 || kernel > 9 || kernel == 8) return UBP_ERR_INVALID_ARG;
+    if (kernel < 0 || kernel > 9) return UBP_ERR_INVALID_ARG;
     if (kernel > 1 && kernel != 3 && p->dtype == UBP_F32) return UBP_ERR_UNSUPPORTED;
     if (kernel == 0 && p->dtype == UBP_F32) kernel = 1;
-    if (kernel == 0) {
-        choose(p, N, ldx_bytes, vec_ok, ysz, s);
-        kernel = s.kernel;
+    if (kernel == 0 || (no_shape && (kernel == 2 || kernel == 6 || kernel == 7))) {
+        // A kernel asked for without a shape: its automatic shapes include the direct kernel's, so that it
+        // computes what the automatic choice does where that lands on one of the two.
+        Shape c;
+        choose(p, N, ldx_bytes, vec_ok, ysz, c);
+        if (kernel == 0 || c.kernel == 8) {
+            if (kernel == 6 && (!blk_eligible(p) || !vec_ok || N < 64)) return UBP_ERR_UNSUPPORTED;
+            if (kernel == 7 && (!tile_able || !all_tiles_kept(p))) return UBP_ERR_UNSUPPORTED;
+            s = c;
+            kernel = c.kernel;
+        }
     }
     s.kernel = kernel;
     if (kernel == 1 || kernel == 3) {
@@ -307,6 +373,17 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
         s.rpr = rpr;
         return UBP_OK;
     }
+    if (kernel == 8) {
+        if (!direct_able(p, N, ldx_bytes)) return UBP_ERR_UNSUPPORTED;
+        s.CT = pl.col_tiles ? pl.col_tiles : direct_tiles(N);
+        if ((s.CT != 1 && s.CT != 2 && s.CT != 4) || N < s.CT) return UBP_ERR_UNSUPPORTED;
+        s.waves = pl.waves;
+        estimate_direct(p, N, s.CT, ysz, s.waves);
+        if (s.waves < 1 || s.waves > 16) return UBP_ERR_UNSUPPORTED;
+        const DirectLayout &L = get_direct_layout(p);
+        s.wg_rows = L.nstripes;
+        return UBP_OK;
+    }
     if (kernel == 5 || kernel == 7 || kernel == 9) {
         if (kernel != 9 && !tile_able) return UBP_ERR_UNSUPPORTED;
         const TileLayout &T = get_tile_layout(p);
@@ -319,7 +396,7 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
         if (!mtile_able(p, N, ldx_bytes)) { // (a K or a pitch beyond this kernel's offsets)
             if (kernel == 9) return UBP_ERR_UNSUPPORTED;
             ubp_plan other = {};
-            other.kernel = 2;
+            other.kernel = direct_able(p, N, ldx_bytes) ? 8 : 2;
             return resolve(p, N, ldx_bytes, vec_ok, ysz, other, s);
         }
         // Of the shapes no larger than what the plan names (kernel 5: in units of 32 rows and 32 pixels,
@@ -552,6 +629,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         case 5:
         case 9:
         case 7: rc = upload_tile_layout(p); break;
+        case 8: rc = upload_direct_layout(p); break;
         case 6:
             rc = upload_blk_layout(p, blk_slot(s.G));
             if (rc == UBP_OK && N % 64 != 0) {
@@ -607,6 +685,22 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         a.sps = (T.nstripes + s.wg_rows - 1) / s.wg_rows;
         if (s.kernel == 4) return launch_xstat(a, bf16, y_f32, s.CT, T.kt_pad, s.waves, stream, dry);
         return launch_mtile(a, bf16, y_f32, s.shape, !(vec_ok && N % 8 == 0), stream, dry);
+    }
+    case 8: {
+        DirectArgs a = {};
+        a.first = p->d_direct.first;
+        a.order = p->d_direct.order;
+        a.ids = p->d_direct.ids;
+        a.frags = p->d_direct.frags;
+        a.X = static_cast<const uint16_t *>(X_dev);
+        a.Y = Y_dev;
+        a.ldx = ldx;
+        a.ldy = ldy;
+        a.M = p->M;
+        a.N = N;
+        a.nstripes = p->direct.nstripes;
+        a.ep = ep;
+        return launch_direct(a, bf16, y_f32, s.CT, s.waves, stream, dry);
     }
     case 6: {
         const int slot = blk_slot(s.G);

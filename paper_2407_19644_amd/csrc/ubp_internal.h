@@ -140,8 +140,25 @@ struct TileLayout {
 // Where blocks lie, counted once per handle (16-bit handles): what the estimates of the kernels need.
 struct MaskStats {
     bool built = false;
+    int64_t steps = 0;      // steps of the direct layout: sum over stripes of ceil(columns with a kept weight / 32)
     int64_t tiles_hit = 0;  // 16 x 32 tiles a block reaches into
     int64_t tiles = 0;      // all of them
+};
+
+// Host image of the direct kernel's layout: for every aligned 16-row stripe the columns of W in which
+// it keeps a weight, ascending, 32 to a step.
+//   first : [nstripes + 1] first step of each stripe
+//   order : [nstripes] stripes, most steps first
+//   ids   : 32 16-bit row numbers of X per step; entry 8 g + e is element e of lane group g.  A
+//           stripe's last step repeats its first row number (with zero weights) to fill up.
+//   frags : 512 16-bit weights per step in MFMA operand order: lane 16 g + n holds, as element e, the
+//           weight of row n of the stripe in column ids[8 g + e]
+struct DirectLayout {
+    bool built = false;
+    int nstripes = 0;                // 0: not usable for this matrix
+    std::vector<int32_t> first, order;
+    std::vector<uint16_t> ids, frags;
+    int64_t nsteps = 0;
 };
 
 struct StripeLayoutDev {
@@ -155,6 +172,13 @@ struct BlkLayoutDev {
     int32_t *rg_order = nullptr;
     uint32_t *meta = nullptr;
     uint32_t *frags = nullptr;
+    bool uploaded = false;
+};
+struct DirectLayoutDev {
+    int32_t *first = nullptr;
+    int32_t *order = nullptr;
+    uint16_t *ids = nullptr;
+    uint16_t *frags = nullptr;
     bool uploaded = false;
 };
 struct TileLayoutDev {
@@ -213,6 +237,16 @@ struct BlkArgs {
     Epilogue ep;
 };
 
+struct DirectArgs {
+    const int32_t *first, *order;
+    const uint16_t *ids, *frags;
+    const uint16_t *X;
+    void *Y;
+    int64_t ldx, ldy;        // (ldx below 2^23, K rows of X below 4 GB: 32-bit byte offsets)
+    int M, N, nstripes, n_tiles;
+    Epilogue ep;
+};
+
 struct TileArgs {
     const uint16_t *frags;   // [nstripes][KT][64][8]
     const uint32_t *occupied; // one bit per tile, ceil(kt_total / 32) words per stripe
@@ -245,6 +279,7 @@ struct ubp_packed {
     mutable ubp::StripeLayout sg[ubp::kNumLayouts];
     mutable ubp::BlkLayout blk[3];           // G = 2, 4, 5
     mutable ubp::TileLayout tiles;
+    mutable ubp::DirectLayout direct;
     mutable ubp::MaskStats stats;
     // device side
     int32_t *d_indptr = nullptr;
@@ -253,6 +288,7 @@ struct ubp_packed {
     mutable ubp::StripeLayoutDev d_sg[ubp::kNumLayouts];
     mutable ubp::BlkLayoutDev d_blk[3];
     mutable ubp::TileLayoutDev d_tiles;
+    mutable ubp::DirectLayoutDev d_direct;
     uint32_t *d_error = nullptr;   // set by a kernel whose bounded wait ran out
     mutable int64_t device_bytes = 0;
 };
@@ -268,6 +304,7 @@ inline int blk_slot(int G) { return G == 2 ? 0 : G == 4 ? 1 : G == 5 ? 2 : -1; }
 const StripeLayout &get_stripe_layout(const ubp_packed *p, int G, int CT);
 const BlkLayout &get_blk_layout(const ubp_packed *p, int G);
 const TileLayout &get_tile_layout(const ubp_packed *p);
+const DirectLayout &get_direct_layout(const ubp_packed *p);
 const MaskStats &get_mask_stats(const ubp_packed *p);
 bool blk_eligible(const ubp_packed *p);
 
@@ -278,6 +315,7 @@ void release_device(ubp_packed *p);
 ubp_status upload_stripe_layout(const ubp_packed *p, int slot);
 ubp_status upload_blk_layout(const ubp_packed *p, int slot);
 ubp_status upload_tile_layout(const ubp_packed *p);
+ubp_status upload_direct_layout(const ubp_packed *p);
 
 // Launchers.  `dry` only raises the kernels' dynamic LDS limit on the current device (what a
 // first launch of a shape would do), so that a later launch is nothing but a launch.
@@ -288,6 +326,7 @@ int stripe_max_waves(int G, int CT);
 ubp_status launch_blk(const BlkArgs &a, bool bf16, bool y_f32, int G, int waves, void *stream, bool dry);
 int blk_max_waves(int G);
 ubp_status launch_xstat(const TileArgs &a, bool bf16, bool y_f32, int CT, int KT, int waves, void *stream, bool dry);
+ubp_status launch_direct(const DirectArgs &a, bool bf16, bool y_f32, int CT, int waves, void *stream, bool dry);
 // shapes of kernel 5 / 7 / 9: rows x pixels of a workgroup's tile, workgroups a CU holds
 struct MtileShape { int rows, pixels, per_cu; };
 constexpr int kNumMtileShapes = 4;

@@ -233,6 +233,63 @@ void build_tiles(const ubp_packed *p, TileLayout &T) {
     for (uint32_t w : T.occupied) T.tiles_nonzero += __builtin_popcount(w);
 }
 
+// Column lists per stripe for the direct kernel.  Stripe by stripe: the columns of the blocks that
+// reach into it are marked in a bitmap (whose set bits come out ascending), then the blocks' weights
+// go to the steps their columns landed in.
+void build_direct(const ubp_packed *p, DirectLayout &L) {
+    const int M = p->M, K = p->K, bh = p->bh, bw = p->bw;
+    L.nstripes = (M + kStripe - 1) / kStripe;
+    L.first.assign((size_t)L.nstripes + 1, 0);
+    const uint16_t *vals = reinterpret_cast<const uint16_t *>(p->values.data());
+    const int32_t nstart = M - bh + 1; // start rows 0..M-bh
+    const size_t words = ((size_t)K + 63) / 64;
+    std::vector<uint64_t> mark(words, 0);
+    std::vector<int32_t> pos((size_t)K);
+    for (int st = 0; st < L.nstripes; ++st) {
+        const int row0 = st * kStripe, row1 = std::min(M, row0 + kStripe);
+        const int i0 = std::max(0, row0 - bh + 1), i1 = std::min(nstart, row1);
+        const int32_t b0 = i0 < i1 ? p->indptr[(size_t)i0] : 0, b1 = i0 < i1 ? p->indptr[(size_t)i1] : 0;
+        for (int32_t b = b0; b < b1; ++b)
+            for (int q = 0; q < bw; ++q) {
+                const int k = p->indices[(size_t)b] + q;
+                mark[(size_t)k / 64] |= uint64_t(1) << (k % 64);
+            }
+        const size_t step0 = (size_t)L.nsteps;
+        L.first[(size_t)st] = (int32_t)L.nsteps;
+        int n = 0;
+        for (size_t w = 0; w < words; ++w) {
+            for (uint64_t m = mark[w]; m; m &= m - 1) {
+                const int k = (int)(64 * w) + __builtin_ctzll(m);
+                pos[(size_t)k] = n;
+                if (n % kStep == 0) L.ids.resize(L.ids.size() + kStep, 0);
+                // the position of entry i of a step: operand element e of lane group g is column 8 g + e
+                L.ids[(step0 + (size_t)n / kStep) * kStep + (size_t)(n % kStep)] = (uint16_t)k;
+                ++n;
+            }
+            mark[w] = 0;
+        }
+        const int steps = (n + kStep - 1) / kStep;
+        for (int i = n; i < steps * kStep; ++i) L.ids[step0 * kStep + (size_t)i] = L.ids[(step0 + (size_t)steps - 1) * kStep];
+        L.nsteps += steps;
+        L.frags.resize((size_t)L.nsteps * 512, 0);
+        for (int i = i0; i < i1; ++i)
+            for (int32_t b = p->indptr[(size_t)i]; b < p->indptr[(size_t)i + 1]; ++b)
+                for (int q = 0; q < bw; ++q) {
+                    const int at = pos[(size_t)(p->indices[(size_t)b] + q)];
+                    const int gi = (at % kStep) / 8, e = at % 8;
+                    uint16_t *frag = &L.frags[(step0 + (size_t)(at / kStep)) * 512 + (size_t)gi * 128 + (size_t)e];
+                    for (int rho = std::max(i, row0); rho < std::min(i + bh, row1); ++rho)
+                        frag[(size_t)(rho - row0) * 8] = vals[((int64_t)b * bw + q) * bh + (rho % bh)]; // rotated storage
+                }
+    }
+    L.first[(size_t)L.nstripes] = (int32_t)L.nsteps;
+    L.order.resize((size_t)L.nstripes);
+    std::iota(L.order.begin(), L.order.end(), 0);
+    std::stable_sort(L.order.begin(), L.order.end(), [&](int32_t a, int32_t b) {
+        return L.first[(size_t)a + 1] - L.first[(size_t)a] > L.first[(size_t)b + 1] - L.first[(size_t)b];
+    });
+}
+
 // ---------------------------------------------------------------- block kernel layout
 struct Half {
     int32_t a;      // first row of the 16-row window of X
@@ -478,6 +535,16 @@ const BlkLayout &get_blk_layout(const ubp_packed *p, int G) {
     return L;
 }
 
+const DirectLayout &get_direct_layout(const ubp_packed *p) {
+    DirectLayout &L = p->direct;
+    if (!L.built) {
+        L.built = true;
+        L.nstripes = 0;
+        if (p->dtype != UBP_F32 && p->K <= 0x10000) build_direct(p, L); // row numbers are 16-bit in the records
+    }
+    return L;
+}
+
 // One bit per (stripe, column) with a kept weight: its words are the columns of one 16 x 32 tile each.
 const MaskStats &get_mask_stats(const ubp_packed *p) {
     MaskStats &S = p->stats;
@@ -492,7 +559,13 @@ const MaskStats &get_mask_stats(const ubp_packed *p) {
                 for (int k = p->indices[(size_t)b]; k < p->indices[(size_t)b] + p->bw; ++k)
                     bits[(size_t)st * words + k / 32] |= 1u << (k % 32);
     for (int st = 0; st < nstripes; ++st) {
-        for (int w = 0; w < words; ++w) S.tiles_hit += bits[(size_t)st * words + w] != 0;
+        int64_t cols = 0;
+        for (int w = 0; w < words; ++w) {
+            const uint32_t v = bits[(size_t)st * words + w];
+            cols += __builtin_popcount(v);
+            S.tiles_hit += v != 0;
+        }
+        S.steps += (cols + kStep - 1) / kStep;
     }
     return S;
 }

@@ -1,4 +1,4 @@
-"""GPU parity of the LDS-staged dense tiles at any alignment (9), at the
+"""GPU parity of the direct kernel (8) and of the LDS-staged dense tiles at any alignment (9), at the
 edges of their tiles, against the CPU oracle."""
 import numpy as np
 import pytest
@@ -25,6 +25,26 @@ def _case(M, K, N, bh, bw, density, dtype, seed):
     W = make_weights(M, K, seed + 1, dtype)
     X = make_activations(K, N, seed + 2, dtype, "normal")
     return blocks, W, X, oracle.spmm(decode_f64(W, dtype), bh, bw, blocks, decode_f64(X, dtype), want_abs=True)
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 7, 8, 15, 16, 17, 31, 32, 33, 49, 63, 64, 65, 130])
+@pytest.mark.parametrize("shape", [(33, 70, 4, 4, 0.3), (130, 600, 16, 16, 0.1), (17, 31, 5, 3, 0.4), (16, 2100, 4, 1, 0.02)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_direct_kernel(shape, N):
+    """Pixel tiles that hang over the right edge, rows of 2-byte alignment, more wavefronts than
+    steps, stripes without any step, a last stripe beyond M."""
+    M, K, bh, bw, d = shape
+    for dtype in ("f16", "bf16"):
+        blocks, W, X, (Yref, Yabs) = _case(M, K, N, bh, bw, d, dtype, seed=M + N)
+        for CT, waves, pad in [(0, 0, 0), (1, 1, 1), (1, 16, 0), (2, 3, 3), (4, 2, 1), (4, 16, 8)]:
+            if N < CT:
+                with pytest.raises(ubp.UBPError):
+                    run_spmm(W, dtype, bh, bw, blocks, X, "f32", _plan(kernel=8, col_tiles=CT))
+                continue
+            for y_dtype in (dtype, "f32"):
+                Y = run_spmm(W, dtype, bh, bw, blocks, X, y_dtype, _plan(kernel=8, col_tiles=CT, waves=waves),
+                             ldx=N + pad, ldy=N + pad)
+                check(Y, Yref, Yabs, dtype, y_dtype)
 
 
 @pytest.mark.parametrize("N", [8, 9, 15, 16, 63, 65, 127, 136, 200, 385])
