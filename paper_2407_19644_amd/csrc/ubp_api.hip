@@ -90,10 +90,21 @@ ubp_status upload_values_f32(const ubp_packed *p) {
             }
         }
     }
+    // behind them the rows of X of the blocks' columns, one after the other (what the kernel loads ahead
+    // may reach kWrosBatch past the end); one allocation and one copy
+    const size_t cols = (size_t)(p->nb * p->bw) + kWrosBatch;
+    f.resize((size_t)n + cols);
+    for (size_t t = 0; t < cols; ++t) {
+        const int32_t row = t < cols - kWrosBatch ? p->indices[t / (size_t)p->bw] + (int32_t)(t % (size_t)p->bw) : 0;
+        std::memcpy(&f[(size_t)n + t], &row, 4);
+    }
     if (!dev_copy(&p->d_values_f32, f.data(), f.size(), &p->device_bytes)) {
         (void)hipGetLastError();
+        if (p->d_values_f32) (void)hipFree(p->d_values_f32);
+        p->d_values_f32 = nullptr;
         return UBP_ERR_ALLOC;
     }
+    p->d_cols = reinterpret_cast<const int32_t *>(p->d_values_f32 + n);
     return UBP_OK;
 }
 
@@ -360,7 +371,15 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
     if (kernel == 1 || kernel == 3) {
         if (p->bh > 16) return UBP_ERR_UNSUPPORTED;
         int rpr = pl.rows_per_range;
-        if (rpr == 0) {
+        if (rpr == 0 && kernel == 1) {
+            // Row ranges of one block height (re-walking bh - 1 rows nearly doubles the work, but a small
+            // layer is a chain of latencies: 64 x 64 with 196 pixels 10.1 us, against 22.5 with ranges of
+            // four) up to 8192 wavefronts of 64 columns, taller beyond (512 x 512 with 25088 pixels
+            // 153 us, 158 with ranges of at least four block heights, 180 and more with half the wavefronts).
+            const int64_t ranges = std::max<int64_t>(1, 8192 / (((int64_t)N + 63) / 64));
+            const int64_t rows = std::max<int64_t>(p->bh, (p->M + ranges - 1) / ranges);
+            rpr = (int)std::min<int64_t>((rows + p->bh - 1) / p->bh * p->bh, 0x7fffffff);
+        } else if (rpr == 0) {
             // enough row ranges to fill the chip, but each at least 4 block heights tall so
             // that re-walking bh-1 start rows stays a small fraction of the work
             const int coltiles = (N + 255) / 256;

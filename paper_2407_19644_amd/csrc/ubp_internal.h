@@ -137,6 +137,9 @@ struct TileLayout {
     int64_t tiles_nonzero = 0;
 };
 
+// Columns of blocks whose rows of X the vector kernel loads together, at most.
+constexpr int kWrosBatch = 8;
+
 // Where blocks lie, counted once per handle (16-bit handles): what the estimates of the kernels need.
 struct MaskStats {
     bool built = false;
@@ -285,6 +288,7 @@ struct ubp_packed {
     int32_t *d_indptr = nullptr;
     int32_t *d_indices = nullptr;
     mutable float *d_values_f32 = nullptr; // rotated values widened to fp32 (exact), for the vector kernel
+    mutable const int32_t *d_cols = nullptr; // (part of d_values_f32) row of X of every block column, in block order, and kWrosBatch zeros, for the vector kernel
     mutable ubp::StripeLayoutDev d_sg[ubp::kNumLayouts];
     mutable ubp::BlkLayoutDev d_blk[3];
     mutable ubp::TileLayoutDev d_tiles;

@@ -1,6 +1,7 @@
 // Vector-ALU kernel of the UBP library: the paper's WROS dataflow, literally (Section 4.2).
 #include "ubp_device.h"
 
+#include <algorithm>
 #include <cstdint>
 
 namespace ubp {
@@ -8,21 +9,36 @@ namespace ubp {
 namespace {
 
 // ------------------------------------------------------------------ WROS vector kernel
-// Grid: x = column tiles of 256*VEC columns, y = ranges of `rpr` output rows.
-// A thread owns VEC columns and BH accumulator rows (slots).  Start rows are walked in
-// increasing order; the loop is unrolled by BH so that "slot = start row mod BH" is a
-// compile-time register name.  After start row i is done, output row i is complete (later
-// blocks start below it): its slot is stored and cleared, the other slots keep
-// accumulating.  A range re-walks the BH-1 start rows above it, whose blocks reach into the
-// range, and drops what those blocks add to rows it does not own.
+// Grid: x = tiles of 64 * VEC columns (a multiple of 8 of them, so that all workgroups of a tile
+// run on one XCD and share its L2), y = groups of row ranges; each wavefront of a workgroup takes
+// one range of `rpr` output rows, and all of them sweep the same columns of X at about the same time.
+// A lane owns VEC columns and BH accumulator rows (slots).  With rotated weights a block adds
+// element s to slot s wherever it starts, so the walk over the blocks' columns, in order of their
+// start rows, is one stream; after start row i is done, output row i is complete (later blocks
+// start below it): its slot, i mod BH, is stored and cleared, the others keep accumulating.  A
+// range re-walks the BH-1 start rows above it, whose blocks reach into the range, and drops what
+// those blocks add to rows it does not own.
+//   The stream is taken U columns at a time, and the U rows of X of the next batch are loaded
+// before the current one is multiplied, over the ends of start rows too: otherwise every column
+// waits for its index and then for its row of X.  512 x 512 in 4 x 1 blocks at 20 % with 6272 pixels:
+// 187 -> 46 us, 64 x 64 with 196 pixels 22 -> 10, 512 x 512 with 49 pixels 95 -> 20.  What bounds
+// the large ones is reading rows of X again from L2 for every start row (11 TB/s).
+// 64 columns of all of X in LDS instead, shared by 16 wavefronts, took longer: 62 us for 6272 pixels,
+// 258 for 25088 (161 from L2) - scalar loads of weights and reads of LDS share one counter.
+//   indptr: blocks per start row; cols: row of X per column of the stream, followed by
+// kWrosBatch spare entries (row 0), which may be loaded and are never multiplied.
 template <typename TX, typename TY, int BH, int VEC>
-__global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ indptr, const int32_t *__restrict__ indices,
+__global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ indptr, const int32_t *__restrict__ cols,
                                                   const float *__restrict__ vals, const TX *__restrict__ X, int64_t ldx,
                                                   TY *__restrict__ Y, int64_t ldy, int M, int N, int bw, int rpr, Epilogue ep) {
-    const int col = (blockIdx.x * 256 + threadIdx.x) * VEC;
-    if (col >= N) return;
-    const int lo = blockIdx.y * rpr;
-    const int hi = min(lo + rpr, M);
+    constexpr int U = BH <= 4 ? 8 : BH <= 8 ? 4 : 2; // (a batch's weights fit the scalar registers)
+    static_assert(U <= kWrosBatch, "spare entries of cols");
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t lo64 = ((int64_t)blockIdx.y * (blockDim.x >> 6) + wave) * rpr;
+    const uint32_t col = (blockIdx.x * 64u + (threadIdx.x & 63u)) * VEC;
+    if (lo64 >= M || col >= (uint32_t)N) return;
+    const int lo = (int)lo64;
+    const int hi = (int)min(lo64 + rpr, (int64_t)M);
     const int last_start = M - BH; // start rows beyond this hold no block (epilogue rows)
     float acc[BH][VEC];
 #pragma unroll
@@ -30,40 +46,64 @@ __global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ i
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[s][v] = 0.f;
 
+    auto load_x = [&](int64_t t, float(&x)[U][VEC]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_row<TX, VEC>(X + (int64_t)cols[t + u] * ldx + col, x[u]);
+    };
+    auto multiply = [&](const float *__restrict__ w, const float(&x)[VEC]) {
+#pragma unroll
+        for (int s = 0; s < BH; ++s)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[s][v] = fmaf(w[s], x[v], acc[s][v]);
+    };
+
     const int first = max(0, lo - BH + 1);
-    for (int base = (first / BH) * BH; base < hi; base += BH) {
+    int slot = first % BH;
+    int64_t t = 0;
+    float x[U][VEC];
+    if (first <= last_start) {
+        const int b0 = indptr[first];
+        t = (int64_t)b0 * bw;
+        if (b0 < indptr[min(hi, last_start + 1)]) load_x(t, x);
+    }
+    for (int i = first; i < hi; ++i) {
+        if (i <= last_start) {
+            const int64_t t1 = (int64_t)indptr[i + 1] * bw;
+            while (t < t1) {
+                const int64_t next = min(t + U, t1);
+                float xn[U][VEC];
+                load_x(next, xn);
+                const float *w = vals + t * BH;
+                if (t + U <= t1) {
 #pragma unroll
-        for (int u = 0; u < BH; ++u) {
-            const int i = base + u; // start row; i mod BH == u
-            if (i < first || i >= hi) continue;
-            if (i <= last_start) {
-                const int b1 = indptr[i + 1];
-                for (int b = indptr[i]; b < b1; ++b) {
-                    const int c = indices[b];
-                    const float *w = vals + (int64_t)b * bw * BH;
-                    for (int q = 0; q < bw; ++q) {
-                        float x[VEC];
-                        load_row<TX, VEC>(X + (int64_t)(c + q) * ldx + col, x);
+                    for (int u = 0; u < U; ++u) multiply(w + u * BH, x[u]);
+                } else {
 #pragma unroll
-                        for (int s = 0; s < BH; ++s) {
-                            const float ws = w[q * BH + s];
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v) acc[s][v] = fmaf(ws, x[v], acc[s][v]);
-                        }
-                    }
+                    for (int u = 0; u < U - 1; ++u)
+                        if (t + u < t1) multiply(w + u * BH, x[u]);
                 }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) x[u][v] = xn[u][v];
+                t = next;
             }
+        }
+#pragma unroll
+        for (int s = 0; s < BH; ++s) {
+            if (s != slot) continue;
             if (i >= lo) {
                 if (ep.on) {
                     const float b = ep.bias ? ep.bias[i] : 0.f;
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[u][v] = epilogue_value(ep, acc[u][v], b);
+                    for (int v = 0; v < VEC; ++v) acc[s][v] = epilogue_value(ep, acc[s][v], b);
                 }
-                store_row<TY, VEC>(Y + (int64_t)i * ldy + col, acc[u]);
+                store_row<TY, VEC>(Y + (int64_t)i * ldy + col, acc[s]);
             }
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[u][v] = 0.f;
+            for (int v = 0; v < VEC; ++v) acc[s][v] = 0.f;
         }
+        slot = slot + 1 == BH ? 0 : slot + 1;
     }
 }
 
@@ -127,12 +167,20 @@ __global__ __launch_bounds__(256) void naive_kernel(const int32_t *__restrict__ 
 template <typename TX, typename TY, int VEC>
 ubp_status launch_wros_bh(const ubp_packed *p, const void *X, int64_t ldx, int N, void *Y, int64_t ldy, int rpr,
                           bool naive, const Epilogue &ep, hipStream_t st) {
-    dim3 grid((unsigned)((N + 256 * VEC - 1) / (256 * VEC)), (unsigned)((p->M + rpr - 1) / rpr));
+    const int64_t ranges = ((int64_t)p->M + rpr - 1) / rpr, tiles = ((int64_t)N + 64 * VEC - 1) / (64 * VEC);
+    const unsigned waves = tiles > (1 << 22) ? 1u : (unsigned)std::min<int64_t>(4, ranges); // (grid size in threads: 32 bits)
+    const dim3 grid((unsigned)((tiles + 7) / 8 * 8), (unsigned)((ranges + waves - 1) / waves));
+    const dim3 naive_grid((unsigned)((N + 256 * VEC - 1) / (256 * VEC)), (unsigned)ranges);
 #define UBP_WROS_CASE(BH)                                                                                              \
     case BH:                                                                                                           \
-        hipLaunchKernelGGL((naive ? (naive_kernel<TX, TY, BH, VEC>) : (wros_kernel<TX, TY, BH, VEC>)), grid, dim3(256), 0, \
-                           st, p->d_indptr, p->d_indices, p->d_values_f32, static_cast<const TX *>(X), ldx,           \
-                           static_cast<TY *>(Y), ldy, p->M, N, p->bw, rpr, ep);                                        \
+        if (naive)                                                                                                     \
+            hipLaunchKernelGGL((naive_kernel<TX, TY, BH, VEC>), naive_grid, dim3(256), 0, st, p->d_indptr, p->d_indices, \
+                               p->d_values_f32, static_cast<const TX *>(X), ldx, static_cast<TY *>(Y), ldy, p->M, N,    \
+                               p->bw, rpr, ep);                                                                        \
+        else                                                                                                           \
+            hipLaunchKernelGGL((wros_kernel<TX, TY, BH, VEC>), grid, dim3(waves * 64), 0, st, p->d_indptr, p->d_cols,   \
+                               p->d_values_f32, static_cast<const TX *>(X), ldx, static_cast<TY *>(Y), ldy, p->M, N,    \
+                               p->bw, rpr, ep);                                                                        \
         break;
     switch (p->bh) {
         UBP_WROS_CASE(1) UBP_WROS_CASE(2) UBP_WROS_CASE(3) UBP_WROS_CASE(4) UBP_WROS_CASE(5) UBP_WROS_CASE(6)
@@ -147,10 +195,14 @@ ubp_status launch_wros_bh(const ubp_packed *p, const void *X, int64_t ldx, int N
 template <typename TX, typename TY>
 ubp_status launch_wros_t(const ubp_packed *p, const void *X, int64_t ldx, int N, void *Y, int64_t ldy, int rpr,
                          bool naive, const Epilogue &ep, hipStream_t st) {
-    // 4 columns per thread when every row of X and Y can be accessed as an aligned 4-vector
-    const bool vec = (N % 4 == 0) && (ldx % 4 == 0) && (ldy % 4 == 0) &&
-                     (reinterpret_cast<uintptr_t>(X) % (4 * sizeof(TX)) == 0) &&
-                     (reinterpret_cast<uintptr_t>(Y) % (4 * sizeof(TY)) == 0) && N >= 2048;
+    // 4 columns per lane where every row of X and Y can be accessed as an aligned 4-vector and about a
+    // wavefront per SIMD is left (512 x 512 with 6272 pixels: 46 us, with one column 60; 256 x 256 with
+    // 784 pixels: 85 us, with one column 25)
+    const bool vec_ok = (N % 4 == 0) && (ldx % 4 == 0) && (ldy % 4 == 0) &&
+                        (reinterpret_cast<uintptr_t>(X) % (4 * sizeof(TX)) == 0) &&
+                        (reinterpret_cast<uintptr_t>(Y) % (4 * sizeof(TY)) == 0);
+    const int64_t waves4 = ((int64_t)N + 255) / 256 * (((int64_t)p->M + rpr - 1) / rpr);
+    const bool vec = vec_ok && (naive ? N >= 2048 : waves4 >= 1000);
     return vec ? launch_wros_bh<TX, TY, 4>(p, X, ldx, N, Y, ldy, rpr, naive, ep, st)
                : launch_wros_bh<TX, TY, 1>(p, X, ldx, N, Y, ldy, rpr, naive, ep, st);
 }

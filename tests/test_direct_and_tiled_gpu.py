@@ -1,4 +1,4 @@
-"""GPU parity of the direct kernel (8) and of the LDS-staged dense tiles at any alignment (9), at the
+"""GPU parity of the vector kernel (1), of the direct kernel (8) and of the LDS-staged dense tiles at any alignment (9), at the
 edges of their tiles, against the CPU oracle."""
 import numpy as np
 import pytest
@@ -73,3 +73,26 @@ def test_kernels_5_and_7_beyond_the_staged_tiles_columns():
     M, K, N, dtype = 16, 20000, 64, "bf16"
     blocks, W, X, (Yref, Yabs) = _case(M, K, N, 4, 4, 0.05, dtype, seed=5)
     check(run_spmm(W, dtype, 4, 4, blocks, X, "f32", _plan(kernel=5)), Yref, Yabs, dtype, "f32")
+
+
+VECTOR = [
+    # M, K, N, bh, bw, density: blocks per start row around the batches of 8, 4 and 2 columns
+    (40, 17, 63, 4, 1, 0.9),
+    (64, 64, 64, 1, 1, 0.13),
+    (33, 45, 65, 5, 3, 0.5),
+    (50, 640, 130, 16, 1, 0.05),
+    (300, 100, 1028, 8, 8, 0.3),
+    (90, 60, 257, 3, 2, 0.004),     # most start rows empty
+    (20, 8, 1, 4, 4, 0.5),
+]
+
+
+@pytest.mark.parametrize("shape", VECTOR, ids=lambda s: "x".join(map(str, s)))
+def test_vector_kernel_batches(shape):
+    M, K, N, bh, bw, d = shape
+    blocks, W, X, (Yref, Yabs) = _case(M, K, N, bh, bw, d, "f32", seed=M + K + N)
+    want = run_spmm(W, "f32", bh, bw, blocks, X, "f32", _plan(kernel=3, rows_per_range=bh))
+    for plan in (None, _plan(kernel=1), _plan(kernel=1, rows_per_range=bh), _plan(kernel=1, rows_per_range=5 * bh)):
+        Y = run_spmm(W, "f32", bh, bw, blocks, X, "f32", plan)
+        check(Y, Yref, Yabs, "f32", "f32")
+        assert np.array_equal(Y, want)  # the same additions in the same order
