@@ -197,14 +197,6 @@ void release_device(ubp_packed *p) {
 
 namespace {
 
-// What a call resolves to: the kernel and its launch shape, every field set.
-struct Shape {
-    int kernel = 0;   // 1 vector, 2 gather, 4 small-K dense tiles, 5 / 7 / 9 dense tiles through LDS, 6 block, 8 direct
-    int shape = 0;    // kernels 5, 7, 9: index into kMtileShapes
-    int G = 0, CT = 0, waves = 0, NP = 0, wg_rows = 0, rpr = 0;
-    bool resident = false;
-};
-
 // ------------------------------------------------------------------ estimates
 // What a 16-bit product would take, in microseconds, by each kernel: linear in the few quantities that
 // cost, coefficients fitted (relative least squares, none negative) to 165 layers drawn over the range of
@@ -638,8 +630,21 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         // Layouts are built and uploaded on first use, under the handle's lock.  A repeated call
         // finds everything in place and allocates nothing.
         std::lock_guard<std::mutex> hold(p->lock);
-        ubp_status rc = resolve(p, N, ldx * 2, vec_ok, ysz, pl, s);
-        if (rc != UBP_OK) return rc;
+        ubp_status rc = UBP_OK;
+        const Choice *known = nullptr;
+        if (!plan)
+            for (const Choice &c : p->choices)
+                if (c.N == N && c.ldx == ldx && c.vec_ok == vec_ok && c.ysz == ysz) known = &c;
+        if (known) {
+            s = known->shape;
+        } else {
+            rc = resolve(p, N, ldx * 2, vec_ok, ysz, pl, s);
+            if (rc != UBP_OK) return rc;
+            if (!plan) {
+                p->choices[p->next_choice] = Choice{N, ldx, vec_ok, ysz, s};
+                p->next_choice = (p->next_choice + 1) % kChoices;
+            }
+        }
         switch (s.kernel) {
         case 1:
         case 3: rc = upload_values_f32(p); break;

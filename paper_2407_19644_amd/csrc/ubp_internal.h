@@ -266,6 +266,25 @@ struct TileArgs {
     Epilogue ep;
 };
 
+// What a call resolves to: the kernel and its launch shape, every field set.
+struct Shape {
+    int kernel = 0;   // 1 vector, 2 gather, 4 small-K dense tiles, 5 / 7 / 9 dense tiles through LDS, 6 block, 8 direct
+    int shape = 0;    // kernels 5, 7, 9: index into kMtileShapes
+    int G = 0, CT = 0, waves = 0, NP = 0, wg_rows = 0, rpr = 0;
+    bool resident = false;
+};
+
+// The last few calls without a plan that a handle chose a kernel for: the choice follows from the
+// handle and these four alone, and working it out again costs a call bound by the host 0.2 to 0.3 us.
+constexpr int kChoices = 4;
+struct Choice {
+    int32_t N = 0; // 0: unused (a product of no pixels chooses nothing)
+    int64_t ldx = 0;
+    bool vec_ok = false;
+    size_t ysz = 0;
+    Shape shape;
+};
+
 } // namespace ubp
 
 struct ubp_packed {
@@ -284,6 +303,8 @@ struct ubp_packed {
     mutable ubp::TileLayout tiles;
     mutable ubp::DirectLayout direct;
     mutable ubp::MaskStats stats;
+    mutable ubp::Choice choices[ubp::kChoices];
+    mutable int next_choice = 0;
     // device side
     int32_t *d_indptr = nullptr;
     int32_t *d_indices = nullptr;
