@@ -275,7 +275,7 @@ struct Shape {
 };
 
 // The last few calls without a plan that a handle chose a kernel for: the choice follows from the
-// handle and these four alone, and working it out again costs a call bound by the host 0.2 to 0.3 us.
+// handle and these four alone, and working it out again costs a call bound by the host about 0.2 us (7.43 -> 7.23).
 constexpr int kChoices = 4;
 struct Choice {
     int32_t N = 0; // 0: unused (a product of no pixels chooses nothing)
