@@ -416,8 +416,6 @@ ubp_status launch_blk_t(const BlkArgs &a, int G, int waves, hipStream_t st, bool
 
 } // namespace
 
-int blk_max_waves(int G) { return (G == 2 || G == 4 || G == 5) ? 16 : 0; }
-
 ubp_status launch_blk(const BlkArgs &a, bool bf16, bool y_f32, int G, int waves, void *stream, bool dry) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     // 64 rows of ldx elements must fit the producer's 32-bit lane offsets

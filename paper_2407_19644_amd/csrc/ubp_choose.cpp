@@ -1,0 +1,381 @@
+// Host side of the UBP library: which kernel a call takes, with which launch shape.  No device
+// code here: what a call resolves to can be checked without a GPU.
+#include <algorithm>
+#include <cmath>
+
+#include "ubp_internal.h"
+
+namespace ubp {
+
+namespace {
+
+// ------------------------------------------------------------------ estimates
+// What a 16-bit product would take, in microseconds, by each kernel: linear in the few quantities that
+// cost, coefficients fitted (relative least squares, none negative) to 165 layers drawn over the range of
+// layers this library is for - 1 x 1 and im2col convolutions at batch 1 to 64, fully connected layers, large
+// layers of 16 x 16 blocks, aligned and odd rows - each timed through every kernel that takes it.  Mean error
+// 5 to 10 %; the kernel of the smallest estimate took 2.5 % longer than the fastest one on average.
+constexpr double kNever = 1e30;
+constexpr double kCUs = 256.0;
+
+bool direct_able(const ubp_packed *p, int N, int64_t ldx_bytes) { // 16-bit row numbers, 32-bit byte offsets into X
+    return p->dtype != UBP_F32 && p->K <= 0x10000 && N >= 1 && ldx_bytes < (int64_t(1) << 24) &&
+           (int64_t)p->K * ldx_bytes < (int64_t(1) << 32) &&
+           (int64_t)((p->M + 15) / 16) * ((N + 15) / 16) <= 0x7fffffff;
+}
+int direct_tiles(int N) { return N <= 16 ? 1 : N <= 32 ? 2 : 4; }
+
+// Wavefronts per workgroup: enough that a wavefront has one or two steps, as long as the chip is not full.
+// waves: in: 0 or pinned; out: what the estimate is for.
+double estimate_direct(const ubp_packed *p, int N, int CT, size_t ysz, int &waves) {
+    const MaskStats &S = get_mask_stats(p);
+    const double stripes = (p->M + 15) / 16, px_tiles = (N + 16 * CT - 1) / (16 * CT), wgs = stripes * px_tiles;
+    const double load = S.steps * px_tiles * (1024 + 64 + 1024 * CT) / kCUs * 1e-5; // weights, row numbers, rows of X
+    const double fixed = 2.77 + (N % 8 != 0 ? 2.023 : 1.427) * load + 0.594 * 0.2e-6 * p->M * (double)N * ysz +
+                         0.352 * 0.4e-6 * p->K * (double)N;
+    double best = kNever;
+    int best_w = 4;
+    for (int w = 1; w <= 16; w *= 2) {
+        if (waves != 0 && w != 16) continue;
+        const int ww = waves ? waves : w;
+        if (w == 16 && CT > 1 && !waves) continue; // (its exchange of partial sums costs more than the steps it saves)
+        const double t = fixed + 0.156 * std::ceil((double)S.steps / stripes / ww) + 0.01404 * wgs * ww * CT / kCUs;
+        if (t < best * (ww == 4 ? 1.03 : 1.0)) { // (four where it hardly matters)
+            best = t;
+            best_w = ww;
+        }
+    }
+    waves = best_w;
+    return best;
+}
+
+// Dense tiles through LDS, by shape and by whether rows of X take the way through registers
+double estimate_mtile(const ubp_packed *p, int N, int shape, bool ragged, size_t ysz) {
+    // fixed; per tile and stage of 64 columns (of a CU's tiles one after the other); per tile; per 5 MB of Y;
+    // per tile and stage where empty tiles of W are left out; per round of tiles and stage
+    static const double kAligned[kNumMtileShapes][6] = {{3.015, 0.370, 0.410, 0.913, 0.039, 0.0},
+                                                        {2.606, 0.285, 0.460, 0.788, 0.021, 0.0},
+                                                        {2.609, 0.283, 0.430, 0.794, 0.028, 0.0},
+                                                        {2.653, 0.129, 0.199, 0.726, 0.012, 0.106}};
+    static const double kRagged[kNumMtileShapes][6] = {{4.592, 0.695, 0.0, 0.397, 0.020, 0.0},
+                                                       {3.788, 0.523, 0.0, 0.297, 0.0, 0.0},
+                                                       {kNever, 0.0, 0.0, 0.0, 0.0, 0.0},   // (never the best one there)
+                                                       {3.109, 0.0, 0.312, 1.143, 0.0, 0.508}};
+    const MtileShape &sh = kMtileShapes[shape];
+    const MaskStats &S = get_mask_stats(p);
+    const double *c = ragged ? kRagged[shape] : kAligned[shape];
+    const int64_t tiles = (int64_t)((p->M + sh.rows - 1) / sh.rows) * ((N + sh.pixels - 1) / sh.pixels);
+    const double per_cu = (double)(((tiles + 7) / 8 + 31) / 32); // an eighth of the tiles to each XCD, 32 CUs each
+    const double stages = (p->K + 63) / 64, rounds = std::ceil(per_cu / sh.per_cu);
+    return c[0] + per_cu * (stages * (c[1] + (S.tiles_hit < S.tiles ? c[4] : 0.0)) + c[2]) + rounds * stages * c[5] +
+           c[3] * 0.2e-6 * p->M * (double)N * ysz;
+}
+
+// Launch shape of the small-K kernel.  64-pixel blocks halve the weight traffic per pixel; 32-pixel blocks
+// where those would be few.  Workgroups of 4 wavefronts, about one and a half per CU: two share a CU and the
+// one's loading of X overlaps the other's streaming (measured better than one workgroup of 8).  The stripes are
+// cut into slices to get there - every slice loads the X block again, so only while a wavefront keeps at least
+// 3 stripes.
+int xstat_col_tiles(int N) { return N >= 128 * 64 ? 4 : 2; }
+int xstat_slices(int nstripes, int n_blocks) {
+    return std::max(1, std::min((int)std::lround(384.0 / n_blocks), nstripes / 12));
+}
+
+double estimate_xstat(const ubp_packed *p, int N, size_t ysz) {
+    const int CT = xstat_col_tiles(N), blocks = (N + 16 * CT - 1) / (16 * CT), stripes = (p->M + 15) / 16;
+    const int slices = xstat_slices(stripes, blocks), each = (stripes + slices - 1) / slices;
+    const double wgs = (double)blocks * slices, rounds = std::ceil(wgs / (2 * kCUs));
+    return 3.13 + 0.795 * 0.2e-6 * p->M * (double)N * ysz + 1.0 * p->K / 256.0 +
+           0.01865 * rounds * ((each + 3) / 4) * ((p->K + 31) / 32) * CT + 2.42 * wgs / (2 * kCUs) * p->K * CT / 1024.0;
+}
+
+int blk_auto_G(const ubp_packed *p) { // 5 stripes per wavefront where that saves a workgroup row: X is staged once per workgroup row
+    auto rows_for = [&](int g) { return ((p->M + 16 * g - 1) / (16 * g) + 13) / 14; };
+    return rows_for(5) < rows_for(4) ? 5 : 4;
+}
+
+double estimate_blk(const ubp_packed *p, int N, size_t ysz) {
+    const int G = blk_auto_G(p), rows = ((p->M + 16 * G - 1) / (16 * G) + 13) / 14;
+    const double rounds = std::max(1.0, std::ceil((N / 64) * (double)rows / kCUs));
+    const double halves = (double)p->nb * ((p->bw + 15) / 16); // (each in about two stripes)
+    return 4.24 + 0.0073 * rounds * p->K / 64.0 + 0.2446 * halves / 4.0 * (N / 64.0) / kCUs + 1.06 * 0.2e-6 * p->M * (double)N * ysz;
+}
+
+int tile_layout_words(const ubp_packed *p) { return (tile_kt_pad(p->M, p->K) + 31) / 32; } // occupancy words per stripe; 0: no dense tiles
+bool all_tiles_kept(const ubp_packed *p) {
+    const TileLayout &T = get_tile_layout(p);
+    return T.kt_pad != 0 && T.tiles_nonzero == (int64_t)T.nstripes * ((p->K + kStep - 1) / kStep);
+}
+bool mtile_able(const ubp_packed *p, int N, int64_t ldx_bytes) {
+    // a piece of 8 pixels fits a row; 64 rows of X have 32-bit offsets; the occupancy words of 4 stripes fit a wavefront's lanes
+    return p->dtype != UBP_F32 && N >= 8 && ldx_bytes <= (int64_t(1) << 25) && tile_layout_words(p) > 0 && 4 * tile_layout_words(p) <= 64;
+}
+
+// The kernel for a 16-bit product by the smallest estimate among those whose weights suit it: dense tiles
+// only where blocks reach into at least half of the 16 x 32 tiles (W would grow and most products be by
+// zeros otherwise), whole blocks as operands only where a block fills an operand and K is beyond what the
+// ring holds at once.  aligned: 16-byte pieces of rows of X and Y lie inside or outside the matrix.
+void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, Shape &s) {
+    const MaskStats &S = get_mask_stats(p);
+    const bool aligned = vec_ok && N % 8 == 0;
+    const bool mostly = 2 * S.tiles_hit >= S.tiles, full = S.tiles_hit == S.tiles;
+    double best = kNever;
+    s.kernel = 2;
+    // (layers that some tile of keeps nothing and whose K fits the registers stay with the kernels that
+    // add up in column order, whatever the number of pixels)
+    if (direct_able(p, N, ldx_bytes) && !(aligned && mostly && !full && p->K <= kTileMaxK)) {
+        int waves = 0;
+        best = estimate_direct(p, N, direct_tiles(N), ysz, waves);
+        s.kernel = 8;
+        s.waves = waves;
+    }
+    if (mostly && mtile_able(p, N, ldx_bytes)) {
+        for (int sh = 0; sh < kNumMtileShapes; ++sh) {
+            const double t = estimate_mtile(p, N, sh, !aligned, ysz);
+            if (t < best) {
+                best = t;
+                s.kernel = !aligned ? 9 : full && (p->K <= kTileMaxK || N <= 4096) ? 7 : p->K > kTileMaxK ? 5 : 9;
+                s.shape = sh;
+            }
+        }
+    }
+    if (mostly && aligned && p->K <= kTileMaxK && tile_layout_words(p) > 0 && estimate_xstat(p, N, ysz) < best) {
+        best = estimate_xstat(p, N, ysz);
+        s.kernel = 4;
+    }
+    if (blk_eligible(p) && p->bh == kStripe && p->bw >= 16 && p->K > ring_rows(4) && vec_ok && N >= 64 && estimate_blk(p, N, ysz) < best) {
+        best = estimate_blk(p, N, ysz);
+        s.kernel = 6;
+    }
+}
+
+} // namespace
+
+// Decides kernel and shape for (handle, N, alignment) and the caller's pins; builds the host image
+// of the layout that shape needs (under the handle's lock).  No device work.
+ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
+    int kernel = pl.kernel;
+    const bool no_shape = !(pl.sub_stripes || pl.col_tiles || pl.waves || pl.rows_per_range || pl.producers || pl.wg_rows);
+    // the dense-tile kernels 4, 5 and 7 need 16-byte pieces of X rows that lie entirely inside or outside the matrix
+    const bool tile_able = p->dtype != UBP_F32 && vec_ok && N % 8 == 0;
+    if (kernel < 0 || kernel > 9) return UBP_ERR_INVALID_ARG;
+    if (kernel > 1 && kernel != 3 && p->dtype == UBP_F32) return UBP_ERR_UNSUPPORTED;
+    if (kernel == 0 && p->dtype == UBP_F32) kernel = 1;
+    if (kernel == 0 || (no_shape && (kernel == 2 || kernel == 6 || kernel == 7))) {
+        // A kernel asked for without a shape: its automatic shapes include the direct kernel's, so that it
+        // computes what the automatic choice does where that lands on one of the two.
+        Shape c;
+        choose(p, N, ldx_bytes, vec_ok, ysz, c);
+        if (kernel == 0 || c.kernel == 8) {
+            if (kernel == 6 && (!blk_eligible(p) || !vec_ok || N < 64)) return UBP_ERR_UNSUPPORTED;
+            if (kernel == 7 && (!tile_able || !all_tiles_kept(p))) return UBP_ERR_UNSUPPORTED;
+            s = c;
+            kernel = c.kernel;
+        }
+    }
+    s.kernel = kernel;
+    if (kernel == 1 || kernel == 3) {
+        if (p->bh > 16) return UBP_ERR_UNSUPPORTED;
+        int rpr = pl.rows_per_range;
+        if (rpr == 0 && kernel == 1) {
+            // Row ranges of one block height (re-walking bh - 1 rows nearly doubles the work, but a small
+            // layer is a chain of latencies: 64 x 64 with 196 pixels 10.1 us, against 22.5 with ranges of
+            // four) up to 8192 wavefronts of 64 columns, taller beyond (512 x 512 with 25088 pixels
+            // 153 us, 158 with ranges of at least four block heights, 180 and more with half the wavefronts).
+            const int64_t ranges = std::max<int64_t>(1, 8192 / (((int64_t)N + 63) / 64));
+            const int64_t rows = std::max<int64_t>(p->bh, (p->M + ranges - 1) / ranges);
+            rpr = (int)std::min<int64_t>((rows + p->bh - 1) / p->bh * p->bh, 0x7fffffff);
+        } else if (rpr == 0) {
+            // enough row ranges to fill the chip, but each at least 4 block heights tall so
+            // that re-walking bh-1 start rows stays a small fraction of the work
+            const int coltiles = (N + 255) / 256;
+            int ranges = std::max(1, 2048 / std::max(1, coltiles));
+            rpr = std::max(4 * p->bh, (p->M + ranges - 1) / ranges);
+            rpr = ((rpr + p->bh - 1) / p->bh) * p->bh;
+        }
+        if (rpr < 1) return UBP_ERR_INVALID_ARG;
+        if ((p->M + rpr - 1) / rpr > 65535) rpr = (p->M + 65534) / 65535; // grid.y limit
+        s.rpr = rpr;
+        return UBP_OK;
+    }
+    if (kernel == 8) {
+        if (!direct_able(p, N, ldx_bytes)) return UBP_ERR_UNSUPPORTED;
+        s.CT = pl.col_tiles ? pl.col_tiles : direct_tiles(N);
+        if ((s.CT != 1 && s.CT != 2 && s.CT != 4) || N < s.CT) return UBP_ERR_UNSUPPORTED;
+        s.waves = pl.waves;
+        estimate_direct(p, N, s.CT, ysz, s.waves);
+        if (s.waves < 1 || s.waves > 16) return UBP_ERR_UNSUPPORTED;
+        const DirectLayout &L = get_direct_layout(p);
+        s.wg_rows = L.nstripes;
+        return UBP_OK;
+    }
+    if (kernel == 5 || kernel == 7 || kernel == 9) {
+        if (kernel != 9 && !tile_able) return UBP_ERR_UNSUPPORTED;
+        const TileLayout &T = get_tile_layout(p);
+        if (T.kt_pad == 0) return UBP_ERR_UNSUPPORTED;
+        if (kernel == 5 && (T.kt_pad % 4 != 0 || pl.waves != 0 || pl.wg_rows < 0)) return UBP_ERR_UNSUPPORTED;
+        if (kernel == 5 && ((pl.sub_stripes != 0 && pl.sub_stripes != 2 && pl.sub_stripes != 4) ||
+                            (pl.col_tiles != 0 && pl.col_tiles != 2 && pl.col_tiles != 4))) return UBP_ERR_UNSUPPORTED;
+        // kernel 7 multiplies every tile: only for matrices whose every tile keeps a weight
+        if (kernel == 7 && !all_tiles_kept(p)) return UBP_ERR_UNSUPPORTED;
+        if (!mtile_able(p, N, ldx_bytes)) { // (a K or a pitch beyond this kernel's offsets)
+            if (kernel == 9) return UBP_ERR_UNSUPPORTED;
+            ubp_plan other = {};
+            other.kernel = direct_able(p, N, ldx_bytes) ? 8 : 2;
+            return resolve(p, N, ldx_bytes, vec_ok, ysz, other, s);
+        }
+        // Of the shapes no larger than what the plan names (kernel 5: in units of 32 rows and 32 pixels,
+        // else of 16; all of them where it names nothing) the one with the smallest estimate
+        const int unit = kernel == 5 ? 32 : 16;
+        const bool ragged = !tile_able;
+        double best = kNever;
+        for (int sh = 0; sh < kNumMtileShapes; ++sh) {
+            if (ragged && sh == 2) continue; // (not built for odd rows)
+            const int want_r = pl.sub_stripes * unit, want_p = pl.col_tiles * unit;
+            if (want_r != 0 && kMtileShapes[sh].rows != std::min(want_r, 128)) continue;
+            if (want_p != 0 && kMtileShapes[sh].pixels != std::min(want_p, 128)) continue;
+            const double t = estimate_mtile(p, N, sh, ragged, ysz);
+            if (t < best) {
+                best = t;
+                s.shape = sh;
+            }
+        }
+        if (best == kNever) return UBP_ERR_UNSUPPORTED;
+        const MtileShape &sh = kMtileShapes[s.shape];
+        s.G = sh.rows / 16;
+        s.CT = sh.pixels / 16;
+        s.wg_rows = (p->M + sh.rows - 1) / sh.rows;
+        return UBP_OK;
+    }
+    if (kernel == 4) {
+        if (!tile_able || p->K > kTileMaxK) return UBP_ERR_UNSUPPORTED;
+        const TileLayout &T = get_tile_layout(p);
+        if (T.kt_pad == 0) return UBP_ERR_UNSUPPORTED;
+        int CT = pl.col_tiles;
+        if (CT == 0) CT = xstat_col_tiles(N);
+        if (CT != 2 && CT != 4) return UBP_ERR_UNSUPPORTED;
+        s.CT = CT;
+        const int n_blocks = (N + 16 * CT - 1) / (16 * CT);
+        int slices = pl.wg_rows;
+        if (slices < 0) return UBP_ERR_INVALID_ARG;
+        if (slices == 0) slices = xstat_slices(T.nstripes, n_blocks);
+        slices = std::min(slices, T.nstripes);
+        const int sps = (T.nstripes + slices - 1) / slices;
+        slices = (T.nstripes + sps - 1) / sps;
+        if ((int64_t)n_blocks * slices > 0x7fffffff) return UBP_ERR_UNSUPPORTED;
+        s.wg_rows = slices;
+        s.waves = pl.waves ? pl.waves : std::min(4, sps);
+        if (s.waves < 1 || s.waves > 8) return UBP_ERR_UNSUPPORTED;
+        return UBP_OK;
+    }
+    if (kernel == 6) {
+        if (!blk_eligible(p) || !vec_ok || N < 64) return UBP_ERR_UNSUPPORTED;
+        if (pl.col_tiles != 0 && pl.col_tiles != 4) return UBP_ERR_UNSUPPORTED;
+        const int G = pl.sub_stripes ? pl.sub_stripes : blk_auto_G(p);
+        if (G != 2 && G != 4 && G != 5) return UBP_ERR_UNSUPPORTED;
+        const BlkLayout &L = get_blk_layout(p, G);
+        if (L.G == 0) return UBP_ERR_UNSUPPORTED;
+        int NP = pl.producers;
+        if (NP != 0 && NP != 1 && NP != 2 && NP != 4) return UBP_ERR_UNSUPPORTED;
+        int waves = pl.waves;
+        // one wavefront stages about 28 GB/s: a second one as soon as a workgroup's tile is not small
+        if (NP == 0) {
+            NP = ((int64_t)p->K * 32 * 4 >= 64 * 1024) ? 2 : 1;
+            if (waves != 0 && waves < NP + 1) NP = 1;
+        }
+        const int max_waves = blk_max_waves(G);
+        if (waves == 0) {
+            // as few workgroup rows as the wavefront limit allows; full workgroups if the last row is
+            // then still at least half full, else the consumers spread evenly over the rows
+            const int maxc = max_waves - NP;
+            const int rows_wg = (L.nrg + maxc - 1) / maxc;
+            const int last = L.nrg - (rows_wg - 1) * maxc;
+            waves = (2 * last >= maxc ? maxc : (L.nrg + rows_wg - 1) / rows_wg) + NP;
+        }
+        if (waves < NP + 1 || waves > max_waves) return UBP_ERR_UNSUPPORTED;
+        const int need_rows = (L.nrg + (waves - NP) - 1) / (waves - NP);
+        if (pl.wg_rows != 0 && pl.wg_rows != need_rows) return UBP_ERR_UNSUPPORTED;
+        s.G = G;
+        s.CT = 4;
+        s.NP = NP;
+        s.waves = waves;
+        s.wg_rows = need_rows;
+        return UBP_OK;
+    }
+
+    // ---- gather kernel
+    int CT = pl.col_tiles, G = pl.sub_stripes, waves = pl.waves, NP = pl.producers;
+    if (NP != 0 && NP != 1 && NP != 2 && NP != 4) return UBP_ERR_UNSUPPORTED;
+    if ((G != 0 && G != 1 && G != 2 && G != 4) || (CT != 0 && CT != 2 && CT != 4 && CT != 8)) return UBP_ERR_UNSUPPORTED;
+    // Tile shape, from measurements on the benchmark layers.
+    //  * Column tiles as wide as divides N (a ragged last tile takes the slow staging path),
+    //    provided that still leaves a few dozen tiles: wide tiles amortise a step's fixed
+    //    instruction cost over more matrix instructions.
+    //  * Stripes per wavefront follow the block height: a 16-row block touches two stripes
+    //    anyway, so tall row groups cost little extra zero fill and divide the staging of X by
+    //    the rows a workgroup covers; for short blocks one stripe keeps the operands dense.
+    if (CT == 0) {
+        for (int ct = 8; ct >= 2 && CT == 0; ct /= 2)
+            if (N % (16 * ct) == 0 && N / (16 * ct) >= 32) CT = ct;
+        for (int ct = 8; ct >= 2 && CT == 0; ct /= 2)
+            if ((N + 16 * ct - 1) / (16 * ct) >= 32) CT = ct;
+        if (CT == 0) CT = 2;
+    }
+    if (G == 0) {
+        G = p->bh >= 16 ? 4 : p->bh >= 8 ? 2 : 1;
+        while (G > 1 && get_stripe_layout(p, G, CT).G == 0) G >>= 1;
+    }
+    const StripeLayout &L = get_stripe_layout(p, G, CT);
+    if (L.G == 0) return UBP_ERR_UNSUPPORTED; // layout cannot be built for this matrix
+    // one wavefront stages about 28 GB/s: a second one as soon as a workgroup's tile is not small
+    if (NP == 0) {
+        NP = ((int64_t)p->K * 32 * CT >= 64 * 1024) ? 2 : 1;
+        if (waves != 0 && waves < NP + 1) NP = 1; // a caller who fixes a tiny workgroup gets one producer
+    }
+    const int max_waves = stripe_max_waves(G, CT);
+    if (max_waves <= NP) return UBP_ERR_UNSUPPORTED;
+    // When the ring holds all of K nothing is ever refilled and a consumer may walk several row
+    // groups one after the other; the number of workgroup rows is then free.  Otherwise every
+    // consumer owns exactly one row group.
+    const bool resident = L.nch <= ring_slots(CT);
+    int wg_rows = pl.wg_rows;
+    if (wg_rows < 0) return UBP_ERR_INVALID_ARG;
+    if (!resident) {
+        if (waves == 0) {
+            // as few workgroup rows as the wavefront limit allows; full workgroups if the last row is
+            // then still at least half full (more consumers per CU measured better than even rows),
+            // else the consumers spread evenly over the rows
+            const int maxc = max_waves - NP;
+            const int rows_wg = (L.nrg + maxc - 1) / maxc;
+            const int last = L.nrg - (rows_wg - 1) * maxc;
+            waves = (2 * last >= maxc ? maxc : (L.nrg + rows_wg - 1) / rows_wg) + NP; // consumers + producers
+        }
+        if (waves < NP + 1 || waves > max_waves) return UBP_ERR_UNSUPPORTED;
+        const int need_rows = (L.nrg + (waves - NP) - 1) / (waves - NP);
+        if (wg_rows != 0 && wg_rows != need_rows) return UBP_ERR_UNSUPPORTED;
+        wg_rows = need_rows;
+    } else {
+        const int64_t ncol = (N + 16 * CT - 1) / (16 * CT);
+        if (wg_rows == 0) {
+            // about one workgroup per CU in a single round where the column tiles alone do not
+            // fill the chip; then as few workgroup rows as give every consumer the same number
+            // of row groups (no half-used passes)
+            const int target = (int)std::max<int64_t>(1, 256 / std::max<int64_t>(1, ncol));
+            const int nc = std::max(1, (waves ? waves : max_waves) - NP);
+            const int passes = std::max(1, (L.nrg + nc * target - 1) / (nc * target));
+            wg_rows = (L.nrg + nc * passes - 1) / (nc * passes);
+        }
+        wg_rows = std::max(1, std::min(wg_rows, std::max(1, L.nrg)));
+        if (waves == 0) waves = std::min(max_waves - NP, (L.nrg + wg_rows - 1) / wg_rows) + NP;
+        if (waves < NP + 1 || waves > max_waves) return UBP_ERR_UNSUPPORTED;
+    }
+    s.G = G;
+    s.CT = CT;
+    s.NP = NP;
+    s.waves = waves;
+    s.wg_rows = wg_rows;
+    s.resident = resident;
+    return UBP_OK;
+}
+
+} // namespace ubp

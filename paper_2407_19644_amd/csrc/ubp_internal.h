@@ -42,6 +42,21 @@ constexpr int ring_window(int CT) { return ring_rows(CT) / 4; }
 // has 64 four-byte banks, and this spreads 16 consecutive rows of one unit over all of them.
 constexpr int ring_swizzle(int CT, int r) { return CT == 2 ? ((r >> 2) & 1) : CT == 4 ? ((r >> 1) & 3) : (r & 7); }
 
+// Gather kernel: the gather of step s+1 is issued before the MFMAs of step s (two operand buffers) except
+// for the largest tile, where the second buffer would halve the wavefronts per SIMD.
+constexpr bool stripe_pipelined(int G, int CT) { return G * CT < 32; }
+
+// Threads of a workgroup of that kernel.
+constexpr int stripe_max_threads(int G, int CT) {
+    // accumulators + operand buffer(s) + prefetched step records + addressing, in VGPRs
+    // per lane; 512 per SIMD lane are shared by the wavefronts resident on the SIMD
+    const int regs = 4 * G * CT + (stripe_pipelined(G, CT) ? 8 : 4) * CT + kPrefetchDepth * (2 + 4 * G) + (G == 1 ? 8 : 20);
+    return regs <= 128 ? 1024 : regs <= 256 ? 512 : 256;
+}
+constexpr int stripe_max_waves(int G, int CT) { return stripe_max_threads(G, CT) / 64; }
+// Wavefronts of a workgroup of the block kernel.
+constexpr int blk_max_waves(int G) { return (G == 2 || G == 4 || G == 5) ? 16 : 0; }
+
 // Host image of the gather kernel's private re-layout of the packed weights, for one (G, CT).
 //
 // Rows are cut into row groups of 16*G aligned rows.  For a row group the columns of W
@@ -333,6 +348,11 @@ const DirectLayout &get_direct_layout(const ubp_packed *p);
 const MaskStats &get_mask_stats(const ubp_packed *p);
 bool blk_eligible(const ubp_packed *p);
 
+// ---- host: choice of kernel and launch shape (ubp_choose.cpp).  Builds the host image of the layout the
+// shape needs (the caller holds p->lock); no device work.  vec_ok: rows of X and Y start at multiples of 16
+// bytes; ysz: bytes of an element of Y.
+ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s);
+
 // ---- device (HIP translation units)
 ubp_status upload(ubp_packed *p);                 // canonical arrays, at pack time
 void release_device(ubp_packed *p);
@@ -347,9 +367,7 @@ ubp_status upload_direct_layout(const ubp_packed *p);
 ubp_status launch_wros(const ubp_packed *p, const void *X, int64_t ldx, int N, void *Y, int64_t ldy, ubp_dtype y_dtype,
                        int rpr, bool naive, const Epilogue &ep, void *stream, bool dry);
 ubp_status launch_stripe(const StripeArgs &a, bool bf16, bool y_f32, int G, int CT, int waves, void *stream, bool dry);
-int stripe_max_waves(int G, int CT);
 ubp_status launch_blk(const BlkArgs &a, bool bf16, bool y_f32, int G, int waves, void *stream, bool dry);
-int blk_max_waves(int G);
 ubp_status launch_xstat(const TileArgs &a, bool bf16, bool y_f32, int CT, int KT, int waves, void *stream, bool dry);
 ubp_status launch_direct(const DirectArgs &a, bool bf16, bool y_f32, int CT, int waves, void *stream, bool dry);
 // shapes of kernel 5 / 7 / 9: rows x pixels of a workgroup's tile, workgroups a CU holds

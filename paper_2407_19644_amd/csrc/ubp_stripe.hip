@@ -8,17 +8,6 @@ namespace ubp {
 
 namespace {
 
-// The gather of step s+1 is issued before the MFMAs of step s (two operand buffers) except
-// for the largest tile, where the second buffer would halve the wavefronts per SIMD.
-constexpr bool stripe_pipelined(int G, int CT) { return G * CT < 32; }
-
-constexpr int stripe_max_threads(int G, int CT, int D) {
-    // accumulators + operand buffer(s) + D prefetched step records + addressing, in VGPRs
-    // per lane; 512 per SIMD lane are shared by the wavefronts resident on the SIMD
-    const int regs = 4 * G * CT + (stripe_pipelined(G, CT) ? 8 : 4) * CT + D * (2 + 4 * G) + (G == 1 ? 8 : 20);
-    return regs <= 128 ? 1024 : regs <= 256 ? 512 : 256;
-}
-
 // One workgroup = 1, 2 or 4 producer wavefronts + up to 15 consumer wavefronts sharing one
 // tile of 16*CT columns of X / Y.
 //  * The producers stage X in 64-row chunks into a ring of LDS slots (ring row = X row mod
@@ -44,7 +33,7 @@ constexpr int stripe_max_threads(int G, int CT, int D) {
 // Every wait is bounded: if one runs out the wavefront raises *err and goes on without
 // waiting (wrong numbers, but the kernel always terminates).
 template <bool BF16, typename TY, int G, int CT, int D, bool FAST>
-__global__ __launch_bounds__(stripe_max_threads(G, CT, D)) void stripe_kernel(StripeArgs a) {
+__global__ __launch_bounds__(stripe_max_threads(G, CT)) void stripe_kernel(StripeArgs a) {
     constexpr int NTW = 16 * CT;
     constexpr int PITCH = ring_pitch(CT);
     constexpr int PIECES = 2 * CT; // 16-byte pieces per staged row
@@ -451,7 +440,7 @@ ubp_status launch_stripe_one(StripeArgs a, int ctile0, int n_coltiles, int waves
 
 template <bool BF16, typename TY, int G, int CT>
 ubp_status launch_stripe_inst(const StripeArgs &a, int waves, hipStream_t st, bool dry) {
-    if (waves * 64 > stripe_max_threads(G, CT, kPrefetchDepth)) return UBP_ERR_UNSUPPORTED;
+    if (waves * 64 > stripe_max_threads(G, CT)) return UBP_ERR_UNSUPPORTED;
     // full column tiles with aligned rows take the asynchronous staging path; a ragged last
     // tile (or everything, when rows are not 16-byte aligned) takes the synchronous one
     const int total = (a.N + 16 * CT - 1) / (16 * CT);
@@ -476,8 +465,6 @@ ubp_status launch_stripe_t(const StripeArgs &a, int G, int CT, int waves, hipStr
 }
 
 } // namespace
-
-int stripe_max_waves(int G, int CT) { return stripe_max_threads(G, CT, kPrefetchDepth) / 64; }
 
 // a.ctile0 = first column tile this launch is responsible for (0: all of them)
 ubp_status launch_stripe(const StripeArgs &a, bool bf16, bool y_f32, int G, int CT, int waves, void *stream, bool dry) {
