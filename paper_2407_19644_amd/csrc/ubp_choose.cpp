@@ -134,7 +134,9 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
             const double t = estimate_mtile(p, N, sh, !aligned, ysz);
             if (t < best) {
                 best = t;
-                s.kernel = !aligned ? 9 : full && (p->K <= kTileMaxK || N <= 4096) ? 7 : p->K > kTileMaxK ? 5 : 9;
+                // (7 is for matrices whose every tile holds a weight that is not zero: blocks that reach into every
+                // tile do not make one)
+                s.kernel = !aligned ? 9 : (p->K <= kTileMaxK || N <= 4096) && all_tiles_kept(p) ? 7 : p->K > kTileMaxK ? 5 : 9;
                 s.shape = sh;
             }
         }

@@ -1,0 +1,89 @@
+"""Which kernel a 16-bit product takes, with which launch shape: ubp_choose.cpp, compiled with the host
+compiler and called without a device."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2407_19644_amd as ubp
+from synthetic import make_weights, select_blocks
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2407_19644_amd", "csrc")
+OK, INVALID, UNSUPPORTED = 0, 1, 4
+
+DRIVER = r"""
+#include "ubp_internal.h"
+
+namespace ubp { // the device half of the library
+ubp_status upload(ubp_packed *) { return UBP_ERR_DEVICE; }
+void release_device(ubp_packed *) {}
+}
+
+extern "C" int choice(const ubp_packed *p, int N, int64_t ldx_bytes, int aligned, int ysz, const ubp_plan *pl, int *out) {
+    ubp::Shape s;
+    std::lock_guard<std::mutex> hold(p->lock);
+    const int rc = ubp::resolve(p, N, ldx_bytes, aligned != 0, (size_t)ysz, *pl, s);
+    const int f[8] = {s.kernel, s.shape, s.G, s.CT, s.waves, s.NP, s.wg_rows, s.rpr};
+    for (int i = 0; i < 8; ++i) out[i] = f[i];
+    return rc;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("needs g++")
+    d = tmp_path_factory.mktemp("choice")
+    (d / "driver.cpp").write_text(DRIVER)
+    so = d / "libchoice.so"
+    subprocess.check_call([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                           str(d / "driver.cpp")] + [os.path.join(CSRC, f) for f in ("ubp_host.cpp", "ubp_layouts.cpp", "ubp_choose.cpp")] +
+                          ["-o", str(so), "-pthread"])
+    return ctypes.CDLL(str(so))
+
+
+class Layer:
+    """A packed host-only handle of the driver's own copy of the host code."""
+
+    def __init__(self, lib, M, K, bh, bw, density, W=None, dtype="bf16", blocks=None):
+        self.lib, self.handle = lib, ctypes.c_void_p()
+        W = make_weights(M, K, 4, dtype) if W is None else W
+        b = np.ascontiguousarray(select_blocks(M, K, bh, bw, density, 3, "uniform", 1.1) if blocks is None else blocks, dtype=np.int32)
+        rc = lib.ubp_pack(W.ctypes.data_as(ctypes.c_void_p), {"f32": 0, "f16": 1, "bf16": 2}[dtype], M, K, ctypes.c_int64(K), bh, bw,
+                          b.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(len(b)), -1, ctypes.byref(self.handle))
+        assert rc == OK
+
+    def choice(self, N, aligned=None, ysz=2, ldx=None, **plan):
+        """(status, {field: value}) of a call on N pixels; plan fields by name."""
+        ldx = N if ldx is None else ldx
+        aligned = ldx % 8 == 0 if aligned is None else aligned
+        pl = ubp.Plan()
+        for k, v in plan.items():
+            setattr(pl, k, v)
+        out = (ctypes.c_int * 8)()
+        rc = self.lib.choice(self.handle, N, ctypes.c_int64(2 * ldx), int(aligned), ysz, ctypes.byref(pl), out)
+        return rc, dict(zip(("kernel", "shape", "G", "CT", "waves", "NP", "wg_rows", "rpr"), out))
+
+    def __del__(self):
+        self.lib.ubp_packed_free(self.handle)
+
+
+@pytest.mark.parametrize("M,K,N,bh,bw,density", [(960, 160, 3136, 4, 4, 0.3), (1024, 1024, 1568, 8, 1, 0.1), (64, 64, 4096, 4, 4, 0.6),
+                                                 (256, 2304, 12544, 4, 4, 0.25)])
+def test_kept_weights_that_are_all_zero_are_no_reason_to_refuse(lib, M, K, N, bh, bw, density):
+    """Blocks reach every 16 x 32 tile; the weights of one tile (or all weights) are zero: the automatic choice takes
+    the call, and not with the kernel that wants a weight in every tile."""
+    for zero in ((slice(0, 16), slice(0, 32)), (slice(None), slice(None)), (slice(M - 16, M), slice(K - 32, K))):
+        W = make_weights(M, K, 4, "bf16")
+        W[zero] = 0
+        layer = Layer(lib, M, K, bh, bw, density, W)
+        for n in (16, 200, N, N + 1):
+            for ysz in (2, 4):
+                rc, c = layer.choice(n, ysz=ysz)
+                assert rc == OK and c["kernel"] != 7, (n, ysz, c)

@@ -96,3 +96,24 @@ def test_vector_kernel_batches(shape):
         Y = run_spmm(W, "f32", bh, bw, blocks, X, "f32", plan)
         check(Y, Yref, Yabs, "f32", "f32")
         assert np.array_equal(Y, want)  # the same additions in the same order
+
+
+@pytest.mark.parametrize("shape", [(960, 160, 1568, 4, 4, 0.3), (1024, 1024, 1568, 8, 1, 0.1)], ids=lambda s: "x".join(map(str, s)))
+def test_blocks_in_every_tile_and_one_tile_of_zeros(shape):
+    """Kept weights may all be zero: the automatic choice computes the layer, prepared, plain and fused."""
+    M, K, N, bh, bw, d = shape
+    blocks = select_blocks(M, K, bh, bw, d, 8, "uniform", 1.1)
+    W = make_weights(M, K, 9, "f16")
+    W[:16, :32] = 0
+    X = make_activations(K, N, 10, "f16", "normal")
+    Yref, Yabs = oracle.spmm(decode_f64(W, "f16"), bh, bw, blocks, decode_f64(X, "f16"), want_abs=True)
+    p = ubp.pack(W, "f16", bh, bw, blocks, device=torch.cuda.current_device())
+    Xd = torch.from_numpy(X).cuda()
+    for tdt, y_dtype in ((torch.float16, "f16"), (torch.float32, "f32")):
+        Yd = torch.full((M, N), float("nan"), dtype=tdt, device="cuda")
+        assert ubp.spmm_prepare(p, Xd.data_ptr(), N, N, Yd.data_ptr(), N, y_dtype).kernel in (4, 5, 9)
+        check(run_spmm(W, "f16", bh, bw, blocks, X, y_dtype, packed=p), Yref, Yabs, "f16", y_dtype)
+        ubp.spmm_fused(p, Xd.data_ptr(), N, N, Yd.data_ptr(), N, y_dtype, None, "relu", 0.0, 0.0,
+                       torch.cuda.current_stream().cuda_stream)
+        check(Yd.cpu().numpy().astype(np.float64), np.maximum(Yref, 0), Yabs, "f16", y_dtype)
+    p.free()
