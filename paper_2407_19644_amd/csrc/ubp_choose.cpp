@@ -18,12 +18,16 @@ namespace {
 constexpr double kNever = 1e30;
 constexpr double kCUs = 256.0;
 
+int direct_tiles(int N) { return N <= 16 ? 1 : N <= 32 ? 2 : 4; }
+// A launch has fewer than 2^32 threads: workgroups (a multiple of 8) of `waves` wavefronts, one per 16 rows x 16 CT pixels.
+bool direct_fits(const ubp_packed *p, int N, int CT, int waves) {
+    const int64_t pairs = (int64_t)((p->M + 15) / 16) * (((int64_t)N + 16 * CT - 1) / (16 * CT));
+    return pairs <= 0x7fffffff && (pairs + 7) / 8 * 8 * waves * 64 < (int64_t(1) << 32);
+}
 bool direct_able(const ubp_packed *p, int N, int64_t ldx_bytes) { // 16-bit row numbers, 32-bit byte offsets into X
     return p->dtype != UBP_F32 && p->K <= 0x10000 && N >= 1 && ldx_bytes < (int64_t(1) << 24) &&
-           (int64_t)p->K * ldx_bytes < (int64_t(1) << 32) &&
-           (int64_t)((p->M + 15) / 16) * ((N + 15) / 16) <= 0x7fffffff;
+           (int64_t)p->K * ldx_bytes < (int64_t(1) << 32) && direct_fits(p, N, direct_tiles(N), 1);
 }
-int direct_tiles(int N) { return N <= 16 ? 1 : N <= 32 ? 2 : 4; }
 
 // Wavefronts per workgroup: enough that a wavefront has one or two steps, as long as the chip is not full.
 // waves: in: 0 or pinned; out: what the estimate is for.
@@ -39,6 +43,7 @@ double estimate_direct(const ubp_packed *p, int N, int CT, size_t ysz, int &wave
         if (waves != 0 && w != 16) continue;
         const int ww = waves ? waves : w;
         if (w == 16 && CT > 1 && !waves) continue; // (its exchange of partial sums costs more than the steps it saves)
+        if (!waves && !direct_fits(p, N, CT, w)) continue;
         const double t = fixed + 0.156 * std::ceil((double)S.steps / stripes / ww) + 0.01404 * wgs * ww * CT / kCUs;
         if (t < best * (ww == 4 ? 1.03 : 1.0)) { // (four where it hardly matters)
             best = t;
@@ -206,7 +211,7 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
         if ((s.CT != 1 && s.CT != 2 && s.CT != 4) || N < s.CT) return UBP_ERR_UNSUPPORTED;
         s.waves = pl.waves;
         estimate_direct(p, N, s.CT, ysz, s.waves);
-        if (s.waves < 1 || s.waves > 16) return UBP_ERR_UNSUPPORTED;
+        if (s.waves < 1 || s.waves > 16 || !direct_fits(p, N, s.CT, s.waves)) return UBP_ERR_UNSUPPORTED;
         const DirectLayout &L = get_direct_layout(p);
         s.wg_rows = L.nstripes;
         return UBP_OK;

@@ -87,3 +87,24 @@ def test_kept_weights_that_are_all_zero_are_no_reason_to_refuse(lib, M, K, N, bh
             for ysz in (2, 4):
                 rc, c = layer.choice(n, ysz=ysz)
                 assert rc == OK and c["kernel"] != 7, (n, ysz, c)
+
+
+@pytest.mark.parametrize("M,N", [(4096, 1 << 20), (65536, 1 << 17), (65536, 1 << 19), (65536, 1 << 21), (1 << 20, 1 << 14), (1 << 20, 1 << 17)])
+def test_direct_launches_have_fewer_than_2_to_the_32_threads(lib, M, N):
+    """Whatever kernel 8 is chosen or pinned with, its workgroups times their threads fit a launch; beyond that the automatic
+    choice takes another kernel and a pin is refused."""
+    layer = Layer(lib, M, 32, 4, 4, 0.002)
+
+    def threads(CT, waves):
+        pairs = -(-M // 16) * -(-N // (16 * CT))
+        return -(-pairs // 8) * 8 * waves * 64
+    rc, c = layer.choice(N)
+    assert rc == OK and c["kernel"] == (8 if threads(4, 1) < 2 ** 32 else 2)
+    assert c["kernel"] == 2 or threads(c["CT"], c["waves"]) < 2 ** 32
+    for CT in (0, 1, 2, 4):
+        for waves in (0, 1, 4, 16):
+            rc, c = layer.choice(N, kernel=8, col_tiles=CT, waves=waves)
+            able = threads(4, 1) < 2 ** 32      # (what kernel 8 takes at all, whatever is pinned)
+            fits = able and threads(CT or 4, waves or 1) < 2 ** 32
+            assert rc == (OK if fits else UNSUPPORTED), (CT, waves, c)
+            assert not fits or threads(c["CT"], c["waves"]) < 2 ** 32
