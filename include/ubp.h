@@ -154,10 +154,11 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                cut into, one workgroup per slice and pixel block; waves 1..8 share a slice's stripes).
  *                5, 7 and 9 are one kernel that stages both operands in LDS, in tiles of 128 or 64 rows x
  *                128 or 64 pixels of Y, K in stages of 64 columns (M x K as zero-filled tiles below 8 MB,
- *                K <= 16384, N >= 8).  5 and 7 need the alignment that 4 needs; 7 multiplies every operand
+ *                N >= 8).  5 and 7 need the alignment that 4 needs; 7 multiplies every operand
  *                tile and is only for matrices whose every tile keeps a weight; 5 leaves the empty ones
  *                out; 9 takes any N and alignment.  sub_stripes x col_tiles names the tile, in units of
- *                16 rows x 16 pixels (kernel 5: of 32, 2 or 4 each); sizes beyond 128 stand for 128.
+ *                16 rows x 16 pixels (kernel 5: of 32, 2 or 4 each); sizes beyond 128 stand for 128, and
+ *                where rows of X lie more than 32 MB apart it is 64 x 64 whatever 5 and 7 are given.
  *                6 = MFMA kernel with whole blocks as operands, stored by row modulo 16 - the
  *                paper's rotation with period 16 (f16 / bf16, bh <= 16, 16 <= K < 65408, N >= 64,
  *                16-byte aligned rows; col_tiles 4 only; sub_stripes 2, 4 or 5 = the most stripes a

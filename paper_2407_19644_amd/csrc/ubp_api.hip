@@ -341,7 +341,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         a.slices = s.wg_rows;
         a.sps = (T.nstripes + s.wg_rows - 1) / s.wg_rows;
         if (s.kernel == 4) return launch_xstat(a, bf16, y_f32, s.CT, T.kt_pad, s.waves, stream, dry);
-        return launch_mtile(a, bf16, y_f32, s.shape, !(vec_ok && N % 8 == 0), stream, dry);
+        return launch_mtile(a, bf16, y_f32, s.shape, s.rows, stream, dry);
     }
     case 8: {
         DirectArgs a = {};

@@ -111,10 +111,13 @@ bool all_tiles_kept(const ubp_packed *p) {
     const TileLayout &T = get_tile_layout(p);
     return T.kt_pad != 0 && T.tiles_nonzero == (int64_t)T.nstripes * ((p->K + kStep - 1) / kStep);
 }
-bool mtile_able(const ubp_packed *p, int N, int64_t ldx_bytes) {
-    // a piece of 8 pixels fits a row; 64 rows of X have 32-bit offsets; the occupancy words of 4 stripes fit a wavefront's lanes
-    return p->dtype != UBP_F32 && N >= 8 && ldx_bytes <= (int64_t(1) << 25) && tile_layout_words(p) > 0 && 4 * tile_layout_words(p) <= 64;
+bool mtile_able(const ubp_packed *p, int N) { // a piece of 8 pixels fits a row
+    return p->dtype != UBP_F32 && N >= 8 && tile_layout_words(p) > 0;
 }
+// The way rows of X take: 0 straight into LDS, 1 through registers (rows that are no 16-byte pieces), 2 through
+// registers with 64-bit offsets (rows more than 32 MB apart, of which 64 have no 32-bit offsets; tiles of 64 x 64 only).
+int mtile_rows(int N, int64_t ldx_bytes, bool vec_ok) { return ldx_bytes > (int64_t(1) << 25) ? 2 : !vec_ok || N % 8 != 0 ? 1 : 0; }
+bool mtile_has(int rows, int shape) { return rows == 0 || (rows == 1 && shape != 2) || shape == 3; }
 
 // The kernel for a 16-bit product by the smallest estimate among those whose weights suit it: dense tiles
 // only where blocks reach into at least half of the 16 x 32 tiles (W would grow and most products be by
@@ -134,9 +137,11 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
         s.kernel = 8;
         s.waves = waves;
     }
-    if (mostly && mtile_able(p, N, ldx_bytes)) {
+    if (mostly && mtile_able(p, N)) {
+        const int rows = mtile_rows(N, ldx_bytes, vec_ok);
         for (int sh = 0; sh < kNumMtileShapes; ++sh) {
-            const double t = estimate_mtile(p, N, sh, !aligned, ysz);
+            if (!mtile_has(rows, sh)) continue;
+            const double t = estimate_mtile(p, N, sh, rows != 0, ysz);
             if (t < best) {
                 best = t;
                 // (7 is for matrices whose every tile holds a weight that is not zero: blocks that reach into every
@@ -225,23 +230,20 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
                             (pl.col_tiles != 0 && pl.col_tiles != 2 && pl.col_tiles != 4))) return UBP_ERR_UNSUPPORTED;
         // kernel 7 multiplies every tile: only for matrices whose every tile keeps a weight
         if (kernel == 7 && !all_tiles_kept(p)) return UBP_ERR_UNSUPPORTED;
-        if (!mtile_able(p, N, ldx_bytes)) { // (a K or a pitch beyond this kernel's offsets)
-            if (kernel == 9) return UBP_ERR_UNSUPPORTED;
-            ubp_plan other = {};
-            other.kernel = direct_able(p, N, ldx_bytes) ? 8 : 2;
-            return resolve(p, N, ldx_bytes, vec_ok, ysz, other, s);
-        }
+        if (!mtile_able(p, N)) return UBP_ERR_UNSUPPORTED;
         // Of the shapes no larger than what the plan names (kernel 5: in units of 32 rows and 32 pixels,
-        // else of 16; all of them where it names nothing) the one with the smallest estimate
+        // else of 16; all of them where it names nothing) the one with the smallest estimate.  Kernels 5 and 7,
+        // which are for aligned rows and have all shapes there, serve rows more than 32 MB apart with the one that is left.
         const int unit = kernel == 5 ? 32 : 16;
-        const bool ragged = !tile_able;
+        const bool pinned = kernel == 9 || mtile_rows(N, ldx_bytes, vec_ok) == 0;
+        s.rows = mtile_rows(N, ldx_bytes, vec_ok);
         double best = kNever;
         for (int sh = 0; sh < kNumMtileShapes; ++sh) {
-            if (ragged && sh == 2) continue; // (not built for odd rows)
-            const int want_r = pl.sub_stripes * unit, want_p = pl.col_tiles * unit;
+            if (!mtile_has(s.rows, sh)) continue;
+            const int want_r = pinned ? pl.sub_stripes * unit : 0, want_p = pinned ? pl.col_tiles * unit : 0;
             if (want_r != 0 && kMtileShapes[sh].rows != std::min(want_r, 128)) continue;
             if (want_p != 0 && kMtileShapes[sh].pixels != std::min(want_p, 128)) continue;
-            const double t = estimate_mtile(p, N, sh, ragged, ysz);
+            const double t = estimate_mtile(p, N, sh, s.rows != 0, ysz);
             if (t < best) {
                 best = t;
                 s.shape = sh;

@@ -287,6 +287,7 @@ struct Shape {
     int shape = 0;    // kernels 5, 7, 9: index into kMtileShapes
     int G = 0, CT = 0, waves = 0, NP = 0, wg_rows = 0, rpr = 0;
     bool resident = false;
+    int rows = 0;        // kernels 5, 7, 9: the way rows of X take (mtile_rows)
 };
 
 // The last few calls without a plan that a handle chose a kernel for: the choice follows from the
@@ -374,7 +375,7 @@ ubp_status launch_direct(const DirectArgs &a, bool bf16, bool y_f32, int CT, int
 struct MtileShape { int rows, pixels, per_cu; };
 constexpr int kNumMtileShapes = 4;
 constexpr MtileShape kMtileShapes[kNumMtileShapes] = {{128, 128, 1}, {128, 64, 1}, {64, 128, 1}, {64, 64, 2}};
-ubp_status launch_mtile(const TileArgs &a, bool bf16, bool y_f32, int shape, bool ragged, void *stream, bool dry);
+ubp_status launch_mtile(const TileArgs &a, bool bf16, bool y_f32, int shape, int rows, void *stream, bool dry);
 ubp_status launch_floor(void *stream);
 
 } // namespace ubp

@@ -3,6 +3,7 @@
 #include "ubp_device.h"
 
 #include <cstdint>
+#include <type_traits>
 
 namespace ubp {
 
@@ -35,7 +36,9 @@ __device__ __forceinline__ uint4v shift_down(uint4v v, int n) {
 // staged X in chunks, and for full matrices both operands): 256 x 2304 with 6272 pixels 18.5 -> 14.4 us, with
 // 12544 20.3 -> 17.2; 1024 x 1024, every tile kept, with 1568 pixels and fp32 results 11.2 -> 8.6.
 // SKIP: W has empty 16 x 32 tiles, whose products are left out by a branch per stripe and step.
-template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, bool SKIP, bool RAG>
+// RAG: 0 rows of X are 16-byte pieces; 1 any alignment, through registers; 2 the same with 64-bit offsets, for
+// rows more than 32 MB apart (64-bit offsets for all odd rows took 2 % longer: 26.5 -> 27.1 us on 256 x 2304 with 6076 pixels).
+template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, bool SKIP, int RAG>
 __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs a) {
     constexpr int KS = 2;                                   // 32-column steps per stage
     constexpr int NC = WM * WN;                             // multiplying wavefronts; NPW more load
@@ -75,7 +78,9 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
         const uint32_t lane16 = (uint32_t)lane * 16u;
         struct Cursor { int tile = -1, st = 0; } cw, cx;   // the next stage whose W / X is requested
         const uint16_t *wsrc[PW];
-        uint32_t xoff[PX];   // byte offset of this lane's piece from the stage's first row
+        // byte offset of this lane's piece from the stage's first row
+        typedef typename std::conditional<RAG == 2, uint64_t, uint32_t>::type off_t;
+        off_t xoff[PX];
         int xcol[PX];        // its first pixel
         auto advance = [&](Cursor &c) { // returns whether the tile changed
             if (c.tile >= 0 && ++c.st < nst) return false;
@@ -105,14 +110,14 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
                 for (int q = 0; q < PX; ++q) {
                     const int r = (me + q * NL) * RPI + row_in;
                     xcol[q] = col0 + ((pp >> 1) ^ tile_swizzle<UNITS>(r)) * 16 + (pp & 1) * 8;
-                    xoff[q] = (uint32_t)(((int64_t)r * a.ldx + min(xcol[q], a.N - 8)) * 2);
+                    xoff[q] = (off_t)(((int64_t)r * a.ldx + min(xcol[q], a.N - 8)) * 2);
                 }
             }
         };
-        auto offset = [&](int q, bool whole) {
+        auto offset = [&](int q, bool whole) -> off_t {
             if (whole) return xoff[q];
             const int k0 = cx.st * (KS * 32), k = min(k0 + (me + q * NL) * RPI + row_in, a.K - 1);
-            return (uint32_t)(((int64_t)(k - k0) * a.ldx + min(xcol[q], a.N - 8)) * 2);
+            return (off_t)(((int64_t)(k - k0) * a.ldx + min(xcol[q], a.N - 8)) * 2);
         };
         uint32_t slot = 0;
         if (!rows) {
@@ -164,7 +169,7 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
                 const bool whole = (cx.st + 1) * (KS * 32) <= a.K;
 #pragma unroll
                 for (int q = 0; q < PX; ++q) {
-                    __builtin_memcpy(&v[q], src + (size_t)offset(q, whole), 16);
+                    __builtin_memcpy(&v[q], src + offset(q, whole), 16);
                     ov[q] = max(0, xcol[q] - (a.N - 8)) & 7;
                 }
             };
@@ -263,14 +268,17 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // SKIP: lane i * words + w holds word w of the occupancy bits (one per 32-column step) of my stripe i,
-    // fetched a tile ahead by a vector load (a scalar one would be waited for together with the LDS reads)
-    [[maybe_unused]] auto load_occ = [&](int t) -> uint32_t {
-        const int i = lane / words, s = ((tile0 + t0 + t * wg_step) % a.slices) * TS + wm * SM + i;
-        return i < SM ? a.occupied[(int64_t)min(s, a.nstripes - 1) * words + lane % words] : 0u;
+    // SKIP: lane OW i + w holds word w0 + w of the occupancy bits (one per 32-column step) of my stripe i,
+    // fetched a tile ahead by a vector load (a scalar one would be waited for together with the LDS reads);
+    // where K has more than OW words (K > 16384) the later ones are fetched when they are reached
+    constexpr int OW = 16;
+    static_assert(OW * SM <= 64, "a wavefront's occupancy words sit in one register");
+    [[maybe_unused]] auto load_occ = [&](int t, int w0) -> uint32_t {
+        const int i = lane / OW, w = w0 + lane % OW, s = ((tile0 + t0 + t * wg_step) % a.slices) * TS + wm * SM + i;
+        return i < SM && w < words ? a.occupied[(int64_t)min(s, a.nstripes - 1) * words + w] : 0u;
     };
     [[maybe_unused]] uint32_t occ_v = 0;
-    if constexpr (SKIP) occ_v = load_occ(0);
+    if constexpr (SKIP) occ_v = load_occ(0, 0);
     lds_barrier(); // stage 0 is there
 #pragma unroll
     for (int r = 0; r < NR; ++r) read_one(0, r, 0u, 0);
@@ -293,12 +301,19 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
 #pragma unroll
             for (int c = 0; c < PN; ++c) acc[i][c] = float4v{0.f, 0.f, 0.f, 0.f};
         [[maybe_unused]] uint32_t occ_next = 0;
-        if constexpr (SKIP) occ_next = load_occ(min(t + 1, n_tiles - 1));
+        if constexpr (SKIP) occ_next = load_occ(min(t + 1, n_tiles - 1), 0);
         for (int st = 0; st < nst; ++st, ++gs) {
             if constexpr (SKIP) {
                 if (((st * KS) & 31) == 0) {
+                    const int w = (st * KS) >> 5;
+                    if (w != 0 && w % OW == 0) {
+                        occ_v = load_occ(t, w); // (used in here too: no other path waits for it)
 #pragma unroll
-                    for (int i = 0; i < SM; ++i) occ[i] = (uint32_t)__builtin_amdgcn_readlane((int)occ_v, i * words + ((st * KS) >> 5));
+                        for (int i = 0; i < SM; ++i) occ[i] = (uint32_t)__builtin_amdgcn_readlane((int)occ_v, i * OW);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < SM; ++i) occ[i] = (uint32_t)__builtin_amdgcn_readlane((int)occ_v, i * OW + w % OW);
+                    }
                 }
             }
             step(0, st * KS, off, 1);
@@ -357,7 +372,7 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
     }
 }
 
-template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, bool SKIP, bool RAG>
+template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, bool SKIP, int RAG>
 ubp_status launch_one(const TileArgs &a, hipStream_t st, bool dry) {
     constexpr int TS = WM * SM, TN = 16 * WN * PN;
     constexpr size_t stage = (size_t)2 * (TS * 1024 + 32 * 2 * TN);
@@ -375,31 +390,34 @@ ubp_status launch_one(const TileArgs &a, hipStream_t st, bool dry) {
     return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
 }
 
-template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NPW, bool RAG>
+template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NPW, int RAG>
 ubp_status launch_shape(const TileArgs &a, hipStream_t st, bool dry) {
     return a.skip ? launch_one<BF16, TY, WM, WN, SM, PN, 4, NPW, true, RAG>(a, st, dry)
                   : launch_one<BF16, TY, WM, WN, SM, PN, 4, NPW, false, RAG>(a, st, dry);
 }
 
 template <bool BF16, typename TY>
-ubp_status launch_t(const TileArgs &a, int shape, bool ragged, hipStream_t st, bool dry) {
+ubp_status launch_t(const TileArgs &a, int shape, int rows, hipStream_t st, bool dry) {
     // (kMtileShapes)
+    if (rows == 2 && shape != 3) return UBP_ERR_UNSUPPORTED;
     switch (shape) {
-    case 0: return ragged ? launch_shape<BF16, TY, 2, 4, 4, 2, 8, true>(a, st, dry) : launch_shape<BF16, TY, 2, 4, 4, 2, 8, false>(a, st, dry);
-    case 1: return ragged ? launch_shape<BF16, TY, 4, 2, 2, 2, 4, true>(a, st, dry) : launch_shape<BF16, TY, 4, 2, 2, 2, 4, false>(a, st, dry);
-    case 2: return ragged ? UBP_ERR_UNSUPPORTED : launch_shape<BF16, TY, 2, 4, 2, 2, 4, false>(a, st, dry);
-    case 3: return ragged ? launch_shape<BF16, TY, 2, 2, 2, 2, 4, true>(a, st, dry) : launch_shape<BF16, TY, 2, 2, 2, 2, 4, false>(a, st, dry);
+    case 0: return rows == 1 ? launch_shape<BF16, TY, 2, 4, 4, 2, 8, 1>(a, st, dry) : launch_shape<BF16, TY, 2, 4, 4, 2, 8, 0>(a, st, dry);
+    case 1: return rows == 1 ? launch_shape<BF16, TY, 4, 2, 2, 2, 4, 1>(a, st, dry) : launch_shape<BF16, TY, 4, 2, 2, 2, 4, 0>(a, st, dry);
+    case 2: return rows == 1 ? UBP_ERR_UNSUPPORTED : launch_shape<BF16, TY, 2, 4, 2, 2, 4, 0>(a, st, dry);
+    case 3:
+        return rows == 2   ? launch_shape<BF16, TY, 2, 2, 2, 2, 4, 2>(a, st, dry)
+               : rows == 1 ? launch_shape<BF16, TY, 2, 2, 2, 2, 4, 1>(a, st, dry)
+                           : launch_shape<BF16, TY, 2, 2, 2, 2, 4, 0>(a, st, dry);
     }
     return UBP_ERR_UNSUPPORTED;
 }
 
 } // namespace
 
-ubp_status launch_mtile(const TileArgs &a, bool bf16, bool y_f32, int shape, bool ragged, void *stream, bool dry) {
+ubp_status launch_mtile(const TileArgs &a, bool bf16, bool y_f32, int shape, int rows, void *stream, bool dry) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (a.skip && 4 * ((a.kt_total + 31) / 32) > 64) return UBP_ERR_UNSUPPORTED; // a wavefront's occupancy words sit in one register
-    if (bf16) return y_f32 ? launch_t<true, float>(a, shape, ragged, st, dry) : launch_t<true, __bf16>(a, shape, ragged, st, dry);
-    return y_f32 ? launch_t<false, float>(a, shape, ragged, st, dry) : launch_t<false, _Float16>(a, shape, ragged, st, dry);
+    if (bf16) return y_f32 ? launch_t<true, float>(a, shape, rows, st, dry) : launch_t<true, __bf16>(a, shape, rows, st, dry);
+    return y_f32 ? launch_t<false, float>(a, shape, rows, st, dry) : launch_t<false, _Float16>(a, shape, rows, st, dry);
 }
 
 } // namespace ubp

@@ -108,3 +108,13 @@ def test_direct_launches_have_fewer_than_2_to_the_32_threads(lib, M, N):
             fits = able and threads(CT or 4, waves or 1) < 2 ** 32
             assert rc == (OK if fits else UNSUPPORTED), (CT, waves, c)
             assert not fits or threads(c["CT"], c["waves"]) < 2 ** 32
+
+
+def test_dense_tiles_at_any_k_and_pitch(lib):
+    """Pinned kernel 5 is kernel 5 wherever its tiles exist: a K of more occupancy words than a register holds, rows of X too
+    far apart for 32-bit offsets."""
+    layer = Layer(lib, 16, 20000, 4, 4, 0.05)
+    for ldx in (64, (1 << 24) + 8, 1 << 26):
+        for pins in ({}, dict(sub_stripes=2, col_tiles=4), dict(sub_stripes=4, wg_rows=3)):
+            rc, c = layer.choice(64, ldx=ldx, kernel=5, **pins)
+            assert rc == OK and c["kernel"] == 5, (ldx, pins, c)

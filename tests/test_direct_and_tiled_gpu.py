@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 import oracle                                    # noqa: E402
 import paper_2407_19644_amd as ubp               # noqa: E402
 from synthetic import decode_f64, make_activations, make_weights, select_blocks   # noqa: E402
-from gpu_util import check, run_spmm             # noqa: E402
+from gpu_util import check, run_spmm, to_device  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -68,11 +68,35 @@ def test_staged_tiles_at_any_alignment(shape, N):
         run_spmm(W, dtype, bh, bw, blocks, X[:, :7], dtype, _plan(kernel=9))
 
 
-def test_kernels_5_and_7_beyond_the_staged_tiles_columns():
-    """A K whose occupancy words do not fit a wavefront's lanes: pinned kernel 5 still computes."""
-    M, K, N, dtype = 16, 20000, 64, "bf16"
-    blocks, W, X, (Yref, Yabs) = _case(M, K, N, 4, 4, 0.05, dtype, seed=5)
-    check(run_spmm(W, dtype, 4, 4, blocks, X, "f32", _plan(kernel=5)), Yref, Yabs, dtype, "f32")
+@pytest.mark.parametrize("shape", [(16, 20000, 64, 0.05, 5), (64, 36000, 200, 0.02, 5), (16, 17000, 64, 0.45, 7)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_kernels_5_and_7_where_the_occupancy_words_pass_a_register(shape):
+    """K beyond 16384: a stripe has more than 16 words of occupancy bits.  The pinned kernel is the one that runs."""
+    M, K, N, d, kernel = shape
+    dtype = "bf16"
+    blocks, W, X, (Yref, Yabs) = _case(M, K, N, 4, 4, d, dtype, seed=5)
+    Xd = torch.empty(K, N, dtype=torch.bfloat16, device="cuda")
+    p = ubp.pack(W, dtype, 4, 4, blocks, device=torch.cuda.current_device())
+    for k in (kernel, 9):
+        plan = _plan(kernel=k, sub_stripes=4, col_tiles=4)
+        assert ubp.spmm_prepare(p, Xd.data_ptr(), N, N, Xd.data_ptr(), N, dtype, plan).kernel == k
+        check(run_spmm(W, dtype, 4, 4, blocks, X, "f32", plan, packed=p), Yref, Yabs, dtype, "f32")
+    p.free()
+
+
+def test_rows_of_x_more_than_32_mb_apart():
+    """64 rows have no 32-bit offsets then: kernels 5, 7 and 9 and the automatic choice, a last stage of fewer than 64 rows."""
+    M, K, N, dtype = 70, 100, 200, "bf16"
+    ldx = (1 << 24) + 8
+    blocks, W, X, (Yref, Yabs) = _case(M, K, N, 4, 4, 0.6, dtype, seed=21)
+    Xd = torch.empty(K * ldx, dtype=torch.bfloat16, device="cuda").view(K, ldx)
+    Xd[:, :N] = to_device(X, dtype)
+    p = ubp.pack(W, dtype, 4, 4, blocks, device=torch.cuda.current_device())
+    for plan in (_plan(kernel=7, sub_stripes=4, col_tiles=8), _plan(kernel=9), _plan(kernel=9, sub_stripes=4, col_tiles=4), None):
+        Yd = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        ubp.spmm(p, Xd.data_ptr(), ldx, N, Yd.data_ptr(), N, "f32", torch.cuda.current_stream().cuda_stream, plan)
+        check(Yd.cpu().numpy().astype(np.float64), Yref, Yabs, dtype, "f32")
+    p.free()
 
 
 VECTOR = [
