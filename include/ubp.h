@@ -169,7 +169,7 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                0 picks 1 for fp32, else the kernel with the smallest estimated time among 8; 4, 5, 7
  *                and 9 while at least half of the 16 x 32 tiles of W keep a weight; and 6 for 16-row blocks
  *                at least 16 wide when K > 1024; or 2 where none of these takes the call.  (3 is never
- *                picked.)  Kernels 2, 6 and 7 asked for without any other field resolve to 8 where 0 does.
+ *                picked.)  A kernel that is named is the one that runs, or the call is refused.
  *   sub_stripes: kernels 2 and 6, 16-row stripes per wavefront (1, 2 or 4; kernel 6: 2, 4 or 5,
  *                by itself 5 where that saves a workgroup row, else 4);
  *                kernels 5, 7 and 9: as above.

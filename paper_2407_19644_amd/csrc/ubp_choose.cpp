@@ -167,23 +167,14 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
 // of the layout that shape needs (under the handle's lock).  No device work.
 ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
     int kernel = pl.kernel;
-    const bool no_shape = !(pl.sub_stripes || pl.col_tiles || pl.waves || pl.rows_per_range || pl.producers || pl.wg_rows);
     // the dense-tile kernels 4, 5 and 7 need 16-byte pieces of X rows that lie entirely inside or outside the matrix
     const bool tile_able = p->dtype != UBP_F32 && vec_ok && N % 8 == 0;
     if (kernel < 0 || kernel > 9) return UBP_ERR_INVALID_ARG;
     if (kernel > 1 && kernel != 3 && p->dtype == UBP_F32) return UBP_ERR_UNSUPPORTED;
     if (kernel == 0 && p->dtype == UBP_F32) kernel = 1;
-    if (kernel == 0 || (no_shape && (kernel == 2 || kernel == 6 || kernel == 7))) {
-        // A kernel asked for without a shape: its automatic shapes include the direct kernel's, so that it
-        // computes what the automatic choice does where that lands on one of the two.
-        Shape c;
-        choose(p, N, ldx_bytes, vec_ok, ysz, c);
-        if (kernel == 0 || c.kernel == 8) {
-            if (kernel == 6 && (!blk_eligible(p) || !vec_ok || N < 64)) return UBP_ERR_UNSUPPORTED;
-            if (kernel == 7 && (!tile_able || !all_tiles_kept(p))) return UBP_ERR_UNSUPPORTED;
-            s = c;
-            kernel = c.kernel;
-        }
+    if (kernel == 0) {
+        choose(p, N, ldx_bytes, vec_ok, ysz, s);
+        kernel = s.kernel;
     }
     s.kernel = kernel;
     if (kernel == 1 || kernel == 3) {

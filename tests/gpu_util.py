@@ -23,6 +23,13 @@ def from_device(t, dtype):
     return t.numpy().astype(np.float64)
 
 
+def check_pin(packed, Xd, ldx, N, Yd, ldy, y_dtype, plan):
+    """A plan that names a kernel runs that kernel."""
+    if plan is not None and plan.kernel:
+        got = ubp.spmm_prepare(packed, Xd.data_ptr(), ldx, N, Yd.data_ptr(), ldy, y_dtype, plan)
+        assert got.kernel == plan.kernel, (got.kernel, plan.kernel)
+
+
 def run_spmm(W_enc, dtype, bh, bw, blocks, X_enc, y_dtype=None, plan=None, ldx=None, ldy=None, packed=None,
              prefill=float("nan")):
     """Y (float64 numpy, exact) computed by the HIP path; Y is pre-filled with NaN."""
@@ -38,6 +45,7 @@ def run_spmm(W_enc, dtype, bh, bw, blocks, X_enc, y_dtype=None, plan=None, ldx=N
     Xd[:, :N] = to_device(X_enc, dtype)
     Yd = torch.full((M, ldy), prefill, dtype=_TORCH[y_dtype], device="cuda")
     stream = torch.cuda.current_stream().cuda_stream
+    check_pin(packed, Xd, ldx, N, Yd, ldy, y_dtype, plan)
     ubp.spmm(packed, Xd.data_ptr(), ldx, N, Yd.data_ptr(), ldy, y_dtype, stream, plan)
     torch.cuda.synchronize()
     assert packed.device_error() == 0, "a bounded wait inside the kernel ran out"

@@ -118,3 +118,12 @@ def test_dense_tiles_at_any_k_and_pitch(lib):
         for pins in ({}, dict(sub_stripes=2, col_tiles=4), dict(sub_stripes=4, wg_rows=3)):
             rc, c = layer.choice(64, ldx=ldx, kernel=5, **pins)
             assert rc == OK and c["kernel"] == 5, (ldx, pins, c)
+
+
+def test_a_pinned_kernel_is_the_kernel_that_runs(lib):
+    """Kernels 2, 6 and 7 named without a shape, on layers where the automatic choice is another kernel."""
+    for M, K, bh, bw, d, N in ((160, 1100, 4, 4, 0.25, 256), (64, 64, 4, 4, 0.6, 128), (90, 1280, 16, 16, 0.15, 1280)):
+        layer = Layer(lib, M, K, bh, bw, d)
+        for kernel in (2, 6, 7, 8, 9):
+            rc, c = layer.choice(N, kernel=kernel)
+            assert rc == UNSUPPORTED and kernel == 7 and bh == 16 or rc == OK and c["kernel"] == kernel, (M, kernel, rc, c)
