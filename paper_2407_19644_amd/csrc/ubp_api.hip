@@ -337,7 +337,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         a.ep = ep;
         a.kt_total = T.kt_pad;
         a.skip = T.tiles_nonzero != (int64_t)T.nstripes * ((p->K + kStep - 1) / kStep) ? 1 : 0; // (padding tiles aside)
-        a.n_blocks = (N + 16 * s.CT - 1) / (16 * s.CT);
+        a.n_blocks = (N + 16 * s.CT - 1) / (16 * s.CT); // (kernel 4; the others count their own tiles)
         a.slices = s.wg_rows;
         a.sps = (T.nstripes + s.wg_rows - 1) / s.wg_rows;
         if (s.kernel == 4) return launch_xstat(a, bf16, y_f32, s.CT, T.kt_pad, s.waves, stream, dry);

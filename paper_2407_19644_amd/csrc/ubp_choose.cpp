@@ -242,8 +242,9 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
         }
         if (best == kNever) return UBP_ERR_UNSUPPORTED;
         const MtileShape &sh = kMtileShapes[s.shape];
-        s.G = sh.rows / 16;
-        s.CT = sh.pixels / 16;
+        s.G = sh.rows / unit;
+        s.CT = sh.pixels / unit;
+        s.waves = 0; // (fixed)
         s.wg_rows = (p->M + sh.rows - 1) / sh.rows;
         return UBP_OK;
     }

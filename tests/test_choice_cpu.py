@@ -127,3 +127,24 @@ def test_a_pinned_kernel_is_the_kernel_that_runs(lib):
         for kernel in (2, 6, 7, 8, 9):
             rc, c = layer.choice(N, kernel=kernel)
             assert rc == UNSUPPORTED and kernel == 7 and bh == 16 or rc == OK and c["kernel"] == kernel, (M, kernel, rc, c)
+
+
+FIELDS = ("sub_stripes", "col_tiles", "waves", "producers", "wg_rows")
+# what a call resolves to, as a plan: layers and calls that reach every kernel
+ROUND_TRIP = [(160, 1100, 4, 4, 0.25, (256, 4608, 4603)), (1024, 1024, 4, 4, 0.45, (1568, 16)), (256, 256, 8, 8, 0.12, (12544, 64)),
+              (90, 1280, 16, 16, 0.15, (1280,)), (40, 2100, 4, 4, 0.02, (64, 4096))]
+
+
+@pytest.mark.parametrize("case", ROUND_TRIP, ids=lambda c: "x".join(map(str, c[:4])))
+def test_the_chosen_plan_is_taken_back(lib, case):
+    """What a call resolves to, automatically or with a named kernel, given as the plan of the same call: the same kernel and shape."""
+    M, K, bh, bw, d, pixels = case
+    layer = Layer(lib, M, K, bh, bw, d)
+    for N in pixels:
+        for kernel in (0, 1, 2, 4, 5, 6, 7, 8, 9):
+            rc, c = layer.choice(N, kernel=kernel)
+            if rc != OK:
+                continue
+            back = dict(kernel=c["kernel"], sub_stripes=c["G"], col_tiles=c["CT"], waves=c["waves"], rows_per_range=c["rpr"],
+                        producers=c["NP"], wg_rows=c["wg_rows"])
+            assert layer.choice(N, **back) == (OK, c), (N, kernel, back)
