@@ -118,6 +118,16 @@ bool mtile_able(const ubp_packed *p, int N) { // a piece of 8 pixels fits a row
 // registers with 64-bit offsets (rows more than 32 MB apart, of which 64 have no 32-bit offsets; tiles of 64 x 64 only).
 int mtile_rows(int N, int64_t ldx_bytes, bool vec_ok) { return ldx_bytes > (int64_t(1) << 25) ? 2 : !vec_ok || N % 8 != 0 ? 1 : 0; }
 bool mtile_has(int rows, int shape) { return rows == 0 || (rows == 1 && shape != 2) || shape == 3; }
+// Tiles a plan may name, 0 for any size: kernel 5 in units of 32 rows x 32 pixels, 7 and 9 of 16 x 16.
+bool mtile_named(int kernel, int sub_stripes, int col_tiles) {
+    static const int kSeven[][2] = {{16, 16}, {8, 16}, {8, 8}, {16, 4}, {4, 8}, {4, 4}};
+    auto in = [](int v, int a, int b, int c) { return v == 0 || v == a || v == b || v == c; };
+    if (kernel == 5) return in(sub_stripes, 2, 4, 4) && in(col_tiles, 2, 4, 4);
+    if (kernel == 9) return in(sub_stripes, 4, 8, 16) && in(col_tiles, 4, 8, 16);
+    for (const int(&t)[2] : kSeven)
+        if ((sub_stripes == 0 || sub_stripes == t[0]) && (col_tiles == 0 || col_tiles == t[1])) return true;
+    return false;
+}
 
 // The kernel for a 16-bit product by the smallest estimate among those whose weights suit it: dense tiles
 // only where blocks reach into at least half of the 16 x 32 tiles (W would grow and most products be by
@@ -216,9 +226,9 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
         if (kernel != 9 && !tile_able) return UBP_ERR_UNSUPPORTED;
         const TileLayout &T = get_tile_layout(p);
         if (T.kt_pad == 0) return UBP_ERR_UNSUPPORTED;
-        if (kernel == 5 && (T.kt_pad % 4 != 0 || pl.waves != 0 || pl.wg_rows < 0)) return UBP_ERR_UNSUPPORTED;
-        if (kernel == 5 && ((pl.sub_stripes != 0 && pl.sub_stripes != 2 && pl.sub_stripes != 4) ||
-                            (pl.col_tiles != 0 && pl.col_tiles != 2 && pl.col_tiles != 4))) return UBP_ERR_UNSUPPORTED;
+        if (!mtile_named(kernel, pl.sub_stripes, pl.col_tiles)) return UBP_ERR_UNSUPPORTED;
+        if (kernel == 5 && (T.kt_pad % 4 != 0 || pl.waves != 0)) return UBP_ERR_UNSUPPORTED;
+        if (kernel == 5 && pl.wg_rows < 0) return UBP_ERR_INVALID_ARG;
         // kernel 7 multiplies every tile: only for matrices whose every tile keeps a weight
         if (kernel == 7 && !all_tiles_kept(p)) return UBP_ERR_UNSUPPORTED;
         if (!mtile_able(p, N)) return UBP_ERR_UNSUPPORTED;

@@ -148,3 +148,23 @@ def test_the_chosen_plan_is_taken_back(lib, case):
             back = dict(kernel=c["kernel"], sub_stripes=c["G"], col_tiles=c["CT"], waves=c["waves"], rows_per_range=c["rpr"],
                         producers=c["NP"], wg_rows=c["wg_rows"])
             assert layer.choice(N, **back) == (OK, c), (N, kernel, back)
+
+
+def test_tiles_that_kernels_5_7_and_9_take(lib):
+    """Kernel 7 takes the workgroup tiles it has always taken, kernel 5 stripes and tiles of 2 or 4, kernel 9 whole 64s up to 256;
+    a negative number of slices is an invalid argument; no size is too large to be refused."""
+    layer = Layer(lib, 160, 1100, 4, 4, 0.45)
+    sizes = (0, 1, 2, 3, 4, 5, 8, 12, 16, 17, 32, 100, 2 ** 27 + 8, 2 ** 31 - 1, -1, -8)
+    seven = {(16, 16), (8, 16), (8, 8), (16, 4), (4, 8), (4, 4)}
+    for G in sizes:
+        for CT in sizes:
+            want = {5: G in (0, 2, 4) and CT in (0, 2, 4), 9: G in (0, 4, 8, 16) and CT in (0, 4, 8, 16),
+                    7: any(G in (0, a) and CT in (0, b) for a, b in seven)}
+            for kernel, ok in want.items():
+                rc, c = layer.choice(512, kernel=kernel, sub_stripes=G, col_tiles=CT)
+                assert rc == (OK if ok else UNSUPPORTED), (kernel, G, CT, rc)
+                unit = 32 if kernel == 5 else 16
+                assert not ok or G == 0 or c["G"] == min(G, 128 // unit)
+                assert not ok or CT == 0 or c["CT"] == min(CT, 128 // unit)
+    assert layer.choice(512, kernel=5, wg_rows=-1)[0] == INVALID
+    assert layer.choice(512, kernel=5, wg_rows=3)[0] == OK and layer.choice(512, kernel=5, waves=4)[0] == UNSUPPORTED
