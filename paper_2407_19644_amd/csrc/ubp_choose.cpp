@@ -171,6 +171,15 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
     }
 }
 
+int kernel_by_matrix(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok) {
+    if (blk_eligible(p) && p->bh == kStripe && p->bw >= 16 && p->K > ring_rows(4) && vec_ok && N >= 64) return 6;
+    if (!vec_ok || N % 8 != 0 || tile_layout_words(p) == 0) return 2;
+    if (all_tiles_kept(p) && (p->K <= kTileMaxK || N <= 4096) && (int64_t)p->K * ldx_bytes < (int64_t(1) << 31)) return 7;
+    const TileLayout &T = get_tile_layout(p);
+    if (2 * T.tiles_nonzero < (int64_t)T.nstripes * ((p->K + kStep - 1) / kStep)) return 2;
+    return p->K <= kTileMaxK ? 4 : 5;
+}
+
 } // namespace
 
 // Decides kernel and shape for (handle, N, alignment) and the caller's pins; builds the host image
@@ -184,6 +193,19 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
     if (kernel == 0 && p->dtype == UBP_F32) kernel = 1;
     if (kernel == 0) {
         choose(p, N, ldx_bytes, vec_ok, ysz, s);
+        if (pl.sub_stripes || pl.col_tiles || pl.waves || pl.rows_per_range || pl.producers || pl.wg_rows) {
+            // Part of a shape is fixed: the automatic choice's kernel where it takes these fields, else the one
+            // that goes by the matrix alone, whose fields do not come and go with the number of pixels.
+            ubp_plan named = pl;
+            ubp_status rc = UBP_ERR_UNSUPPORTED;
+            for (int k : {s.kernel, kernel_by_matrix(p, N, ldx_bytes, vec_ok)}) {
+                named.kernel = k;
+                s = Shape();
+                rc = resolve(p, N, ldx_bytes, vec_ok, ysz, named, s);
+                if (rc == UBP_OK) break;
+            }
+            return rc;
+        }
         kernel = s.kernel;
     }
     s.kernel = kernel;

@@ -168,3 +168,35 @@ def test_tiles_that_kernels_5_7_and_9_take(lib):
                 assert not ok or CT == 0 or c["CT"] == min(CT, 128 // unit)
     assert layer.choice(512, kernel=5, wg_rows=-1)[0] == INVALID
     assert layer.choice(512, kernel=5, wg_rows=3)[0] == OK and layer.choice(512, kernel=5, waves=4)[0] == UNSUPPORTED
+
+
+def _kernel_by_matrix(layer, M, K, bh, bw, N, aligned, ldx):
+    """The kernel a plan of fields without a name has always meant: by the matrix and the alignment alone."""
+    tiles_kept, tiles = (layer.lib.ubp_packed_info(layer.handle, w) for w in (10, 11))
+    if bh == 16 and bw >= 16 and K > 1024 and aligned and N >= 64:
+        return 6
+    if not (aligned and N % 8 == 0) or tiles < 0:
+        return 2
+    if tiles_kept == tiles and (K <= 256 or N <= 4096) and K * ldx * 2 < 2 ** 31:
+        return 7
+    return 2 if 2 * tiles_kept < tiles else 4 if K <= 256 else 5
+
+
+@pytest.mark.parametrize("case", ROUND_TRIP + [(96, 200, 4, 4, 0.5, (392, 49)), (300, 300, 16, 16, 0.05, (8,))],
+                         ids=lambda c: "x".join(map(str, c[:4])))
+def test_fields_without_a_kernel(lib, case):
+    """A plan may fix part of a shape and leave the kernel open: what the automatic choice's kernel takes is taken by it, and
+    what the kernel that goes by the matrix alone takes stays accepted; nothing else is."""
+    M, K, bh, bw, d, pixels = case
+    layer = Layer(lib, M, K, bh, bw, d)
+    layer.lib.ubp_packed_info.restype = ctypes.c_int64
+    plans = [{f: v} for f in FIELDS for v in (-1, 1, 2, 3, 4, 5, 8, 12, 17)] + [dict(rows_per_range=8), dict(sub_stripes=2, col_tiles=8),
+             dict(sub_stripes=4, waves=6, producers=2), dict(col_tiles=2, waves=3, wg_rows=2), dict(col_tiles=4, waves=8)]
+    for N in pixels:
+        automatic = layer.choice(N)[1]["kernel"]
+        by_matrix = _kernel_by_matrix(layer, M, K, bh, bw, N, N % 8 == 0, N)
+        for plan in plans:
+            named = [layer.choice(N, kernel=k, **plan) for k in (automatic, by_matrix)]
+            rc, c = layer.choice(N, **plan)
+            taken = [n for n in named if n[0] == OK]
+            assert (rc, c) == taken[0] if taken else rc == named[1][0], (N, plan, rc, c, named)
