@@ -7,6 +7,8 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
+#include <stdexcept>
 #include <vector>
 
 #include "ubp_internal.h"
@@ -231,7 +233,7 @@ StripeArgs stripe_args(const ubp_packed *p, const Shape &s, const void *X, int64
 
 // The whole of ubp_spmm_plan / ubp_spmm_prepare.  dry: everything but the launch.
 ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t N, void *Y_dev, int64_t ldy, ubp_dtype y_dtype,
-                   void *stream, const ubp_plan *plan, bool dry, ubp_plan *chosen, const ubp_epilogue *fused) {
+                   void *stream, const ubp_plan *plan, bool dry, ubp_plan *chosen, const ubp_epilogue *fused) try {
     if (!p || N < 0) return UBP_ERR_INVALID_ARG;
     Epilogue ep = {nullptr, 0, 0.f, 0.f};
     if (fused) {
@@ -394,6 +396,10 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
     }
     }
     return UBP_ERR_INVALID_ARG;
+} catch (const std::bad_alloc &) { // (the widened weights of kernels 1 and 3, on the host)
+    return UBP_ERR_ALLOC;
+} catch (const std::length_error &) {
+    return UBP_ERR_ALLOC;
 }
 
 } // namespace

@@ -2,6 +2,8 @@
 // code here: what a call resolves to can be checked without a GPU.
 #include <algorithm>
 #include <cmath>
+#include <new>
+#include <stdexcept>
 
 #include "ubp_internal.h"
 
@@ -180,11 +182,7 @@ int kernel_by_matrix(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok)
     return p->K <= kTileMaxK ? 4 : 5;
 }
 
-} // namespace
-
-// Decides kernel and shape for (handle, N, alignment) and the caller's pins; builds the host image
-// of the layout that shape needs (under the handle's lock).  No device work.
-ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
+ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
     int kernel = pl.kernel;
     // the dense-tile kernels 4, 5 and 7 need 16-byte pieces of X rows that lie entirely inside or outside the matrix
     const bool tile_able = p->dtype != UBP_F32 && vec_ok && N % 8 == 0;
@@ -201,7 +199,7 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
             for (int k : {s.kernel, kernel_by_matrix(p, N, ldx_bytes, vec_ok)}) {
                 named.kernel = k;
                 s = Shape();
-                rc = resolve(p, N, ldx_bytes, vec_ok, ysz, named, s);
+                rc = decide(p, N, ldx_bytes, vec_ok, ysz, named, s);
                 if (rc == UBP_OK) break;
             }
             return rc;
@@ -409,6 +407,21 @@ ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, s
     s.wg_rows = wg_rows;
     s.resident = resident;
     return UBP_OK;
+}
+
+} // namespace
+
+// Decides kernel and shape for (handle, N, alignment) and the caller's pins; builds the host image
+// of the layout that shape needs (under the handle's lock).  No device work; a layout that does not
+// fit the host's memory is an error, not an exception that would pass the C boundary.
+ubp_status resolve(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
+    try {
+        return decide(p, N, ldx_bytes, vec_ok, ysz, pl, s);
+    } catch (const std::bad_alloc &) {
+        return UBP_ERR_ALLOC;
+    } catch (const std::length_error &) {
+        return UBP_ERR_ALLOC;
+    }
 }
 
 } // namespace ubp

@@ -6,6 +6,7 @@
 #include <cstring>
 #include <new>
 #include <numeric>
+#include <stdexcept>
 
 #include "ubp_internal.h"
 
@@ -254,7 +255,7 @@ const void *ubp_packed_values(const ubp_packed *p, int64_t *len_elems) {
     return p->values.data();
 }
 
-int64_t ubp_packed_info(const ubp_packed *p, int32_t what) {
+int64_t ubp_packed_info(const ubp_packed *p, int32_t what) try {
     if (!p) return -1;
     switch (what) {
     case 0: return p->M;
@@ -293,11 +294,15 @@ int64_t ubp_packed_info(const ubp_packed *p, int32_t what) {
         return item == 0 ? L.total_mfma : item == 1 ? L.nsteps : item == 2 ? L.halves : L.paired;
     }
     return -1;
+} catch (const std::bad_alloc &) {
+    return -1;
+} catch (const std::length_error &) {
+    return -1;
 }
 
 ubp_status ubp_packed_layout(const ubp_packed *p, int32_t sub_stripes, int32_t col_tiles, int32_t which,
                              int32_t *row_groups, const int32_t **rg_ptr, const int32_t **rg_order,
-                             const uint32_t **stream, int64_t *stream_words, const uint32_t **meta, int64_t *meta_words) {
+                             const uint32_t **stream, int64_t *stream_words, const uint32_t **meta, int64_t *meta_words) try {
     if (!p || which < 1 || which > 3) return UBP_ERR_INVALID_ARG;
     if (p->dtype == UBP_F32) return UBP_ERR_UNSUPPORTED;
     std::lock_guard<std::mutex> hold(p->lock);
@@ -340,6 +345,10 @@ ubp_status ubp_packed_layout(const ubp_packed *p, int32_t sub_stripes, int32_t c
     if (stream) *stream = L.stream.data();
     if (stream_words) *stream_words = (int64_t)L.stream.size();
     return UBP_OK;
+} catch (const std::bad_alloc &) {
+    return UBP_ERR_ALLOC;
+} catch (const std::length_error &) {
+    return UBP_ERR_ALLOC;
 }
 
 void ubp_packed_free(ubp_packed *p) {

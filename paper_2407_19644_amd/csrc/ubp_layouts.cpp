@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cstring>
 #include <numeric>
+#include <utility>
 
 #include "ubp_internal.h"
 
@@ -514,70 +515,74 @@ bool blk_eligible(const ubp_packed *p) {
     return p->dtype != UBP_F32 && p->bh <= kStripe && p->K >= 16 && (p->K + kSlotRows - 1) / kSlotRows < 1023;
 }
 
+namespace {
+
+// A layout becomes the handle's only when it is whole: an allocation that fails on the way leaves the handle as it was.
+template <class L, class Build> const L &built_once(L &slot, Build build) {
+    if (!slot.built) {
+        L fresh;
+        build(fresh);
+        fresh.built = true;
+        slot = std::move(fresh);
+    }
+    return slot;
+}
+
+// Counts stripe by stripe with one bit per column, so that memory follows K and time the blocks, not M x K.
+void count_mask(const ubp_packed *p, MaskStats &S) {
+    const int nstripes = (p->M + kStripe - 1) / kStripe, words = (p->K + 31) / 32;
+    S.tiles = (int64_t)nstripes * words;
+    std::vector<uint32_t> bits((size_t)words, 0u); // a word holds the columns of one 16 x 32 tile
+    std::vector<int32_t> hit;                      // its words that are not zero
+    for (int st = 0; st < nstripes; ++st) {
+        const int row0 = st * kStripe, row1 = std::min(p->M, row0 + kStripe);
+        for (int i = std::max(0, row0 - p->bh + 1); i < std::min(p->M - p->bh + 1, row1); ++i)
+            for (int32_t b = p->indptr[(size_t)i]; b < p->indptr[(size_t)i + 1]; ++b)
+                for (int k = p->indices[(size_t)b]; k < p->indices[(size_t)b] + p->bw; ++k) {
+                    uint32_t &w = bits[(size_t)k / 32];
+                    if (w == 0) hit.push_back(k / 32);
+                    w |= 1u << (k % 32);
+                }
+        int64_t cols = 0;
+        for (int32_t w : hit) {
+            cols += __builtin_popcount(bits[(size_t)w]);
+            bits[(size_t)w] = 0;
+        }
+        S.tiles_hit += (int64_t)hit.size();
+        S.steps += (cols + kStep - 1) / kStep;
+        hit.clear();
+    }
+}
+
+} // namespace
+
 const StripeLayout &get_stripe_layout(const ubp_packed *p, int G, int CT) {
-    StripeLayout &L = p->sg[layout_slot(G, CT)];
-    if (!L.built) {
-        L.built = true;
-        L.G = 0;
+    return built_once(p->sg[layout_slot(G, CT)], [&](StripeLayout &L) {
         // chunk indices are 16-bit in the records
         if (p->dtype != UBP_F32 && (p->K + kSlotRows - 1) / kSlotRows <= 0xffff) build_one(p, L, G, CT);
-    }
-    return L;
+    });
 }
 
 const BlkLayout &get_blk_layout(const ubp_packed *p, int G) {
-    BlkLayout &L = p->blk[blk_slot(G)];
-    if (!L.built) {
-        L.built = true;
-        L.G = 0;
+    return built_once(p->blk[blk_slot(G)], [&](BlkLayout &L) {
         if (blk_eligible(p)) build_blk(p, L, G);
-    }
-    return L;
+    });
 }
 
 const DirectLayout &get_direct_layout(const ubp_packed *p) {
-    DirectLayout &L = p->direct;
-    if (!L.built) {
-        L.built = true;
-        L.nstripes = 0;
+    return built_once(p->direct, [&](DirectLayout &L) {
         if (p->dtype != UBP_F32 && p->K <= 0x10000) build_direct(p, L); // row numbers are 16-bit in the records
-    }
-    return L;
+    });
 }
 
-// One bit per (stripe, column) with a kept weight: its words are the columns of one 16 x 32 tile each.
 const MaskStats &get_mask_stats(const ubp_packed *p) {
-    MaskStats &S = p->stats;
-    if (S.built) return S;
-    S.built = true;
-    const int nstripes = (p->M + kStripe - 1) / kStripe, words = (p->K + 31) / 32;
-    S.tiles = (int64_t)nstripes * words;
-    std::vector<uint32_t> bits((size_t)S.tiles, 0u);
-    for (int i = 0; i + p->bh <= p->M; ++i)
-        for (int32_t b = p->indptr[(size_t)i]; b < p->indptr[(size_t)i + 1]; ++b)
-            for (int st = i / kStripe; st <= (i + p->bh - 1) / kStripe; ++st)
-                for (int k = p->indices[(size_t)b]; k < p->indices[(size_t)b] + p->bw; ++k)
-                    bits[(size_t)st * words + k / 32] |= 1u << (k % 32);
-    for (int st = 0; st < nstripes; ++st) {
-        int64_t cols = 0;
-        for (int w = 0; w < words; ++w) {
-            const uint32_t v = bits[(size_t)st * words + w];
-            cols += __builtin_popcount(v);
-            S.tiles_hit += v != 0;
-        }
-        S.steps += (cols + kStep - 1) / kStep;
-    }
-    return S;
+    return built_once(p->stats, [&](MaskStats &S) { count_mask(p, S); });
 }
 
 const TileLayout &get_tile_layout(const ubp_packed *p) {
-    TileLayout &T = p->tiles;
-    if (!T.built) {
-        T.built = true;
-        T.kt_pad = 0;
+    return built_once(p->tiles, [&](TileLayout &T) {
         if (p->dtype != UBP_F32) build_tiles(p, T);
-    }
-    return T;
+    });
 }
 
 } // namespace ubp

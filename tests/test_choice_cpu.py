@@ -16,7 +16,41 @@ CSRC = os.path.join(ROOT, "paper_2407_19644_amd", "csrc")
 OK, INVALID, UNSUPPORTED = 0, 1, 4
 
 DRIVER = r"""
+#include <cstdlib>
+#include <new>
 #include "ubp_internal.h"
+
+// allocations left until one fails (< 0: none does), the bytes in use and their peak
+static long left_ = -1, now_ = 0, peak_ = 0;
+void *operator new(std::size_t n, const std::nothrow_t &) noexcept {
+    if (left_ == 0) return nullptr;
+    if (left_ > 0) --left_;
+    char *q = static_cast<char *>(std::malloc(n + 16));
+    if (!q) return nullptr;
+    *reinterpret_cast<std::size_t *>(q) = n;
+    now_ += (long)n;
+    if (now_ > peak_) peak_ = now_;
+    return q + 16;
+}
+void *operator new(std::size_t n) {
+    void *q = operator new(n, std::nothrow);
+    if (!q) throw std::bad_alloc();
+    return q;
+}
+void operator delete(void *q) noexcept {
+    if (!q) return;
+    char *b = static_cast<char *>(q) - 16;
+    now_ -= (long)*reinterpret_cast<std::size_t *>(b);
+    std::free(b);
+}
+void operator delete(void *q, std::size_t) noexcept { operator delete(q); }
+void operator delete(void *q, const std::nothrow_t &) noexcept { operator delete(q); }
+extern "C" void fail_after(long n) { left_ = n; }
+extern "C" long peak_bytes() { // since the last call
+    const long v = peak_ - now_;
+    peak_ = now_;
+    return v;
+}
 
 namespace ubp { // the device half of the library
 ubp_status upload(ubp_packed *) { return UBP_ERR_DEVICE; }
@@ -44,8 +78,11 @@ def lib(tmp_path_factory):
     so = d / "libchoice.so"
     subprocess.check_call([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                            str(d / "driver.cpp")] + [os.path.join(CSRC, f) for f in ("ubp_host.cpp", "ubp_layouts.cpp", "ubp_choose.cpp")] +
-                          ["-o", str(so), "-pthread"])
-    return ctypes.CDLL(str(so))
+                          ["-o", str(so), "-pthread", "-Wl,-Bsymbolic"])
+    lib = ctypes.CDLL(str(so))
+    lib.fail_after.argtypes, lib.peak_bytes.restype = [ctypes.c_long], ctypes.c_long
+    lib.ubp_packed_info.restype = ctypes.c_int64
+    return lib
 
 
 class Layer:
@@ -189,7 +226,6 @@ def test_fields_without_a_kernel(lib, case):
     what the kernel that goes by the matrix alone takes stays accepted; nothing else is."""
     M, K, bh, bw, d, pixels = case
     layer = Layer(lib, M, K, bh, bw, d)
-    layer.lib.ubp_packed_info.restype = ctypes.c_int64
     plans = [{f: v} for f in FIELDS for v in (-1, 1, 2, 3, 4, 5, 8, 12, 17)] + [dict(rows_per_range=8), dict(sub_stripes=2, col_tiles=8),
              dict(sub_stripes=4, waves=6, producers=2), dict(col_tiles=2, waves=3, wg_rows=2), dict(col_tiles=4, waves=8)]
     for N in pixels:
@@ -200,3 +236,47 @@ def test_fields_without_a_kernel(lib, case):
             rc, c = layer.choice(N, **plan)
             taken = [n for n in named if n[0] == OK]
             assert (rc, c) == taken[0] if taken else rc == named[1][0], (N, plan, rc, c, named)
+
+
+ALLOC = 6
+
+
+@pytest.mark.parametrize("M,K,bh,bw,density,N", [(160, 1100, 4, 4, 0.25, 256), (256, 256, 8, 8, 0.12, 12544), (90, 1280, 16, 16, 0.15, 1280),
+                                                 (40, 70000, 4, 4, 0.02, 64)])
+def test_an_allocation_that_fails_is_an_error_and_leaves_the_handle_whole(lib, M, K, bh, bw, density, N):
+    """One of the host allocations of a choice and of the layouts behind it fails, the first few and then every sixth or so: the call reports it, nothing is thrown, and the
+    same call afterwards resolves to what a fresh handle resolves to, with the same layouts."""
+    for kernel in (0, 2, 5, 6, 8):
+        fresh = Layer(lib, M, K, bh, bw, density)
+        want = fresh.choice(N, kernel=kernel)
+        n = 0
+        while True:
+            layer = Layer(lib, M, K, bh, bw, density)
+            lib.fail_after(n)
+            rc, _ = layer.choice(N, kernel=kernel)
+            lib.fail_after(-1)
+            assert rc in (want[0], ALLOC), (kernel, n, rc)
+            assert layer.choice(N, kernel=kernel) == want, (kernel, n)
+            if kernel == 2 and rc == ALLOC:
+                for what in (10, 11) + tuple(range(100, 109)) + tuple(range(200, 209)):
+                    assert lib.ubp_packed_info(layer.handle, what) == lib.ubp_packed_info(fresh.handle, what)
+            if rc == want[0]:
+                break
+            n += 1 + n // 6
+    layer = Layer(lib, M, K, bh, bw, density)
+    for what in (10, 100, 300):
+        lib.fail_after(0)
+        assert lib.ubp_packed_info(layer.handle, what) == -1
+        lib.fail_after(-1)
+        assert lib.ubp_packed_info(layer.handle, what) == lib.ubp_packed_info(fresh.handle, what)
+
+
+def test_a_choice_takes_no_memory_by_rows_times_columns(lib):
+    """A large sparse layer: choosing a kernel counts its blocks without a bitmap of the matrix (8 MB here, one bit a stripe and column)."""
+    M, K = 1 << 15, 1 << 15
+    W = np.zeros((M, K), np.uint16)     # (never touched: no memory behind it)
+    layer = Layer(lib, M, K, 4, 4, 0, W, blocks=[(8 * i, 4 * (i % 1000)) for i in range(1000)])
+    lib.peak_bytes()
+    rc, c = layer.choice(8, kernel=8)
+    assert rc == OK and c["kernel"] == 8
+    assert lib.peak_bytes() < 4 << 20
