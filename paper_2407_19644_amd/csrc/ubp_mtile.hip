@@ -16,6 +16,9 @@ template <int UNITS> __device__ __forceinline__ constexpr int tile_swizzle(int r
     return UNITS >= 8 ? (r & 7) : UNITS == 4 ? ((r >> 1) & 3) : UNITS == 2 ? ((r >> 2) & 1) : 0;
 }
 
+// Occupancy words (of 32 steps) per stripe that a register of a wavefront with 4 stripes holds: K up to 16384
+constexpr int kOccWords = 16;
+
 // 8 16-bit values moved down by n places (0 .. 7)
 __device__ __forceinline__ uint4v shift_down(uint4v v, int n) {
     if (n & 4) v = uint4v{v[2], v[3], 0u, 0u};
@@ -35,10 +38,12 @@ __device__ __forceinline__ uint4v shift_down(uint4v v, int n) {
 // instructions alone could do it in 0.22).  Against the kernels before this one (the multiplying wavefronts
 // staged X in chunks, and for full matrices both operands): 256 x 2304 with 6272 pixels 18.5 -> 14.4 us, with
 // 12544 20.3 -> 17.2; 1024 x 1024, every tile kept, with 1568 pixels and fp32 results 11.2 -> 8.6.
-// SKIP: W has empty 16 x 32 tiles, whose products are left out by a branch per stripe and step.
+// SKIP: W has empty 16 x 32 tiles, whose products are left out by a branch per stripe and step; 2 where K is
+// above 16384 (in an instantiation of its own: a fetch inside the loop made layers with
+// empty tiles 2 % slower, 256 x 2304 with 6272 pixels 14.4 -> 14.75 us).
 // RAG: 0 rows of X are 16-byte pieces; 1 any alignment, through registers; 2 the same with 64-bit offsets, for
 // rows more than 32 MB apart (64-bit offsets for all odd rows took 2 % longer: 26.5 -> 27.1 us on 256 x 2304 with 6076 pixels).
-template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, bool SKIP, int RAG>
+template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, int SKIP, int RAG>
 __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs a) {
     constexpr int KS = 2;                                   // 32-column steps per stage
     constexpr int NC = WM * WN;                             // multiplying wavefronts; NPW more load
@@ -268,13 +273,15 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // SKIP: lane OW i + w holds word w0 + w of the occupancy bits (one per 32-column step) of my stripe i,
-    // fetched a tile ahead by a vector load (a scalar one would be waited for together with the LDS reads);
-    // where K has more than OW words (K > 16384) the later ones are fetched when they are reached
-    constexpr int OW = 16;
-    static_assert(OW * SM <= 64, "a wavefront's occupancy words sit in one register");
+    // SKIP: lane ow i + w holds word w (SKIP 2: w0 + w) of the occupancy bits (one per 32-column step) of my
+    // stripe i, fetched a tile ahead by a vector load (a scalar one would be waited for together with the LDS
+    // reads); SKIP 2: the words behind the first ow are fetched when they are reached
+    [[maybe_unused]] const int ow = SKIP == 2 ? kOccWords : words;
+    static_assert(kOccWords * SM <= 64, "a wavefront's occupancy words sit in one register");
     [[maybe_unused]] auto load_occ = [&](int t, int w0) -> uint32_t {
-        const int i = lane / OW, w = w0 + lane % OW, s = ((tile0 + t0 + t * wg_step) % a.slices) * TS + wm * SM + i;
+        const int i = lane / ow, s = ((tile0 + t0 + t * wg_step) % a.slices) * TS + wm * SM + i;
+        if constexpr (SKIP != 2) return i < SM ? a.occupied[(int64_t)min(s, a.nstripes - 1) * words + lane % words] : 0u;
+        const int w = w0 + lane % ow;
         return i < SM && w < words ? a.occupied[(int64_t)min(s, a.nstripes - 1) * words + w] : 0u;
     };
     [[maybe_unused]] uint32_t occ_v = 0;
@@ -306,13 +313,13 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
             if constexpr (SKIP) {
                 if (((st * KS) & 31) == 0) {
                     const int w = (st * KS) >> 5;
-                    if (w != 0 && w % OW == 0) {
+                    if (SKIP == 2 && w != 0 && w % ow == 0) {
                         occ_v = load_occ(t, w); // (used in here too: no other path waits for it)
 #pragma unroll
-                        for (int i = 0; i < SM; ++i) occ[i] = (uint32_t)__builtin_amdgcn_readlane((int)occ_v, i * OW);
+                        for (int i = 0; i < SM; ++i) occ[i] = (uint32_t)__builtin_amdgcn_readlane((int)occ_v, i * ow);
                     } else {
 #pragma unroll
-                        for (int i = 0; i < SM; ++i) occ[i] = (uint32_t)__builtin_amdgcn_readlane((int)occ_v, i * OW + w % OW);
+                        for (int i = 0; i < SM; ++i) occ[i] = (uint32_t)__builtin_amdgcn_readlane((int)occ_v, i * ow + (SKIP == 2 ? w % ow : w));
                     }
                 }
             }
@@ -372,7 +379,7 @@ __global__ __launch_bounds__((WM * WN + NPW) * 64, 2) void mtile_kernel(TileArgs
     }
 }
 
-template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, bool SKIP, int RAG>
+template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NS, int NPW, int SKIP, int RAG>
 ubp_status launch_one(const TileArgs &a, hipStream_t st, bool dry) {
     constexpr int TS = WM * SM, TN = 16 * WN * PN;
     constexpr size_t stage = (size_t)2 * (TS * 1024 + 32 * 2 * TN);
@@ -392,8 +399,9 @@ ubp_status launch_one(const TileArgs &a, hipStream_t st, bool dry) {
 
 template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NPW, int RAG>
 ubp_status launch_shape(const TileArgs &a, hipStream_t st, bool dry) {
-    return a.skip ? launch_one<BF16, TY, WM, WN, SM, PN, 4, NPW, true, RAG>(a, st, dry)
-                  : launch_one<BF16, TY, WM, WN, SM, PN, 4, NPW, false, RAG>(a, st, dry);
+    if (!a.skip) return launch_one<BF16, TY, WM, WN, SM, PN, 4, NPW, 0, RAG>(a, st, dry);
+    return a.kt_total <= 32 * kOccWords ? launch_one<BF16, TY, WM, WN, SM, PN, 4, NPW, 1, RAG>(a, st, dry)
+                             : launch_one<BF16, TY, WM, WN, SM, PN, 4, NPW, 2, RAG>(a, st, dry);
 }
 
 template <bool BF16, typename TY>
