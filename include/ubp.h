@@ -180,8 +180,7 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                as above.
  *   waves      : wavefronts per workgroup (kernels 2 and 6: producers + 1 .. 16, fewer for shapes
  *                that need many registers; kernels 4 and 8 as above).
- *   rows_per_range : kernels 1 and 3, output rows owned by one wavefront (kernel 1) or workgroup row
- *                (kernel 3); a multiple of bh.
+ *   rows_per_range : kernels 1 and 3, output rows owned by one wavefront; a multiple of bh.
  *   producers  : kernels 2 and 6, wavefronts of a workgroup that stage X into LDS (1, 2 or 4);
  *                the others each own a row group.
  *   wg_rows    : kernels 2 and 6, workgroups that share one column tile (each takes a share of

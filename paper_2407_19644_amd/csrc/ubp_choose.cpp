@@ -210,7 +210,7 @@ ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, si
     if (kernel == 1 || kernel == 3) {
         if (p->bh > 16) return UBP_ERR_UNSUPPORTED;
         int rpr = pl.rows_per_range;
-        if (rpr == 0 && kernel == 1) {
+        if (rpr == 0) {
             // Row ranges of one block height (re-walking bh - 1 rows nearly doubles the work, but a small
             // layer is a chain of latencies: 64 x 64 with 196 pixels 10.1 us, against 22.5 with ranges of
             // four) up to 8192 wavefronts of 64 columns, taller beyond (512 x 512 with 25088 pixels
@@ -218,13 +218,6 @@ ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, si
             const int64_t ranges = std::max<int64_t>(1, 8192 / (((int64_t)N + 63) / 64));
             const int64_t rows = std::max<int64_t>(p->bh, (p->M + ranges - 1) / ranges);
             rpr = (int)std::min<int64_t>((rows + p->bh - 1) / p->bh * p->bh, 0x7fffffff);
-        } else if (rpr == 0) {
-            // enough row ranges to fill the chip, but each at least 4 block heights tall so
-            // that re-walking bh-1 start rows stays a small fraction of the work
-            const int coltiles = (N + 255) / 256;
-            int ranges = std::max(1, 2048 / std::max(1, coltiles));
-            rpr = std::max(4 * p->bh, (p->M + ranges - 1) / ranges);
-            rpr = ((rpr + p->bh - 1) / p->bh) * p->bh;
         }
         if (rpr < 1) return UBP_ERR_INVALID_ARG;
         if ((p->M + rpr - 1) / rpr > 65535) rpr = (p->M + 65534) / 65535; // grid.y limit

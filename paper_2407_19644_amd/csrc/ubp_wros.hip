@@ -20,17 +20,23 @@ namespace {
 // those blocks add to rows it does not own.
 //   The stream is taken U columns at a time, and the U rows of X of the next batch are loaded
 // before the current one is multiplied, over the ends of start rows too: otherwise every column
-// waits for its index and then for its row of X.  512 x 512 in 4 x 1 blocks at 20 % with 6272 pixels:
-// 187 -> 46 us, 64 x 64 with 196 pixels 22 -> 10, 512 x 512 with 49 pixels 95 -> 20.  What bounds
+// waits for its index and then for its row of X.  fp32, a call among others: 512 x 512 in 4 x 1 blocks at 20 %
+// with 6272 pixels 187 -> 53 us, 64 x 64 with 196 pixels 22 -> 10, 512 x 512 with 49 pixels 95 -> 20.  What bounds
 // the large ones is reading rows of X again from L2 for every start row (11 TB/s).
 // 64 columns of all of X in LDS instead, shared by 16 wavefronts, took longer: 62 us for 6272 pixels,
 // 258 for 25088 (161 from L2) - scalar loads of weights and reads of LDS share one counter.
 //   indptr: blocks per start row; cols: row of X per column of the stream, followed by
 // kWrosBatch spare entries (row 0), which may be loaded and are never multiplied.
-template <typename TX, typename TY, int BH, int VEC>
-__global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ indptr, const int32_t *__restrict__ cols,
-                                                  const float *__restrict__ vals, const TX *__restrict__ X, int64_t ldx,
-                                                  TY *__restrict__ Y, int64_t ldy, int M, int N, int bw, int rpr, Epilogue ep) {
+//   SHIFT: the dataflow that the weight rotation replaces (Section 3.3), for comparison only.  Accumulator
+// row t always belongs to the output row t below the current start row: after a start row, row 0 is stored
+// and the others move up by one register row.  Everything else is the same - grid, ranges, loads, batches
+// and the order of additions per output element; a weight is read from the rotated array at the slot its row
+// has there.  2 x 1, 4 x 1 and 8 x 1 blocks (256 x 256 with 25088 pixels, 512 x 512 with 6272, 1024 x 1024 with
+// 1568, f16): 82, 51 and 64 us, with SHIFT 88, 57 and 76.
+template <typename TX, typename TY, int BH, int VEC, bool SHIFT>
+__device__ __forceinline__ void vector_walk(const int32_t *__restrict__ indptr, const int32_t *__restrict__ cols,
+                                            const float *__restrict__ vals, const TX *__restrict__ X, int64_t ldx,
+                                            TY *__restrict__ Y, int64_t ldy, int M, int N, int bw, int rpr, Epilogue ep) {
     constexpr int U = BH <= 4 ? 8 : BH <= 8 ? 4 : 2; // (a batch's weights fit the scalar registers)
     static_assert(U <= kWrosBatch, "spare entries of cols");
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -50,15 +56,17 @@ __global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ i
 #pragma unroll
         for (int u = 0; u < U; ++u) load_row<TX, VEC>(X + (int64_t)cols[t + u] * ldx + col, x[u]);
     };
+    const int first = max(0, lo - BH + 1);
+    int slot = first % BH; // of the current start row
     auto multiply = [&](const float *__restrict__ w, const float(&x)[VEC]) {
 #pragma unroll
-        for (int s = 0; s < BH; ++s)
+        for (int s = 0; s < BH; ++s) {
+            const float ws = w[!SHIFT ? s : slot + s >= BH ? slot + s - BH : slot + s];
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[s][v] = fmaf(w[s], x[v], acc[s][v]);
+            for (int v = 0; v < VEC; ++v) acc[s][v] = fmaf(ws, x[v], acc[s][v]);
+        }
     };
 
-    const int first = max(0, lo - BH + 1);
-    int slot = first % BH;
     int64_t t = 0;
     float x[U][VEC];
     if (first <= last_start) {
@@ -91,7 +99,7 @@ __global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ i
         }
 #pragma unroll
         for (int s = 0; s < BH; ++s) {
-            if (s != slot) continue;
+            if (s != (SHIFT ? 0 : slot)) continue;
             if (i >= lo) {
                 if (ep.on) {
                     const float b = ep.bias ? ep.bias[i] : 0.f;
@@ -103,65 +111,30 @@ __global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ i
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[s][v] = 0.f;
         }
+        if constexpr (SHIFT) {
+#pragma unroll
+            for (int s = 0; s + 1 < BH; ++s)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[s][v] = acc[s + 1][v];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[BH - 1][v] = 0.f;
+        }
         slot = slot + 1 == BH ? 0 : slot + 1;
     }
 }
 
-// ------------------------------------------------------------------ naive dataflow (comparison only)
-// The dataflow the weight rotation replaces (Section 3.3): accumulator row t always belongs to
-// the output row t below the current start row.  After start row i is done, row 0 is stored, rows
-// 1 .. BH-1 move up by one register row and the last one is cleared.  Same grid, same ranges, same
-// loads and the same order of additions per output element as wros_kernel; the weights are read
-// from the rotated array at the slot their row has there.
 template <typename TX, typename TY, int BH, int VEC>
-__global__ __launch_bounds__(256) void naive_kernel(const int32_t *__restrict__ indptr, const int32_t *__restrict__ indices,
+__global__ __launch_bounds__(256) void wros_kernel(const int32_t *__restrict__ indptr, const int32_t *__restrict__ cols,
+                                                  const float *__restrict__ vals, const TX *__restrict__ X, int64_t ldx,
+                                                  TY *__restrict__ Y, int64_t ldy, int M, int N, int bw, int rpr, Epilogue ep) {
+    vector_walk<TX, TY, BH, VEC, false>(indptr, cols, vals, X, ldx, Y, ldy, M, N, bw, rpr, ep);
+}
+
+template <typename TX, typename TY, int BH, int VEC>
+__global__ __launch_bounds__(256) void naive_kernel(const int32_t *__restrict__ indptr, const int32_t *__restrict__ cols,
                                                    const float *__restrict__ vals, const TX *__restrict__ X, int64_t ldx,
                                                    TY *__restrict__ Y, int64_t ldy, int M, int N, int bw, int rpr, Epilogue ep) {
-    const int col = (blockIdx.x * 256 + threadIdx.x) * VEC;
-    if (col >= N) return;
-    const int lo = blockIdx.y * rpr;
-    const int hi = min(lo + rpr, M);
-    const int last_start = M - BH;
-    float acc[BH][VEC];
-#pragma unroll
-    for (int t = 0; t < BH; ++t)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[t][v] = 0.f;
-
-    for (int i = max(0, lo - BH + 1); i < hi; ++i) {
-        if (i <= last_start) {
-            const int u = i % BH; // slot of the block's first row in the rotated array
-            const int b1 = indptr[i + 1];
-            for (int b = indptr[i]; b < b1; ++b) {
-                const int c = indices[b];
-                const float *w = vals + (int64_t)b * bw * BH;
-                for (int q = 0; q < bw; ++q) {
-                    float x[VEC];
-                    load_row<TX, VEC>(X + (int64_t)(c + q) * ldx + col, x);
-#pragma unroll
-                    for (int t = 0; t < BH; ++t) {
-                        const float wt = w[q * BH + (u + t >= BH ? u + t - BH : u + t)];
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) acc[t][v] = fmaf(wt, x[v], acc[t][v]);
-                    }
-                }
-            }
-        }
-        if (i >= lo) {
-            if (ep.on) {
-                const float b = ep.bias ? ep.bias[i] : 0.f;
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[0][v] = epilogue_value(ep, acc[0][v], b);
-            }
-            store_row<TY, VEC>(Y + (int64_t)i * ldy + col, acc[0]);
-        }
-#pragma unroll
-        for (int t = 0; t + 1 < BH; ++t)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[t][v] = acc[t + 1][v];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[BH - 1][v] = 0.f;
-    }
+    vector_walk<TX, TY, BH, VEC, true>(indptr, cols, vals, X, ldx, Y, ldy, M, N, bw, rpr, ep);
 }
 
 template <typename TX, typename TY, int VEC>
@@ -170,17 +143,11 @@ ubp_status launch_wros_bh(const ubp_packed *p, const void *X, int64_t ldx, int N
     const int64_t ranges = ((int64_t)p->M + rpr - 1) / rpr, tiles = ((int64_t)N + 64 * VEC - 1) / (64 * VEC);
     const unsigned waves = tiles > (1 << 22) ? 1u : (unsigned)std::min<int64_t>(4, ranges); // (grid size in threads: 32 bits)
     const dim3 grid((unsigned)((tiles + 7) / 8 * 8), (unsigned)((ranges + waves - 1) / waves));
-    const dim3 naive_grid((unsigned)((N + 256 * VEC - 1) / (256 * VEC)), (unsigned)ranges);
 #define UBP_WROS_CASE(BH)                                                                                              \
     case BH:                                                                                                           \
-        if (naive)                                                                                                     \
-            hipLaunchKernelGGL((naive_kernel<TX, TY, BH, VEC>), naive_grid, dim3(256), 0, st, p->d_indptr, p->d_indices, \
-                               p->d_values_f32, static_cast<const TX *>(X), ldx, static_cast<TY *>(Y), ldy, p->M, N,    \
-                               p->bw, rpr, ep);                                                                        \
-        else                                                                                                           \
-            hipLaunchKernelGGL((wros_kernel<TX, TY, BH, VEC>), grid, dim3(waves * 64), 0, st, p->d_indptr, p->d_cols,   \
-                               p->d_values_f32, static_cast<const TX *>(X), ldx, static_cast<TY *>(Y), ldy, p->M, N,    \
-                               p->bw, rpr, ep);                                                                        \
+        hipLaunchKernelGGL((naive ? (naive_kernel<TX, TY, BH, VEC>) : (wros_kernel<TX, TY, BH, VEC>)), grid,            \
+                           dim3(waves * 64), 0, st, p->d_indptr, p->d_cols, p->d_values_f32,                           \
+                           static_cast<const TX *>(X), ldx, static_cast<TY *>(Y), ldy, p->M, N, p->bw, rpr, ep);       \
         break;
     switch (p->bh) {
         UBP_WROS_CASE(1) UBP_WROS_CASE(2) UBP_WROS_CASE(3) UBP_WROS_CASE(4) UBP_WROS_CASE(5) UBP_WROS_CASE(6)
@@ -202,7 +169,7 @@ ubp_status launch_wros_t(const ubp_packed *p, const void *X, int64_t ldx, int N,
                         (reinterpret_cast<uintptr_t>(X) % (4 * sizeof(TX)) == 0) &&
                         (reinterpret_cast<uintptr_t>(Y) % (4 * sizeof(TY)) == 0);
     const int64_t waves4 = ((int64_t)N + 255) / 256 * (((int64_t)p->M + rpr - 1) / rpr);
-    const bool vec = vec_ok && (naive ? N >= 2048 : waves4 >= 1000);
+    const bool vec = vec_ok && waves4 >= 1000;
     return vec ? launch_wros_bh<TX, TY, 4>(p, X, ldx, N, Y, ldy, rpr, naive, ep, st)
                : launch_wros_bh<TX, TY, 1>(p, X, ldx, N, Y, ldy, rpr, naive, ep, st);
 }

@@ -280,3 +280,12 @@ def test_a_choice_takes_no_memory_by_rows_times_columns(lib):
     rc, c = layer.choice(8, kernel=8)
     assert rc == OK and c["kernel"] == 8
     assert lib.peak_bytes() < 4 << 20
+
+
+def test_the_two_vector_dataflows_walk_the_same_ranges(lib):
+    """Kernel 3 is there to be timed beside kernel 1: the same row ranges, whatever the layer and the pixels."""
+    for M, K, bh, bw, d in ((512, 512, 4, 1, 0.2), (64, 64, 4, 4, 0.5), (1024, 1024, 8, 1, 0.1), (257, 31, 1, 1, 0.3)):
+        layer = Layer(lib, M, K, bh, bw, d, dtype="f16")
+        for N in (1, 49, 196, 1568, 6272, 25088):
+            (rc1, a), (rc3, b) = layer.choice(N, kernel=1), layer.choice(N, kernel=3)
+            assert rc1 == rc3 == OK and a["rpr"] == b["rpr"] > 0, (M, N, a, b)
