@@ -101,11 +101,16 @@ int blk_auto_G(const ubp_packed *p) { // 5 stripes per wavefront where that save
     return rows_for(5) < rows_for(4) ? 5 : 4;
 }
 
+// Whole blocks as operands: per round of workgroups the staging of X and a wavefront's share of the steps (two halves of
+// 16 columns each); behind them, where the last columns are no whole tile of 64, a launch of the gather kernel for those.
 double estimate_blk(const ubp_packed *p, int N, size_t ysz) {
-    const int G = blk_auto_G(p), rows = ((p->M + 16 * G - 1) / (16 * G) + 13) / 14;
-    const double rounds = std::max(1.0, std::ceil((N / 64) * (double)rows / kCUs));
-    const double halves = (double)p->nb * ((p->bw + 15) / 16); // (each in about two stripes)
-    return 4.24 + 0.0073 * rounds * p->K / 64.0 + 0.2446 * halves / 4.0 * (N / 64.0) / kCUs + 1.06 * 0.2e-6 * p->M * (double)N * ysz;
+    const int G = blk_auto_G(p), stripes = (p->M + 15) / 16;
+    const int rows = ((stripes + G - 1) / G + kBlkConsumers - 1) / kBlkConsumers; // of workgroups
+    const double runs = std::min(stripes, rows * kBlkConsumers), stage = 1e-3 * p->K * 4 / 2;
+    const double steps = 0.5 * (double)p->nb * ((p->bw + 15) / 16);
+    const double rounds = std::ceil((N / 64 + 7) / 8 * (double)rows / 32);
+    return 5.213 + rounds * (0.289 + 1.907 * stage + 0.4327 * steps / runs) + 0.757 * 0.2e-6 * p->M * (double)N * ysz +
+           (N % 64 != 0 ? 17.59 + 15.19 * stage : 0.0);
 }
 
 int tile_layout_words(const ubp_packed *p) { return (tile_kt_pad(p->M, p->K) + 31) / 32; } // occupancy words per stripe; 0: no dense tiles

@@ -55,6 +55,7 @@ constexpr int stripe_max_threads(int G, int CT) {
 }
 constexpr int stripe_max_waves(int G, int CT) { return stripe_max_threads(G, CT) / 64; }
 // Wavefronts of a workgroup of the block kernel.
+constexpr int kBlkConsumers = 14; // of them multiplying, at most
 constexpr int blk_max_waves(int G) { return (G == 2 || G == 4 || G == 5) ? 16 : 0; }
 
 // Host image of the gather kernel's private re-layout of the packed weights, for one (G, CT).

@@ -307,7 +307,6 @@ struct Half {
 // and the others long ones.  The number of runs is the smallest possible, rounded up to a whole
 // number of workgroup rows of kBlkConsumers wavefronts (the spare runs cost nothing there); the
 // cut minimises the sum of cubed costs.  first[g] = first stripe of run g, first[runs] = nstripes.
-constexpr int kBlkConsumers = 14;
 
 std::vector<int32_t> cut_row_groups(const ubp_packed *p, int G) {
     const int M = p->M, bh = p->bh;

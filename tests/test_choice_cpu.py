@@ -289,3 +289,17 @@ def test_the_two_vector_dataflows_walk_the_same_ranges(lib):
         for N in (1, 49, 196, 1568, 6272, 25088):
             (rc1, a), (rc3, b) = layer.choice(N, kernel=1), layer.choice(N, kernel=3)
             assert rc1 == rc3 == OK and a["rpr"] == b["rpr"] > 0, (M, N, a, b)
+
+
+# M, K, bh, bw, density, {pixels: kernel}
+WEIGHED = [(1656, 2080, 16, 16, 0.06, {800: 8, 64: 8}), (4096, 4096, 16, 16, 0.1, {8192: 6, 16: 8})]
+
+
+@pytest.mark.parametrize("case", WEIGHED, ids=lambda c: "x".join(map(str, c[:4])))
+def test_every_kernel_is_weighed(lib, case):
+    """Whole blocks as operands only where there are workgroups enough and no launch for a last ragged tile behind them."""
+    M, K, bh, bw, d, want = case
+    layer = Layer(lib, M, K, bh, bw, d)
+    for N, kernel in want.items():
+        rc, c = layer.choice(N)
+        assert rc == OK and c["kernel"] == kernel, (N, c)

@@ -162,8 +162,9 @@ AUTOMATIC = [  # M, K, N, bh, bw, density, dtype, the kernel ubp_spmm picks
     (512, 512, 6275, 4, 4, 0.45, "bf16", 9),        # odd rows
     (1024, 256, 12544, 8, 8, 0.12, "f16", 4),       # some tiles empty, most not, a small K
     (160, 1100, 256, 4, 4, 0.01, "bf16", 8),        # most tiles empty
-    (256, 4608, 2048, 16, 16, 0.1, "bf16", 6),      # 72 chunks of X against a ring of 16
+    (256, 4608, 12288, 16, 16, 0.1, "bf16", 6),     # 72 chunks of X against a ring of 16
     (64, 64, 196, 4, 4, 0.5, "f32", 1),
+    (1656, 2080, 800, 16, 16, 0.06, "f16", 8),      # whole blocks, but few workgroups and a ragged last tile
 ]
 
 
