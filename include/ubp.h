@@ -167,10 +167,10 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                8 = MFMA kernel without LDS staging: the wavefronts of a workgroup split the nonempty
  *                columns of one 16-row stripe and read X straight into registers (f16 / bf16, K <= 65536,
  *                any N >= col_tiles, any alignment; col_tiles 1, 2 or 4; waves 1 .. 16).
- *                0 picks 1 for fp32, else the kernel with the smallest estimated time among 8; 4, 5, 7
- *                and 9 while at least half of the 16 x 32 tiles of W keep a weight; and 6 for 16-row blocks
- *                at least 16 wide when K > 1024; or 2 where none of these takes the call.  (3 is never
- *                picked.)  A kernel that is named is the one that runs, or the call is refused.  0 with
+ *                0 picks 1 for fp32, else the kernel with the smallest estimated time among 8; 2 on aligned
+ *                rows; 4, 5, 7 and 9 while at least half of the 16 x 32 tiles of W keep a weight; and 6 for
+ *                16-row blocks at least 16 wide when K > 1024; or 2 where none of these takes the call.  (3 is
+ *                never picked.)  A kernel that is named is the one that runs, or the call is refused.  0 with
  *                other fields set: that kernel if it takes them, else the one the matrix alone gives (6 for
  *                16-row blocks as above; on aligned rows 7, 4 or 5 by how many tiles keep a weight; 2).
  *   sub_stripes: kernels 2 and 6, 16-row stripes per wavefront (1, 2 or 4; kernel 6: 2, 4 or 5,

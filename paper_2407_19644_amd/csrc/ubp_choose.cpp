@@ -13,10 +13,11 @@ namespace {
 
 // ------------------------------------------------------------------ estimates
 // What a 16-bit product would take, in microseconds, by each kernel: linear in the few quantities that
-// cost, coefficients fitted (relative least squares, none negative) to 165 layers drawn over the range of
-// layers this library is for - 1 x 1 and im2col convolutions at batch 1 to 64, fully connected layers, large
-// layers of 16 x 16 blocks, aligned and odd rows - each timed through every kernel that takes it.  Mean error
-// 5 to 10 %; the kernel of the smallest estimate took 2.5 % longer than the fastest one on average.
+// cost, coefficients fitted (relative least squares, none negative) to layers drawn over the range of layers this
+// library is for - 1 x 1 and im2col convolutions at batch 1 to 64, fully connected layers, large layers of 16 x 16
+// blocks, aligned and odd rows.  On 3172 layers timed through kernels 2, 8 and the one chosen (up to 4096 x 4096 with 16384
+// pixels, densities of 0.4 to 30 %, blocks of 1 x 1 to 16 x 32) the kernel of the smallest estimate took 1.2 % longer than
+// the fastest one on average, 7 % at the 95th percentile, 59 % at most.
 constexpr double kNever = 1e30;
 constexpr double kCUs = 256.0;
 
@@ -113,6 +114,90 @@ double estimate_blk(const ubp_packed *p, int N, size_t ysz) {
            (N % 64 != 0 ? 17.59 + 15.19 * stage : 0.0);
 }
 
+int gather_col_tiles(int N) {
+    // Column tiles as wide as divides N (a ragged last tile takes the slow staging path), provided that still
+    // leaves a few dozen tiles: wide tiles amortise a step's fixed instruction cost over more matrix instructions
+    // (from measurements on the benchmark layers).
+    for (int ct = 8; ct >= 2; ct /= 2)
+        if (N % (16 * ct) == 0 && N / (16 * ct) >= 32) return ct;
+    for (int ct = 8; ct >= 2; ct /= 2)
+        if ((N + 16 * ct - 1) / (16 * ct) >= 32) return ct;
+    return 2;
+}
+
+// Launch shape of the gather kernel on row groups of G stripes and tiles of 16 CT pixels.
+ubp_status gather_launch(const ubp_packed *p, int N, int G, int CT, const ubp_plan &pl, Shape &s) {
+    int waves = pl.waves, NP = pl.producers;
+    const int nrg = (p->M + kStripe * G - 1) / (kStripe * G);
+    // one wavefront stages about 28 GB/s: a second one as soon as a workgroup's tile is not small
+    if (NP == 0) {
+        NP = ((int64_t)p->K * 32 * CT >= 64 * 1024) ? 2 : 1;
+        if (waves != 0 && waves < NP + 1) NP = 1; // a caller who fixes a tiny workgroup gets one producer
+    }
+    const int max_waves = stripe_max_waves(G, CT);
+    if (max_waves <= NP) return UBP_ERR_UNSUPPORTED;
+    // When the ring holds all of K nothing is ever refilled and a consumer may walk several row
+    // groups one after the other; the number of workgroup rows is then free.  Otherwise every
+    // consumer owns exactly one row group.
+    const bool resident = (p->K + kSlotRows - 1) / kSlotRows <= ring_slots(CT);
+    int wg_rows = pl.wg_rows;
+    if (wg_rows < 0) return UBP_ERR_INVALID_ARG;
+    if (!resident) {
+        if (waves == 0) {
+            // as few workgroup rows as the wavefront limit allows; full workgroups if the last row is
+            // then still at least half full (more consumers per CU measured better than even rows),
+            // else the consumers spread evenly over the rows
+            const int maxc = max_waves - NP;
+            const int rows_wg = (nrg + maxc - 1) / maxc;
+            const int last = nrg - (rows_wg - 1) * maxc;
+            waves = (2 * last >= maxc ? maxc : (nrg + rows_wg - 1) / rows_wg) + NP; // consumers + producers
+        }
+        if (waves < NP + 1 || waves > max_waves) return UBP_ERR_UNSUPPORTED;
+        const int need_rows = (nrg + (waves - NP) - 1) / (waves - NP);
+        if (wg_rows != 0 && wg_rows != need_rows) return UBP_ERR_UNSUPPORTED;
+        wg_rows = need_rows;
+    } else {
+        const int64_t ncol = (N + 16 * CT - 1) / (16 * CT);
+        if (wg_rows == 0) {
+            // about one workgroup per CU in a single round where the column tiles alone do not
+            // fill the chip; then as few workgroup rows as give every consumer the same number
+            // of row groups (no half-used passes)
+            const int target = (int)std::max<int64_t>(1, 256 / std::max<int64_t>(1, ncol));
+            const int nc = std::max(1, (waves ? waves : max_waves) - NP);
+            const int passes = std::max(1, (nrg + nc * target - 1) / (nc * target));
+            wg_rows = (nrg + nc * passes - 1) / (nc * passes);
+        }
+        wg_rows = std::max(1, std::min(wg_rows, std::max(1, nrg)));
+        if (waves == 0) waves = std::min(max_waves - NP, (nrg + wg_rows - 1) / wg_rows) + NP;
+        if (waves < NP + 1 || waves > max_waves) return UBP_ERR_UNSUPPORTED;
+    }
+    s.G = G;
+    s.CT = CT;
+    s.NP = NP;
+    s.waves = waves;
+    s.wg_rows = wg_rows;
+    s.resident = resident;
+    return UBP_OK;
+}
+
+// The gather kernel, aligned rows only (on odd rows it was never the fastest, on none of 298 layers): per round of
+// workgroups (an XCD's workgroups on its 32 CUs) the staging of X, the workgroup's steps and the longest wavefront's; a
+// ragged last tile is a launch of its own behind the others, whose X passes through registers.
+double estimate_gather(const ubp_packed *p, int N, size_t ysz) {
+    Shape s;
+    const int G = gather_stripes(p), CT = gather_col_tiles(N);
+    if (gather_launch(p, N, G, CT, ubp_plan{}, s) != UBP_OK) return kNever;
+    const double steps = (double)get_mask_stats(p).gather_steps, nrg = (p->M + kStripe * G - 1) / (kStripe * G);
+    if (steps * (512 + 1024 * G) >= (double)(int64_t(1) << 31)) return kNever; // (its records have 32-bit byte offsets)
+    const double walks = s.resident ? std::ceil(nrg / ((double)s.wg_rows * (s.waves - s.NP))) : 1; // row groups of a wavefront
+    const double stage = 1e-3 * p->K * CT / s.NP;
+    const int tiles = N / (16 * CT);
+    const double rounds = std::ceil((tiles + 7) / 8 * (double)s.wg_rows / 32);
+    return 2.445 + rounds * (1.756 * stage + (0.777e-3 * CT * G + 4.846e-3) * steps / s.wg_rows +
+                             (0.1542 + 2.15e-3 * CT * G) * walks * steps / nrg + 1.361) +
+           1.433 * 0.2e-6 * p->M * (double)N * ysz + (N % (16 * CT) != 0 ? 12.82 + 15.17 * stage : 0.0);
+}
+
 int tile_layout_words(const ubp_packed *p) { return (tile_kt_pad(p->M, p->K) + 31) / 32; } // occupancy words per stripe; 0: no dense tiles
 bool all_tiles_kept(const ubp_packed *p) {
     const TileLayout &T = get_tile_layout(p);
@@ -133,6 +218,13 @@ bool mtile_named(int kernel, int sub_stripes, int col_tiles) {
     if (kernel == 9) return in(sub_stripes, 4, 8, 16) && in(col_tiles, 4, 8, 16);
     for (const int(&t)[2] : kSeven)
         if ((sub_stripes == 0 || sub_stripes == t[0]) && (col_tiles == 0 || col_tiles == t[1])) return true;
+    return false;
+}
+
+// Whether a gather layout exists: not for a stripe whose columns lie too far apart for the ring, nor beyond 2 GB.
+bool gather_usable(const ubp_packed *p, int CT) {
+    for (int G = gather_stripes(p); G >= 1; G >>= 1)
+        if (get_stripe_layout(p, G, CT).G != 0) return true;
     return false;
 }
 
@@ -170,11 +262,21 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
     }
     if (mostly && aligned && p->K <= kTileMaxK && tile_layout_words(p) > 0 && estimate_xstat(p, N, ysz) < best) {
         best = estimate_xstat(p, N, ysz);
+        s = Shape();
         s.kernel = 4;
     }
     if (blk_eligible(p) && p->bh == kStripe && p->bw >= 16 && p->K > ring_rows(4) && vec_ok && N >= 64 && estimate_blk(p, N, ysz) < best) {
         best = estimate_blk(p, N, ysz);
+        s = Shape();
         s.kernel = 6;
+    }
+    // (a margin of twice this estimate's mean error, since it is the coarsest: of the 56 layers that it gives to kernel 2
+    // one took more than 5 % longer than before, most half to three quarters of the time - 2928 x 1744 in 8 x 1 blocks
+    // with 13120 pixels 429 -> 183 us, 3336 x 2288 in 4 x 4 with 2048 133 -> 59)
+    if (best != kNever && aligned && ldx_bytes <= (int64_t(1) << 25) && 1.2 * estimate_gather(p, N, ysz) < best &&
+        gather_usable(p, gather_col_tiles(N))) {
+        s = Shape();
+        s.kernel = 2;
     }
 }
 
@@ -333,78 +435,17 @@ ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, si
     }
 
     // ---- gather kernel
-    int CT = pl.col_tiles, G = pl.sub_stripes, waves = pl.waves, NP = pl.producers;
-    if (NP != 0 && NP != 1 && NP != 2 && NP != 4) return UBP_ERR_UNSUPPORTED;
+    int CT = pl.col_tiles, G = pl.sub_stripes;
+    if (pl.producers != 0 && pl.producers != 1 && pl.producers != 2 && pl.producers != 4) return UBP_ERR_UNSUPPORTED;
     if ((G != 0 && G != 1 && G != 2 && G != 4) || (CT != 0 && CT != 2 && CT != 4 && CT != 8)) return UBP_ERR_UNSUPPORTED;
-    // Tile shape, from measurements on the benchmark layers.
-    //  * Column tiles as wide as divides N (a ragged last tile takes the slow staging path),
-    //    provided that still leaves a few dozen tiles: wide tiles amortise a step's fixed
-    //    instruction cost over more matrix instructions.
-    //  * Stripes per wavefront follow the block height: a 16-row block touches two stripes
-    //    anyway, so tall row groups cost little extra zero fill and divide the staging of X by
-    //    the rows a workgroup covers; for short blocks one stripe keeps the operands dense.
-    if (CT == 0) {
-        for (int ct = 8; ct >= 2 && CT == 0; ct /= 2)
-            if (N % (16 * ct) == 0 && N / (16 * ct) >= 32) CT = ct;
-        for (int ct = 8; ct >= 2 && CT == 0; ct /= 2)
-            if ((N + 16 * ct - 1) / (16 * ct) >= 32) CT = ct;
-        if (CT == 0) CT = 2;
-    }
+    if (CT == 0) CT = gather_col_tiles(N);
     if (G == 0) {
-        G = p->bh >= 16 ? 4 : p->bh >= 8 ? 2 : 1;
+        G = gather_stripes(p);
         while (G > 1 && get_stripe_layout(p, G, CT).G == 0) G >>= 1;
     }
     const StripeLayout &L = get_stripe_layout(p, G, CT);
     if (L.G == 0) return UBP_ERR_UNSUPPORTED; // layout cannot be built for this matrix
-    // one wavefront stages about 28 GB/s: a second one as soon as a workgroup's tile is not small
-    if (NP == 0) {
-        NP = ((int64_t)p->K * 32 * CT >= 64 * 1024) ? 2 : 1;
-        if (waves != 0 && waves < NP + 1) NP = 1; // a caller who fixes a tiny workgroup gets one producer
-    }
-    const int max_waves = stripe_max_waves(G, CT);
-    if (max_waves <= NP) return UBP_ERR_UNSUPPORTED;
-    // When the ring holds all of K nothing is ever refilled and a consumer may walk several row
-    // groups one after the other; the number of workgroup rows is then free.  Otherwise every
-    // consumer owns exactly one row group.
-    const bool resident = L.nch <= ring_slots(CT);
-    int wg_rows = pl.wg_rows;
-    if (wg_rows < 0) return UBP_ERR_INVALID_ARG;
-    if (!resident) {
-        if (waves == 0) {
-            // as few workgroup rows as the wavefront limit allows; full workgroups if the last row is
-            // then still at least half full (more consumers per CU measured better than even rows),
-            // else the consumers spread evenly over the rows
-            const int maxc = max_waves - NP;
-            const int rows_wg = (L.nrg + maxc - 1) / maxc;
-            const int last = L.nrg - (rows_wg - 1) * maxc;
-            waves = (2 * last >= maxc ? maxc : (L.nrg + rows_wg - 1) / rows_wg) + NP; // consumers + producers
-        }
-        if (waves < NP + 1 || waves > max_waves) return UBP_ERR_UNSUPPORTED;
-        const int need_rows = (L.nrg + (waves - NP) - 1) / (waves - NP);
-        if (wg_rows != 0 && wg_rows != need_rows) return UBP_ERR_UNSUPPORTED;
-        wg_rows = need_rows;
-    } else {
-        const int64_t ncol = (N + 16 * CT - 1) / (16 * CT);
-        if (wg_rows == 0) {
-            // about one workgroup per CU in a single round where the column tiles alone do not
-            // fill the chip; then as few workgroup rows as give every consumer the same number
-            // of row groups (no half-used passes)
-            const int target = (int)std::max<int64_t>(1, 256 / std::max<int64_t>(1, ncol));
-            const int nc = std::max(1, (waves ? waves : max_waves) - NP);
-            const int passes = std::max(1, (L.nrg + nc * target - 1) / (nc * target));
-            wg_rows = (L.nrg + nc * passes - 1) / (nc * passes);
-        }
-        wg_rows = std::max(1, std::min(wg_rows, std::max(1, L.nrg)));
-        if (waves == 0) waves = std::min(max_waves - NP, (L.nrg + wg_rows - 1) / wg_rows) + NP;
-        if (waves < NP + 1 || waves > max_waves) return UBP_ERR_UNSUPPORTED;
-    }
-    s.G = G;
-    s.CT = CT;
-    s.NP = NP;
-    s.waves = waves;
-    s.wg_rows = wg_rows;
-    s.resident = resident;
-    return UBP_OK;
+    return gather_launch(p, N, G, CT, pl, s);
 }
 
 } // namespace

@@ -160,6 +160,7 @@ constexpr int kWrosBatch = 8;
 struct MaskStats {
     bool built = false;
     int64_t steps = 0;      // steps of the direct layout: sum over stripes of ceil(columns with a kept weight / 32)
+    int64_t gather_steps = 0; // the same over row groups of gather_stripes(p) stripes, each a multiple of kPrefetchDepth
     int64_t tiles_hit = 0;  // 16 x 32 tiles a block reaches into
     int64_t tiles = 0;      // all of them
 };
@@ -348,6 +349,10 @@ const BlkLayout &get_blk_layout(const ubp_packed *p, int G);
 const TileLayout &get_tile_layout(const ubp_packed *p);
 const DirectLayout &get_direct_layout(const ubp_packed *p);
 const MaskStats &get_mask_stats(const ubp_packed *p);
+// Stripes per wavefront of the gather kernel.  They follow the block height: a 16-row block touches two stripes
+// anyway, so tall row groups cost little extra zero fill and divide the staging of X by the rows a workgroup
+// covers; for short blocks one stripe keeps the operands dense.
+inline int gather_stripes(const ubp_packed *p) { return p->bh >= 16 ? 4 : p->bh >= 8 ? 2 : 1; }
 bool blk_eligible(const ubp_packed *p);
 
 // ---- host: choice of kernel and launch shape (ubp_choose.cpp).  Builds the host image of the layout the

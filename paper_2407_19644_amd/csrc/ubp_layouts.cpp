@@ -527,29 +527,42 @@ template <class L, class Build> const L &built_once(L &slot, Build build) {
     return slot;
 }
 
-// Counts stripe by stripe with one bit per column, so that memory follows K and time the blocks, not M x K.
-void count_mask(const ubp_packed *p, MaskStats &S) {
-    const int nstripes = (p->M + kStripe - 1) / kStripe, words = (p->K + 31) / 32;
-    S.tiles = (int64_t)nstripes * words;
-    std::vector<uint32_t> bits((size_t)words, 0u); // a word holds the columns of one 16 x 32 tile
-    std::vector<int32_t> hit;                      // its words that are not zero
-    for (int st = 0; st < nstripes; ++st) {
-        const int row0 = st * kStripe, row1 = std::min(p->M, row0 + kStripe);
-        for (int i = std::max(0, row0 - p->bh + 1); i < std::min(p->M - p->bh + 1, row1); ++i)
-            for (int32_t b = p->indptr[(size_t)i]; b < p->indptr[(size_t)i + 1]; ++b)
-                for (int k = p->indices[(size_t)b]; k < p->indices[(size_t)b] + p->bw; ++k) {
-                    uint32_t &w = bits[(size_t)k / 32];
-                    if (w == 0) hit.push_back(k / 32);
-                    w |= 1u << (k % 32);
-                }
+// Columns of W, one bit each, with a list of the words that are not zero.
+struct ColumnSet {
+    std::vector<uint32_t> bits;
+    std::vector<int32_t> hit;
+    explicit ColumnSet(int K) : bits(((size_t)K + 31) / 32, 0u) {}
+    void add(int word, uint32_t v) {
+        uint32_t &w = bits[(size_t)word];
+        if (w == 0) hit.push_back(word);
+        w |= v;
+    }
+    int64_t count_and_clear() {
         int64_t cols = 0;
         for (int32_t w : hit) {
             cols += __builtin_popcount(bits[(size_t)w]);
             bits[(size_t)w] = 0;
         }
-        S.tiles_hit += (int64_t)hit.size();
-        S.steps += (cols + kStep - 1) / kStep;
         hit.clear();
+        return cols;
+    }
+};
+
+// Counts stripe by stripe with one bit per column, so that memory follows K and time the blocks, not M x K.
+void count_mask(const ubp_packed *p, MaskStats &S) {
+    const int nstripes = (p->M + kStripe - 1) / kStripe, G = gather_stripes(p);
+    S.tiles = (int64_t)nstripes * ((p->K + 31) / 32);
+    ColumnSet stripe(p->K), group(p->K); // of the stripe (a word: a 16 x 32 tile), of the gather kernel's row group
+    for (int st = 0; st < nstripes; ++st) {
+        const int row0 = st * kStripe, row1 = std::min(p->M, row0 + kStripe);
+        for (int i = std::max(0, row0 - p->bh + 1); i < std::min(p->M - p->bh + 1, row1); ++i)
+            for (int32_t b = p->indptr[(size_t)i]; b < p->indptr[(size_t)i + 1]; ++b)
+                for (int k = p->indices[(size_t)b]; k < p->indices[(size_t)b] + p->bw; ++k) stripe.add(k / 32, 1u << (k % 32));
+        S.tiles_hit += (int64_t)stripe.hit.size();
+        for (int32_t w : stripe.hit) group.add(w, stripe.bits[(size_t)w]);
+        S.steps += (stripe.count_and_clear() + kStep - 1) / kStep;
+        if ((st + 1) % G == 0 || st + 1 == nstripes)
+            S.gather_steps += (group.count_and_clear() + kStep * kPrefetchDepth - 1) / (kStep * kPrefetchDepth) * kPrefetchDepth;
     }
 }
 

@@ -164,6 +164,7 @@ AUTOMATIC = [  # M, K, N, bh, bw, density, dtype, the kernel ubp_spmm picks
     (160, 1100, 256, 4, 4, 0.01, "bf16", 8),        # most tiles empty
     (256, 4608, 12288, 16, 16, 0.1, "bf16", 6),     # 72 chunks of X against a ring of 16
     (64, 64, 196, 4, 4, 0.5, "f32", 1),
+    (3336, 2288, 2048, 4, 4, 0.27, "bf16", 2),      # small blocks, a W too large for dense tiles, many pixels
     (1656, 2080, 800, 16, 16, 0.06, "f16", 8),      # whole blocks, but few workgroups and a ragged last tile
 ]
 
