@@ -16,8 +16,8 @@ namespace {
 // cost, coefficients fitted (relative least squares, none negative) to layers drawn over the range of layers this
 // library is for - 1 x 1 and im2col convolutions at batch 1 to 64, fully connected layers, large layers of 16 x 16
 // blocks, aligned and odd rows.  On 3172 layers timed through kernels 2, 8 and the one chosen (up to 4096 x 4096 with 16384
-// pixels, densities of 0.4 to 30 %, blocks of 1 x 1 to 16 x 32) the kernel of the smallest estimate took 1.2 % longer than
-// the fastest one on average, 7 % at the 95th percentile, 59 % at most.
+// pixels, densities of 0.4 to 30 %, blocks of 1 x 1 to 16 x 32) the kernel of the smallest estimate took 0.6 % longer than
+// the fastest one on average, 3 % at the 95th percentile, 59 % at most.
 constexpr double kNever = 1e30;
 constexpr double kCUs = 256.0;
 
@@ -235,12 +235,10 @@ bool gather_usable(const ubp_packed *p, int CT) {
 void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, Shape &s) {
     const MaskStats &S = get_mask_stats(p);
     const bool aligned = vec_ok && N % 8 == 0;
-    const bool mostly = 2 * S.tiles_hit >= S.tiles, full = S.tiles_hit == S.tiles;
+    const bool mostly = 2 * S.tiles_hit >= S.tiles;
     double best = kNever;
     s.kernel = 2;
-    // (layers that some tile of keeps nothing and whose K fits the registers stay with the kernels that
-    // add up in column order, whatever the number of pixels)
-    if (direct_able(p, N, ldx_bytes) && !(aligned && mostly && !full && p->K <= kTileMaxK)) {
+    if (direct_able(p, N, ldx_bytes)) {
         int waves = 0;
         best = estimate_direct(p, N, direct_tiles(N), ysz, waves);
         s.kernel = 8;

@@ -294,13 +294,13 @@ def test_the_two_vector_dataflows_walk_the_same_ranges(lib):
 # layers of many pixels whose zero-filled W passes 8 MB or whose tiles are mostly empty: M, K, bh, bw, density, {pixels: kernel}
 WEIGHED = [(3336, 2288, 4, 4, 0.27, {2048: 2, 64: 8, 2049: 8}), (2928, 1744, 8, 1, 0.28, {13120: 2, 100: 8, 13117: 8}),
            (1784, 3608, 2, 1, 0.07, {14592: 2, 49: 8}), (1656, 2080, 16, 16, 0.06, {800: 8, 64: 8}),
-           (4096, 4096, 16, 16, 0.1, {8192: 6, 16: 8})]
+           (4096, 4096, 16, 16, 0.1, {8192: 6, 16: 8}), (256, 256, 8, 8, 0.12, {64: 8, 784: 8}), (1024, 256, 8, 8, 0.12, {12544: 4})]
 
 
 @pytest.mark.parametrize("case", WEIGHED, ids=lambda c: "x".join(map(str, c[:4])))
 def test_every_kernel_is_weighed(lib, case):
     """The gather kernel where it was measured to be the fastest and not beside it; whole blocks as operands only where there
-    are workgroups enough and no launch for a last ragged tile behind them."""
+    are workgroups enough and no launch for a last ragged tile behind them; the direct kernel on few pixels whatever the tiles."""
     M, K, bh, bw, d, want = case
     layer = Layer(lib, M, K, bh, bw, d)
     for N, kernel in want.items():
