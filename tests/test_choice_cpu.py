@@ -65,6 +65,17 @@ extern "C" int choice(const ubp_packed *p, int N, int64_t ldx_bytes, int aligned
     for (int i = 0; i < 8; ++i) out[i] = f[i];
     return rc;
 }
+
+// the direct kernel's layout: sizes, then the four arrays
+extern "C" int direct_layout(const ubp_packed *p, int64_t *sizes, const void **arrays) {
+    std::lock_guard<std::mutex> hold(p->lock);
+    const ubp::DirectLayout &L = ubp::get_direct_layout(p);
+    const int64_t n[5] = {L.nsteps, (int64_t)L.first.size(), (int64_t)L.order.size(), (int64_t)L.ids.size(), (int64_t)L.frags.size()};
+    const void *a[4] = {L.first.data(), L.order.data(), L.ids.data(), L.frags.data()};
+    for (int i = 0; i < 5; ++i) sizes[i] = n[i];
+    for (int i = 0; i < 4; ++i) arrays[i] = a[i];
+    return L.nstripes;
+}
 """
 
 
@@ -306,3 +317,36 @@ def test_every_kernel_is_weighed(lib, case):
     for N, kernel in want.items():
         rc, c = layer.choice(N)
         assert rc == OK and c["kernel"] == kernel, (N, c)
+
+
+@pytest.mark.parametrize("M,K,bh,bw,density", [(64, 64, 4, 4, 0.5), (33, 70, 4, 4, 0.3), (17, 31, 5, 3, 0.4), (130, 600, 16, 16, 0.1), (257, 31, 1, 1, 0.3),
+                                               (90, 130, 20, 3, 0.2), (16, 2100, 4, 1, 0.02), (200, 100, 8, 8, 0.01)])
+def test_the_direct_layout_is_the_matrix(lib, M, K, bh, bw, density):
+    """Decoded: every weight once, in the order of the kernel's operands, padding and all; columns ascending within a stripe, and each
+    step's padding a row of X that the stripe reads anyway."""
+    W, blocks = make_weights(M, K, 4, "bf16"), select_blocks(M, K, bh, bw, density, 3, "uniform", 1.1)
+    layer = Layer(lib, M, K, bh, bw, density, W, blocks=blocks)
+    want, kept = np.zeros((-(-M // 16) * 16, K), np.uint16), np.zeros((-(-M // 16) * 16, K), bool)
+    for r, c in blocks:
+        want[r:r + bh, c:c + bw] = W[r:r + bh, c:c + bw]
+        kept[r:r + bh, c:c + bw] = True
+    sizes, arrays = (ctypes.c_int64 * 5)(), (ctypes.c_void_p * 4)()
+    nstripes = lib.direct_layout(layer.handle, sizes, arrays)
+    assert nstripes == -(-M // 16) and sizes[1] == nstripes + 1 and sizes[2] == nstripes
+    nsteps = sizes[0]
+    assert sizes[3] == 32 * nsteps and sizes[4] == 512 * nsteps
+
+    def view(i, n, dt):
+        return np.frombuffer((ctypes.c_char * (n * np.dtype(dt).itemsize)).from_address(arrays[i]), dt).copy() if n else np.zeros(0, dt)
+    first, order = view(0, nstripes + 1, np.int32), view(1, nstripes, np.int32)
+    ids, frags = view(2, 32 * nsteps, np.uint16).reshape(-1, 32), view(3, 512 * nsteps, np.uint16).reshape(-1, 4, 16, 8)
+    assert first[0] == 0 and first[-1] == nsteps and sorted(order) == list(range(nstripes))
+    assert (np.diff(np.diff(first)[order]) <= 0).all()                          # most steps first
+    for st in range(nstripes):
+        cols = np.flatnonzero(kept[16 * st:16 * st + 16].any(axis=0))
+        assert first[st + 1] - first[st] == -(-len(cols) // 32)
+        got = ids[first[st]:first[st + 1]].reshape(-1).astype(np.int64)
+        assert np.array_equal(got[:len(cols)], cols) and np.isin(got[len(cols):], cols).all()
+        # lane 16 g + n, element e: row n of the stripe in column 8 g + e of the step
+        w = frags[first[st]:first[st + 1]].transpose(2, 0, 1, 3).reshape(16, -1)
+        assert np.array_equal(w[:, :len(cols)], want[16 * st:16 * st + 16][:, cols]) and not w[:, len(cols):].any()
