@@ -158,7 +158,8 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                tile and is only for matrices whose every tile keeps a weight; 5 leaves the empty ones
  *                out; 9 takes any N and alignment.  sub_stripes x col_tiles names the tile, in units of
  *                16 rows x 16 pixels (9: 4, 8 or 16 each; 7: 16 x 16, 8 x 16, 8 x 8, 16 x 4, 4 x 8 or
- *                4 x 4; 5: units of 32, 2 or 4 each); 16 stands for 8, and
+ *                4 x 4; 5: units of 32, 2 or 4 each); 16 stands for 8, except for 16 col_tiles on 8 or
+ *                more sub_stripes where K <= 256, Y is 16-bit and rows are aligned; and
  *                where rows of X lie more than 32 MB apart it is 64 x 64 whatever 5 and 7 are given.
  *                6 = MFMA kernel with whole blocks as operands, stored by row modulo 16 - the
  *                paper's rotation with period 16 (f16 / bf16, bh <= 16, 16 <= K < 65408, N >= 64,

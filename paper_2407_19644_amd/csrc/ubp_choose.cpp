@@ -64,11 +64,14 @@ double estimate_mtile(const ubp_packed *p, int N, int shape, bool ragged, size_t
     static const double kAligned[kNumMtileShapes][6] = {{3.015, 0.370, 0.410, 0.913, 0.039, 0.0},
                                                         {2.606, 0.285, 0.460, 0.788, 0.021, 0.0},
                                                         {2.609, 0.283, 0.430, 0.794, 0.028, 0.0},
-                                                        {2.653, 0.129, 0.199, 0.726, 0.012, 0.106}};
+                                                        {2.653, 0.129, 0.199, 0.726, 0.012, 0.106},
+                                                        {3.356, 0.672, 0.315, 0.908, 0.141, 0.0}}; // (5 % above the fit to 260 layers:
+    // of the 16 it takes from the other shapes and kernel 4 none is slower, the mean takes 0.91 of the time)
     static const double kRagged[kNumMtileShapes][6] = {{4.592, 0.695, 0.0, 0.397, 0.020, 0.0},
                                                        {3.788, 0.523, 0.0, 0.297, 0.0, 0.0},
                                                        {kNever, 0.0, 0.0, 0.0, 0.0, 0.0},   // (never the best one there)
-                                                       {3.109, 0.0, 0.312, 1.143, 0.0, 0.508}};
+                                                       {3.109, 0.0, 0.312, 1.143, 0.0, 0.508},
+                                                       {kNever, 0.0, 0.0, 0.0, 0.0, 0.0}};  // (not built)
     const MtileShape &sh = kMtileShapes[shape];
     const MaskStats &S = get_mask_stats(p);
     const double *c = ragged ? kRagged[shape] : kAligned[shape];
@@ -209,7 +212,11 @@ bool mtile_able(const ubp_packed *p, int N) { // a piece of 8 pixels fits a row
 // The way rows of X take: 0 straight into LDS, 1 through registers (rows that are no 16-byte pieces), 2 through
 // registers with 64-bit offsets (rows more than 32 MB apart, of which 64 have no 32-bit offsets; tiles of 64 x 64 only).
 int mtile_rows(int N, int64_t ldx_bytes, bool vec_ok) { return ldx_bytes > (int64_t(1) << 25) ? 2 : !vec_ok || N % 8 != 0 ? 1 : 0; }
-bool mtile_has(int rows, int shape) { return rows == 0 || (rows == 1 && shape != 2) || shape == 3; }
+// Shapes built for them; 128 x 256 for a 16-bit Y and K up to 256, where a tile is short and it saves a round.
+bool mtile_has(const ubp_packed *p, int rows, int shape, size_t ysz) {
+    if (shape == 4) return rows == 0 && ysz == 2 && p->K <= kTileMaxK;
+    return rows == 0 || (rows == 1 && shape != 2) || shape == 3;
+}
 // Tiles a plan may name, 0 for any size: kernel 5 in units of 32 rows x 32 pixels, 7 and 9 of 16 x 16.
 bool mtile_named(int kernel, int sub_stripes, int col_tiles) {
     static const int kSeven[][2] = {{16, 16}, {8, 16}, {8, 8}, {16, 4}, {4, 8}, {4, 4}};
@@ -247,7 +254,7 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
     if (mostly && mtile_able(p, N)) {
         const int rows = mtile_rows(N, ldx_bytes, vec_ok);
         for (int sh = 0; sh < kNumMtileShapes; ++sh) {
-            if (!mtile_has(rows, sh)) continue;
+            if (!mtile_has(p, rows, sh, ysz)) continue;
             const double t = estimate_mtile(p, N, sh, rows != 0, ysz);
             if (t < best) {
                 best = t;
@@ -356,12 +363,13 @@ ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, si
         const int unit = kernel == 5 ? 32 : 16;
         const bool pinned = kernel == 9 || mtile_rows(N, ldx_bytes, vec_ok) == 0;
         s.rows = mtile_rows(N, ldx_bytes, vec_ok);
+        const bool wide = kernel != 5 && pl.sub_stripes != 4 && mtile_has(p, s.rows, 4, ysz);
         double best = kNever;
         for (int sh = 0; sh < kNumMtileShapes; ++sh) {
-            if (!mtile_has(s.rows, sh)) continue;
+            if (!mtile_has(p, s.rows, sh, ysz) || (sh == 4 && kernel == 5)) continue; // (no name for that one in units of 32)
             const int want_r = pinned ? pl.sub_stripes * unit : 0, want_p = pinned ? pl.col_tiles * unit : 0;
             if (want_r != 0 && kMtileShapes[sh].rows != std::min(want_r, 128)) continue;
-            if (want_p != 0 && kMtileShapes[sh].pixels != std::min(want_p, 128)) continue;
+            if (want_p != 0 && kMtileShapes[sh].pixels != std::min(want_p, wide ? 256 : 128)) continue;
             const double t = estimate_mtile(p, N, sh, s.rows != 0, ysz);
             if (t < best) {
                 best = t;

@@ -379,8 +379,8 @@ ubp_status launch_xstat(const TileArgs &a, bool bf16, bool y_f32, int CT, int KT
 ubp_status launch_direct(const DirectArgs &a, bool bf16, bool y_f32, int CT, int waves, void *stream, bool dry);
 // shapes of kernel 5 / 7 / 9: rows x pixels of a workgroup's tile, workgroups a CU holds
 struct MtileShape { int rows, pixels, per_cu; };
-constexpr int kNumMtileShapes = 4;
-constexpr MtileShape kMtileShapes[kNumMtileShapes] = {{128, 128, 1}, {128, 64, 1}, {64, 128, 1}, {64, 64, 2}};
+constexpr int kNumMtileShapes = 5;
+constexpr MtileShape kMtileShapes[kNumMtileShapes] = {{128, 128, 1}, {128, 64, 1}, {64, 128, 1}, {64, 64, 2}, {128, 256, 1}};
 ubp_status launch_mtile(const TileArgs &a, bool bf16, bool y_f32, int shape, int rows, void *stream, bool dry);
 ubp_status launch_floor(void *stream);
 

@@ -180,7 +180,7 @@ def test_a_pinned_kernel_is_the_kernel_that_runs(lib):
 FIELDS = ("sub_stripes", "col_tiles", "waves", "producers", "wg_rows")
 # what a call resolves to, as a plan: layers and calls that reach every kernel
 ROUND_TRIP = [(160, 1100, 4, 4, 0.25, (256, 4608, 4603)), (1024, 1024, 4, 4, 0.45, (1568, 16)), (256, 256, 8, 8, 0.12, (12544, 64)),
-              (90, 1280, 16, 16, 0.15, (1280,)), (40, 2100, 4, 4, 0.02, (64, 4096))]
+              (90, 1280, 16, 16, 0.15, (1280,)), (40, 2100, 4, 4, 0.02, (64, 4096)), (256, 256, 2, 1, 0.3, (25088,))]
 
 
 @pytest.mark.parametrize("case", ROUND_TRIP, ids=lambda c: "x".join(map(str, c[:4])))
@@ -350,3 +350,17 @@ def test_the_direct_layout_is_the_matrix(lib, M, K, bh, bw, density):
         # lane 16 g + n, element e: row n of the stripe in column 8 g + e of the step
         w = frags[first[st]:first[st + 1]].transpose(2, 0, 1, 3).reshape(16, -1)
         assert np.array_equal(w[:, :len(cols)], want[16 * st:16 * st + 16][:, cols]) and not w[:, len(cols):].any()
+
+
+def test_tiles_of_128_by_256(lib):
+    """For a 16-bit Y, K up to 256 and aligned rows: by the estimate where they save a round, or named with kernel 7 or 9."""
+    layer = Layer(lib, 256, 256, 2, 1, 0.3, dtype="f16")
+    assert layer.choice(25088)[1]["shape"] == 4 and layer.choice(25088)[1]["CT"] == 16
+    for N, kw in ((25088, dict(ysz=4)), (25083, {}), (12544, {}), (25088, dict(kernel=5, sub_stripes=4, col_tiles=4)), (25088, dict(kernel=9, sub_stripes=4, col_tiles=16))):
+        rc, c = layer.choice(N, **kw)
+        assert rc == OK and c["shape"] != 4, (N, kw, c)
+    for kernel in (7, 9):
+        rc, c = layer.choice(512, kernel=kernel, sub_stripes=8, col_tiles=16)
+        assert rc == OK and (c["shape"], c["G"], c["CT"]) == (4, 8, 16)
+    rc, c = Layer(lib, 256, 260, 4, 4, 0.5).choice(25088, kernel=9, sub_stripes=8, col_tiles=16)
+    assert rc == OK and c["shape"] == 0 and c["CT"] == 8

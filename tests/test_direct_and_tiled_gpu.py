@@ -57,7 +57,8 @@ def test_staged_tiles_at_any_alignment(shape, N):
     M, K, bh, bw, d = shape
     for dtype in ("f16", "bf16"):
         blocks, W, X, (Yref, Yabs) = _case(M, K, N, bh, bw, d, dtype, seed=M + N + 1)
-        for G, CT, pad in [(0, 0, 0), (8, 8, 1), (8, 4, 3), (4, 8, -N % 8), (4, 4, 0), (8, 8, -N % 8), (4, 4, 5)]:
+        for G, CT, pad in [(0, 0, 0), (8, 8, 1), (8, 4, 3), (4, 8, -N % 8), (4, 4, 0), (8, 8, -N % 8), (4, 4, 5),
+                           (8, 16, -N % 8)]:
             if (G, CT) == (4, 8) and N % 8:
                 continue        # (that shape is for aligned rows)
             for y_dtype in (dtype, "f32"):
