@@ -140,11 +140,14 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  * Same product with the kernel choice pinned (tests and tuning).  Fields set to 0 mean
  * "choose automatically"; an impossible combination returns UBP_ERR_UNSUPPORTED.
  *   kernel     : 1 = vector-ALU kernel that follows the WROS dataflow literally (any
- *                dtype, bh <= 16).
+ *                dtype, bh <= 16).  For fp32 with K <= 1272, rows of X at most 64 MB apart and at least
+ *                2 (bh <= 2: 6) block columns per output row on average it forms the same sums in the
+ *                same order, bit for bit, by 4 x 4 x 1 matrix instructions from X staged in LDS.
  *                3 = the same kernel with the dataflow the weight rotation replaces (Section
  *                3.3): one output row stored per start row, the other accumulator rows shifted
  *                up by one.  Never chosen automatically; it exists so that the cost of the
- *                shifting can be measured next to kernel 1 (same results bit for bit).
+ *                shifting can be measured next to kernel 1 on 16-bit layers (same results bit for
+ *                bit, for fp32 too).
  *                2 = MFMA kernel on aligned 16-row stripes that gathers the rows of X a row
  *                group needs (f16 / bf16).
  *                4, 5, 7 and 9 = MFMA kernels that use W as zero-filled 16 x 32 operand tiles (f16 / bf16).

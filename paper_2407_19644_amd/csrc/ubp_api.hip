@@ -165,6 +165,38 @@ ubp_status upload_direct_layout(const ubp_packed *p) {
     return UBP_OK;
 }
 
+ubp_status upload_wros4_layout(const ubp_packed *p) {
+    Wros4LayoutDev &D = p->d_wros4;
+    if (D.weights) return UBP_OK;
+    // one allocation and one copy: weights, offsets, rec_of_row, rec_of_end, row_of_rec
+    const Wros4Layout &L = p->wros4;
+    std::vector<uint32_t> all(L.weights.size() + L.offsets.size() + L.rec_of_row.size() + L.rec_of_end.size() + L.row_of_rec.size());
+    size_t at[6] = {0};
+    int n = 0;
+    auto add = [&](const auto &v) {
+        if (!v.empty()) std::memcpy(&all[at[n]], v.data(), v.size() * 4);
+        at[n + 1] = at[n] + v.size();
+        ++n;
+    };
+    add(L.weights);
+    add(L.offsets);
+    add(L.rec_of_row);
+    add(L.rec_of_end);
+    add(L.row_of_rec);
+    uint32_t *d = nullptr;
+    if (!dev_copy_vec(&d, all, &p->device_bytes)) {
+        (void)hipGetLastError();
+        if (d) (void)hipFree(d);
+        return UBP_ERR_ALLOC;
+    }
+    D.offsets = d + at[1];
+    D.rec_of_row = reinterpret_cast<const int32_t *>(d + at[2]);
+    D.rec_of_end = reinterpret_cast<const int32_t *>(d + at[3]);
+    D.row_of_rec = reinterpret_cast<const int32_t *>(d + at[4]);
+    D.weights = reinterpret_cast<float *>(d);
+    return UBP_OK;
+}
+
 void release_device(ubp_packed *p) {
     if (!p || p->device == UBP_HOST_ONLY) return;
     DeviceGuard guard(p->device);
@@ -183,6 +215,7 @@ void release_device(ubp_packed *p) {
     rel(p->d_direct.order);
     rel(p->d_direct.ids);
     rel(p->d_direct.frags);
+    rel(p->d_wros4.weights);
     for (int s = 0; s < kNumLayouts; ++s) {
         rel(p->d_sg[s].rg_ptr);
         rel(p->d_sg[s].rg_order);
@@ -282,7 +315,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         }
         switch (s.kernel) {
         case 1:
-        case 3: rc = upload_values_f32(p); break;
+        case 3: rc = s.px ? upload_wros4_layout(p) : upload_values_f32(p); break;
         case 2: rc = upload_stripe_layout(p, layout_slot(s.G, s.CT)); break;
         case 4:
         case 5:
@@ -317,6 +350,31 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
 
     switch (s.kernel) {
     case 1:
+        if (s.px) {
+            const Wros4Layout &L = p->wros4;
+            Wros4Args a = {};
+            a.weights = p->d_wros4.weights;
+            a.offsets = p->d_wros4.offsets;
+            a.rec_of_row = p->d_wros4.rec_of_row;
+            a.rec_of_end = p->d_wros4.rec_of_end;
+            a.row_of_rec = p->d_wros4.row_of_rec;
+            a.weight_bytes = (uint32_t)(L.weights.size() * sizeof(float));
+            a.offset_bytes = (uint32_t)(L.offsets.size() * sizeof(uint32_t));
+            a.X = static_cast<const float *>(X_dev);
+            a.Y = static_cast<float *>(Y_dev);
+            a.ldx = ldx;
+            a.ldy = ldy;
+            a.M = p->M;
+            a.K = p->K;
+            a.N = N;
+            a.n_tiles = (N + s.px - 1) / s.px;
+            a.rpr = s.rpr;
+            a.slices = (int)(((int64_t)p->M + (int64_t)s.rpr * s.px_waves - 1) / ((int64_t)s.rpr * s.px_waves));
+            a.vec4 = (N % 4 == 0) && (ldx % 4 == 0) && (reinterpret_cast<uintptr_t>(X_dev) % 16 == 0);
+            a.ep = ep;
+            return launch_wros4(a, p->bh, s.px, s.px_waves, stream, dry);
+        }
+        [[fallthrough]];
     case 3: return launch_wros(p, X_dev, ldx, N, Y_dev, ldy, y_dtype, s.rpr, s.kernel == 3, ep, stream, dry);
     case 2: return launch_stripe(stripe_args(p, s, X_dev, ldx, N, Y_dev, ldy, vec_ok, 0, ep), bf16, y_f32, s.G, s.CT, s.waves, stream, dry);
     case 4:

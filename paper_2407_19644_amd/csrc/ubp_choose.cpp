@@ -294,6 +294,58 @@ int kernel_by_matrix(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok)
     return p->K <= kTileMaxK ? 4 : 5;
 }
 
+// ------------------------------------------------------------------ fp32 matrix kernel
+// Where blocks are few the vector kernel, which reads the rows of X that they need and no others, is the faster one:
+// 512 x 512 in 4 x 1 blocks with 6272 pixels at 0.26, 0.64, 1.3 and 2.6 columns per start row 8.6, 10.6, 12.9 and 14.5 us
+// against 10.6, 10.5, 11.4 and 11.1; lower blocks fill less of a matrix instruction: 128 x 128 in 1 x 1 blocks with 12544 pixels at
+// 2.6, 6.4 and 26 columns 6.1, 7.6 and 12.4 us against 6.8, 7.6 and 10.9, 700 x 700 in 2 x 1 blocks with 5 pixels at 3.5 and 7 columns 6.1 and 7.6
+// against 6.7 and 5.6.
+bool wros4_able(const ubp_packed *p, int64_t ldx_bytes) {
+    return p->dtype == UBP_F32 && p->bh <= 16 && p->K <= wros4_max_K(32) && p->nb * p->bw >= (p->bh > 2 ? 2 : 6) * (int64_t)p->M && ldx_bytes <= (int64_t(1) << 25) && get_wros4_layout(p).usable;
+}
+
+// What it would take, in microseconds: per round of workgroups (an XCD's on its 32 CUs, as many to a CU as LDS and
+// wavefronts allow) the staging of X and a wavefront's groups and rows, each of them either a chain of latencies or the
+// SIMD's share.  Coefficients fitted to 190 layers of the range the benchmark draws from, each timed in 20 to 40 shapes:
+// mean error 7 %, and the shape of the smallest estimate took 1.7 % longer than the fastest on average, 21 % at most.
+double estimate_wros4(const ubp_packed *p, int N, int px, int waves, int rpr) {
+    const Wros4Layout &L = get_wros4_layout(p);
+    const double M = p->M, per_row = (double)L.n_records * (4 / wros4_quads(p->bh)) / M; // groups
+    const int lds = (((p->K + 7) & ~7) + 1) * 4 * px;
+    const int64_t wgs = ((int64_t)N + px - 1) / px * (((int64_t)p->M + (int64_t)rpr * waves - 1) / ((int64_t)rpr * waves));
+    const double a_cu = (double)(((wgs + 7) / 8 + 31) / 32), held = std::min({160 * 1024 / lds, 32 / waves, 16});
+    const double rounds = std::ceil(a_cu / held), together = std::min(a_cu, held), simd = std::max(1.0, together * waves / 4);
+    const double rows = std::min((double)rpr, M) + std::min<double>(p->bh - 1, std::max(0.0, M - rpr));
+    const int quads = (p->bh + 3) / 4;
+    return 3.55 + rounds * (together * lds * 1.176e-5 + 0.0197 * lds / 1024 / waves * (N % 4 == 0 ? 1 : 4) +
+                            rows * per_row * std::max(0.0232 + 0.0218 * quads, simd * (0.0035 + 0.016 * quads)) +
+                            rows * std::max(0.0311, simd * 0.0472)) +
+           0.504 * 0.8e-6 * M * N;
+}
+
+// Pixels and wavefronts of a workgroup and, unless it is pinned, rows of a wavefront by the smallest estimate; px = 0: none.
+void wros4_shape(const ubp_packed *p, int N, int rpr, Shape &s) {
+    double best = kNever;
+    for (int px : {64, 32}) {
+        if (p->K > wros4_max_K(px)) continue;
+        for (int r : {rpr, p->bh, 2 * p->bh, 4 * p->bh, 16, 32, 64}) {
+            if (rpr != 0 ? r != rpr : r < p->bh) continue;
+            for (int waves : {4, 8, 16}) {
+                const int w = (int)std::min<int64_t>(waves, ((int64_t)p->M + r - 1) / r);
+                const int64_t slices = ((int64_t)p->M + (int64_t)r * w - 1) / ((int64_t)r * w);
+                if (((int64_t)N + px - 1) / px * slices >= (int64_t(1) << 22)) continue; // a launch has fewer than 2^32 threads
+                const double t = estimate_wros4(p, N, px, w, r);
+                if (t < best) {
+                    best = t;
+                    s.px = px;
+                    s.px_waves = w;
+                    s.rpr = r;
+                }
+            }
+        }
+    }
+}
+
 ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t ysz, const ubp_plan &pl, Shape &s) {
     int kernel = pl.kernel;
     // the dense-tile kernels 4, 5 and 7 need 16-byte pieces of X rows that lie entirely inside or outside the matrix
@@ -322,6 +374,10 @@ ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, si
     if (kernel == 1 || kernel == 3) {
         if (p->bh > 16) return UBP_ERR_UNSUPPORTED;
         int rpr = pl.rows_per_range;
+        if (kernel == 1 && rpr >= 0 && wros4_able(p, ldx_bytes)) {
+            wros4_shape(p, N, rpr, s);
+            if (s.px != 0) return UBP_OK;
+        }
         if (rpr == 0) {
             // Row ranges of one block height (re-walking bh - 1 rows nearly doubles the work, but a small
             // layer is a chain of latencies: 64 x 64 with 196 pixels 10.1 us, against 22.5 with ranges of

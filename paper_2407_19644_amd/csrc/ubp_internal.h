@@ -181,6 +181,30 @@ struct DirectLayout {
     int64_t nsteps = 0;
 };
 
+// Accumulator quads per block column of the fp32 matrix kernel, as a power of two (it has 4 slots each).
+constexpr int wros4_quads(int bh) { return bh <= 4 ? 1 : bh <= 8 ? 2 : 4; }
+// Rows of X that its LDS holds at PX pixels: all of K rounded up to 8, and a row of zeros, of 4 PX bytes each.
+constexpr int wros4_max_K(int PX) { return (160 * 1024 / (4 * PX) - 1) / 8 * 8; }
+
+// Host image of the fp32 matrix kernel's layout: the blocks' columns in canonical order (start rows, then column
+// origins, then columns), 4 of one start row to a group (filled up with zero weights), 4 / wros4_quads(bh) groups to a record.
+//   weights : 64 floats per record: per column 4 wros4_quads(bh) slots, the block's rotated weights and zeros
+//   offsets : 16 pairs per record.  First of pair c: 256 x the row of X of column c mod (columns per record), 256 x
+//             (K rounded up to 8), where the kernel keeps zeros, for a column that fills up.  Second: byte
+//             g = output rows that are complete after group g.  (Where more than 255 rows end behind one group,
+//             groups without columns follow.)
+//   rec_of_row : [M] the record with the first group of this or a later start row
+//   rec_of_end : [M] the record with the group behind which the output row is complete, -1 before the first group
+//   row_of_rec : [n_records + 1] the output row that is next to be complete when the record begins, M at the end
+struct Wros4Layout {
+    bool built = false;
+    int n_records = 0;       // (0 also where nothing is kept)
+    bool usable = false;
+    std::vector<float> weights;
+    std::vector<uint32_t> offsets;
+    std::vector<int32_t> rec_of_row, rec_of_end, row_of_rec;
+};
+
 struct StripeLayoutDev {
     int32_t *rg_ptr = nullptr;
     int32_t *rg_order = nullptr;
@@ -200,6 +224,11 @@ struct DirectLayoutDev {
     uint16_t *ids = nullptr;
     uint16_t *frags = nullptr;
     bool uploaded = false;
+};
+struct Wros4LayoutDev {
+    float *weights = nullptr; // (the allocation; the others lie behind them)
+    const uint32_t *offsets = nullptr;
+    const int32_t *rec_of_row = nullptr, *rec_of_end = nullptr, *row_of_rec = nullptr;
 };
 struct TileLayoutDev {
     uint16_t *frags = nullptr;
@@ -267,6 +296,21 @@ struct DirectArgs {
     Epilogue ep;
 };
 
+struct Wros4Args {
+    const float *weights;
+    const uint32_t *offsets;
+    const int32_t *rec_of_row, *rec_of_end, *row_of_rec;
+    uint32_t weight_bytes, offset_bytes; // (buffer-addressed: below 2 GB)
+    const float *X;
+    float *Y;
+    int64_t ldx, ldy;        // (ldx at most 2^24: 32-bit byte offsets within 8 rows)
+    int M, K, N;
+    int n_tiles, slices;     // pixel tiles, workgroups that share one
+    int rpr;                 // output rows per wavefront
+    int vec4;                // rows of X consist of 16-byte pieces
+    Epilogue ep;
+};
+
 struct TileArgs {
     const uint16_t *frags;   // [nstripes][KT][64][8]
     const uint32_t *occupied; // one bit per tile, ceil(kt_total / 32) words per stripe
@@ -288,6 +332,8 @@ struct Shape {
     int kernel = 0;   // 1 vector, 2 gather, 4 small-K dense tiles, 5 / 7 / 9 dense tiles through LDS, 6 block, 8 direct
     int shape = 0;    // kernels 5, 7, 9: index into kMtileShapes
     int G = 0, CT = 0, waves = 0, NP = 0, wg_rows = 0, rpr = 0;
+    int px = 0;       // kernel 1: pixels of a workgroup of the fp32 matrix kernel; 0: the vector kernel
+    int px_waves = 0; // its wavefronts
     bool resident = false;
     int rows = 0;        // kernels 5, 7, 9: the way rows of X take (mtile_rows)
 };
@@ -320,6 +366,7 @@ struct ubp_packed {
     mutable ubp::BlkLayout blk[3];           // G = 2, 4, 5
     mutable ubp::TileLayout tiles;
     mutable ubp::DirectLayout direct;
+    mutable ubp::Wros4Layout wros4;
     mutable ubp::MaskStats stats;
     mutable ubp::Choice choices[ubp::kChoices];
     mutable int next_choice = 0;
@@ -332,6 +379,7 @@ struct ubp_packed {
     mutable ubp::BlkLayoutDev d_blk[3];
     mutable ubp::TileLayoutDev d_tiles;
     mutable ubp::DirectLayoutDev d_direct;
+    mutable ubp::Wros4LayoutDev d_wros4;
     uint32_t *d_error = nullptr;   // set by a kernel whose bounded wait ran out
     mutable int64_t device_bytes = 0;
 };
@@ -348,6 +396,7 @@ const StripeLayout &get_stripe_layout(const ubp_packed *p, int G, int CT);
 const BlkLayout &get_blk_layout(const ubp_packed *p, int G);
 const TileLayout &get_tile_layout(const ubp_packed *p);
 const DirectLayout &get_direct_layout(const ubp_packed *p);
+const Wros4Layout &get_wros4_layout(const ubp_packed *p);
 const MaskStats &get_mask_stats(const ubp_packed *p);
 // Stripes per wavefront of the gather kernel.  They follow the block height: a 16-row block touches two stripes
 // anyway, so tall row groups cost little extra zero fill and divide the staging of X by the rows a workgroup
@@ -368,11 +417,13 @@ ubp_status upload_stripe_layout(const ubp_packed *p, int slot);
 ubp_status upload_blk_layout(const ubp_packed *p, int slot);
 ubp_status upload_tile_layout(const ubp_packed *p);
 ubp_status upload_direct_layout(const ubp_packed *p);
+ubp_status upload_wros4_layout(const ubp_packed *p);
 
 // Launchers.  `dry` only raises the kernels' dynamic LDS limit on the current device (what a
 // first launch of a shape would do), so that a later launch is nothing but a launch.
 ubp_status launch_wros(const ubp_packed *p, const void *X, int64_t ldx, int N, void *Y, int64_t ldy, ubp_dtype y_dtype,
                        int rpr, bool naive, const Epilogue &ep, void *stream, bool dry);
+ubp_status launch_wros4(const Wros4Args &a, int bh, int PX, int waves, void *stream, bool dry);
 ubp_status launch_stripe(const StripeArgs &a, bool bf16, bool y_f32, int G, int CT, int waves, void *stream, bool dry);
 ubp_status launch_blk(const BlkArgs &a, bool bf16, bool y_f32, int G, int waves, void *stream, bool dry);
 ubp_status launch_xstat(const TileArgs &a, bool bf16, bool y_f32, int CT, int KT, int waves, void *stream, bool dry);

@@ -291,6 +291,48 @@ void build_direct(const ubp_packed *p, DirectLayout &L) {
     });
 }
 
+// Stream of block columns for the fp32 matrix kernel.
+void build_wros4(const ubp_packed *p, Wros4Layout &L) {
+    const int M = p->M, bh = p->bh, bw = p->bw;
+    const int slots = 4 * wros4_quads(bh), per = 16 / slots; // groups of a record
+    const uint32_t zeros = (uint32_t)((p->K + 7) & ~7) * 256u;
+    const float *vals = reinterpret_cast<const float *>(p->values.data());
+    int64_t groups = 0;
+    int64_t last = -1; // the group that rows which end now end behind
+    L.rec_of_row.resize((size_t)M);
+    L.rec_of_end.assign((size_t)M, -1);
+    auto ends_byte = [&](int64_t g) { return reinterpret_cast<uint8_t *>(&L.offsets[(size_t)(g / per) * 32 + 16]) + g % per; };
+    auto open_group = [&](int row) {
+        if (groups % per == 0) {
+            L.row_of_rec.push_back(row);
+            L.weights.resize(L.weights.size() + 64, 0.f);
+            const size_t o = L.offsets.size();
+            L.offsets.resize(o + 32, 0u);
+            std::fill_n(L.offsets.begin() + (std::ptrdiff_t)o, 16, zeros);
+        }
+        last = groups++;
+    };
+    for (int i = 0; i < M; ++i) {
+        L.rec_of_row[(size_t)i] = (int32_t)(groups / per);
+        const int64_t t0 = i + bh <= M ? (int64_t)p->indptr[(size_t)i] * bw : 0, t1 = i + bh <= M ? (int64_t)p->indptr[(size_t)i + 1] * bw : 0;
+        for (int64_t t = t0; t < t1; ++t) {
+            if ((t - t0) % 4 == 0) open_group(i);
+            const size_t rec = (size_t)(last / per), c = (size_t)(last % per) * 4 + (size_t)((t - t0) % 4);
+            for (int u = 0; u < bh; ++u) L.weights[rec * 64 + c * (size_t)slots + (size_t)u] = vals[t * bh + (i + u) % bh]; // (stored rotated)
+            const uint32_t row = (uint32_t)(p->indices[(size_t)(t / bw)] + (int32_t)(t % bw));
+            L.offsets[rec * 32 + c] = row * 256u;
+        }
+        if (last < 0) continue; // (nothing to end behind yet)
+        if (*ends_byte(last) == 255) open_group(i);
+        ++*ends_byte(last);
+        L.rec_of_end[(size_t)i] = (int32_t)(last / per);
+    }
+    L.row_of_rec.push_back(M);
+    const size_t records = L.weights.size() / 64;
+    L.usable = L.weights.size() * 4 < (size_t(1) << 31);
+    L.n_records = (int)records;
+}
+
 // ---------------------------------------------------------------- block kernel layout
 struct Half {
     int32_t a;      // first row of the 16-row window of X
@@ -584,6 +626,12 @@ const BlkLayout &get_blk_layout(const ubp_packed *p, int G) {
 const DirectLayout &get_direct_layout(const ubp_packed *p) {
     return built_once(p->direct, [&](DirectLayout &L) {
         if (p->dtype != UBP_F32 && p->K <= 0x10000) build_direct(p, L); // row numbers are 16-bit in the records
+    });
+}
+
+const Wros4Layout &get_wros4_layout(const ubp_packed *p) {
+    return built_once(p->wros4, [&](Wros4Layout &L) {
+        if (p->dtype == UBP_F32 && p->bh <= 16 && p->K <= wros4_max_K(32)) build_wros4(p, L);
     });
 }
 
