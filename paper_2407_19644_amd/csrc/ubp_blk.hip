@@ -16,8 +16,12 @@ namespace ubp {
 
 namespace {
 
-constexpr int kBlkCT = 4; // 64-pixel column tiles (the ring geometry of CT = 4)
-
+constexpr int kBlkCT = 4; // 64-pixel column tiles (as many ring rows as the ring of CT = 4 has)
+// A kilobyte of the ring holds 8 rows, the 4 pixel tiles one after the other, 8 x 32 bytes each: the 8 rows that half a
+// wavefront reads together are 256 consecutive bytes (no bank conflicts without a swizzle), and the tiles' addresses
+// differ by constants.
+constexpr int kBlkTile = 256;
+constexpr int kBlkRing = ring_rows(kBlkCT) * ring_pitch(kBlkCT);
 
 // One workgroup = NP producer wavefronts + up to 16 - NP consumer wavefronts on one tile of 64
 // columns of X / Y.
@@ -36,21 +40,24 @@ constexpr int kBlkCT = 4; // 64-pixel column tiles (the ring geometry of CT = 4)
 //    LDS reads per pixel tile gather their 32 rows of X; two compares and eight selects split the
 //    operand into its lower-stripe and upper-stripe part; 4 + 4 MFMAs (16x16x32).  A lane reads
 //    the window row congruent to its entry number modulo 16 (the columns of a half are rotated
-//    like its rows), so the ring's bank swizzle, which depends on the row modulo 8, is a lane
-//    constant and an address is one select and one add away from the window's first row.
+//    like its rows), so an address is one select and one add away from the window's first row and
+//    the four tiles' reads differ by an immediate (with rows of 128 bytes and a swizzle six more vector instructions:
+//    4096 x 4096 with 8192 pixels 88.0 -> 86.2 us in a graph with skewed blocks, 85.4 -> 82.6 with even ones).
+// What bounds it: a wavefront's chain of scalar and vector instructions and branches, 3.5 of them to a SIMD.  Scalar
+// masks in the place of the four vector compares took 91.7 us; the reads of step s + 1 issued behind the products
+// of step s, with masks and addresses worked out while they run, 95.3; no staging at all would give 77.8.
 // Every wait is bounded: if one runs out the wavefront raises *err and goes on without waiting
 // (wrong numbers, but the kernel always terminates).
 template <bool BF16, typename TY, int G, int MAXT>
 __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     constexpr int CT = kBlkCT;
     constexpr int NTW = 16 * CT;
-    constexpr int PITCH = ring_pitch(CT);
-    constexpr int PIECES = 2 * CT; // 16-byte pieces per staged row
     constexpr int R = ring_slots(CT), KS = kSlotRows, RR = ring_rows(CT);
     constexpr int D = kPrefetchDepth;
-    constexpr int NINST = KS * PIECES / 64; // direct-to-LDS instructions per chunk (1 KB each)
+    constexpr int PITCH = ring_pitch(CT);
+    constexpr int NINST = KS / 8; // direct-to-LDS instructions per chunk (1 KB each: 8 rows)
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    uint32_t *published_p = reinterpret_cast<uint32_t *>(smem + a.ring_bytes); // [4] chunks landed, per producer
+    uint32_t *published_p = reinterpret_cast<uint32_t *>(smem + kBlkRing); // [4] chunks landed, per producer
     uint32_t *released_p = published_p + 16;                                   // [16] per consumer wavefront
 
     // workgroup -> (column tile, workgroup row): consecutive workgroup ids go round-robin over the
@@ -96,27 +103,20 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
             return v;
         };
         __builtin_amdgcn_s_setprio(3); // little work, but everyone else waits for it
-        const int r_in = lane / PIECES, pp = lane % PIECES;
-        constexpr int RPI = 64 / PIECES; // rows covered by one 1 KB instruction
-        // byte offset of this lane's 16-byte piece for instruction i of a chunk, from the chunk's
-        // first element
-        auto piece_offset = [&](int i, int rows) {
-            const int r = i * RPI + r_in;                        // row inside the chunk
-            const int u = (pp >> 1) ^ ring_swizzle(CT, r);       // logical unit stored at this position
-            // rows past K load the chunk's last row again (never read): every chunk then issues
-            // the same number of loads, which the in-order vmcnt bookkeeping relies on
-            return (uint32_t)(((int64_t)min(r, rows - 1) * a.ldx + u * 16 + (pp & 1) * 8) * 2);
-        };
-        // Full chunks: the swizzle depends on the row modulo 8 at most and an instruction covers 8
-        // rows from a multiple of 8, so relative to the first row of ITS instruction a lane's
-        // offset is the same for every instruction; the wave-uniform base moves instead.
         // (Staging through a register ring of ordinary loads instead - 24 loads of 1 KB in flight
         // per producer - was built and measured slower: 113 us against 101 us on the largest layer.)
         const uint32_t ring0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-        const uint32_t voff = piece_offset(0, KS);
+        // byte offset of this lane's 16-byte piece (row, pixel tile, half of its 32 bytes) for instruction i of a chunk
+        // of `rows` rows, from the instruction's first element; rows past K load the chunk's last row again (never
+        // read): every chunk then issues the same number of loads, which the in-order vmcnt bookkeeping relies on
+        auto piece = [&](int i, int rows) {
+            const int r = min((lane >> 1) & 7, rows - 1 - 8 * i);
+            return (uint32_t)(((int64_t)max(r, 0) * a.ldx + (lane >> 4) * 16 + (lane & 1) * 8) * 2);
+        };
+        const uint32_t voff = piece(0, KS);
         const int per = NINST / NP;                    // instructions of a chunk that are mine
         const int lag = max(1, min(48 / per, R / 2));  // chunks kept in flight before they are published
-        const int64_t inst_stride = (int64_t)RPI * a.ldx; // elements between the rows of two instructions
+        const int64_t inst_stride = 8 * a.ldx;         // elements between the rows of two instructions
         for (int c = 0; c < a.nch; ++c) {
             const int slot = c % R;
             if (c >= free_upto && !broken) {
@@ -146,12 +146,13 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
             }
             const int k0 = c * KS;
             const int rows = min(KS, a.K - k0);
-            const uint32_t lds0 = ring0 + (uint32_t)(slot * KS * PITCH);
+            const uint32_t dst = ring0 + (uint32_t)(slot * KS * PITCH);
             const uint16_t *base = a.X + (int64_t)k0 * a.ldx + col0; // wave-uniform
             if (rows == KS) {
-                for (int i = me; i < NINST; i += NP) load16_to_lds(base + i * inst_stride, voff, lds0 + (uint32_t)i * 1024u);
+                for (int i = me; i < NINST; i += NP) load16_to_lds(base + i * inst_stride, voff, dst + (uint32_t)i * 1024u);
             } else {
-                for (int i = me; i < NINST; i += NP) load16_to_lds(base, piece_offset(i, rows), lds0 + (uint32_t)i * 1024u);
+                for (int i = me; i < NINST; i += NP)
+                    load16_to_lds(base + min(8 * i, rows - 1) * a.ldx, piece(i, rows), dst + (uint32_t)i * 1024u);
             }
             if (c + 1 - published > lag) {
                 wait_vmcnt_at_most(lag * per); // vector memory completes in order: chunks <= c - lag have landed
@@ -219,8 +220,8 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
         int spins = 0;
         for (;;) {
             const uint32_t seen = flag_load(published_p + (lane & 3)); // unused producer slots were set to "all"
-            ready_upto = (int)min(min(__builtin_amdgcn_readlane(seen, 0), __builtin_amdgcn_readlane(seen, 1)),
-                                  min(__builtin_amdgcn_readlane(seen, 2), __builtin_amdgcn_readlane(seen, 3)));
+            ready_upto = __builtin_amdgcn_readfirstlane((int)min(min(__builtin_amdgcn_readlane(seen, 0), __builtin_amdgcn_readlane(seen, 1)),
+                                                                 min(__builtin_amdgcn_readlane(seen, 2), __builtin_amdgcn_readlane(seen, 3))));
             if (chunk < ready_upto) return;
             if (++spins > kSpinLimit) {
                 broken = true; // reported after the step loop (no global atomic inside it)
@@ -245,9 +246,9 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     const uint32_t ring_base = __builtin_amdgcn_readfirstlane(lds_address(smem));
     const int g = lane >> 4, n = lane & 15;
     // this lane's part in a transposed read of a 16-row window: window row congruent to e modulo
-    // 16, 8 bytes (4 pixels) number n & 3 of the 32-byte unit of pixel tile 0
+    // 16, 8 bytes (4 pixels) number n & 3 of the 32 bytes of pixel tile 0
     const uint32_t e = (uint32_t)(4 * g + (n >> 2));
-    const uint32_t k0 = e * (uint32_t)PITCH + ((uint32_t)ring_swizzle(CT, (int)e) << 5) + (uint32_t)(n & 3) * 8u;
+    const uint32_t k0 = ring_base + (e >> 3) * 1024u + (e & 7u) * 32u + (uint32_t)(n & 3) * 8u, k1 = k0 + 16u * (uint32_t)PITCH;
 
     if (s_first < s_all) {
         uint2v mcur = load_meta();
@@ -283,17 +284,19 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
                 // ---- gather: the 16 + 16 window rows, four pixel tiles
                 short8v xf[CT];
                 {
+                    // (a window's rows lie 16-row aligned from row rA & ~15; those congruent to less than rA come 16 rows later)
                     const uint32_t rA = aA & (uint32_t)(RR - 1), rB = aB & (uint32_t)(RR - 1);
-                    const uint32_t loA = ring_base + (rA & ~15u) * (uint32_t)PITCH;
-                    const uint32_t hiA = ring_base + (((rA & ~15u) + 16u) & (uint32_t)(RR - 1)) * (uint32_t)PITCH;
-                    const uint32_t loB = ring_base + (rB & ~15u) * (uint32_t)PITCH;
-                    const uint32_t hiB = ring_base + (((rB & ~15u) + 16u) & (uint32_t)(RR - 1)) * (uint32_t)PITCH;
-                    const uint32_t tA = (e < (rA & 15u) ? hiA : loA) + k0;
-                    const uint32_t tB = (e < (rB & 15u) ? hiB : loB) + k0;
+                    uint32_t tA = (e < (rA & 15u) ? k1 : k0) + (rA & ~15u) * (uint32_t)PITCH;
+                    uint32_t tB = (e < (rB & 15u) ? k1 : k0) + (rB & ~15u) * (uint32_t)PITCH;
+                    if (max(rA, rB) > (uint32_t)(RR - 16)) { // rare: over the ring's end
+                        asm volatile("");
+                        tA = ring_base + ((tA - ring_base) & (uint32_t)(RR * PITCH - 1));
+                        tB = ring_base + ((tB - ring_base) & (uint32_t)(RR * PITCH - 1));
+                    }
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
-                        const short4v p0 = lds_read_tr(tA ^ (uint32_t)(c << 5));
-                        const short4v p1 = lds_read_tr(tB ^ (uint32_t)(c << 5));
+                        const short4v p0 = lds_read_tr(tA, c * kBlkTile);
+                        const short4v p1 = lds_read_tr(tB, c * kBlkTile);
                         xf[c] = __builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, 6, 7);
                     }
                 }
@@ -347,7 +350,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
             constexpr int PR = RB / 16;       // 16-byte pieces per row
             constexpr int RP = 256 / RB;      // rows per 256 bytes (one pass over the banks)
             constexpr int NI = PR / 4;        // store instructions per stripe
-            char *scratch = smem + a.ring_bytes + 32 * sizeof(uint32_t) + wave * a.out_bytes;
+            char *scratch = smem + kBlkRing + 32 * sizeof(uint32_t) + wave * a.out_bytes;
 #pragma unroll
             for (int j = 0; j < G; ++j) {
                 if (j >= stripes) break;
@@ -395,9 +398,9 @@ ubp_status launch_blk_inst(BlkArgs a, int waves, hipStream_t st, bool dry) {
     // ring + the progress counters + (16-bit Y, where it fits) the consumers' output rows
     if (sizeof(TY) == 2) {
         const size_t want = (size_t)16 * 16 * kBlkCT * 2;
-        if ((size_t)a.ring_bytes + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * want <= 160 * 1024) a.out_bytes = (int)want;
+        if ((size_t)kBlkRing + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * want <= 160 * 1024) a.out_bytes = (int)want;
     }
-    const size_t lds = (size_t)a.ring_bytes + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * a.out_bytes;
+    const size_t lds = (size_t)kBlkRing + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * a.out_bytes;
     static LdsLimit limit; // per instantiation
     const ubp_status rc = limit.raise(reinterpret_cast<const void *>(&blk_kernel<BF16, TY, G, MAXT>));
     if (rc != UBP_OK || dry) return rc;

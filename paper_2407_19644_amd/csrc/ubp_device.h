@@ -77,6 +77,13 @@ __device__ __forceinline__ short4v lds_read_tr(uint32_t lds_addr) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)lds_addr);
 }
 
+// the same, a constant number of bytes further on
+__device__ __forceinline__ short4v lds_read_tr(uint32_t lds_addr, int offset) {
+    typedef __attribute__((address_space(3))) short4v *lds_ptr;
+    typedef __attribute__((address_space(3))) char *lds_char_ptr;
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)((lds_char_ptr)(uintptr_t)lds_addr + offset));
+}
+
 // 16 bytes per lane from global memory straight into LDS at lds_base + 16 * lane (lds_base
 // wave-uniform).  Written as inline assembly on purpose: the compiler then does not treat
 // the load as a pending LDS write, which would make it wait for ALL outstanding vector

@@ -277,7 +277,6 @@ struct BlkArgs {
     int64_t ldx, ldy;
     int M, K, N;
     int nrg, nch;
-    int ring_bytes;
     int n_coltiles;          // full 64-pixel column tiles this launch covers (from pixel 0)
     int n_wgrows;
     int n_producers;
