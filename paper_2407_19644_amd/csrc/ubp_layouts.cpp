@@ -297,6 +297,10 @@ void build_wros4(const ubp_packed *p, Wros4Layout &L) {
     const int slots = 4 * wros4_quads(bh), per = 16 / slots; // groups of a record
     const uint32_t zeros = (uint32_t)((p->K + 7) & ~7) * 256u;
     const float *vals = reinterpret_cast<const float *>(p->values.data());
+    int64_t most = M / 255 + 1; // groups, at most
+    for (int i = 0; i + bh <= M; ++i) most += ((int64_t)(p->indptr[(size_t)i + 1] - p->indptr[(size_t)i]) * bw + 3) / 4;
+    L.weights.reserve((size_t)((most + per - 1) / per) * 64);
+    L.offsets.reserve((size_t)((most + per - 1) / per) * 32);
     int64_t groups = 0;
     int64_t last = -1; // the group that rows which end now end behind
     L.rec_of_row.resize((size_t)M);
@@ -318,7 +322,9 @@ void build_wros4(const ubp_packed *p, Wros4Layout &L) {
         for (int64_t t = t0; t < t1; ++t) {
             if ((t - t0) % 4 == 0) open_group(i);
             const size_t rec = (size_t)(last / per), c = (size_t)(last % per) * 4 + (size_t)((t - t0) % 4);
-            for (int u = 0; u < bh; ++u) L.weights[rec * 64 + c * (size_t)slots + (size_t)u] = vals[t * bh + (i + u) % bh]; // (stored rotated)
+            // (stored rotated: element u of the block in slot (i + u) mod bh)
+            float *to = &L.weights[rec * 64 + c * (size_t)slots];
+            std::rotate_copy(vals + t * bh, vals + t * bh + i % bh, vals + t * bh + bh, to);
             const uint32_t row = (uint32_t)(p->indices[(size_t)(t / bw)] + (int32_t)(t % bw));
             L.offsets[rec * 32 + c] = row * 256u;
         }
