@@ -23,6 +23,55 @@ constexpr int kBlkCT = 4; // 64-pixel column tiles (as many ring rows as the rin
 constexpr int kBlkTile = 256;
 constexpr int kBlkRing = ring_rows(kBlkCT) * ring_pitch(kBlkCT);
 
+// The products of a step (m1: its second metadata word), behind one jump.  Case j = 0 .. G, 72 bytes: 4 products of the
+// upper part into stripe j (32 bytes, jumped over where the step has none), 4 of the lower part into stripe j - 1, a
+// branch to the end; behind the last case an empty step ends.  In assembly because an accumulator is fixed by its
+// instruction and the compiler has no cheap way to choose one: a chain of comparisons runs through all G + 1 of them,
+// most as taken branches, and with a switch or a tree the register allocator spills.
+// Wait states are kept by hand: four scalar instructions lie between what writes the operands and the first product,
+// products of one accumulator are at least a step's other half apart, and the caller waits before it reads them.
+template <bool BF16, int G>
+__device__ __forceinline__ void multiply(float4v (&acc)[G][kBlkCT], const short8v (&x)[kBlkCT], short8v wl, short8v wh, uint32_t m1) {
+    // from behind s_getpc: the 12 bytes of the jump itself, the case, its upper part where m1's bit 13 is clear
+    const uint32_t skip = min((m1 >> 8) & 15u, (uint32_t)(G + 1)) * 72u + 44u - ((m1 >> 8) & 32u);
+#define UBP_JUMP "s_getpc_b64 vcc\n\ts_add_u32 vcc_lo, vcc_lo, %[skip]\n\ts_addc_u32 vcc_hi, vcc_hi, 0\n\ts_setpc_b64 vcc\n\t"
+#define UBP_ONE(T, J, C, W) "v_mfma_f32_16x16x32_" T " %[a" #J #C "], %[x" #C "], %[" W "], %[a" #J #C "]\n\t"
+#define UBP_FOUR(T, J, W) UBP_ONE(T, J, 0, W) UBP_ONE(T, J, 1, W) UBP_ONE(T, J, 2, W) UBP_ONE(T, J, 3, W)
+#define UBP_NONE "s_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\t"
+#define UBP_LEAVE "s_branch .Lstep_done%=\n\ts_nop 0\n\t"
+#define UBP_CASE(T, J, BELOW) UBP_FOUR(T, J, "wh") UBP_FOUR(T, BELOW, "wl") UBP_LEAVE
+#define UBP_FIRST(T) UBP_JUMP UBP_FOUR(T, 0, "wh") UBP_NONE UBP_LEAVE
+#define UBP_LAST(T, BELOW) UBP_NONE UBP_FOUR(T, BELOW, "wl") UBP_LEAVE UBP_NONE ".Lstep_done%=:"
+#define UBP_ACC(J) [a##J##0] "+v"(acc[J][0]), [a##J##1] "+v"(acc[J][1]), [a##J##2] "+v"(acc[J][2]), [a##J##3] "+v"(acc[J][3])
+#define UBP_IN [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [wl] "v"(wl), [wh] "v"(wh), [skip] "s"(skip)
+#define UBP_MULTIPLY(T)                                                                                                                 \
+    if constexpr (G == 5)                                                                                                               \
+        asm(UBP_FIRST(T) UBP_CASE(T, 1, 0) UBP_CASE(T, 2, 1) UBP_CASE(T, 3, 2) UBP_CASE(T, 4, 3) UBP_LAST(T, 4)                          \
+            : UBP_ACC(0), UBP_ACC(1), UBP_ACC(2), UBP_ACC(3), UBP_ACC(4) : UBP_IN : "vcc", "scc");                                       \
+    else if constexpr (G == 4)                                                                                                          \
+        asm(UBP_FIRST(T) UBP_CASE(T, 1, 0) UBP_CASE(T, 2, 1) UBP_CASE(T, 3, 2) UBP_LAST(T, 3)                                            \
+            : UBP_ACC(0), UBP_ACC(1), UBP_ACC(2), UBP_ACC(3) : UBP_IN : "vcc", "scc");                                                   \
+    else                                                                                                                                \
+        asm(UBP_FIRST(T) UBP_CASE(T, 1, 0) UBP_LAST(T, 1) : UBP_ACC(0), UBP_ACC(1) : UBP_IN : "vcc", "scc")
+    static_assert(G == 5 || G == 4 || G == 2, "its cases are written out");
+    if constexpr (BF16) {
+        UBP_MULTIPLY("bf16");
+    } else {
+        UBP_MULTIPLY("f16");
+    }
+#undef UBP_MULTIPLY
+#undef UBP_IN
+#undef UBP_ACC
+#undef UBP_LAST
+#undef UBP_FIRST
+#undef UBP_CASE
+#undef UBP_LEAVE
+#undef UBP_NONE
+#undef UBP_FOUR
+#undef UBP_ONE
+#undef UBP_JUMP
+}
+
 // One workgroup = NP producer wavefronts + up to 16 - NP consumer wavefronts on one tile of 64
 // columns of X / Y.
 //  * Producers stage X in 64-row chunks into a ring of LDS slots (ring row = X row mod 1024)
@@ -309,24 +358,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
                 const bool inA = (uint32_t)n >= oA, inB = (uint32_t)n >= oB;
                 const uint4v wl = {inA ? f[0] : 0u, inA ? f[1] : 0u, inB ? f[2] : 0u, inB ? f[3] : 0u};
                 const uint4v wh = {inA ? 0u : f[0], inA ? 0u : f[1], inB ? 0u : f[2], inB ? 0u : f[3]};
-                const short8v wlo = __builtin_bit_cast(short8v, wl), whi = __builtin_bit_cast(short8v, wh);
-                const uint32_t jj = (m1 >> 8) & 15u;
-                const bool do_hi = (m1 & 0x2000u) != 0;
-#pragma unroll
-                for (int j1 = 0; j1 <= G; ++j1) {
-                    if (jj == (uint32_t)j1) {
-                        constexpr int kLast = G - 1;
-                        const int jl = j1 >= 1 ? j1 - 1 : 0, jh = j1 < G ? j1 : kLast; // (clamped: the guarded-out uses are dead code)
-                        if (j1 >= 1) {
-#pragma unroll
-                            for (int c = 0; c < CT; ++c) acc[jl][c] = mfma16<BF16>(xf[c], wlo, acc[jl][c]);
-                        }
-                        if (j1 < G && do_hi) {
-#pragma unroll
-                            for (int c = 0; c < CT; ++c) acc[jh][c] = mfma16<BF16>(xf[c], whi, acc[jh][c]);
-                        }
-                    }
-                }
+                multiply<BF16, G>(acc, xf, __builtin_bit_cast(short8v, wl), __builtin_bit_cast(short8v, wh), m1);
                 issue(d);
             }
             li += D;
@@ -334,6 +366,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     }
     release_upto(a.nch); // the last step's reads were consumed by its MFMAs
     if (broken && lane == 0) atomicOr(a.err, 2u);
+    asm volatile("s_nop 15\n\ts_nop 15"); // (the last products, which the compiler does not see as such, are in the accumulators)
 
     // ---- store: lane (g = lane/16, n = lane%16) holds pixels col0 + 16*c + 4*g + v of row
     // 16*(stripe0 + j) + n, j < stripes.  Rows no block touches are stored as zeros like any other.
