@@ -23,7 +23,13 @@ constexpr int kBlkCT = 4; // 64-pixel column tiles (as many ring rows as the rin
 constexpr int kBlkTile = 256;
 constexpr int kBlkRing = ring_rows(kBlkCT) * ring_pitch(kBlkCT);
 
-// The products of a step (m1: its second metadata word), behind one jump.  Case j = 0 .. G, 72 bytes: 4 products of the
+// Where a step's products begin (m1: its second metadata word), in dwords from behind the s_getpc in multiply(): the 12
+// bytes of the jump itself, the case, its upper part where bit 13 is clear.
+template <int G> __device__ __forceinline__ uint32_t multiply_entry(uint32_t m1) {
+    return min((m1 >> 8) & 15u, (uint32_t)(G + 1)) * 18u + 11u - ((m1 >> 10) & 8u);
+}
+
+// The products of a step, behind one jump.  Case j = 0 .. G, 72 bytes: 4 products of the
 // upper part into stripe j (32 bytes, jumped over where the step has none), 4 of the lower part into stripe j - 1, a
 // branch to the end; behind the last case an empty step ends.  In assembly because an accumulator is fixed by its
 // instruction and the compiler has no cheap way to choose one: a chain of comparisons runs through all G + 1 of them,
@@ -31,10 +37,8 @@ constexpr int kBlkRing = ring_rows(kBlkCT) * ring_pitch(kBlkCT);
 // Wait states are kept by hand: four scalar instructions lie between what writes the operands and the first product,
 // products of one accumulator are at least a step's other half apart, and the caller waits before it reads them.
 template <bool BF16, int G>
-__device__ __forceinline__ void multiply(float4v (&acc)[G][kBlkCT], const short8v (&x)[kBlkCT], short8v wl, short8v wh, uint32_t m1) {
-    // from behind s_getpc: the 12 bytes of the jump itself, the case, its upper part where m1's bit 13 is clear
-    const uint32_t skip = min((m1 >> 8) & 15u, (uint32_t)(G + 1)) * 72u + 44u - ((m1 >> 8) & 32u);
-#define UBP_JUMP "s_getpc_b64 vcc\n\ts_add_u32 vcc_lo, vcc_lo, %[skip]\n\ts_addc_u32 vcc_hi, vcc_hi, 0\n\ts_setpc_b64 vcc\n\t"
+__device__ __forceinline__ void multiply(float4v (&acc)[G][kBlkCT], const short8v (&x)[kBlkCT], short8v wl, short8v wh, uint32_t entry) {
+#define UBP_JUMP "s_getpc_b64 vcc\n\ts_lshl2_add_u32 vcc_lo, %[entry], vcc_lo\n\ts_addc_u32 vcc_hi, vcc_hi, 0\n\ts_setpc_b64 vcc\n\t"
 #define UBP_ONE(T, J, C, W) "v_mfma_f32_16x16x32_" T " %[a" #J #C "], %[x" #C "], %[" W "], %[a" #J #C "]\n\t"
 #define UBP_FOUR(T, J, W) UBP_ONE(T, J, 0, W) UBP_ONE(T, J, 1, W) UBP_ONE(T, J, 2, W) UBP_ONE(T, J, 3, W)
 #define UBP_NONE "s_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\t"
@@ -43,7 +47,7 @@ __device__ __forceinline__ void multiply(float4v (&acc)[G][kBlkCT], const short8
 #define UBP_FIRST(T) UBP_JUMP UBP_FOUR(T, 0, "wh") UBP_NONE UBP_LEAVE
 #define UBP_LAST(T, BELOW) UBP_NONE UBP_FOUR(T, BELOW, "wl") UBP_LEAVE UBP_NONE ".Lstep_done%=:"
 #define UBP_ACC(J) [a##J##0] "+v"(acc[J][0]), [a##J##1] "+v"(acc[J][1]), [a##J##2] "+v"(acc[J][2]), [a##J##3] "+v"(acc[J][3])
-#define UBP_IN [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [wl] "v"(wl), [wh] "v"(wh), [skip] "s"(skip)
+#define UBP_IN [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [wl] "v"(wl), [wh] "v"(wh), [entry] "s"(entry)
 #define UBP_MULTIPLY(T)                                                                                                                 \
     if constexpr (G == 5)                                                                                                               \
         asm(UBP_FIRST(T) UBP_CASE(T, 1, 0) UBP_CASE(T, 2, 1) UBP_CASE(T, 3, 2) UBP_CASE(T, 4, 3) UBP_LAST(T, 4)                          \
@@ -260,12 +264,22 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
         return m;
     };
 
-    int released = 0;   // chunks this wavefront has handed back
+    // What a step asks of its metadata, worked out for 64 steps at once, one per lane, and laid so that most of it is used as
+    // it stands: bits 0-6 multiply_entry, 7-16 ring row of half A's window, 17-27 last chunk read, 28-31 row offset of
+    // half A;  7-16 ring row of half B's window, 17-26 chunks handed back, 28-31 row offset of half B.  Taking the words apart
+    // step by step: 25 scalar and vector instructions more, 4096 x 4096 with 8192 pixels 81.7 us instead of 74.5.
+    auto derive = [](uint2v m) -> uint2v {
+        const uint32_t aA = m[0] & 0xffffu, aB = m[0] >> 16;
+        static_assert(RR == 1024 && KS == 64, "10 bits of ring row, 11 of a chunk");
+        return uint2v{multiply_entry<G>(m[1]) | (aA & 1023u) << 7 | ((max(aA, aB) + 15u) >> 6) << 17 | m[1] << 28,
+                      (aB & 1023u) << 7 | (m[1] >> 22) << 17 | (m[1] >> 4) << 28};
+    };
+
     int ready_upto = 0; // chunks known to be resident
-    bool broken = false;
-    uint32_t *mine = released_p + pos; // (the producers look at positions 0 .. active - 1)
+    constexpr int kBroken = 0x7fffffff;
+    const uint32_t mine_at = lds_address(reinterpret_cast<char *>(released_p + pos)); // (the producers look at positions 0 .. active - 1)
     auto wait_published = [&](int chunk) {
-        if (chunk < ready_upto) return;
+        if (__builtin_expect(chunk < ready_upto, 1)) return;
         int spins = 0;
         for (;;) {
             const uint32_t seen = flag_load(published_p + (lane & 3)); // unused producer slots were set to "all"
@@ -273,8 +287,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
                                                                  min(__builtin_amdgcn_readlane(seen, 2), __builtin_amdgcn_readlane(seen, 3))));
             if (chunk < ready_upto) return;
             if (++spins > kSpinLimit) {
-                broken = true; // reported after the step loop (no global atomic inside it)
-                ready_upto = 0x7fffffff;
+                ready_upto = kBroken; // reported after the step loop (no global atomic inside it)
                 return;
             }
             __builtin_amdgcn_s_sleep(1);
@@ -282,22 +295,21 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     };
     // A counter only says "I will not read chunks below this again", so it can run ahead of the
     // producer (chunks this wavefront never reads) without harm.
-    auto release_upto = [&](int upto) {
-        if (upto > released) {
-            released = upto;
-            // relaxed + a compiler barrier: LDS executes this wavefront's operations in order, so
-            // every read issued before this store is served before the store becomes visible
-            asm volatile("" ::: "memory");
-            if (lane == 0) __hip_atomic_store(mine, (uint32_t)upto, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+    auto release_upto = [&](uint32_t upto) {
+        // one lane's store, without a branch and without a wait: LDS executes this wavefront's operations in order, so
+        // every read issued before it is served before it becomes visible
+        uint64_t all;
+        asm volatile("s_and_saveexec_b64 %0, 1\n\tds_write_b32 %1, %2\n\ts_mov_b64 exec, %0" : "=&s"(all) : "v"(mine_at), "v"(upto) : "memory", "scc");
     };
 
     const uint32_t ring_base = __builtin_amdgcn_readfirstlane(lds_address(smem));
     const int g = lane >> 4, n = lane & 15;
-    // this lane's part in a transposed read of a 16-row window: window row congruent to e modulo
-    // 16, 8 bytes (4 pixels) number n & 3 of the 32 bytes of pixel tile 0
+    // this lane's part in a transposed read of a 16-row window that begins at ring row r: window row congruent to e modulo
+    // 16, which is 16 ((r + 15 - e) / 16) + e, 8 bytes (4 pixels) number n & 3 of the 32 bytes of pixel tile 0.  The ring
+    // begins at LDS address 0 (the kernel has no other LDS), so that its wrap is a mask and the parts can be or-ed together.
     const uint32_t e = (uint32_t)(4 * g + (n >> 2));
-    const uint32_t k0 = ring_base + (e >> 3) * 1024u + (e & 7u) * 32u + (uint32_t)(n & 3) * 8u, k1 = k0 + 16u * (uint32_t)PITCH;
+    const uint32_t up = (15u - e) << 7, at = ring_base + (e >> 3) * 1024u + (e & 7u) * 32u + (uint32_t)(n & 3) * 8u;
+    const uint32_t nlast = (uint32_t)n << 28 | 0x0fffffffu;
 
     if (s_first < s_all) {
         uint2v mcur = load_meta();
@@ -315,33 +327,26 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
             // nothing below the first step's windows is ever read: say so before the first wait, or
             // a row group whose first block lies beyond the ring would hold the producers back
             const uint32_t first = __builtin_amdgcn_readlane(mcur[0], 0);
-            release_upto((int)(min(first & 0xffffu, first >> 16) >> 6));
+            release_upto(min(first & 0xffffu, first >> 16) >> 6);
         }
+        mcur = derive(mcur);
         int li = 0; // index of the round's first step within the metadata block
         for (int s = s_first; s < s_all; s += D) {
             if (li == 64) {
                 li = 0;
-                mcur = mnext;
+                mcur = derive(mnext);
                 mnext = load_meta();
             }
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 const uint32_t m0 = __builtin_amdgcn_readlane(mcur[0], li + d);
                 const uint32_t m1 = __builtin_amdgcn_readlane(mcur[1], li + d);
-                const uint32_t aA = m0 & 0xffffu, aB = m0 >> 16;
-                wait_published((int)((max(aA, aB) + 15u) >> 6));
+                wait_published((int)((m0 >> 17) & 2047u));
                 // ---- gather: the 16 + 16 window rows, four pixel tiles
                 short8v xf[CT];
                 {
-                    // (a window's rows lie 16-row aligned from row rA & ~15; those congruent to less than rA come 16 rows later)
-                    const uint32_t rA = aA & (uint32_t)(RR - 1), rB = aB & (uint32_t)(RR - 1);
-                    uint32_t tA = (e < (rA & 15u) ? k1 : k0) + (rA & ~15u) * (uint32_t)PITCH;
-                    uint32_t tB = (e < (rB & 15u) ? k1 : k0) + (rB & ~15u) * (uint32_t)PITCH;
-                    if (max(rA, rB) > (uint32_t)(RR - 16)) { // rare: over the ring's end
-                        asm volatile("");
-                        tA = ring_base + ((tA - ring_base) & (uint32_t)(RR * PITCH - 1));
-                        tB = ring_base + ((tB - ring_base) & (uint32_t)(RR * PITCH - 1));
-                    }
+                    static_assert(PITCH == 128, "a ring row's bytes are 7 bits");
+                    const uint32_t tA = ((m0 + up) & 0x1f800u) | at, tB = ((m1 + up) & 0x1f800u) | at;
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
                         const short4v p0 = lds_read_tr(tA, c * kBlkTile);
@@ -351,21 +356,20 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
                 }
                 // hand back the chunks that no later step reads: LDS executes this wavefront's
                 // operations in order, so the reads above are served before the counter moves
-                release_upto((int)(m1 >> 22));
+                release_upto((m1 >> 17) & 1023u);
                 // ---- the operand's two parts: rows n >= o stay in the stripe the block starts in
-                const uint32_t oA = m1 & 15u, oB = (m1 >> 4) & 15u;
                 const uint4v f = wf[d];
-                const bool inA = (uint32_t)n >= oA, inB = (uint32_t)n >= oB;
+                const bool inA = nlast >= m0, inB = nlast >= m1;
                 const uint4v wl = {inA ? f[0] : 0u, inA ? f[1] : 0u, inB ? f[2] : 0u, inB ? f[3] : 0u};
                 const uint4v wh = {inA ? 0u : f[0], inA ? 0u : f[1], inB ? 0u : f[2], inB ? 0u : f[3]};
-                multiply<BF16, G>(acc, xf, __builtin_bit_cast(short8v, wl), __builtin_bit_cast(short8v, wh), m1);
+                multiply<BF16, G>(acc, xf, __builtin_bit_cast(short8v, wl), __builtin_bit_cast(short8v, wh), m0 & 127u);
                 issue(d);
             }
             li += D;
         }
     }
-    release_upto(a.nch); // the last step's reads were consumed by its MFMAs
-    if (broken && lane == 0) atomicOr(a.err, 2u);
+    release_upto((uint32_t)a.nch); // the last step's reads were consumed by its MFMAs
+    if (ready_upto == kBroken && lane == 0) atomicOr(a.err, 2u);
     asm volatile("s_nop 15\n\ts_nop 15"); // (the last products, which the compiler does not see as such, are in the accumulators)
 
     // ---- store: lane (g = lane/16, n = lane%16) holds pixels col0 + 16*c + 4*g + v of row
