@@ -370,7 +370,11 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     }
     release_upto((uint32_t)a.nch); // the last step's reads were consumed by its MFMAs
     if (ready_upto == kBroken && lane == 0) atomicOr(a.err, 2u);
-    asm volatile("s_nop 15\n\ts_nop 15"); // (the last products, which the compiler does not see as such, are in the accumulators)
+    // the last products, which the compiler does not see as such, are in the accumulators behind this, and no read of them
+    // is moved ahead of it
+    asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+    for (int j = 0; j < G; ++j) asm volatile("" : "+v"(acc[j][0]), "+v"(acc[j][1]), "+v"(acc[j][2]), "+v"(acc[j][3]));
 
     // ---- store: lane (g = lane/16, n = lane%16) holds pixels col0 + 16*c + 4*g + v of row
     // 16*(stripe0 + j) + n, j < stripes.  Rows no block touches are stored as zeros like any other.
