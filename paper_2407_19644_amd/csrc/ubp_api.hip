@@ -17,14 +17,14 @@ namespace ubp {
 
 struct DeviceGuard {
     int prev = -1;
-    bool ok = true;
+    bool ok = true, changed = false; // (setting the device that is set already costs a call bound by the host, too)
     explicit DeviceGuard(int dev) {
-        if (hipGetDevice(&prev) != hipSuccess) { ok = false; prev = -1; }
-        else if (prev != dev && hipSetDevice(dev) != hipSuccess) { ok = false; prev = -1; }
+        if (hipGetDevice(&prev) != hipSuccess) ok = false;
+        else if (prev != dev) ok = changed = hipSetDevice(dev) == hipSuccess;
         if (!ok) (void)hipGetLastError(); // do not leave a sticky error for the caller's next HIP call
     }
     ~DeviceGuard() {
-        if (prev >= 0) (void)hipSetDevice(prev);
+        if (changed) (void)hipSetDevice(prev);
     }
 };
 

@@ -446,8 +446,7 @@ ubp_status launch_blk_inst(BlkArgs a, int waves, hipStream_t st, bool dry) {
     const ubp_status rc = limit.raise(reinterpret_cast<const void *>(&blk_kernel<BF16, TY, G, MAXT>));
     if (rc != UBP_OK || dry) return rc;
     const unsigned grid = 8u * (unsigned)((a.n_coltiles + 7) / 8) * (unsigned)a.n_wgrows;
-    hipLaunchKernelGGL((blk_kernel<BF16, TY, G, MAXT>), dim3(grid), dim3((unsigned)waves * 64), lds, st, a);
-    return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
+    return launch_kernel(&blk_kernel<BF16, TY, G, MAXT>, dim3(grid), dim3((unsigned)waves * 64), lds, st, a);
 }
 
 template <bool BF16, typename TY>

@@ -154,4 +154,14 @@ struct LdsLimit {
     }
 };
 
+// One launch.  By hipLaunchKernel and not by <<< >>>, whose way through the runtime's stack of launch configurations is
+// two more calls into it: small calls are bound by the host.
+template <class T> struct SameType { using type = T; };
+template <class... P>
+ubp_status launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, typename SameType<P>::type... a) {
+    void *args[] = {static_cast<void *>(&a)...};
+    (void)hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, lds, st);
+    return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
+}
+
 } // namespace ubp

@@ -167,8 +167,7 @@ ubp_status launch_direct_inst(const DirectArgs &a, int waves, hipStream_t st, bo
     DirectArgs b = a;
     b.n_tiles = (a.N + 16 * CT - 1) / (16 * CT);
     const unsigned grid = 8u * (unsigned)(((int64_t)a.nstripes * b.n_tiles + 7) / 8);
-    hipLaunchKernelGGL((direct_kernel<BF16, TY, CT>), dim3(grid), dim3((unsigned)waves * 64), lds, st, b);
-    return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
+    return launch_kernel(&direct_kernel<BF16, TY, CT>, dim3(grid), dim3((unsigned)waves * 64), lds, st, b);
 }
 
 template <bool BF16, typename TY>

@@ -393,8 +393,7 @@ ubp_status launch_one(const TileArgs &a, hipStream_t st, bool dry) {
     b.slices = (a.nstripes + TS - 1) / TS;
     const unsigned per_cu = lds <= 80 * 1024 ? 2 : 1;
     const unsigned grid = std::min(8u * (unsigned)(((int64_t)b.n_blocks * b.slices + 7) / 8), 256u * per_cu);
-    hipLaunchKernelGGL((mtile_kernel<BF16, TY, WM, WN, SM, PN, NS, NPW, SKIP, RAG>), dim3(grid), dim3((WM * WN + NPW) * 64), lds, st, b);
-    return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
+    return launch_kernel(&mtile_kernel<BF16, TY, WM, WN, SM, PN, NS, NPW, SKIP, RAG>, dim3(grid), dim3((WM * WN + NPW) * 64), lds, st, b);
 }
 
 template <bool BF16, typename TY, int WM, int WN, int SM, int PN, int NPW, int RAG>

@@ -434,8 +434,7 @@ ubp_status launch_stripe_one(StripeArgs a, int ctile0, int n_coltiles, int waves
     a.ctile0 = ctile0;
     a.n_coltiles = n_coltiles;
     const unsigned grid = 8u * (unsigned)((n_coltiles + 7) / 8) * (unsigned)a.n_wgrows;
-    hipLaunchKernelGGL((stripe_kernel<BF16, TY, G, CT, D, FAST>), dim3(grid), dim3((unsigned)waves * 64), lds, st, a);
-    return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
+    return launch_kernel(&stripe_kernel<BF16, TY, G, CT, D, FAST>, dim3(grid), dim3((unsigned)waves * 64), lds, st, a);
 }
 
 template <bool BF16, typename TY, int G, int CT>

@@ -237,9 +237,7 @@ ubp_status launch_xstat_inst(const TileArgs &a, int waves, hipStream_t st, bool 
     if (dry) return UBP_OK;
     const size_t lds = (size_t)KT * CT * 1024 + (size_t)waves * 256 * CT * sizeof(TY);
     const dim3 grid((unsigned)(8 * ((a.n_blocks + 7) / 8) * a.slices)), block((unsigned)waves * 64);
-    if (a.skip) hipLaunchKernelGGL((xstat_kernel<BF16, TY, CT, KT, true>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((xstat_kernel<BF16, TY, CT, KT, false>), grid, block, lds, st, a);
-    return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
+    return launch_kernel(a.skip ? &xstat_kernel<BF16, TY, CT, KT, true> : &xstat_kernel<BF16, TY, CT, KT, false>, grid, block, lds, st, a);
 }
 
 template <bool BF16, typename TY>

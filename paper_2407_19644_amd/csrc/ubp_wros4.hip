@@ -178,9 +178,7 @@ template <int BH> ubp_status launch_bh(const Wros4Args &a, int PX, int waves, hi
                                    : limit32.raise(reinterpret_cast<const void *>(&wros4_kernel<BH, 32>));
     if (rc != UBP_OK || dry) return rc;
     const dim3 grid(8u * (unsigned)(((int64_t)a.n_tiles * a.slices + 7) / 8)), block((unsigned)waves * 64);
-    if (PX == 64) hipLaunchKernelGGL((wros4_kernel<BH, 64>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((wros4_kernel<BH, 32>), grid, block, lds, st, a);
-    return hipGetLastError() == hipSuccess ? UBP_OK : UBP_ERR_DEVICE;
+    return launch_kernel(PX == 64 ? &wros4_kernel<BH, 64> : &wros4_kernel<BH, 32>, grid, block, lds, st, a);
 }
 
 } // namespace
