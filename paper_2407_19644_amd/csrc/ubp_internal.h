@@ -183,6 +183,10 @@ struct DirectLayout {
 
 // Accumulator quads per block column of the fp32 matrix kernel, as a power of two (it has 4 slots each).
 constexpr int wros4_quads(int bh) { return bh <= 4 ? 1 : bh <= 8 ? 2 : 4; }
+// Records in flight per wavefront, and records to a round of its loop: it loads, and walks for nothing, up to 2 x kWros4Depth - 1
+// records behind the last one.
+constexpr int kWros4Depth = 4;
+constexpr int kWros4Spare = 2 * kWros4Depth - 1;
 // Rows of X that its LDS holds at PX pixels: all of K rounded up to 8, and a row of zeros, of 4 PX bytes each.
 constexpr int wros4_max_K(int PX) { return (160 * 1024 / (4 * PX) - 1) / 8 * 8; }
 
@@ -193,12 +197,13 @@ constexpr int wros4_max_K(int PX) { return (160 * 1024 / (4 * PX) - 1) / 8 * 8; 
 //             (K rounded up to 8), where the kernel keeps zeros, for a column that fills up.  Second: byte
 //             g = output rows that are complete after group g.  (Where more than 255 rows end behind one group,
 //             groups without columns follow.)
+//   (Both end with kWros4Spare records that hold nothing: zero weights, rows of zeros, no row complete.)
 //   rec_of_row : [M] the record with the first group of this or a later start row
 //   rec_of_end : [M] the record with the group behind which the output row is complete, -1 before the first group
 //   row_of_rec : [n_records + 1] the output row that is next to be complete when the record begins, M at the end
 struct Wros4Layout {
     bool built = false;
-    int n_records = 0;       // (0 also where nothing is kept)
+    int n_records = 0;       // without the spare ones (0 also where nothing is kept)
     bool usable = false;
     std::vector<float> weights;
     std::vector<uint32_t> offsets;

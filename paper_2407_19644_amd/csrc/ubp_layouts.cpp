@@ -299,20 +299,23 @@ void build_wros4(const ubp_packed *p, Wros4Layout &L) {
     const float *vals = reinterpret_cast<const float *>(p->values.data());
     int64_t most = M / 255 + 1; // groups, at most
     for (int i = 0; i + bh <= M; ++i) most += ((int64_t)(p->indptr[(size_t)i + 1] - p->indptr[(size_t)i]) * bw + 3) / 4;
-    L.weights.reserve((size_t)((most + per - 1) / per) * 64);
-    L.offsets.reserve((size_t)((most + per - 1) / per) * 32);
+    L.weights.reserve((size_t)((most + per - 1) / per + kWros4Spare) * 64);
+    L.offsets.reserve((size_t)((most + per - 1) / per + kWros4Spare) * 32);
     int64_t groups = 0;
     int64_t last = -1; // the group that rows which end now end behind
     L.rec_of_row.resize((size_t)M);
     L.rec_of_end.assign((size_t)M, -1);
     auto ends_byte = [&](int64_t g) { return reinterpret_cast<uint8_t *>(&L.offsets[(size_t)(g / per) * 32 + 16]) + g % per; };
+    auto add_record = [&]() {
+        L.weights.resize(L.weights.size() + 64, 0.f);
+        const size_t o = L.offsets.size();
+        L.offsets.resize(o + 32, 0u);
+        std::fill_n(L.offsets.begin() + (std::ptrdiff_t)o, 16, zeros);
+    };
     auto open_group = [&](int row) {
         if (groups % per == 0) {
             L.row_of_rec.push_back(row);
-            L.weights.resize(L.weights.size() + 64, 0.f);
-            const size_t o = L.offsets.size();
-            L.offsets.resize(o + 32, 0u);
-            std::fill_n(L.offsets.begin() + (std::ptrdiff_t)o, 16, zeros);
+            add_record();
         }
         last = groups++;
     };
@@ -335,6 +338,7 @@ void build_wros4(const ubp_packed *p, Wros4Layout &L) {
     }
     L.row_of_rec.push_back(M);
     const size_t records = L.weights.size() / 64;
+    for (int i = 0; i < kWros4Spare; ++i) add_record();
     L.usable = L.weights.size() * 4 < (size_t(1) << 31);
     L.n_records = (int)records;
 }

@@ -29,7 +29,8 @@ __device__ __forceinline__ void load4_to_lds(const void *gbase, uint32_t lane_of
 //    results are the same bit for bit, Inf and NaN included.
 //  * The accumulator of a product is fixed by its instruction, so rotating the weights would ask for a branch per
 //    row (4 us more on the layer below); after a row the other accumulator rows move up by one register instead.
-//  * The columns come as a stream of records (64 weights in one load, row offsets in another, D records ahead), in
+//  * The columns come as a stream of records (64 weights in one load, row offsets in another, D records ahead, so that the
+//    stream ends with spare records: a buffer's bounds check does not count the scalar offset that the records are reached by), in
 //    groups of 4 columns of one start row, the last ones filled up with zero weights and a row of zeros.
 //    A group's addresses are formed two groups ahead and its rows of X read one group ahead.
 // What bounds it: the matrix instructions' and the LDS reads' issue and the row ends, each about a third of the
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(1024) void wros4_kernel(Wros4Args a) {
     constexpr int Q = (BH + 3) / 4;                          // accumulator quads
     constexpr int QP = wros4_quads(BH), COLS = 16 / QP, GROUPS = COLS / 4;
     constexpr int PITCH = 4 * PX;
-    constexpr int D = 4;
+    constexpr int D = kWros4Depth;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int NW = (int)(blockDim.x >> 6);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

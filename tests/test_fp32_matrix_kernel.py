@@ -85,7 +85,8 @@ def test_the_stream_walked_as_the_kernel_walks_it(lib, case):
 
     def view(i, dt):
         return np.frombuffer((ctypes.c_char * (sizes[i] * 4)).from_address(arrays[i]), dt).copy() if sizes[i] else np.zeros(0, dt)
-    weights, offsets = view(0, np.float32).reshape(records, 64), view(1, np.uint32).reshape(records, 32)
+    weights, offsets = view(0, np.float32).reshape(-1, 64), view(1, np.uint32).reshape(-1, 32)
+    assert len(weights) == len(offsets)
     rec_of_row, rec_of_end, row_of_rec = (view(i, np.int32) for i in (2, 3, 4))
     lib.ubp_packed_free(h)
     slots = 4 if bh <= 4 else 8 if bh <= 8 else 16
@@ -115,20 +116,23 @@ def test_the_stream_walked_as_the_kernel_walks_it(lib, case):
                     i += 1
             finish(row_of_rec[rec0] - i)
             rec = rec0
+            loaded = rec0 + 4                                       # records of which the first 4 are under way before the loop
             while rec < rec1:
-                for _ in range(4):                                  # a round of the kernel; it reads zeros behind the stream's end
-                    if rec < records:
-                        for c in range(cols):
-                            row = int(offsets[rec, c])
-                            assert row % 256 == 0 and (row // 256 < K or row // 256 == zero)
-                            w = weights[rec, c * slots:(c + 1) * slots]
-                            assert row // 256 < K or not w.any()
-                            assert not w[bh:].any()
-                            for s in range(bh if row // 256 < K else 0):
-                                acc[s].append((row // 256, w[s]))
-                            if c % 4 == 3:
-                                finish((int(offsets[rec, 16]) >> (8 * (c // 4))) & 255)
+                for _ in range(4):                                  # a round of the kernel; each record walked is replaced by one more
+                    for c in range(cols):
+                        row = int(offsets[rec, c])
+                        assert row % 256 == 0 and (row // 256 < K or row // 256 == zero)
+                        w = weights[rec, c * slots:(c + 1) * slots]
+                        assert row // 256 < K or not w.any()
+                        assert not w[bh:].any()
+                        assert rec < records or (row // 256 == zero and offsets[rec, 16] == 0)
+                        for s in range(bh if row // 256 < K else 0):
+                            acc[s].append((row // 256, w[s]))
+                        if c % 4 == 3:
+                            finish((int(offsets[rec, 16]) >> (8 * (c // 4))) & 255)
                     rec += 1
+                    loaded += 1
+            assert loaded <= len(weights), "records are loaded past the stream's end"
             assert done == list(range(lo, hi)), (rpr, lo, done)
 
 
