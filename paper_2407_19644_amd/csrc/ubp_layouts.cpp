@@ -307,7 +307,7 @@ void build_wros4(const ubp_packed *p, Wros4Layout &L) {
     L.rec_of_end.assign((size_t)M, -1);
     auto ends_byte = [&](int64_t g) { return reinterpret_cast<uint8_t *>(&L.offsets[(size_t)(g / per) * 32 + 16]) + g % per; };
     auto add_record = [&]() {
-        L.weights.resize(L.weights.size() + 64, 0.f);
+        L.weights.resize(L.weights.size() + 64, -0.f); // (times +0 a sum's bits stay as they are, those of -0 too)
         const size_t o = L.offsets.size();
         L.offsets.resize(o + 32, 0u);
         std::fill_n(L.offsets.begin() + (std::ptrdiff_t)o, 16, zeros);

@@ -31,7 +31,7 @@ __device__ __forceinline__ void load4_to_lds(const void *gbase, uint32_t lane_of
 //    row (4 us more on the layer below); after a row the other accumulator rows move up by one register instead.
 //  * The columns come as a stream of records (64 weights in one load, row offsets in another, D records ahead, so that the
 //    stream ends with spare records: a buffer's bounds check does not count the scalar offset that the records are reached by), in
-//    groups of 4 columns of one start row, the last ones filled up with zero weights and a row of zeros.
+//    groups of 4 columns of one start row, the last ones filled up with weights -0 and a row of +0, whose products leave every sum as it is.
 //    A group's addresses are formed two groups ahead and its rows of X read one group ahead.
 // What bounds it: the matrix instructions' and the LDS reads' issue and the row ends, each about a third of the
 // time; an address per vector instruction, which gets in the way of the matrix instructions, took 25 us instead of 21.
