@@ -439,6 +439,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         a.N = N;
         a.nrg = L.nrg;
         a.nch = L.nch;
+        a.ring_bytes = std::min(ring_rows(4), L.nch * kSlotRows) * ring_pitch(4);
         a.n_coltiles = N / 64;
         a.n_wgrows = s.wg_rows;
         a.n_producers = s.NP;

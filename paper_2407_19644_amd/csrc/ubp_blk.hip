@@ -21,7 +21,6 @@ constexpr int kBlkCT = 4; // 64-pixel column tiles (as many ring rows as the rin
 // wavefront reads together are 256 consecutive bytes (no bank conflicts without a swizzle), and the tiles' addresses
 // differ by constants.
 constexpr int kBlkTile = 256;
-constexpr int kBlkRing = ring_rows(kBlkCT) * ring_pitch(kBlkCT);
 
 // Where a step's products begin (m1: its second metadata word), in dwords from behind the s_getpc in multiply(): the 12
 // bytes of the jump itself, the case, its upper part where bit 13 is clear.
@@ -110,7 +109,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     constexpr int PITCH = ring_pitch(CT);
     constexpr int NINST = KS / 8; // direct-to-LDS instructions per chunk (1 KB each: 8 rows)
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    uint32_t *published_p = reinterpret_cast<uint32_t *>(smem + kBlkRing); // [4] chunks landed, per producer
+    uint32_t *published_p = reinterpret_cast<uint32_t *>(smem + a.ring_bytes); // [4] chunks landed, per producer
     uint32_t *released_p = published_p + 16;                                   // [16] per consumer wavefront
 
     // workgroup -> (column tile, workgroup row): consecutive workgroup ids go round-robin over the
@@ -391,7 +390,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
             constexpr int PR = RB / 16;       // 16-byte pieces per row
             constexpr int RP = 256 / RB;      // rows per 256 bytes (one pass over the banks)
             constexpr int NI = PR / 4;        // store instructions per stripe
-            char *scratch = smem + kBlkRing + 32 * sizeof(uint32_t) + wave * a.out_bytes;
+            char *scratch = smem + a.ring_bytes + 32 * sizeof(uint32_t) + wave * a.out_bytes;
 #pragma unroll
             for (int j = 0; j < G; ++j) {
                 if (j >= stripes) break;
@@ -439,9 +438,9 @@ ubp_status launch_blk_inst(BlkArgs a, int waves, hipStream_t st, bool dry) {
     // ring + the progress counters + (16-bit Y, where it fits) the consumers' output rows
     if (sizeof(TY) == 2) {
         const size_t want = (size_t)16 * 16 * kBlkCT * 2;
-        if ((size_t)kBlkRing + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * want <= 160 * 1024) a.out_bytes = (int)want;
+        if ((size_t)a.ring_bytes + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * want <= 160 * 1024) a.out_bytes = (int)want;
     }
-    const size_t lds = (size_t)kBlkRing + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * a.out_bytes;
+    const size_t lds = (size_t)a.ring_bytes + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * a.out_bytes;
     static LdsLimit limit; // per instantiation
     const ubp_status rc = limit.raise(reinterpret_cast<const void *>(&blk_kernel<BF16, TY, G, MAXT>));
     if (rc != UBP_OK || dry) return rc;
