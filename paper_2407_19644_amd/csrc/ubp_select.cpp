@@ -88,15 +88,8 @@ struct MaxTree {
         scores.resize(padded((int64_t)scores.size()), kNegInf); // (room for that: see copy_of)
         level.push_back(std::move(scores));
         while (level.back().size() > kWidth) level.emplace_back(padded((int64_t)(level.back().size() / kWidth)), kNegInf);
-        fill();
-    }
-    void fill() {
         for (size_t l = 0; l + 1 < level.size(); ++l)
             for (size_t i = 0; i < level[l].size() / kWidth; ++i) level[l + 1][i] = largest(&level[l][i * kWidth]);
-    }
-    void scale(double by) {
-        for (double &s : level[0]) s *= by;
-        fill();
     }
     static size_t padded(int64_t n) { return (size_t)((n + kWidth - 1) / kWidth * kWidth); }
 #if defined(__SSE2__)
@@ -218,9 +211,7 @@ int64_t expand(std::vector<double> &&S, int32_t N, int64_t m, int64_t *I) {
     Remaining list(b);
     std::vector<int64_t> right((size_t)std::min<int64_t>(N, b));
     std::vector<uint64_t> kept((size_t)(b + 63) / 64, 0);
-    // (The sum of two scores stays finite: an infinity would make differences that have no order.)
     MaxTree tree(std::move(S));
-    if (tree.most() > 0x1p1015) tree.scale(0x1p-8);
     Changes changes{tree};
     int64_t got = 0;
     while (got < m) {
@@ -238,7 +229,10 @@ int64_t expand(std::vector<double> &&S, int32_t N, int64_t m, int64_t *I) {
             if (left < 0) break;
             const double joined = N - n < n_right ? tree.score(right[(size_t)(N - n)]) : kNegInf;
             double &s = tree.score(left);
-            s = s + joined - top;
+            // (Where two scores pass the largest double their difference to top does not: s, joined <= top.  An infinity would
+            // make differences that have no order.)
+            const double sum = s + joined;
+            s = sum <= std::numeric_limits<double>::max() ? sum - top : ((0.25 * s + 0.25 * joined) - 0.25 * top) * 4.0;
             changes.add(left);
         }
         // k and the N-1 entries after it leave the list

@@ -38,6 +38,17 @@ def test_scores_whose_sums_pass_the_largest_double():
         assert ubp.select_bed(np.ldexp(S, 1024), N, m).tolist() == ubp.select_bed(S, N, m).tolist()
 
 
+def test_the_smallest_scores_beside_the_largest():
+    """Scores keep all their bits beside ones whose sums pass the largest double."""
+    tiny = 2.0 ** -1074
+    for top in (2.0 ** 1000, 2.0 ** 1016, 1.7e308):
+        S = np.array([3 * tiny, top, 5 * tiny, 4 * tiny, 6 * tiny, -tiny])
+        for m in range(1, 7):
+            assert ubp.select_bed(S, 1, m).tolist() == sel.select_bed(S, 1, m), (top, m)
+    S = np.array([top, -np.inf, 3 * tiny, -np.inf, 5 * tiny, -np.inf, 4 * tiny, -np.inf, top, 0.75 * top, 0.5 * top, -np.inf])
+    assert [ubp.select_bed(S, 2, m).tolist() for m in (1, 2, 3, 4, 5)] == [[0], [0, 8], [0, 8, 10], [0, 4, 8, 10], [0, 4, 6, 8, 10]]
+
+
 @pytest.mark.parametrize("M,K,bh,bw", [(1, 1, 1, 1), (7, 130, 7, 1), (9, 65, 3, 1), (64, 64, 4, 2), (129, 200, 16, 3), (3000, 3, 5, 1), (140000, 2, 2, 1)])
 def test_scores_of_odd_shapes(M, K, bh, bw):
     """Pieces of 8 rows by 64 column groups, and single columns where M is large; every fp16 and bf16 bit pattern that is a number."""
