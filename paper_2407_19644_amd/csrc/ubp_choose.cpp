@@ -341,7 +341,8 @@ void wros4_shape(const ubp_packed *p, int N, int rpr, Shape &s) {
             for (int waves : {4, 8, 16}) {
                 const int w = (int)std::min<int64_t>(waves, ((int64_t)p->M + r - 1) / r);
                 const int64_t slices = ((int64_t)p->M + (int64_t)r * w - 1) / ((int64_t)r * w);
-                if (((int64_t)N + px - 1) / px * slices >= (int64_t(1) << 22)) continue; // a launch has fewer than 2^32 threads
+                // (a launch has fewer than 2^32 threads: workgroups, which come in eights, times up to 1024)
+                if ((((int64_t)N + px - 1) / px * slices + 7) / 8 * 8 >= (int64_t(1) << 22)) continue;
                 const double t = estimate_wros4(p, N, px, w, r);
                 if (t < best) {
                     best = t;

@@ -154,6 +154,21 @@ def test_where_it_is_used(lib):
         lib.ubp_packed_free(h)
 
 
+def test_launches_have_fewer_than_2_to_the_32_threads(lib):
+    """Workgroups come in eights: 64-pixel tiles times slices of rows up to 2^22 - 1 would be a launch of 2^22 workgroups of 1024."""
+    M, K = 23 * 64, 16                                              # 23 slices of 16 wavefronts of 4 rows
+    W = make_weights(M, K, 5, "f32")
+    h = _pack(lib, W, 4, 4, select_blocks(M, K, 4, 4, 0.5, 3, "uniform", 1.1))
+    out = (ctypes.c_int * 4)()
+    for tiles in (1000, 182360, 182361, 182362):                    # 23 x 182361 = 2^22 - 1
+        for rpr in (0, 4):
+            assert lib.shape_of(h, 64 * tiles, ctypes.c_int64(64 * tiles), rpr, out) == 0
+            _, px, waves, rows = out
+            assert px == 0 or -(-(-(-64 * tiles // px) * -(-M // (rows * waves))) // 8) * 8 * waves * 64 < 2 ** 32, (tiles, rpr, list(out))
+            assert rpr == 0 or (px != 0) == (tiles < 182361), (tiles, list(out))
+    lib.ubp_packed_free(h)
+
+
 # ------------------------------------------------------------------ on the device
 # M, K, N, bh, bw, density: every block height; K around the limits of 64 and 32 pixels and of the kernel, K mod 8; N around a tile
 PRODUCTS = [(60 + bh, 40 + bh, 61 + bh, bh, 1 + bh % 3, 0.45) for bh in range(1, 17)] + [
