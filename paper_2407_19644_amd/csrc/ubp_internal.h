@@ -204,7 +204,7 @@ constexpr int wros4_max_K(int PX) { return (160 * 1024 / (4 * PX) - 1) / 8 * 8; 
 struct Wros4Layout {
     bool built = false;
     int n_records = 0;       // without the spare ones (0 also where nothing is kept)
-    bool usable = false;
+    bool usable = false;     // (the weights take less than 2 GB)
     std::vector<float> weights;
     std::vector<uint32_t> offsets;
     std::vector<int32_t> rec_of_row, rec_of_end, row_of_rec;

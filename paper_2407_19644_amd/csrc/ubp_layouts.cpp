@@ -299,8 +299,10 @@ void build_wros4(const ubp_packed *p, Wros4Layout &L) {
     const float *vals = reinterpret_cast<const float *>(p->values.data());
     int64_t most = M / 255 + 1; // groups, at most
     for (int i = 0; i + bh <= M; ++i) most += ((int64_t)(p->indptr[(size_t)i + 1] - p->indptr[(size_t)i]) * bw + 3) / 4;
-    L.weights.reserve((size_t)((most + per - 1) / per + kWros4Spare) * 64);
-    L.offsets.reserve((size_t)((most + per - 1) / per + kWros4Spare) * 32);
+    const int64_t most_records = (most + per - 1) / per + kWros4Spare;
+    if (most_records * 256 >= (int64_t(1) << 31)) return; // (asked first: a stream that is not used would take up to 6 times the weights' memory)
+    L.weights.reserve((size_t)most_records * 64);
+    L.offsets.reserve((size_t)most_records * 32);
     int64_t groups = 0;
     int64_t last = -1; // the group that rows which end now end behind
     L.rec_of_row.resize((size_t)M);
@@ -337,10 +339,9 @@ void build_wros4(const ubp_packed *p, Wros4Layout &L) {
         L.rec_of_end[(size_t)i] = (int32_t)(last / per);
     }
     L.row_of_rec.push_back(M);
-    const size_t records = L.weights.size() / 64;
+    L.n_records = (int)(L.weights.size() / 64);
     for (int i = 0; i < kWros4Spare; ++i) add_record();
-    L.usable = L.weights.size() * 4 < (size_t(1) << 31);
-    L.n_records = (int)records;
+    L.usable = true;
 }
 
 // ---------------------------------------------------------------- block kernel layout

@@ -168,6 +168,15 @@ def test_dense_tiles_at_any_k_and_pitch(lib):
             assert rc == OK and c["kernel"] == 5, (ldx, pins, c)
 
 
+def test_a_stream_too_large_for_the_fp32_matrix_kernel_is_not_built(lib):
+    """140 million columns, 16 bytes each in that kernel's stream: the vector kernel takes the layer, and nothing is laid out for the other."""
+    M, K = 200000, 700
+    layer = Layer(lib, M, K, 1, K, None, W=np.zeros((M, K), np.float32), dtype="f32", blocks=np.stack([np.arange(M), np.zeros(M)], axis=1))
+    lib.peak_bytes()
+    rc, c = layer.choice(64)
+    assert rc == OK and c["kernel"] == 1 and lib.peak_bytes() < 1 << 20
+
+
 def test_a_pinned_kernel_is_the_kernel_that_runs(lib):
     """Kernels 2, 6 and 7 named without a shape, on layers where the automatic choice is another kernel."""
     for M, K, bh, bw, d, N in ((160, 1100, 4, 4, 0.25, 256), (64, 64, 4, 4, 0.6, 128), (90, 1280, 16, 16, 0.15, 1280)):
