@@ -289,6 +289,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
     const size_t ysz = (y_dtype == UBP_F32) ? 4 : 2;
     const bool vec_ok = (ldx % 8 == 0) && (reinterpret_cast<uintptr_t>(X_dev) % 16 == 0) && ((ldy * ysz) % 16 == 0) &&
                         (reinterpret_cast<uintptr_t>(Y_dev) % 16 == 0);
+    const int64_t ldx_bytes = std::min(ldx, int64_t(1) << 60) * dtype_size(p->dtype); // (a single row may claim any pitch)
     const bool bf16 = p->dtype == UBP_BF16, y_f32 = y_dtype == UBP_F32;
 
     Shape s;
@@ -306,7 +307,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         if (known) {
             s = known->shape;
         } else {
-            rc = resolve(p, N, ldx * 2, vec_ok, ysz, pl, s);
+            rc = resolve(p, N, ldx_bytes, vec_ok, ysz, pl, s);
             if (rc != UBP_OK) return rc;
             if (!plan) {
                 p->choices[p->next_choice] = Choice{N, ldx, vec_ok, ysz, s};
@@ -329,7 +330,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
                 std::memset(&tp, 0, sizeof tp);
                 tp.kernel = 2;
                 tp.col_tiles = 4;
-                rc = resolve(p, N, ldx * 2, vec_ok, ysz, tp, tail);
+                rc = resolve(p, N, ldx_bytes, vec_ok, ysz, tp, tail);
                 if (rc == UBP_OK) rc = upload_stripe_layout(p, layout_slot(tail.G, tail.CT));
                 has_tail = true;
             }

@@ -308,8 +308,10 @@ int kernel_by_matrix(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok)
 // against 10.6, 10.5, 11.4 and 11.1; lower blocks fill less of a matrix instruction: 128 x 128 in 1 x 1 blocks with 12544 pixels at
 // 2.6, 6.4 and 26 columns 6.1, 7.6 and 12.4 us against 6.8, 7.6 and 10.9, 700 x 700 in 2 x 1 blocks with 5 pixels at 3.5 and 7 columns 6.1 and 7.6
 // against 6.7 and 5.6.
+// (Rows of X at most 64 MB apart: 32-bit byte offsets within 8 of them.)
 bool wros4_able(const ubp_packed *p, int64_t ldx_bytes) {
-    return p->dtype == UBP_F32 && p->bh <= 16 && p->K <= wros4_max_K(32) && p->nb * p->bw >= (p->bh > 2 ? 2 : 6) * (int64_t)p->M && ldx_bytes <= (int64_t(1) << 25) && get_wros4_layout(p).usable;
+    return p->dtype == UBP_F32 && p->bh <= 16 && p->K <= wros4_max_K(32) && p->nb * p->bw >= (p->bh > 2 ? 2 : 6) * (int64_t)p->M &&
+           ldx_bytes <= (int64_t(1) << 26) && get_wros4_layout(p).usable;
 }
 
 // What it would take, in microseconds: per round of workgroups (an XCD's on its 32 CUs, as many to a CU as LDS and

@@ -100,7 +100,7 @@ class Layer:
     """A packed host-only handle of the driver's own copy of the host code."""
 
     def __init__(self, lib, M, K, bh, bw, density, W=None, dtype="bf16", blocks=None):
-        self.lib, self.handle = lib, ctypes.c_void_p()
+        self.lib, self.handle, self.esz = lib, ctypes.c_void_p(), 4 if dtype == "f32" else 2
         W = make_weights(M, K, 4, dtype) if W is None else W
         b = np.ascontiguousarray(select_blocks(M, K, bh, bw, density, 3, "uniform", 1.1) if blocks is None else blocks, dtype=np.int32)
         rc = lib.ubp_pack(W.ctypes.data_as(ctypes.c_void_p), {"f32": 0, "f16": 1, "bf16": 2}[dtype], M, K, ctypes.c_int64(K), bh, bw,
@@ -115,7 +115,7 @@ class Layer:
         for k, v in plan.items():
             setattr(pl, k, v)
         out = (ctypes.c_int * 8)()
-        rc = self.lib.choice(self.handle, N, ctypes.c_int64(2 * ldx), int(aligned), ysz, ctypes.byref(pl), out)
+        rc = self.lib.choice(self.handle, N, ctypes.c_int64(self.esz * ldx), int(aligned), ysz, ctypes.byref(pl), out)
         return rc, dict(zip(("kernel", "shape", "G", "CT", "waves", "NP", "wg_rows", "rpr"), out))
 
     def __del__(self):

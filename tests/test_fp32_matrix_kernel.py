@@ -33,7 +33,7 @@ extern "C" int shape_of(const ubp_packed *p, int N, int64_t ldx, int rpr, int *o
     ubp_plan pl = {};
     pl.kernel = 1;
     pl.rows_per_range = rpr;
-    const int rc = ubp::resolve(p, N, 2 * ldx, true, 4, pl, s);
+    const int rc = ubp::resolve(p, N, 4 * ldx, true, 4, pl, s);
     const int f[4] = {s.kernel, s.px, s.px_waves, s.rpr};
     for (int i = 0; i < 4; ++i) out[i] = f[i];
     return rc;
@@ -149,6 +149,7 @@ def test_where_it_is_used(lib):
                 assert lib.shape_of(h, N, ctypes.c_int64(N), rpr, out) == 0 and out[0] == 1 and out[1] in want, (K, N, rpr, list(out))
                 assert rpr == 0 or out[3] == rpr
                 assert lib.shape_of(h, N, ctypes.c_int64(N), out[3], again) == 0 and list(again) == list(out)
+            assert lib.shape_of(h, N, ctypes.c_int64(1 << 24), 0, out) == 0 and out[1] in want   # 64 MB
             assert lib.shape_of(h, N, ctypes.c_int64((1 << 24) + 8), 0, out) == 0 and out[1] == 0
         assert lib.shape_of(h, 64, ctypes.c_int64(64), -1, out) == 1
         lib.ubp_packed_free(h)
