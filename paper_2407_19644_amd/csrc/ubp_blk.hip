@@ -305,7 +305,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     const int g = lane >> 4, n = lane & 15;
     // this lane's part in a transposed read of a 16-row window that begins at ring row r: window row congruent to e modulo
     // 16, which is 16 ((r + 15 - e) / 16) + e, 8 bytes (4 pixels) number n & 3 of the 32 bytes of pixel tile 0.  The ring
-    // begins at LDS address 0 (the kernel has no other LDS), so that its wrap is a mask and the parts can be or-ed together.
+    // begins at LDS address 0 (the kernel has no other LDS, see LdsLimit), so that its wrap is a mask and the parts can be or-ed together.
     const uint32_t e = (uint32_t)(4 * g + (n >> 2));
     const uint32_t up = (15u - e) << 7, at = ring_base + (e >> 3) * 1024u + (e & 7u) * 32u + (uint32_t)(n & 3) * 8u;
     const uint32_t nlast = (uint32_t)n << 28 | 0x0fffffffu;
@@ -442,7 +442,7 @@ ubp_status launch_blk_inst(BlkArgs a, int waves, hipStream_t st, bool dry) {
     }
     const size_t lds = (size_t)a.ring_bytes + 32 * sizeof(uint32_t) + (size_t)(waves - a.n_producers) * a.out_bytes;
     static LdsLimit limit; // per instantiation
-    const ubp_status rc = limit.raise(reinterpret_cast<const void *>(&blk_kernel<BF16, TY, G, MAXT>));
+    const ubp_status rc = limit.raise(reinterpret_cast<const void *>(&blk_kernel<BF16, TY, G, MAXT>), true);
     if (rc != UBP_OK || dry) return rc;
     const unsigned grid = 8u * (unsigned)((a.n_coltiles + 7) / 8) * (unsigned)a.n_wgrows;
     return launch_kernel(&blk_kernel<BF16, TY, G, MAXT>, dim3(grid), dim3((unsigned)waves * 64), lds, st, a);

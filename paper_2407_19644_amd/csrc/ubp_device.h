@@ -134,10 +134,11 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // Raises a kernel's dynamic LDS limit to all of a CU's LDS, once per device ordinal (the limit
-// belongs to the function on a device).  One instance per kernel instantiation.
+// belongs to the function on a device).  One instance per kernel instantiation.  at_zero: the kernel counts on its dynamic
+// LDS beginning at LDS address 0, which it does as long as there is no static LDS; otherwise the kernel is refused.
 struct LdsLimit {
     std::atomic<uint64_t> done{0};
-    ubp_status raise(const void *fn) {
+    ubp_status raise(const void *fn, bool at_zero = false) {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess) {
             (void)hipGetLastError();
@@ -146,6 +147,11 @@ struct LdsLimit {
         const uint64_t bit = (dev >= 0 && dev < 64) ? (uint64_t(1) << dev) : 0;
         if (bit && (done.load(std::memory_order_acquire) & bit)) return UBP_OK;
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+            (void)hipGetLastError();
+            return UBP_ERR_DEVICE;
+        }
+        hipFuncAttributes f;
+        if (at_zero && (hipFuncGetAttributes(&f, fn) != hipSuccess || f.sharedSizeBytes != 0)) {
             (void)hipGetLastError();
             return UBP_ERR_DEVICE;
         }
