@@ -1,4 +1,4 @@
-"""GPU parity of the vector kernel (1), of the direct kernel (8) and of the LDS-staged dense tiles at any alignment (9), at the
+"""GPU parity of kernel 1 on fp32 layers, of the direct kernel (8) and of the LDS-staged dense tiles at any alignment (9), at the
 edges of their tiles, against the CPU oracle."""
 import numpy as np
 import pytest
@@ -101,7 +101,8 @@ def test_rows_of_x_more_than_32_mb_apart():
 
 
 VECTOR = [
-    # M, K, N, bh, bw, density: blocks per start row around the batches of 8, 4 and 2 columns
+    # M, K, N, bh, bw, density: blocks per start row around the vector kernel's batches of 8, 4 and 2 columns.  (The fp32 matrix kernel
+    # takes the layers with several columns per row; test_fp32_matrix_kernel.py has ones that stay with the vector kernel.)
     (40, 36, 63, 4, 1, 0.5),
     (64, 64, 64, 1, 1, 0.13),
     (33, 45, 65, 5, 3, 0.5),

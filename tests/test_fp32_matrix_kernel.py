@@ -1,4 +1,5 @@
-"""The fp32 matrix kernel (kernel 1 on fp32 handles): its stream of block columns, walked on the CPU, and its products on the GPU."""
+"""The fp32 matrix kernel (kernel 1 on fp32 handles): its stream of block columns, walked on the CPU, and its products on the GPU;
+the fp32 layers that the vector kernel keeps."""
 import ctypes
 import os
 import shutil
@@ -155,6 +156,24 @@ def test_where_it_is_used(lib):
         lib.ubp_packed_free(h)
 
 
+# M, K, N, bh, bw, density: layers of the vector kernel, K too large or too few blocks for the other.  Around its batches of 8 (blocks of
+# up to 4 rows), 4 (up to 8) and 2 columns: start rows with no, one and several batches and every remainder, ends of the matrix and
+# of a pixel tile, one column and four columns a lane.
+VECTOR = [(40, 1273, 63, 4, 1, 0.02), (24, 1300, 65, 1, 1, 0.13), (33, 1275, 65, 5, 3, 0.05), (50, 1280, 130, 16, 1, 0.02), (60, 1290, 64, 8, 2, 0.1),
+          (90, 2000, 31, 3, 2, 0.002), (70, 1301, 129, 9, 4, 0.1), (30, 1273, 1, 12, 1, 0.1), (800, 1280, 1536, 4, 1, 0.02), (1040, 1288, 1028, 8, 8, 0.05),
+          (1600, 1300, 1028, 16, 2, 0.02), (90, 60, 257, 3, 2, 0.004), (512, 512, 100, 4, 1, 0.01), (300, 100, 40, 1, 1, 0.03)]
+
+
+@pytest.mark.parametrize("shape", VECTOR, ids=lambda s: "x".join(map(str, s)))
+def test_layers_of_the_vector_kernel(lib, shape):
+    M, K, N, bh, bw, d = shape
+    h = _pack(lib, make_weights(M, K, 5, "f32"), bh, bw, select_blocks(M, K, bh, bw, d, M + 1, "uniform", 1.1))
+    out = (ctypes.c_int * 4)()
+    for rpr in (0, bh, 5 * bh):
+        assert lib.shape_of(h, N, ctypes.c_int64(N), rpr, out) == 0 and list(out[:3]) == [1, 0, 0]
+    lib.ubp_packed_free(h)
+
+
 def test_launches_have_fewer_than_2_to_the_32_threads(lib):
     """Workgroups come in eights: 64-pixel tiles times slices of rows up to 2^22 - 1 would be a launch of 2^22 workgroups of 1024."""
     M, K = 23 * 64, 16                                              # 23 slices of 16 wavefronts of 4 rows
@@ -223,3 +242,21 @@ def test_product(shape):
     got, want = run(Xn, None), run(Xn, vector)
     assert np.array_equal(np.isnan(got), np.isnan(want)) and same_bits(got[~np.isnan(want)], want[~np.isnan(want)])
     p.free()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", VECTOR, ids=lambda s: "x".join(map(str, s)))
+def test_vector_kernel(shape):
+    """The layers above against the oracle and bit for bit the shifting dataflow (kernel 3)."""
+    import oracle
+    from gpu_util import check, run_spmm
+    from synthetic import decode_f64
+    M, K, N, bh, bw, d = shape
+    blocks = select_blocks(M, K, bh, bw, d, M + 1, "uniform", 1.1)
+    W, X = make_weights(M, K, K, "f32"), make_activations(K, N, N, "f32", "normal")
+    Yref, Yabs = oracle.spmm(decode_f64(W, "f32"), bh, bw, blocks, decode_f64(X, "f32"), want_abs=True)
+    want = run_spmm(W, "f32", bh, bw, blocks, X, "f32", ubp.Plan(kernel=3, rows_per_range=bh))
+    for plan, pad in ((None, 0), (ubp.Plan(kernel=1, rows_per_range=bh), 0), (ubp.Plan(kernel=1, rows_per_range=5 * bh), 3)):
+        Y = run_spmm(W, "f32", bh, bw, blocks, X, "f32", plan, ldx=N + pad, ldy=N + pad)
+        check(Y, Yref, Yabs, "f32", "f32")
+        assert np.array_equal(Y.view(np.uint64), want.view(np.uint64)), plan
