@@ -22,8 +22,8 @@ constexpr int kBlkCT = 4; // 64-pixel column tiles (as many ring rows as the rin
 // differ by constants.
 constexpr int kBlkTile = 256;
 
-// Where a step's products begin (m1: its second metadata word), in dwords from behind the s_getpc in multiply(): the 12
-// bytes of the jump itself, the case, its upper part where bit 13 is clear.
+// Where a step's products begin (m1: its second metadata word), in dwords from behind the s_getpc in multiply(): 3 of the
+// jump itself, 18 for each case before, and 8 of the upper part where that is passed over (bit 13 clear).
 template <int G> __device__ __forceinline__ uint32_t multiply_entry(uint32_t m1) {
     return min((m1 >> 8) & 15u, (uint32_t)(G + 1)) * 18u + 11u - ((m1 >> 10) & 8u);
 }
@@ -92,12 +92,16 @@ __device__ __forceinline__ void multiply(float4v (&acc)[G][kBlkCT], const short8
 //    LDS reads per pixel tile gather their 32 rows of X; two compares and eight selects split the
 //    operand into its lower-stripe and upper-stripe part; 4 + 4 MFMAs (16x16x32).  A lane reads
 //    the window row congruent to its entry number modulo 16 (the columns of a half are rotated
-//    like its rows), so an address is one select and one add away from the window's first row and
-//    the four tiles' reads differ by an immediate (with rows of 128 bytes and a swizzle six more vector instructions:
-//    4096 x 4096 with 8192 pixels 88.0 -> 86.2 us in a graph with skewed blocks, 85.4 -> 82.6 with even ones).
-// What bounds it: a wavefront's chain of scalar and vector instructions and branches, 3.5 of them to a SIMD.  Scalar
-// masks in the place of the four vector compares took 91.7 us; the reads of step s + 1 issued behind the products
-// of step s, with masks and addresses worked out while they run, 95.3; no staging at all would give 77.8.
+//    like its rows), so an address is one addition and one and-or away from the window's first row and
+//    the four tiles' reads differ by an immediate (with rows of 128 bytes and a swizzle six more vector instructions).
+// 4096 x 4096 with 8192 pixels, skewed blocks, in a graph, all in one run: 92 us, with the tiles an immediate apart 88.7,
+// the products behind one jump 86.1, the metadata taken apart for 64 steps at once 78.
+// What bounds it there: waiting as much as issue.  A SIMD takes 370 cycles per step; the step's own 18 vector and
+// 6.7 matrix instructions are 179 of them, and 40 % of the vector instructions belong to no step (polls, start-up, staging,
+// stores).  A wavefront spends 40 % of its time waiting for a counter or a load - the first chunks of a workgroup,
+// a chunk behind the heaviest row group -, 28 % waiting to issue and 32 % issuing; 12.5 of 16 are there on average.
+// Before the last two of those steps (at 86 us) scalar masks in the place of the vector compares took 91.7, and the reads of
+// step s + 1 issued behind the products of step s, with masks and addresses worked out while they run, 95.3.
 // Every wait is bounded: if one runs out the wavefront raises *err and goes on without waiting
 // (wrong numbers, but the kernel always terminates).
 template <bool BF16, typename TY, int G, int MAXT>
@@ -266,7 +270,7 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     // What a step asks of its metadata, worked out for 64 steps at once, one per lane, and laid so that most of it is used as
     // it stands: bits 0-6 multiply_entry, 7-16 ring row of half A's window, 17-27 last chunk read, 28-31 row offset of
     // half A;  7-16 ring row of half B's window, 17-26 chunks handed back, 28-31 row offset of half B.  Taking the words apart
-    // step by step: 25 scalar and vector instructions more, 4096 x 4096 with 8192 pixels 81.7 us instead of 74.5.
+    // step by step: 25 scalar and vector instructions more, 4096 x 4096 with 8192 pixels 86.1 us instead of 78.
     auto derive = [](uint2v m) -> uint2v {
         const uint32_t aA = m[0] & 0xffffu, aB = m[0] >> 16;
         static_assert(RR == 1024 && KS == 64, "10 bits of ring row, 11 of a chunk");

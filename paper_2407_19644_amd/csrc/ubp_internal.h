@@ -193,10 +193,10 @@ constexpr int wros4_max_K(int PX) { return (160 * 1024 / (4 * PX) - 1) / 8 * 8; 
 // Host image of the fp32 matrix kernel's layout: the blocks' columns in canonical order (start rows, then column
 // origins, then columns), 4 of one start row to a group (filled up with weights -0), 4 / wros4_quads(bh) groups to a record.
 //   weights : 64 floats per record: per column 4 wros4_quads(bh) slots, the block's weights from its first row on, then -0
-//   offsets : 16 pairs per record.  First of pair c: 256 x the row of X of column c mod (columns per record), 256 x
-//             (K rounded up to 8), where the kernel keeps zeros, for a column that fills up.  Second: byte
-//             g = output rows that are complete after group g.  (Where more than 255 rows end behind one group,
-//             groups without columns follow.)
+//   offsets : 32 words per record, a cache line.  Word c < 16 / wros4_quads(bh): 256 x the row of X of column c, or
+//             256 x (K rounded up to 8), where the kernel keeps zeros, for a column that fills up.  Word 16, byte g: output rows that
+//             are complete after group g.  (Where more than 255 rows end behind one group, groups without columns follow.)
+//             The other words are not used.
 //   (Both end with kWros4Spare records that hold nothing: weights -0, the row of zeros, no row complete.)
 //   rec_of_row : [M] the record with the first group of this or a later start row
 //   rec_of_end : [M] the record with the group behind which the output row is complete, -1 before the first group
