@@ -293,7 +293,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
     const bool bf16 = p->dtype == UBP_BF16, y_f32 = y_dtype == UBP_F32;
 
     Shape s;
-    Shape tail;          // block kernel: the gather kernel's shape for a ragged last column tile
+    Shape tail;          // block kernel: the gather kernel's shape for a last column tile that it leaves
     bool has_tail = false;
     {
         // Layouts are built and uploaded on first use, under the handle's lock.  A repeated call
@@ -325,7 +325,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         case 8: rc = upload_direct_layout(p); break;
         case 6:
             rc = upload_blk_layout(p, blk_slot(s.G));
-            if (rc == UBP_OK && N % 64 != 0) {
+            if (rc == UBP_OK && blk_leaves_tail(N)) {
                 ubp_plan tp;
                 std::memset(&tp, 0, sizeof tp);
                 tp.kernel = 2;
@@ -441,7 +441,7 @@ ubp_status execute(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t 
         a.nrg = L.nrg;
         a.nch = L.nch;
         a.ring_bytes = std::min(ring_rows(4), L.nch * kSlotRows) * ring_pitch(4);
-        a.n_coltiles = N / 64;
+        a.n_coltiles = blk_leaves_tail(N) ? N / 64 : (N + 63) / 64;
         a.n_wgrows = s.wg_rows;
         a.n_producers = s.NP;
         a.out_bytes = 0; // set per launch

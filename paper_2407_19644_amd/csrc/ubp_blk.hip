@@ -129,7 +129,9 @@ __global__ __launch_bounds__(MAXT) void blk_kernel(BlkArgs a) {
     const int NC = (int)(blockDim.x >> 6) - NP; // consumer wavefronts; the last NP wavefronts produce
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int col0 = ctile * NTW;
+    // the last tile of a row that is no whole number of tiles begins further left: it overlaps the one before it, whose pixels
+    // both compute and store alike
+    const int col0 = min(ctile * NTW, a.N - NTW);
     const int active = min(NC, a.nrg - wgrow * NC); // consumers the producers wait for
 
     // counters start at zero; the slots of producers that do not exist never hold anything back

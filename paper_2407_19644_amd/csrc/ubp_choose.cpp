@@ -106,16 +106,17 @@ int blk_auto_G(const ubp_packed *p) { // 5 stripes per wavefront where that save
 }
 
 // Whole blocks as operands: per round of workgroups the staging of X and a wavefront's share of the steps (two halves of
-// 16 columns each); behind them, where the last columns are no whole tile of 64, a launch of the gather kernel for those.
+// 16 columns each); behind them a launch of the gather kernel for the last columns, where they are left to it.
 // Coefficients fitted to 170 layers of 512 to 4096 rows, 1152 to 4096 columns and 64 to 8192 pixels at 3 to 20 %, even and skewed: mean error 6 %.
 double estimate_blk(const ubp_packed *p, int N, size_t ysz) {
     const int G = blk_auto_G(p), stripes = (p->M + 15) / 16;
     const int rows = ((stripes + G - 1) / G + kBlkConsumers - 1) / kBlkConsumers; // of workgroups
     const double runs = std::min(stripes, rows * kBlkConsumers), stage = 1e-3 * p->K * 4 / 2;
     const double steps = 0.5 * (double)p->nb * ((p->bw + 15) / 16);
-    const double rounds = std::ceil((N / 64 + 7) / 8 * (double)rows / 32);
+    const int tiles = blk_leaves_tail(N) ? N / 64 : (N + 63) / 64;
+    const double rounds = std::ceil((tiles + 7) / 8 * (double)rows / 32);
     return 6.663 + rounds * (1.593 * stage + 0.2611 * steps / runs) + 1.069 * 0.2e-6 * p->M * (double)N * ysz +
-           (N % 64 != 0 ? 17.59 + 15.19 * stage : 0.0);
+           (blk_leaves_tail(N) ? 17.59 + 15.19 * stage : 0.0);
 }
 
 int gather_col_tiles(int N) {

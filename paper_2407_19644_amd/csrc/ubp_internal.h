@@ -56,6 +56,10 @@ constexpr int stripe_max_threads(int G, int CT) {
 constexpr int stripe_max_waves(int G, int CT) { return stripe_max_threads(G, CT) / 64; }
 // Wavefronts of a workgroup of the block kernel.
 constexpr int kBlkConsumers = 14; // of them multiplying, at most
+// Whether the last N % 64 pixels go to the gather kernel.  Not where N is a multiple of 8: the last tile then overlaps the one
+// before it, its pieces of rows still aligned, for at most a tile's work (16 x 16 blocks, by this kernel: 4096 x 4096 at 10 % with
+// 1000 pixels 196.7 -> 35.1 us, 2048 x 4096 at 5 % with 4040 191 -> 30.1; by the kernel chosen before, which was the direct one, 40.2 and 65.1).
+constexpr bool blk_leaves_tail(int N) { return N % 8 != 0; }
 constexpr int blk_max_waves(int G) { return (G == 2 || G == 4 || G == 5) ? 16 : 0; }
 
 // Host image of the gather kernel's private re-layout of the packed weights, for one (G, CT).
@@ -285,7 +289,7 @@ struct BlkArgs {
     // of the LDS ring that are used, all of K where K is shorter than the ring: a CU then holds several workgroups (plans that
     // name this kernel: 4096 x 512 with 8192 pixels in workgroups of 8 wavefronts, one producer, 28.1 us, 37.0 with the whole ring)
     int ring_bytes;
-    int n_coltiles;          // full 64-pixel column tiles this launch covers (from pixel 0)
+    int n_coltiles;          // 64-pixel column tiles this launch covers (from pixel 0; the last one may overlap the one before)
     int n_wgrows;
     int n_producers;
     int out_bytes;           // LDS bytes per consumer for leaving 16-bit tiles as whole rows; 0: none

@@ -195,8 +195,8 @@ BLOCK_SHAPES = [(130, 600, 1000, 16, 16, 0.15), (100, 300, 328, 8, 8, 0.2), (96,
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_block_kernel(shape, dtype):
     """Whole blocks as operands (kernel 6): blocks of 16 rows and fewer, widths below, at and
-    above 16 and not a multiple of it, K below and beyond the ring, a ragged last column tile
-    (which the gather kernel serves), one or several producers, few and many consumers."""
+    above 16 and not a multiple of it, K below and beyond the ring, a ragged last column tile,
+    one or several producers, few and many consumers."""
     M, K, N, bh, bw, d = shape
     blocks, W, X = _layer(M, K, N, bh, bw, d, dtype, seed=M + K + 7)
     Yref, Yabs = _oracle(W, dtype, bh, bw, blocks, X)
@@ -207,6 +207,22 @@ def test_block_kernel(shape, dtype):
     for G, waves, NP in [(4, 3, 1), (2, 16, 4), (5, 5, 2), (2, 2, 1), (4, 16, 1), (5, 16, 2)]:
         Y = run_spmm(W, dtype, bh, bw, blocks, X, dtype, _plan(kernel=6, sub_stripes=G, waves=waves, producers=NP))
         check(Y, Yref, Yabs, dtype)
+
+
+@pytest.mark.parametrize("N,pad", [(72, 0), (120, 8), (136, 0), (1000, 0), (100, 4), (67, 5)])   # overlapping last tile; the two last: the gather kernel's
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_block_kernel_last_tile(N, pad, dtype):
+    """Rows that are no whole number of 64-pixel tiles: every pixel against the oracle, nothing beyond column N, and where the
+    last tile overlaps the one before it the bits of the same columns as a product of their own (a pixel's sums know no other)."""
+    M, K = 200, 1300
+    blocks, W, X = _layer(M, K, N, 16, 16, 0.1, dtype, seed=N)
+    Yref, Yabs = _oracle(W, dtype, 16, 16, blocks, X)
+    for y_dtype in (dtype, "f32"):
+        Y = run_spmm(W, dtype, 16, 16, blocks, X, y_dtype, _plan(kernel=6), ldx=N + pad, ldy=N + pad)
+        check(Y, Yref, Yabs, dtype, y_dtype)
+        if N % 8 == 0:
+            last = run_spmm(W, dtype, 16, 16, blocks, X[:, N - 64:], y_dtype, _plan(kernel=6))
+            assert np.array_equal(Y[:, N - 64:], last)
 
 
 GEMM_SHAPES = [(100, 200, 328, 4, 4, 0.5), (270, 700, 520, 4, 4, 0.45), (64, 64, 200, 4, 4, 0.6), (530, 96, 1000, 4, 4, 0.5),
