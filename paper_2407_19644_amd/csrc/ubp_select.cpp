@@ -88,7 +88,8 @@ bool selector_args_ok(const double *S, int64_t b, int32_t N, int64_t m, const in
 // one of them throws is thrown here, after all have ended.  A thread that cannot be had is done without.
 template <class State, class F> void share_out(size_t parts, size_t threads, F &&f) {
     constexpr size_t kMost = 8; // (a thread takes some 15 us to start)
-    threads = std::min({threads, parts, kMost, (size_t)std::thread::hardware_concurrency()});
+    threads = std::min({threads, parts, kMost});
+    if (threads > 1) threads = std::min(threads, (size_t)std::thread::hardware_concurrency()); // (which asks the system: some 2 us)
     std::atomic<size_t> next{0};
     std::mutex lock;
     std::exception_ptr thrown;
@@ -133,6 +134,15 @@ struct MaxTree {
         level[0].resize(padded(n));
         std::copy_n(S, n, level[0].data());
         std::fill(level[0].begin() + n, level[0].end(), kNegInf);
+        build();
+    }
+    void take(std::vector<double> &&scores) { // (with room for the fill at their end)
+        if (level.empty()) level.emplace_back();
+        scores.resize(padded((int64_t)scores.size()), kNegInf);
+        level[0] = std::move(scores);
+        build();
+    }
+    void build() {
         levels = 1;
         while (level[levels - 1].size() > kWidth) {
             const size_t below = level[levels - 1].size() / kWidth;
@@ -270,6 +280,11 @@ struct Workspace {
     MaxTree tree;
     Remaining list;
     std::vector<int64_t> right;
+    std::vector<double> *own = nullptr; // the scores, where they are all of them and the caller has no more use for them: not copied (16 us of 160 for 49600)
+    void fill(const double *S, int64_t n) {
+        if (own) tree.take(std::move(*own));
+        else tree.reset(S, n);
+    }
 };
 
 // Rounds over the candidates first .. first + n - 1, appended to `out`: at most `most`, and none whose score lies below `bound`.
@@ -279,7 +294,7 @@ typedef void (*Rounds)(Workspace &w, const double *S, int64_t first, int64_t n, 
 void expand(Workspace &w, const double *S, int64_t first, int64_t n, int32_t N, double bound, int64_t most, std::vector<Taken> &out) {
     MaxTree &tree = w.tree;
     Remaining &list = w.list;
-    tree.reset(S + first, n);
+    w.fill(S + first, n);
     list.reset(n);
     std::vector<int64_t> &right = w.right;
     right.resize((size_t)std::min<int64_t>(N, n));
@@ -318,7 +333,7 @@ void expand(Workspace &w, const double *S, int64_t first, int64_t n, int32_t N, 
 
 void greedy(Workspace &w, const double *S, int64_t first, int64_t n, int32_t N, double bound, int64_t most, std::vector<Taken> &out) {
     MaxTree &tree = w.tree;
-    tree.reset(S + first, n);
+    w.fill(S + first, n);
     for (int64_t got = 0; got < most; ++got) {
         const double top = tree.most();
         if (top == kNegInf || top < bound) break;
@@ -363,7 +378,7 @@ std::vector<int64_t> find_runs(const double *S, int64_t b, int32_t N) {
 // the rounds over all candidates take.
 // A selection of 13107 blocks (512 x 512 in 4 x 1 blocks at 20 %, expansion, on 16 cores): 1.74 ms by one tree over all, 1.35 by
 // runs in one thread (50 ns a round instead of 100), 1.02 in eight, scores in eight as well; one of 2048 x 512, 2 x 1, 50 %: 30 -> 11.6.
-std::vector<Taken> pick(Rounds rounds, const double *S, int64_t b, int32_t N, int64_t m) {
+std::vector<Taken> pick(Rounds rounds, const double *S, int64_t b, int32_t N, int64_t m, std::vector<double> *own) {
     std::vector<Taken> out;
     constexpr size_t kRuns = 16; // (fewer have no sample)
     constexpr int64_t kRounds = 4096; // (with fewer the sample and the threads cost what they save: 2900 rounds 485 us, by runs 567)
@@ -371,6 +386,8 @@ std::vector<Taken> pick(Rounds rounds, const double *S, int64_t b, int32_t N, in
     const size_t runs = first.size() - 1;
     if (runs < kRuns) {
         Workspace w;
+        w.own = own;
+        out.reserve((size_t)std::min(m, b));
         rounds(w, S, 0, b, N, kNegInf, m, out);
         return out;
     }
@@ -431,10 +448,10 @@ std::vector<Taken> pick(Rounds rounds, const double *S, int64_t b, int32_t N, in
 }
 
 // Expansion, then division (Algorithm 2).
-int64_t expand_and_divide(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I) {
+int64_t expand_and_divide(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I, std::vector<double> *own = nullptr) {
     if (b == 0 || m == 0) return 0;
     std::vector<uint64_t> kept((size_t)(b + 63) / 64, 0);
-    for (const Taken &t : pick(expand, S, b, N, m)) kept[(size_t)t.k / 64] |= uint64_t(1) << (t.k % 64);
+    for (const Taken &t : pick(expand, S, b, N, m, own)) kept[(size_t)t.k / 64] |= uint64_t(1) << (t.k % 64);
     int64_t got = 0;
     for (size_t w = 0; w < kept.size(); ++w)
         for (uint64_t bits = kept[w]; bits; bits &= bits - 1) I[got++] = (int64_t)(64 * w) + __builtin_ctzll(bits);
@@ -447,26 +464,29 @@ int64_t expand_and_divide(const double *S, int64_t b, int32_t N, int64_t m, int6
     return got;
 }
 
-int64_t greedy_in_order(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I) {
+int64_t greedy_in_order(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I, std::vector<double> *own = nullptr) {
     if (b == 0 || m == 0) return 0;
-    std::vector<Taken> all = pick(greedy, S, b, N, m);
+    std::vector<Taken> all = pick(greedy, S, b, N, m, own);
     if (all.empty()) return 0;
-    // (in order already where there was one run; 8 bits of the scores at a time, from the lowest, keeps equal ones in the order of the runs)
+    // (in order already where there was one run; else 8 bits of the scores at a time, from the lowest, keeps equal ones in the order of the runs)
     const auto key = [](double x) { // larger ones first; the same for zeros of either sign
         uint64_t u;
         x += 0.0;
         std::memcpy(&u, &x, 8);
         return u >> 63 ? u : ~u & ~(uint64_t(1) << 63);
     };
-    std::vector<Taken> other(all.size());
-    for (int shift = 0; shift < 64; shift += 8) {
-        size_t count[256] = {0};
-        for (const Taken &t : all) ++count[(key(t.score) >> shift) & 255];
-        if (count[(key(all[0].score) >> shift) & 255] == all.size()) continue;
-        size_t at = 0;
-        for (size_t &c : count) at += std::exchange(c, at);
-        for (const Taken &t : all) other[count[(key(t.score) >> shift) & 255]++] = t;
-        all.swap(other);
+    const auto before = [](const Taken &x, const Taken &y) { return x.score > y.score; };
+    if (!std::is_sorted(all.begin(), all.end(), before)) {
+        std::vector<Taken> other(all.size());
+        for (int shift = 0; shift < 64; shift += 8) {
+            size_t count[256] = {0};
+            for (const Taken &t : all) ++count[(key(t.score) >> shift) & 255];
+            if (count[(key(all[0].score) >> shift) & 255] == all.size()) continue;
+            size_t at = 0;
+            for (size_t &c : count) at += std::exchange(c, at);
+            for (const Taken &t : all) other[count[(key(t.score) >> shift) & 255]++] = t;
+            all.swap(other);
+        }
     }
     for (size_t t = 0; t < all.size(); ++t) I[t] = all[t].k;
     return (int64_t)all.size();
@@ -626,7 +646,9 @@ ubp_status ubp_select_blocks(const void *W, ubp_dtype dtype, int64_t ldw, int32_
     if (capacity < m || (m > 0 && !out)) { *out_nb = m; return UBP_ERR_INVALID_ARG; }
     try {
         const int64_t b = (int64_t)M * (K / bw);
-        std::vector<double> S((size_t)b);
+        std::vector<double> S;
+        S.reserve(MaxTree::padded(b));
+        S.resize((size_t)b);
         std::vector<int64_t> I((size_t)std::max<int64_t>(m, 1));
         ubp_status rc = ubp_block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S.data(), b);
         if (rc != UBP_OK) return rc;
@@ -636,7 +658,8 @@ ubp_status ubp_select_blocks(const void *W, ubp_dtype dtype, int64_t ldw, int32_
             if (rc != UBP_OK) return rc;
         } else {
             if (!scores_ok(S.data(), b)) return UBP_ERR_INVALID_ARG;
-            got = method == 0 ? greedy_in_order(S.data(), b, bh, m, I.data()) : expand_and_divide(S.data(), b, bh, m, I.data());
+            got = method == 0 ? greedy_in_order(S.data(), b, bh, m, I.data(), &S)
+                              : expand_and_divide(S.data(), b, bh, m, I.data(), &S);
         }
         rc = ubp_selection_to_blocks(I.data(), got, M, bw, out);
         if (rc != UBP_OK) return rc;
