@@ -178,7 +178,9 @@ ubp_status ubp_spmm(const ubp_packed *p, const void *X_dev, int64_t ldx, int32_t
  *                other fields set: that kernel if it takes them, else the one the matrix alone gives (6 for
  *                16-row blocks as above; on aligned rows 7, 4 or 5 by how many tiles keep a weight; 2).
  *   sub_stripes: kernels 2 and 6, 16-row stripes per wavefront (1, 2 or 4; kernel 6: 2, 4 or 5,
- *                by itself 5 where that saves a workgroup row, else 4);
+ *                by itself - with the producers, where nothing else is given - of the smallest
+ *                estimated time, and in a plan that gives waves, producers or wg_rows 5 where that
+ *                saves a workgroup row, else 4);
  *                kernels 5, 7 and 9: as above.
  *   col_tiles  : kernel 2, 16-column tiles per wavefront (2, 4 or 8); kernels 4, 5, 7, 8 and 9:
  *                as above.

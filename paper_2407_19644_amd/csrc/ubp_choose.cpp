@@ -107,16 +107,34 @@ int blk_auto_G(const ubp_packed *p) { // 5 stripes per wavefront where that save
 
 // Whole blocks as operands: per round of workgroups the staging of X and a wavefront's share of the steps (two halves of
 // 16 columns each); behind them a launch of the gather kernel for the last columns, where they are left to it.
-// Coefficients fitted to 170 layers of 512 to 4096 rows, 1152 to 4096 columns and 64 to 8192 pixels at 3 to 20 %, even and skewed: mean error 6 %.
-double estimate_blk(const ubp_packed *p, int N, size_t ysz) {
-    const int G = blk_auto_G(p), stripes = (p->M + 15) / 16;
-    const int rows = ((stripes + G - 1) / G + kBlkConsumers - 1) / kBlkConsumers; // of workgroups
-    const double runs = std::min(stripes, rows * kBlkConsumers), stage = 1e-3 * p->K * 4 / 2;
-    const double steps = 0.5 * (double)p->nb * ((p->bw + 15) / 16);
-    const int tiles = blk_leaves_tail(N) ? N / 64 : (N + 63) / 64;
-    const double rounds = std::ceil((tiles + 7) / 8 * (double)rows / 32);
-    return 6.663 + rounds * (1.593 * stage + 0.2611 * steps / runs) + 1.069 * 0.2e-6 * p->M * (double)N * ysz +
-           (blk_leaves_tail(N) ? 17.59 + 15.19 * stage : 0.0);
+// Which split - stripes of a wavefront, producers among 16 wavefronts - is a matter of rounds: X is staged once per workgroup
+// row, so that 5 stripes and 2 producers do the least work, but as long as more workgroup rows run beside each other and
+// not one after the other, each is through sooner with fewer steps per wavefront and with more producers.  4096 x 4096 at 10 %, by
+// stripes / producers: 1024 pixels 5/2 34.8, 4/2 31.9, 2/2 27.8, 2/4 25.1 us, 8192 pixels 77, 94, 130, 131; 2048 x 4096 at 5 % with 4096 pixels
+// 30.5, 28.5, 45.0 and by 4/4 26.1.
+// Coefficients fitted to 600 layers of 512 to 4096 rows, 1152 to 4096 columns and 128 to 8192 pixels at 3 to 20 %, even and skewed: mean
+// error 4 to 7 %; the split of the smallest estimate takes 0.5 % longer than the fastest of the six, 17 % at most.
+struct BlkSplit {
+    int G, NP;
+    double fixed, per_stage, per_step, per_y;
+};
+constexpr BlkSplit kBlkSplits[] = {{2, 2, 5.25, 4.017, 0.2483, 1.272}, {2, 4, 5.27, 3.757, 0.1902, 1.305}, {4, 2, 6.18, 3.543, 0.2561, 0.972},
+                                   {4, 4, 6.34, 3.213, 0.2054, 1.011}, {5, 2, 6.64, 3.371, 0.2651, 0.901}, {5, 4, 6.97, 2.961, 0.2171, 0.943}};
+double estimate_blk(const ubp_packed *p, int N, size_t ysz, const BlkSplit *&split) {
+    const int stripes = (p->M + 15) / 16, tiles = blk_leaves_tail(N) ? N / 64 : (N + 63) / 64;
+    const double stage = 1e-3 * p->K, steps = 0.5 * (double)p->nb * ((p->bw + 15) / 16), y = 0.2e-6 * p->M * (double)N * ysz;
+    double best = kNever;
+    for (const BlkSplit &c : kBlkSplits) {
+        const int runs = std::min(stripes, ((stripes + c.G - 1) / c.G + kBlkConsumers - 1) / kBlkConsumers * kBlkConsumers); // (cut_row_groups)
+        const int rows = (runs + 15 - c.NP) / (16 - c.NP);                                                                   // of workgroups
+        const double rounds = std::ceil((double)((tiles + 7) / 8) * rows / 32);
+        const double t = c.fixed + rounds * (c.per_stage * stage + c.per_step * steps / runs) + c.per_y * y;
+        if (t < best) {
+            best = t;
+            split = &c;
+        }
+    }
+    return best + (blk_leaves_tail(N) ? 17.59 + 30.38 * stage : 0.0);
 }
 
 int gather_col_tiles(int N) {
@@ -277,7 +295,8 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
         // more than the others: with it there too 2800 x 3904 at 10 % with 1472 pixels stays at 45 us and 1024 x 2864 at 5 %,
         // skewed, with 6144 at 47.3, which take 33.7 and 23.3 here; without any 2048 x 1488 at 20 % with 2624 takes 29.9
         // instead of 26.7.)
-        const double t = estimate_blk(p, N, ysz);
+        const BlkSplit *split = nullptr;
+        const double t = estimate_blk(p, N, ysz, split);
         if ((s.kernel == 8 ? t : 1.06 * t) < best) {
             best = 1.06 * t;
             s = Shape();
@@ -476,11 +495,16 @@ ubp_status decide(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, si
     if (kernel == 6) {
         if (!blk_eligible(p) || !vec_ok || N < 64) return UBP_ERR_UNSUPPORTED;
         if (pl.col_tiles != 0 && pl.col_tiles != 4) return UBP_ERR_UNSUPPORTED;
-        const int G = pl.sub_stripes ? pl.sub_stripes : blk_auto_G(p);
+        int G = pl.sub_stripes ? pl.sub_stripes : blk_auto_G(p), NP = pl.producers;
         if (G != 2 && G != 4 && G != 5) return UBP_ERR_UNSUPPORTED;
+        if (pl.sub_stripes == 0 && pl.producers == 0 && pl.waves == 0 && pl.wg_rows == 0) { // (the rest of a plan goes with what it pins)
+            const BlkSplit *split = nullptr;
+            estimate_blk(p, N, ysz, split);
+            G = split->G;
+            NP = split->NP;
+        }
         const BlkLayout &L = get_blk_layout(p, G);
         if (L.G == 0) return UBP_ERR_UNSUPPORTED;
-        int NP = pl.producers;
         if (NP != 0 && NP != 1 && NP != 2 && NP != 4) return UBP_ERR_UNSUPPORTED;
         int waves = pl.waves;
         // one wavefront stages about 28 GB/s: a second one as soon as a workgroup's tile is not small

@@ -373,3 +373,19 @@ def test_tiles_of_128_by_256(lib):
         assert rc == OK and (c["shape"], c["G"], c["CT"]) == (4, 8, 16)
     rc, c = Layer(lib, 256, 260, 4, 4, 0.5).choice(25088, kernel=9, sub_stripes=8, col_tiles=16)
     assert rc == OK and c["shape"] == 0 and c["CT"] == 8
+
+
+@pytest.mark.parametrize("M,K,N,want", [(4096, 4096, 1024, (2, 4)), (2048, 4096, 4096, (4, 4)), (4096, 4096, 8192, (5, 2)), (512, 1152, 64, (2, 4)), (16, 1152, 64, (2, 4))])
+def test_split_of_the_block_kernel(lib, M, K, N, want):
+    """Kernel 6 by itself: light wavefronts and four producers while the workgroups run beside each other, few workgroup rows where they
+    come in rounds; what a plan pins goes with the rest as it always did, and the plan that comes out is taken back."""
+    layer = Layer(lib, M, K, 16, 16, 0.1)
+    rc, c = layer.choice(N, kernel=6)
+    assert rc == OK and (c["G"], c["NP"]) == want
+    assert c["waves"] - c["NP"] >= 1 and c["wg_rows"] * (c["waves"] - c["NP"]) * c["G"] * 16 >= M
+    rc, back = layer.choice(N, kernel=6, sub_stripes=c["G"], col_tiles=c["CT"], waves=c["waves"], producers=c["NP"], wg_rows=c["wg_rows"])
+    assert rc == OK and back == c
+    for pins, G, NP in ((dict(waves=16), None, 2), (dict(producers=4), None, 4), (dict(sub_stripes=2), 2, 2)):
+        rc, c = layer.choice(N, kernel=6, **pins)
+        rows = lambda g: -(-(-(-M // (16 * g))) // 14)
+        assert rc == OK and (c["G"], c["NP"]) == (G or (5 if rows(5) < rows(4) else 4), NP), pins
