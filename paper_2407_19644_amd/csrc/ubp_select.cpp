@@ -379,6 +379,7 @@ std::vector<int64_t> find_runs(const double *S, int64_t b, int32_t N) {
 // A selection of 13107 blocks (512 x 512 in 4 x 1 blocks at 20 %, expansion, on 16 cores): 1.74 ms by one tree over all, 1.35 by
 // runs in one thread (50 ns a round instead of 100), 1.02 in eight, scores in eight as well; one of 2048 x 512, 2 x 1, 50 %: 30 -> 11.6.
 std::vector<Taken> pick(Rounds rounds, const double *S, int64_t b, int32_t N, int64_t m, std::vector<double> *own) {
+    m = std::min(m, b); // (a share of any other would be out of range)
     std::vector<Taken> out;
     constexpr size_t kRuns = 16; // (fewer have no sample)
     constexpr int64_t kRounds = 4096; // (with fewer the sample and the threads cost what they save: 2900 rounds 485 us, by runs 567)

@@ -18,6 +18,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2407_19644_amd", "csrc")
 
 DRIVER = r"""
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -114,8 +115,24 @@ static int one(int M, int K, int bh, int bw, double density, int mode, ubp_dtype
     return 0;
 }
 
+// More blocks asked for than can be: what fits is taken, as with any number that is too large.
+static int too_many() {
+    const int64_t rows[] = {150, 9000};
+    std::vector<double> S;
+    for (int j = 0; j < 20; ++j)
+        for (int64_t i = 0; i < rows[j == 1]; ++i) S.push_back(i + 1 == rows[j == 1] ? -HUGE_VAL : 1.0 + (double)((i * 7919 + j) % 1000));
+    const int64_t b = (int64_t)S.size();
+    std::vector<int64_t> some((size_t)b), all((size_t)b);
+    for (const auto select : {ubp_select_greedy, ubp_select_bed}) {
+        int64_t n = 0, n_all = 0;
+        CHECK(select(S.data(), b, 2, b, some.data(), &n) == UBP_OK && n > 0);
+        CHECK(select(S.data(), b, 2, INT64_MAX, all.data(), &n_all) == UBP_OK && n_all == n && some == all);
+    }
+    return 0;
+}
+
 int main() {
-    int rc = 0;
+    int rc = too_many();
     rc |= one(64, 64, 4, 4, 0.5, 0, UBP_F32);
     rc |= one(240, 160, 4, 4, 0.3, 0, UBP_F16);
     rc |= one(256, 256, 8, 8, 0.2, 0, UBP_F16);
@@ -139,7 +156,7 @@ def test_host_code_under_asan_and_ubsan(tmp_path):
     drv.write_text(textwrap.dedent(DRIVER))
     exe = tmp_path / "driver"
     orc = tmp_path / "oracle.o"
-    san = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer", "-g", "-O1"]
+    san = ["-fsanitize=address,undefined,float-cast-overflow", "-fno-sanitize-recover=undefined,float-cast-overflow", "-fno-omit-frame-pointer", "-g", "-O1"]
     subprocess.check_call(["gcc", "-std=c99", "-c", os.path.join(ROOT, "oracle", "ubp_oracle.c"), "-o", str(orc)] + san)
     subprocess.check_call(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, str(drv),
                            os.path.join(CSRC, "ubp_host.cpp"), os.path.join(CSRC, "ubp_layouts.cpp"),
