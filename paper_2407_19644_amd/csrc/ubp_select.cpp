@@ -5,15 +5,17 @@
 // The selectors return what the paper's step-by-step descriptions return, but not by those
 // steps where a faster route gives the same indices:
 //   greedy   : the arg max comes from a tree of maxima (leftmost leaf wins a tie), so one of the m
-//              rounds costs O(N + log b) instead of O(b), and where -inf separates columns from each other they are gone
-//              through one by one, by several threads, and what they give is merged;
-//   expansion: the shrinking score list is a set of the original indices, its arg max from the same tree, by columns as well;
+//              rounds costs O(N + log b) instead of O(b), and where -inf separates columns from each other several threads go
+//              through parts of them side by side, and what they give is merged;
+//   expansion: the shrinking score list is a set of the original indices, its arg max from the same tree, by parts as well;
 //   optimal  : Eq. 4's table row by row with one decision bit per cell and a walk back from
 //              (b, m) instead of carrying index sets, cells that cannot lie on a path to (b, m)
 //              left out: O(b m) time, b m bits.
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <exception>
 #include <limits>
@@ -23,6 +25,7 @@
 #include <stdexcept>
 #include <system_error>
 #include <thread>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -84,43 +87,126 @@ bool selector_args_ok(const double *S, int64_t b, int32_t N, int64_t m, const in
     return b >= 0 && (b == 0 || S) && N >= 1 && m >= 0 && (m == 0 || I) && count;
 }
 
-// f(state, part) for parts 0 .. parts - 1, each once, by up to `threads` threads (the caller among them) with a State each; what
-// one of them throws is thrown here, after all have ended.  A thread that cannot be had is done without.
-template <class State, class F> void share_out(size_t parts, size_t threads, F &&f) {
-    constexpr size_t kMost = 8; // (a thread takes some 15 us to start)
-    threads = std::min({threads, parts, kMost});
-    if (threads > 1) threads = std::min(threads, (size_t)std::thread::hardware_concurrency()); // (which asks the system: some 2 us)
-    std::atomic<size_t> next{0};
-    std::mutex lock;
-    std::exception_ptr thrown;
-    const auto work = [&]() {
-        try {
-            State state;
-            for (size_t p; (p = next.fetch_add(1)) < parts;) f(state, p);
-        } catch (...) {
+// Waits for `done`, for about as long as a thread that sleeps takes to wake up.
+template <class F> void spin(F &&done) {
+    const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(50);
+    do {
+        for (int i = 0; i < 16; ++i) {
+            if (done()) return;
+#if defined(__SSE2__)
+            _mm_pause();
+#endif
+        }
+    } while (std::chrono::steady_clock::now() < end);
+}
+
+// Up to kMost threads for the length of one call, the caller among them.  A thread that cannot be had is done without.
+class Team {
+  public:
+    explicit Team(size_t want, size_t cores = 0) { // (0: as many as there are)
+        want = std::min(want, kMost);
+        if (want > 1) threads = std::max<size_t>(1, std::min(want, cores ? cores : (size_t)std::thread::hardware_concurrency()));
+        start(1);
+    }
+    ~Team() {
+        {
             std::lock_guard<std::mutex> hold(lock);
-            thrown = std::current_exception();
-            next = parts;
+            over = true;
+            ++turn;
         }
-    };
-    struct Pool {
-        std::thread thread[kMost];
-        ~Pool() {
-            for (std::thread &t : thread)
-                if (t.joinable()) t.join();
+        wake.notify_all();
+        for (std::thread &t : thread) // (the ones that start others come before those)
+            if (t.joinable()) t.join();
+    }
+    Team(const Team &) = delete;
+    Team &operator=(const Team &) = delete;
+    size_t size() const { return threads; }
+
+    // f(part, member) for parts 0 .. parts - 1, each once, by the same thread as the last time where that one is not late: what a part
+    // reads and writes is then in that core's caches (a line out of another core's takes 100 to 200 ns).  What one of them
+    // throws is thrown here, after all have ended.
+    template <class F> void share(size_t parts, F &&f) {
+        if (threads == 1 || parts < 2) {
+            for (size_t p = 0; p < parts; ++p) f(p, 0);
+            return;
         }
-    };
-    {
-        Pool pool;
+        typedef typename std::remove_reference<F>::type Body;
+        {
+            std::lock_guard<std::mutex> hold(lock);
+            body = [](void *what, size_t p, size_t me) { (*static_cast<Body *>(what))(p, me); };
+            with = const_cast<void *>(static_cast<const void *>(&f));
+            for (size_t t = 0; t < size(); ++t) {
+                share_of[t].next = parts * t / size();
+                share_of[t].end = parts * (t + 1) / size();
+            }
+            open = true;
+            ++turn;
+        }
+        wake.notify_all();
+        work(0);
+        spin([this] { return inside == 0; });
+        std::unique_lock<std::mutex> hold(lock);
+        open = false; // (who wakes up only now has nothing left to do)
+        done.wait(hold, [this] { return inside == 0; });
+        if (thrown) std::rethrow_exception(std::exchange(thrown, nullptr));
+    }
+
+  private:
+    static constexpr size_t kMost = 8;
+    // A thread takes some 15 us to start, so that it starts the next ones by itself: 1 those from 2 on, 2 and 3 two each.
+    void start(size_t t) {
+        if (t >= threads) return;
         try {
-            for (size_t t = 1; t < threads; ++t) pool.thread[t] = std::thread(work);
+            thread[t] = std::thread([this, t] { member(t); });
         } catch (const std::system_error &) {
         } catch (const std::bad_alloc &) {
         }
-        work();
     }
-    if (thrown) std::rethrow_exception(thrown);
-}
+    void member(size_t me) {
+        start(2 * me);
+        start(2 * me + 1);
+        for (uint64_t seen = 0;;) {
+            spin([&] { return turn != seen; });
+            std::unique_lock<std::mutex> hold(lock);
+            wake.wait(hold, [&] { return turn != seen; });
+            seen = turn;
+            if (over) return;
+            if (!open) continue;
+            ++inside;
+            hold.unlock();
+            work(me);
+            hold.lock();
+            if (--inside == 0) done.notify_one();
+        }
+    }
+    void work(size_t me) {
+        try {
+            for (size_t t = 0; t < size(); ++t) { // its own share, then what is left of the others'
+                Share &s = share_of[(me + t) % size()];
+                for (size_t p; (p = s.next.fetch_add(1)) < s.end;) body(with, p, me);
+            }
+        } catch (...) {
+            std::lock_guard<std::mutex> hold(lock);
+            thrown = std::current_exception();
+            for (size_t t = 0; t < size(); ++t) share_of[t].next = share_of[t].end;
+        }
+    }
+    struct alignas(64) Share {
+        std::atomic<size_t> next{0};
+        size_t end = 0;
+    };
+    Share share_of[kMost];
+    std::mutex lock; // of what follows, but for reads while spinning
+    std::condition_variable wake, done;
+    std::atomic<uint64_t> turn{0}; // goes up with every share(), and at the end
+    std::atomic<size_t> inside{0};
+    size_t threads = 1;
+    bool open = false, over = false;
+    void (*body)(void *, size_t, size_t) = nullptr;
+    void *with = nullptr;
+    std::exception_ptr thrown;
+    std::thread thread[kMost];
+};
 
 // Tree of maxima over the scores of n candidates, 8 children to a node: a node's children fill a cache line, n = 2^18 has 6
 // levels, and the neighbouring candidates that a round changes share almost all of their nodes.  best() is the leftmost
@@ -128,32 +214,12 @@ template <class State, class F> void share_out(size_t parts, size_t threads, F &
 struct MaxTree {
     static constexpr int kWidth = 8;
     std::vector<std::vector<double>> level; // [0]: the scores; [l + 1][i] = the largest of [l][8 i .. 8 i + 7]
-    size_t levels = 0;                      // of them in use (a tree is filled again and again, see pick)
-    void reset(const double *S, int64_t n) {
-        if (level.empty()) level.emplace_back();
-        level[0].resize(padded(n));
-        std::copy_n(S, n, level[0].data());
-        std::fill(level[0].begin() + n, level[0].end(), kNegInf);
-        build();
-    }
-    void take(std::vector<double> &&scores) { // (with room for the fill at their end)
-        if (level.empty()) level.emplace_back();
+    void fill(std::vector<double> &&scores) { // (with room for the fill at their end)
         scores.resize(padded((int64_t)scores.size()), kNegInf);
-        level[0] = std::move(scores);
-        build();
-    }
-    void build() {
-        levels = 1;
-        while (level[levels - 1].size() > kWidth) {
-            const size_t below = level[levels - 1].size() / kWidth;
-            if (level.size() == levels) level.emplace_back();
-            std::vector<double> &up = level[levels];
-            const std::vector<double> &down = level[levels - 1];
-            up.resize(padded((int64_t)below));
-            for (size_t i = 0; i < below; ++i) up[i] = largest(&down[i * kWidth]);
-            std::fill(up.begin() + (std::ptrdiff_t)below, up.end(), kNegInf);
-            ++levels;
-        }
+        level.push_back(std::move(scores));
+        while (level.back().size() > kWidth) level.emplace_back(padded((int64_t)(level.back().size() / kWidth)), kNegInf);
+        for (size_t l = 0; l + 1 < level.size(); ++l)
+            for (size_t i = 0; i < level[l].size() / kWidth; ++i) level[l + 1][i] = largest(&level[l][i * kWidth]);
     }
     static size_t padded(int64_t n) { return (size_t)((n + kWidth - 1) / kWidth * kWidth); }
 #if defined(__SSE2__)
@@ -171,15 +237,15 @@ struct MaxTree {
     static int first_equal(const double *v, double x) { return (int)std::min<std::ptrdiff_t>(std::find(v, v + kWidth, x) - v, kWidth - 1); }
 #endif
     double &score(int64_t k) { return level[0][(size_t)k]; }
-    double most() const { return largest(level[levels - 1].data()); }
+    double most() const { return largest(level.back().data()); }
     int64_t best(double x) const { // x = most()
         int64_t at = 0;
-        for (size_t l = levels; l-- > 0;) at = at * kWidth + first_equal(&level[l][(size_t)at * kWidth], x);
+        for (size_t l = level.size(); l-- > 0;) at = at * kWidth + first_equal(&level[l][(size_t)at * kWidth], x);
         return at;
     }
     // The scores of candidates in the nodes lo .. hi of the lowest level (candidate / 8) have changed.
     void refresh(int64_t lo, int64_t hi) {
-        for (size_t l = 0; l + 1 < levels; ++l) {
+        for (size_t l = 0; l + 1 < level.size(); ++l) {
             bool changed = false;
             for (int64_t i = lo; i <= hi; ++i) {
                 const double x = largest(&level[l][(size_t)i * kWidth]);
@@ -228,27 +294,23 @@ template <class T, class Mag> void row_norms(const T *w, int32_t bw, int32_t n, 
 // is (32 KB in the first cache level for b = 2^18, where links between neighbours were 2 to 4 MB).
 struct Remaining {
     std::vector<std::vector<uint64_t>> level;
-    size_t levels = 0; // of them in use
-    void reset(int64_t b) {
-        levels = 0;
+    void fill(int64_t b) {
         do {
-            if (level.size() == levels) level.emplace_back();
-            std::vector<uint64_t> &words = level[levels++];
-            words.assign((size_t)((b + 63) / 64), ~uint64_t(0));
-            if (b % 64) words.back() = (uint64_t(1) << (b % 64)) - 1;
+            level.emplace_back((size_t)((b + 63) / 64), ~uint64_t(0));
+            if (b % 64) level.back().back() = (uint64_t(1) << (b % 64)) - 1;
             b = (b + 63) / 64;
         } while (b > 1);
     }
     void remove(int64_t k) {
-        for (size_t l = 0; l < levels; ++l) {
-            uint64_t &w = level[l][(size_t)(k / 64)];
+        for (std::vector<uint64_t> &words : level) {
+            uint64_t &w = words[(size_t)(k / 64)];
             w &= ~(uint64_t(1) << (k % 64));
             if (w) return;
             k /= 64;
         }
     }
     int64_t after(int64_t k) const { // -1: none
-        for (size_t l = 0; l < levels; ++l, k /= 64) {
+        for (size_t l = 0; l < level.size(); ++l, k /= 64) {
             if (k % 64 == 63) continue;
             const uint64_t w = level[l][(size_t)(k / 64)] & (~uint64_t(1) << (k % 64));
             if (!w) continue;
@@ -259,7 +321,7 @@ struct Remaining {
         return -1;
     }
     int64_t before(int64_t k) const {
-        for (size_t l = 0; l < levels; ++l, k /= 64) {
+        for (size_t l = 0; l < level.size(); ++l, k /= 64) {
             const uint64_t w = level[l][(size_t)(k / 64)] & ((uint64_t(1) << (k % 64)) - 1);
             if (!w) continue;
             k = k / 64 * 64 + 63 - __builtin_clzll(w);
@@ -276,32 +338,35 @@ struct Taken {
     int64_t k;
 };
 
-struct Workspace {
+// Neighbouring candidates, which rounds go through: what is left of them and what has been taken, in order.
+struct Part {
     MaxTree tree;
     Remaining list;
     std::vector<int64_t> right;
-    std::vector<double> *own = nullptr; // the scores, where they are all of them and the caller has no more use for them: not copied (16 us of 160 for 49600)
-    void fill(const double *S, int64_t n) {
-        if (own) tree.take(std::move(*own));
-        else tree.reset(S, n);
+    int64_t first = 0, n = 0;
+    std::vector<Taken> taken;
+    void fill(std::vector<double> &&scores) { // (with room for the fill at their end)
+        n = (int64_t)scores.size();
+        tree.fill(std::move(scores));
     }
 };
 
-// Rounds over the candidates first .. first + n - 1, appended to `out`: at most `most`, and none whose score lies below `bound`.
-typedef void (*Rounds)(Workspace &w, const double *S, int64_t first, int64_t n, int32_t N, double bound, int64_t most, std::vector<Taken> &out);
+// Up to `most` rounds whose scores lie above `above`.  False: there may be more.
+typedef bool (*Rounds)(Part &part, int32_t N, double above, int64_t most);
 
 // Expansion (Algorithm 1).
-void expand(Workspace &w, const double *S, int64_t first, int64_t n, int32_t N, double bound, int64_t most, std::vector<Taken> &out) {
-    MaxTree &tree = w.tree;
-    Remaining &list = w.list;
-    w.fill(S + first, n);
-    list.reset(n);
-    std::vector<int64_t> &right = w.right;
-    right.resize((size_t)std::min<int64_t>(N, n));
+bool expand(Part &part, int32_t N, double above, int64_t most) {
+    MaxTree &tree = part.tree;
+    Remaining &list = part.list;
+    std::vector<int64_t> &right = part.right;
+    if (list.level.empty()) {
+        list.fill(part.n);
+        right.resize((size_t)std::min<int64_t>(N, part.n));
+    }
     Changes changes{tree};
     for (int64_t got = 0; got < most; ++got) {
         const double top = tree.most();
-        if (top == kNegInf || top < bound) break;
+        if (!(top > above)) return true;
         const int64_t k = tree.best(top);
         // right[t] = the t-th entry after k in the list as it stands, for t < n_right
         int32_t n_right = 0;
@@ -327,132 +392,218 @@ void expand(Workspace &w, const double *S, int64_t first, int64_t n, int32_t N, 
             list.remove(right[(size_t)t]);
         }
         changes.flush();
-        out.push_back(Taken{top, first + k});
+        part.taken.push_back(Taken{top, part.first + k});
     }
+    return false;
 }
 
-void greedy(Workspace &w, const double *S, int64_t first, int64_t n, int32_t N, double bound, int64_t most, std::vector<Taken> &out) {
-    MaxTree &tree = w.tree;
-    w.fill(S + first, n);
+bool greedy(Part &part, int32_t N, double above, int64_t most) {
+    MaxTree &tree = part.tree;
     for (int64_t got = 0; got < most; ++got) {
         const double top = tree.most();
-        if (top == kNegInf || top < bound) break;
+        if (!(top > above)) return true;
         const int64_t k = tree.best(top);
-        out.push_back(Taken{top, first + k});
-        const int64_t lo = std::max<int64_t>(0, k - N + 1), hi = std::min<int64_t>(n - 1, k + N - 1);
+        part.taken.push_back(Taken{top, part.first + k});
+        const int64_t lo = std::max<int64_t>(0, k - N + 1), hi = std::min<int64_t>(part.n - 1, k + N - 1);
         std::fill(&tree.score(lo), &tree.score(hi) + 1, kNegInf);
         tree.refresh(lo / MaxTree::kWidth, hi / MaxTree::kWidth);
     }
+    return false;
 }
 
-// Where each run of candidates that no round reaches out of begins, and b at the end.  N - 1 or more scores of -inf one
-// after the other separate what lies before them from what lies behind:
+constexpr size_t kLeastTeam = 2;
+constexpr int64_t kLeastRounds = 4096;
+size_t threads_for_rounds(int64_t m) { return m < kLeastRounds ? 1 : (size_t)std::min<int64_t>(m / 1024, 64); }
+
+// Where to cut b candidates into up to `most` parts that no round reaches out of, some b / most each.  N - 1 or more scores of
+// -inf one after the other separate what lies before them from what lies behind:
 //  * greedy shuts out N - 1 candidates to either side;
-//  * in expansion a candidate with fewer than N - 1 others left between it and the end of its run has -inf: from the
+//  * in expansion a candidate with fewer than N - 1 others left between it and the end of its part has -inf: from the
 //    beginning, and when a round brings one there, since what it is joined with has as few behind it.  So a block that is
-//    taken leaves with entries of its own run, and those before the run that it would be joined with have -inf and keep it.
-// (At least kLeast candidates to a run: aligned blocks would make one each.)
-std::vector<int64_t> find_runs(const double *S, int64_t b, int32_t N) {
-    constexpr int64_t kLeast = 128;
+//    taken leaves with entries of its own part, and those before the part that it would be joined with have -inf and keep it.
+std::vector<int64_t> cuts(const double *S, int64_t b, int32_t N, int64_t most) {
     std::vector<int64_t> first(1, 0);
-    for (int64_t k = kLeast; k < b;) { // k: could begin a run
-        int64_t at = k - 1;            // ... if the N - 1 scores before it are -inf
-        while (at >= 0 && k - 1 - at < N - 1 && S[at] == kNegInf) --at;
-        if (k - 1 - at >= N - 1) {
-            first.push_back(k);
-            k += kLeast;
-        } else {
-            k = at + N; // (behind the first score from there that is not -inf)
-        }
+    for (int64_t p = 1; p < most; ++p) {
+        const int64_t from = b / most * p, to = from + b / most;
+        int64_t at = from, gone = 0; // scores of -inf right before at
+        while (gone < N - 1 && gone < from && S[from - 1 - gone] == kNegInf) ++gone;
+        for (; gone < N - 1 && at < to; ++at) gone = S[at] == kNegInf ? gone + 1 : 0;
+        if (gone >= N - 1 && at < to) first.push_back(at);
     }
     first.push_back(b);
     return first;
 }
 
-// The m rounds over all candidates, in order.
+// The scores that part p has taken lie above x before this one.
+inline std::vector<Taken>::const_iterator above(const Part &p, double x) {
+    return std::partition_point(p.taken.begin(), p.taken.end(), [x](const Taken &t) { return t.score > x; });
+}
+
+inline double below(double x) { return std::nextafter(x, kNegInf); }
+
+// The m rounds over all candidates: what they take, part by part, in order within each.
 //
-// One run after the other, by several threads - its scores, its tree and its list then stay in the first cache level, where
-// those of 2^18 candidates ask for lines of the second and third at every step - as far as its scores are at least a
-// bound, which a sample of the runs gives with some to spare.  A round gives no candidate more than the score it takes, so
-// that a run's scores never rise, and the m largest of all, in the order of the runs where they are equal, are what
-// the rounds over all candidates take.
-// A selection of 13107 blocks (512 x 512 in 4 x 1 blocks at 20 %, expansion, on 16 cores): 1.74 ms by one tree over all, 1.35 by
-// runs in one thread (50 ns a round instead of 100), 1.02 in eight, scores in eight as well; one of 2048 x 512, 2 x 1, 50 %: 30 -> 11.6.
-std::vector<Taken> pick(Rounds rounds, const double *S, int64_t b, int32_t N, int64_t m, std::vector<double> *own) {
-    m = std::min(m, b); // (a share of any other would be out of range)
-    std::vector<Taken> out;
-    constexpr size_t kRuns = 16; // (fewer have no sample)
-    constexpr int64_t kRounds = 4096; // (with fewer the sample and the threads cost what they save: 2900 rounds 485 us, by runs 567)
-    const std::vector<int64_t> first = N >= 2 && m >= kRounds ? find_runs(S, b, N) : std::vector<int64_t>{0, b};
-    const size_t runs = first.size() - 1;
-    if (runs < kRuns) {
-        Workspace w;
-        w.own = own;
-        out.reserve((size_t)std::min(m, b));
-        rounds(w, S, 0, b, N, kNegInf, m, out);
-        return out;
-    }
-    const size_t threads = (size_t)std::min<int64_t>(m / 1024, 64); // (a round: 50 ns)
-    // the sample: a quarter of few runs, some 48 of many, spread so that nothing that comes back every so many runs is all there is
-    // of it, each as far as twice its share of m
-    const size_t samples = std::min<size_t>((runs + 3) / 4, 48);
-    double share = 0.0;
-    std::vector<double> sample;
-    {
-        std::vector<std::vector<Taken>> part(samples);
-        std::vector<size_t> run(samples);
-        for (size_t i = 0; i < samples; ++i) {
-            run[i] = std::min(runs - 1, (size_t)((double)runs * std::fmod((double)(i + 1) * 0.6180339887498949, 1.0)));
-            share += (double)m * (double)(first[run[i] + 1] - first[run[i]]) / (double)b;
+// The rounds over a part take what those over all candidates take of it, in the same order, and a round gives no candidate
+// more than the score it takes, so that the scores that are taken never rise: what all rounds take is the m largest of what the
+// parts give, those of earlier parts where they are equal.  So parts are gone through side by side, all down to the same
+// score, then to a lower one, until m are taken.  The scores to stop at are those of a sample of the candidates: a block has a
+// candidate's score or less, so that there are at most as many blocks above a score as candidates, and how many there
+// have been so far says where m will be reached.  Equal scores at the last of them are taken in order.
+// When m / 8 more than m have been made the bound was too low for parts that came first, and the m-th score so far takes its
+// place.  Whatever the scores are there are 2.2 m rounds at most; 1.0 to 1.1 m where columns differ by any smooth law or many have no
+// weight, up to 1.4 m where a few of them are a hundred times the others.
+//
+// 512 x 512 in 4 x 1 blocks at 20 % (13107 rounds) with scores, by one tree -> by parts on 16 cores: rows of different size, greedy 1.56 -> 0.8,
+// expansion 1.74 -> 0.7 ms; columns of different size (log-normal, sigma 2) 1.45 -> 0.75 and 1.65 -> 0.7; four columns in five zero 1.25
+// -> 0.8 and 1.6 -> 0.7; all zero 0.82 -> 0.8.  1024 x 512, 2 x 1, 2 %, sigma 2: 1.1 -> 0.9, 1.15 -> 0.85.  On 4 cores the first two 1.57 -> 0.87, 1.73
+// -> 0.74.  Slower are small layers without a weight, whose rounds are made in order all the same: 1024 x 64, 9830 rounds, 0.34 -> 0.5.
+std::vector<Part> pick(Rounds rounds, const double *S, int64_t b, int32_t N, int64_t m, std::vector<double> *own, Team &team) {
+    constexpr int64_t kParts = 64;
+    constexpr double kSamples = 128.0; // among the m best candidates
+    constexpr std::ptrdiff_t kEqual = 3; // (2 % of m)
+    m = std::min(m, b);
+    std::vector<int64_t> first(1, 0);
+    if (team.size() >= kLeastTeam && m >= kLeastRounds) first = cuts(S, b, N, std::min<int64_t>(kParts, b / 1024));
+    else first.push_back(b);
+    const size_t parts = first.size() - 1;
+    std::vector<Part> part(parts);
+    if (parts < 2) {
+        std::vector<double> copy;
+        if (!own) {
+            copy.reserve(MaxTree::padded(b));
+            copy.assign(S, S + b);
         }
-        share_out<Workspace>(samples, threads / 2, [&](Workspace &w, size_t i) {
-            const int64_t n = first[run[i] + 1] - first[run[i]];
-            rounds(w, S, first[run[i]], n, N, kNegInf, (int64_t)(2.0 * (double)m * (double)n / (double)b) + 8, part[i]);
-        });
-        for (const std::vector<Taken> &p : part)
-            for (const Taken &t : p) sample.push_back(t.score);
+        part[0].taken.reserve((size_t)m);
+        part[0].fill(std::move(own ? *own : copy));
+        rounds(part[0], N, kNegInf, m);
+        return part;
     }
-    const size_t parts = std::min<size_t>(runs, 64);
-    std::vector<std::vector<Taken>> part(parts);
-    for (double spare = 1.1;; spare *= 1.5) {
-        const size_t at = (size_t)(spare * share) + 4;
-        double bound = kNegInf;
-        if (at < sample.size()) {
-            std::nth_element(sample.begin(), sample.begin() + (std::ptrdiff_t)at, sample.end(), std::greater<double>());
-            bound = sample[at];
+    const double per_sample = std::max(1.0, (double)m / kSamples); // candidates
+    std::vector<size_t> from(parts + 1, 0);
+    for (size_t p = 0; p < parts; ++p) from[p + 1] = from[p] + (size_t)((double)(first[p + 1] - first[p]) / per_sample);
+    std::vector<double> sample(from[parts]);
+    team.share(parts, [&](size_t p, size_t) {
+        Part &here = part[p];
+        const double *scores = S + first[p];
+        const int64_t n = first[p + 1] - first[p];
+        double at = 0.5;
+        for (size_t i = from[p]; i < from[p + 1]; ++i) { // spread so that nothing that comes back every so many candidates is all there is of it
+            at += 0.6180339887498949;
+            at -= at >= 1.0;
+            sample[i] = scores[std::min(n - 1, (int64_t)(at * (double)n))];
         }
-        share_out<Workspace>(parts, threads, [&](Workspace &w, size_t p) {
-            part[p].clear();
-            for (size_t r = runs * p / parts; r < runs * (p + 1) / parts; ++r) rounds(w, S, first[r], first[r + 1] - first[r], N, bound, m, part[p]);
+        std::vector<double> copy;
+        copy.reserve(MaxTree::padded(n));
+        copy.assign(scores, scores + n);
+        here.first = first[p];
+        here.fill(std::move(copy));
+    });
+    const auto taken = [&] {
+        int64_t all = 0;
+        for (const Part &p : part) all += (int64_t)p.taken.size();
+        return all;
+    };
+    // every part down to `bound`; false: `most` rounds have been made before
+    const auto walk = [&](double bound, int64_t most) {
+        constexpr int64_t kChunk = 32;
+        std::atomic<int64_t> left{most};
+        std::atomic<bool> all{true};
+        team.share(parts, [&](size_t p, size_t) {
+            for (;;) {
+                if (left.fetch_sub(kChunk) <= 0) {
+                    if (part[p].tree.most() > bound) all = false;
+                    return;
+                }
+                const size_t before = part[p].taken.size();
+                const bool end = rounds(part[p], N, bound, kChunk);
+                left += kChunk - (int64_t)(part[p].taken.size() - before);
+                if (end) return;
+            }
         });
-        size_t all = 0;
-        for (const std::vector<Taken> &p : part) all += p.size();
-        if ((int64_t)all < m && bound != kNegInf) continue;
-        out.reserve(all);
-        for (const std::vector<Taken> &p : part) out.insert(out.end(), p.begin(), p.end());
-        break;
+        return all.load();
+    };
+    // the m-th largest of the scores taken, of which fewer than m lie above `sure`
+    const auto mth = [&](double sure) {
+        std::vector<double> rest;
+        int64_t nth = m;
+        for (const Part &p : part) {
+            auto t = above(p, sure);
+            nth -= t - p.taken.begin();
+            for (; t != p.taken.end(); ++t) rest.push_back(t->score);
+        }
+        std::nth_element(rest.begin(), rest.begin() + (std::ptrdiff_t)(nth - 1), rest.end(), std::greater<double>());
+        return rest[(size_t)(nth - 1)];
+    };
+    // All above `score` are taken: those equal to it, as far as m asks for them.  True: m are taken.
+    const auto take_equal = [&](double score) {
+        int64_t want = m;
+        for (const Part &p : part) want -= above(p, score) - p.taken.begin();
+        for (size_t p = 0; p < parts && want > 0; ++p) {
+            want -= above(part[p], below(score)) - above(part[p], score);
+            if (want <= 0) break;
+            const size_t before = part[p].taken.size();
+            rounds(part[p], N, below(score), want);
+            want -= (int64_t)(part[p].taken.size() - before);
+        }
+        return want <= 0;
+    };
+    double bound = std::numeric_limits<double>::infinity(); // all above it are taken, `have` of them
+    size_t rank = 0, step = (size_t)kSamples;               // of the bound among the sample, and how much lower the next one is
+    double slope = 0.0;                                     // blocks that a sample further down has brought
+    for (int64_t have = 0;;) {
+        double next = kNegInf;
+        if (rank + step < sample.size()) {
+            const auto begin = sample.begin() + (std::ptrdiff_t)rank, at = begin + (std::ptrdiff_t)step;
+            std::nth_element(begin, at, sample.end(), std::greater<double>());
+            next = *at;
+        }
+        if (next == bound || std::count(sample.begin() + (std::ptrdiff_t)rank, sample.end(), bound) > kEqual) {
+            if (take_equal(bound)) break;
+            have = taken();
+            sample.erase(std::remove(sample.begin() + (std::ptrdiff_t)rank, sample.end(), bound), sample.end());
+        } else {
+            bool end = walk(next, m - have + m / 8);
+            while (!end && taken() < m) end = walk(next, m / 8);
+            const int64_t now = taken();
+            if (!end) {
+                next = mth(bound);
+                walk(next, std::numeric_limits<int64_t>::max() / 2);
+                take_equal(next);
+                break;
+            }
+            if (now >= m || next == kNegInf) break;
+            rank += step;
+            slope = (double)(now - have) / (double)step;
+            have = now;
+            bound = next;
+        }
+        // a little short of m while that is far, then a little beyond; and while it is far as if a sample brought half of what it has on
+        // the whole, since what comes may be unlike what came last (a few heavy columns, all taken)
+        const double still = (double)(m - have);
+        const bool far = 4 * still > (double)m;
+        const double least = far ? 0.5 * (double)have / (double)std::max<size_t>(rank, 1) : 0.0;
+        step = (size_t)std::max(1.0, std::min(4.0 * (double)(rank + kEqual), (far ? 0.9 * still : still + (double)m / 64) / std::max({slope, least, 1e-3})));
     }
-    if ((int64_t)out.size() > m) { // the m largest, the first ones of equal scores
-        std::vector<double> score(out.size());
-        for (size_t t = 0; t < out.size(); ++t) score[t] = out[t].score;
-        std::nth_element(score.begin(), score.begin() + (std::ptrdiff_t)(m - 1), score.end(), std::greater<double>());
-        const double least = score[(size_t)(m - 1)];
+    if (taken() > m) {
+        const double least = mth(bound);
         int64_t equal = m;
-        for (const Taken &t : out) equal -= t.score > least;
-        const auto out_of = [&](const Taken &t) { return t.score < least || (t.score == least && equal-- <= 0); };
-        size_t n = 0;
-        for (const Taken &t : out)
-            if (!out_of(t)) out[n++] = t;
-        out.resize(n);
+        for (const Part &p : part) equal -= above(p, least) - p.taken.begin();
+        for (Part &p : part) {
+            const int64_t more = above(p, least) - p.taken.begin(), all = above(p, below(least)) - p.taken.begin();
+            const int64_t kept = std::min(all - more, equal);
+            equal -= kept;
+            p.taken.resize((size_t)(more + kept));
+        }
     }
-    return out;
+    return part;
 }
 
 // Expansion, then division (Algorithm 2).
-int64_t expand_and_divide(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I, std::vector<double> *own = nullptr) {
+int64_t expand_and_divide(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I, std::vector<double> *own, Team &team) {
     if (b == 0 || m == 0) return 0;
     std::vector<uint64_t> kept((size_t)(b + 63) / 64, 0);
-    for (const Taken &t : pick(expand, S, b, N, m, own)) kept[(size_t)t.k / 64] |= uint64_t(1) << (t.k % 64);
+    for (const Part &p : pick(expand, S, b, N, m, own, team))
+        for (const Taken &t : p.taken) kept[(size_t)t.k / 64] |= uint64_t(1) << (t.k % 64);
     int64_t got = 0;
     for (size_t w = 0; w < kept.size(); ++w)
         for (uint64_t bits = kept[w]; bits; bits &= bits - 1) I[got++] = (int64_t)(64 * w) + __builtin_ctzll(bits);
@@ -465,32 +616,84 @@ int64_t expand_and_divide(const double *S, int64_t b, int32_t N, int64_t m, int6
     return got;
 }
 
-int64_t greedy_in_order(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I, std::vector<double> *own = nullptr) {
+int64_t greedy_in_order(const double *S, int64_t b, int32_t N, int64_t m, int64_t *I, std::vector<double> *own, Team &team) {
     if (b == 0 || m == 0) return 0;
-    std::vector<Taken> all = pick(greedy, S, b, N, m, own);
-    if (all.empty()) return 0;
-    // (in order already where there was one run; else 8 bits of the scores at a time, from the lowest, keeps equal ones in the order of the runs)
-    const auto key = [](double x) { // larger ones first; the same for zeros of either sign
-        uint64_t u;
-        x += 0.0;
-        std::memcpy(&u, &x, 8);
-        return u >> 63 ? u : ~u & ~(uint64_t(1) << 63);
-    };
-    const auto before = [](const Taken &x, const Taken &y) { return x.score > y.score; };
-    if (!std::is_sorted(all.begin(), all.end(), before)) {
-        std::vector<Taken> other(all.size());
-        for (int shift = 0; shift < 64; shift += 8) {
-            size_t count[256] = {0};
-            for (const Taken &t : all) ++count[(key(t.score) >> shift) & 255];
-            if (count[(key(all[0].score) >> shift) & 255] == all.size()) continue;
-            size_t at = 0;
-            for (size_t &c : count) at += std::exchange(c, at);
-            for (const Taken &t : all) other[count[(key(t.score) >> shift) & 255]++] = t;
-            all.swap(other);
+    const std::vector<Part> part = pick(greedy, S, b, N, m, own, team);
+    if (part.size() == 1) {
+        for (size_t t = 0; t < part[0].taken.size(); ++t) I[t] = part[0].taken[t].k;
+        return (int64_t)part[0].taken.size();
+    }
+    // The parts' are in order: a range of scores at a time, cut at scores that are taken about as often.
+    constexpr size_t kRanges = 32, kFromEach = 16;
+    std::vector<double> edge;
+    for (const Part &p : part)
+        for (size_t i = 0; i < kFromEach && !p.taken.empty(); ++i) edge.push_back(p.taken[p.taken.size() * i / kFromEach].score);
+    if (edge.empty()) return 0;
+    std::sort(edge.begin(), edge.end(), std::greater<double>());
+    team.share(kRanges, [&](size_t r, size_t) {
+        const double from = r == 0 ? std::numeric_limits<double>::infinity() : edge[edge.size() * r / kRanges];
+        const double to = r + 1 == kRanges ? kNegInf : edge[edge.size() * (r + 1) / kRanges];
+        std::vector<Taken> here;
+        int64_t *out = I;
+        for (const Part &p : part) {
+            const auto begin = above(p, from), end = above(p, to);
+            out += begin - p.taken.begin();
+            here.insert(here.end(), begin, end);
+        }
+        const auto before = [](const Taken &x, const Taken &y) { return x.score > y.score || (x.score == y.score && x.k < y.k); };
+        if (!std::is_sorted(here.begin(), here.end(), before)) std::sort(here.begin(), here.end(), before);
+        for (size_t t = 0; t < here.size(); ++t) out[t] = here[t].k;
+    });
+    int64_t got = 0;
+    for (const Part &p : part) got += (int64_t)p.taken.size();
+    return got;
+}
+
+// The scores of n groups of columns from j0 on.  Rows of W are read as they lie, and the scores, which lie column by column,
+// leave in pieces of kRows (walking W down its columns took 2.9 ms for 512 x 512 in fp16, this 0.6).
+constexpr int32_t kScoreCols = 64;
+void scores_of(const void *W, ubp_dtype dtype, int64_t ldw, int32_t M, int32_t bh, int32_t bw, int32_t aligned, int32_t j0, int32_t n,
+               std::vector<double> &norm, double *S) {
+    constexpr int32_t kRows = 8;
+    double part[kRows][kScoreCols];
+    norm.resize((size_t)M * (size_t)n); // of the rows' weights in these columns
+    for (int32_t i = 0; i < M; ++i) {
+        const int64_t at = (int64_t)i * ldw + (int64_t)j0 * bw;
+        double *out = &norm[(size_t)i * (size_t)n];
+        switch (dtype) {
+        case UBP_F32: row_norms(static_cast<const float *>(W) + at, bw, n, out, magnitude); break;
+        case UBP_F16: row_norms(static_cast<const uint16_t *>(W) + at, bw, n, out, magnitude_f16); break;
+        default: row_norms(static_cast<const uint16_t *>(W) + at, bw, n, out, magnitude_bf16); break;
         }
     }
-    for (size_t t = 0; t < all.size(); ++t) I[t] = all[t].k;
-    return (int64_t)all.size();
+    for (int32_t i0 = 0; i0 < M; i0 += kRows) {
+        const int32_t rows = std::min(kRows, M - i0);
+        for (int32_t r = 0; r < rows; ++r) {
+            const int32_t i = i0 + r;
+            if (i + bh > M || (aligned && i % bh)) {
+                std::fill_n(part[r], n, kNegInf);
+                continue;
+            }
+            const double *from = &norm[(size_t)i * (size_t)n];
+            std::copy_n(from, n, part[r]);
+            for (int32_t t = 1; t < bh; ++t)
+                for (int32_t j = 0; j < n; ++j) part[r][j] += from[(size_t)t * (size_t)n + (size_t)j];
+        }
+        for (int32_t j = 0; j < n; ++j)
+            for (int32_t r = 0; r < rows; ++r) S[(int64_t)(j0 + j) * M + i0 + r] = part[r][j];
+    }
+}
+
+size_t threads_for_scores(int32_t M, int32_t K) { return (size_t)std::min<int64_t>((int64_t)M * K / 32768, 64); } // (a weight: about 1 ns)
+
+void block_scores(const void *W, ubp_dtype dtype, int64_t ldw, int32_t M, int32_t K, int32_t bh, int32_t bw, int32_t aligned, double *S,
+                  Team &team) {
+    const int32_t groups = K / bw, cols = std::max(1, std::min(kScoreCols, (1 << 17) / M)); // (at most 1 MB of norms, or one column)
+    std::vector<std::vector<double>> norms(team.size());
+    team.share((size_t)((groups + cols - 1) / cols), [&](size_t piece, size_t member) {
+        const int32_t j0 = (int32_t)piece * cols;
+        scores_of(W, dtype, ldw, M, bh, bw, aligned, j0, std::min(cols, groups - j0), norms[member], S);
+    });
 }
 
 }  // namespace
@@ -500,49 +703,9 @@ extern "C" {
 ubp_status ubp_block_scores(const void *W, ubp_dtype dtype, int64_t ldw, int32_t M, int32_t K, int32_t bh, int32_t bw,
                             int32_t aligned, double *S, int64_t b) {
     if (!layer_ok(W, dtype, ldw, M, K, bh, bw) || !S || b != (int64_t)M * (K / bw)) return UBP_ERR_INVALID_ARG;
-    // Rows of W are read as they lie, kCols groups at a time, and the scores, which lie column by column, leave in pieces of
-    // kRows (walking W down its columns took 2.9 ms for 512 x 512 in fp16, this 0.6).
-    constexpr int32_t kCols = 64, kRows = 8;
-    const int32_t groups = K / bw;
-    struct Buffers {
-        std::vector<double> norm; // of the rows' weights in some columns
-        double part[kRows][kCols];
-    };
     try {
-        const int32_t cols = std::max(1, std::min(kCols, (1 << 17) / M)); // (at most 1 MB, or one column)
-        const size_t threads = (size_t)std::min<int64_t>((int64_t)M * K / 32768, 64); // (a weight: about 1 ns)
-        share_out<Buffers>((size_t)((groups + cols - 1) / cols), threads, [&](Buffers &buffers, size_t piece) {
-            std::vector<double> &norm = buffers.norm;
-            double(&part)[kRows][kCols] = buffers.part;
-            norm.resize((size_t)M * (size_t)cols);
-            const int32_t j0 = (int32_t)piece * cols;
-            const int32_t n = std::min(cols, groups - j0);
-            for (int32_t i = 0; i < M; ++i) {
-                const int64_t at = (int64_t)i * ldw + (int64_t)j0 * bw;
-                double *out = &norm[(size_t)i * (size_t)cols];
-                switch (dtype) {
-                case UBP_F32: row_norms(static_cast<const float *>(W) + at, bw, n, out, magnitude); break;
-                case UBP_F16: row_norms(static_cast<const uint16_t *>(W) + at, bw, n, out, magnitude_f16); break;
-                default: row_norms(static_cast<const uint16_t *>(W) + at, bw, n, out, magnitude_bf16); break;
-                }
-            }
-            for (int32_t i0 = 0; i0 < M; i0 += kRows) {
-                const int32_t rows = std::min(kRows, M - i0);
-                for (int32_t r = 0; r < rows; ++r) {
-                    const int32_t i = i0 + r;
-                    if (i + bh > M || (aligned && i % bh)) {
-                        std::fill_n(part[r], n, kNegInf);
-                        continue;
-                    }
-                    const double *from = &norm[(size_t)i * (size_t)cols];
-                    std::copy_n(from, n, part[r]);
-                    for (int32_t t = 1; t < bh; ++t)
-                        for (int32_t j = 0; j < n; ++j) part[r][j] += from[(size_t)t * (size_t)cols + (size_t)j];
-                }
-                for (int32_t j = 0; j < n; ++j)
-                    for (int32_t r = 0; r < rows; ++r) S[(int64_t)(j0 + j) * M + i0 + r] = part[r][j];
-            }
-        });
+        Team team(threads_for_scores(M, K));
+        block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S, team);
     } catch (const std::bad_alloc &) {
         return UBP_ERR_ALLOC;
     } catch (const std::length_error &) {
@@ -556,7 +719,8 @@ ubp_status ubp_select_greedy(const double *S, int64_t b, int32_t N, int64_t m, i
     *count = 0;
     if (!scores_ok(S, b)) return UBP_ERR_INVALID_ARG;
     try {
-        *count = greedy_in_order(S, b, N, m, I);
+        Team team(threads_for_rounds(m));
+        *count = greedy_in_order(S, b, N, m, I, nullptr, team);
     } catch (const std::bad_alloc &) {
         return UBP_ERR_ALLOC;
     } catch (const std::length_error &) {
@@ -570,7 +734,8 @@ ubp_status ubp_select_bed(const double *S, int64_t b, int32_t N, int64_t m, int6
     *count = 0;
     if (!scores_ok(S, b)) return UBP_ERR_INVALID_ARG;
     try {
-        *count = expand_and_divide(S, b, N, m, I);
+        Team team(threads_for_rounds(m));
+        *count = expand_and_divide(S, b, N, m, I, nullptr, team);
     } catch (const std::bad_alloc &) {
         return UBP_ERR_ALLOC;
     } catch (const std::length_error &) {
@@ -651,16 +816,17 @@ ubp_status ubp_select_blocks(const void *W, ubp_dtype dtype, int64_t ldw, int32_
         S.reserve(MaxTree::padded(b));
         S.resize((size_t)b);
         std::vector<int64_t> I((size_t)std::max<int64_t>(m, 1));
-        ubp_status rc = ubp_block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S.data(), b);
-        if (rc != UBP_OK) return rc;
+        Team team(std::max(threads_for_scores(M, K), method == 2 ? 1 : threads_for_rounds(m)));
+        block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S.data(), team);
+        ubp_status rc = UBP_OK;
         int64_t got = 0;
         if (method == 2) {
             rc = ubp_select_optimal(S.data(), b, bh, m, I.data(), &got);
             if (rc != UBP_OK) return rc;
         } else {
             if (!scores_ok(S.data(), b)) return UBP_ERR_INVALID_ARG;
-            got = method == 0 ? greedy_in_order(S.data(), b, bh, m, I.data(), &S)
-                              : expand_and_divide(S.data(), b, bh, m, I.data(), &S);
+            got = method == 0 ? greedy_in_order(S.data(), b, bh, m, I.data(), &S, team)
+                              : expand_and_divide(S.data(), b, bh, m, I.data(), &S, team);
         }
         rc = ubp_selection_to_blocks(I.data(), got, M, bw, out);
         if (rc != UBP_OK) return rc;
