@@ -334,7 +334,8 @@ ubp_status ubp_block_scores(const void *W_host, ubp_dtype dtype, int64_t ldw, in
  *     that join across the gap and the entry with its N-1 successors leaves the list -- then
  *     block division of the expanded runs into blocks of N.  I ascending.  O(b + m N log b).
  *     (Both use up to 8 threads, which have ended when the call returns, for 4096 blocks and more of a layer whose columns
- *     are kept apart by -inf, as ubp_block_scores gives them; ubp_block_scores does for layers of 65536 weights and more.)
+ *     are kept apart by -inf, as ubp_block_scores gives them, where the caller may run on 4 cores or more; ubp_block_scores does
+ *     for layers of 65536 weights and more.)
  * ubp_select_optimal (Section 3.2, Eq. 4): the selection of exactly m non-overlapping candidates
  *     with the largest total score; of equal totals the one Eq. 4's strict comparison reaches.
  *     I ascending.  O(b m) time and b m bits of memory; UBP_ERR_UNSUPPORTED above 2 GiB of those.

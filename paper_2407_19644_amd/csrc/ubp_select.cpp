@@ -29,6 +29,9 @@
 #include <utility>
 #include <vector>
 
+#if defined(__linux__)
+#include <sched.h>
+#endif
 #if defined(__SSE2__)
 #include <emmintrin.h>
 #endif
@@ -100,12 +103,21 @@ template <class F> void spin(F &&done) {
     } while (std::chrono::steady_clock::now() < end);
 }
 
+// Those that this process may run on (std::thread::hardware_concurrency counts all of the machine's).
+inline size_t usable_cores() {
+#if defined(__linux__)
+    cpu_set_t set;
+    if (sched_getaffinity(0, sizeof set, &set) == 0) return (size_t)CPU_COUNT(&set);
+#endif
+    return std::thread::hardware_concurrency();
+}
+
 // Up to kMost threads for the length of one call, the caller among them.  A thread that cannot be had is done without.
 class Team {
   public:
     explicit Team(size_t want, size_t cores = 0) { // (0: as many as there are)
         want = std::min(want, kMost);
-        if (want > 1) threads = std::max<size_t>(1, std::min(want, cores ? cores : (size_t)std::thread::hardware_concurrency()));
+        if (want > 1) threads = std::max<size_t>(1, std::min(want, cores ? cores : usable_cores()));
         start(1);
     }
     ~Team() {
@@ -411,9 +423,13 @@ bool greedy(Part &part, int32_t N, double above, int64_t most) {
     return false;
 }
 
-constexpr size_t kLeastTeam = 2;
+// Threads that go through parts side by side: where there are fewer, or fewer rounds, one goes through all candidates.
+constexpr size_t kLeastTeam = 4;
 constexpr int64_t kLeastRounds = 4096;
-size_t threads_for_rounds(int64_t m) { return m < kLeastRounds ? 1 : (size_t)std::min<int64_t>(m / 1024, 64); }
+size_t threads_for_rounds(int64_t m) {
+    if (m < kLeastRounds || usable_cores() < kLeastTeam) return 1;
+    return (size_t)std::min<int64_t>(m / 1024, 64);
+}
 
 // Where to cut b candidates into up to `most` parts that no round reaches out of, some b / most each.  N - 1 or more scores of
 // -inf one after the other separate what lies before them from what lies behind:
@@ -456,7 +472,8 @@ inline double below(double x) { return std::nextafter(x, kNegInf); }
 // 512 x 512 in 4 x 1 blocks at 20 % (13107 rounds) with scores, by one tree -> by parts on 16 cores: rows of different size, greedy 1.56 -> 0.8,
 // expansion 1.74 -> 0.7 ms; columns of different size (log-normal, sigma 2) 1.45 -> 0.75 and 1.65 -> 0.7; four columns in five zero 1.25
 // -> 0.8 and 1.6 -> 0.7; all zero 0.82 -> 0.8.  1024 x 512, 2 x 1, 2 %, sigma 2: 1.1 -> 0.9, 1.15 -> 0.85.  On 4 cores the first two 1.57 -> 0.87, 1.73
-// -> 0.74.  Slower are small layers without a weight, whose rounds are made in order all the same: 1024 x 64, 9830 rounds, 0.34 -> 0.5.
+// -> 0.74; on 3, with 4259 rounds, up to 1.3 times one tree's time, which is why kLeastTeam is 4.  Slower are small layers without a
+// weight, whose rounds are made in order all the same: 1024 x 64, 9830 rounds, 0.34 -> 0.5.
 std::vector<Part> pick(Rounds rounds, const double *S, int64_t b, int32_t N, int64_t m, std::vector<double> *own, Team &team) {
     constexpr int64_t kParts = 64;
     constexpr double kSamples = 128.0; // among the m best candidates

@@ -200,7 +200,29 @@ static int64_t caller(int c, int64_t m_shift, int kinds) {
     return bad + (by_parts == 0);
 }
 
+// As many threads as there are cores to run on, and one tree where those are few.
+static int cores() {
+    cpu_set_t had, set;
+    if (sched_getaffinity(0, sizeof had, &had) != 0) return 1;
+    const std::vector<double> S(100000, 1.0);
+    int bad = 0;
+    for (int few = 1; few <= 3; ++few) {
+        CPU_ZERO(&set);
+        for (int c = 0, n = 0; c < CPU_SETSIZE && n < few; ++c)
+            if (CPU_ISSET(c, &had)) CPU_SET(c, &set), ++n;
+        const size_t n = (size_t)CPU_COUNT(&set);
+        if (sched_setaffinity(0, sizeof set, &set) != 0) return 1;
+        Team team(8);
+        bad += team.size() != n || threads_for_rounds(50000) != 1 || pick(greedy, S.data(), 100000, 1, 50000, nullptr, team).size() != 1;
+    }
+    return bad + (sched_setaffinity(0, sizeof had, &had) != 0);
+}
+
 int main(int argc, char **) { // (any argument: fewer scores)
+    if (cores() != 0) {
+        std::printf("threads for cores that there are not\n");
+        return 1;
+    }
     const int kinds = argc > 1 ? 4 : 8;
     int64_t bad[2] = {0, 0};
     std::thread second([&] { bad[1] = caller(1, 1, kinds); });
