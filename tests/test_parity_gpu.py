@@ -204,7 +204,7 @@ def test_block_kernel(shape, dtype):
         for y_dtype in (dtype, "f32"):
             Y = run_spmm(W, dtype, bh, bw, blocks, X, y_dtype, _plan(kernel=6, sub_stripes=G))
             check(Y, Yref, Yabs, dtype, y_dtype)
-    for G, waves, NP in [(4, 3, 1), (2, 16, 4), (5, 5, 2), (2, 2, 1), (4, 16, 1), (5, 16, 2)]:
+    for G, waves, NP in [(4, 3, 1), (2, 16, 4), (5, 5, 2), (2, 2, 1), (4, 16, 1), (5, 16, 2), (4, 16, 4), (5, 16, 4)]:
         Y = run_spmm(W, dtype, bh, bw, blocks, X, dtype, _plan(kernel=6, sub_stripes=G, waves=waves, producers=NP))
         check(Y, Yref, Yabs, dtype)
 
@@ -223,6 +223,35 @@ def test_block_kernel_last_tile(N, pad, dtype):
         if N % 8 == 0:
             last = run_spmm(W, dtype, 16, 16, blocks, X[:, N - 64:], y_dtype, _plan(kernel=6))
             assert np.array_equal(Y[:, N - 64:], last)
+
+
+# M, K, N, density, stripes of a wavefront, producers: row groups of several stripes, several workgroup rows, an overlapping last tile
+SPLITS = [(2048, 2048, 3144, 0.1, 4, 4), (2560, 1152, 6152, 0.1, 5, 4), (1664, 1200, 3144, 0.2, 2, 2), (1024, 2048, 8200, 0.1, 5, 2), (1024, 2048, 3144, 0.1, 2, 4)]
+
+
+@pytest.mark.parametrize("case", SPLITS, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_splits_that_the_block_kernel_chooses(case, dtype):
+    """The automatic split of each kind, with bias and clamp: rows of every position in a stripe against the oracle, and the last 64 pixels
+    the bits of a product of their own."""
+    M, K, N, d, G, NP = case
+    blocks, W, X = _layer(M, K, N, 16, 16, d, dtype, seed=M + N)
+    p = ubp.pack(W, dtype, 16, 16, blocks, device=torch.cuda.current_device())
+    Xd, Yd = to_device(X, dtype), torch.empty((M, N), dtype=torch.float32, device="cuda")
+    got = ubp.spmm_prepare(p, Xd.data_ptr(), N, N, Yd.data_ptr(), N, dtype)
+    assert (got.kernel, got.sub_stripes, got.producers) == (6, G, NP)
+    p.free()
+    rows = np.arange(0, M, M // 48 | 1)
+    Yref, Yabs = _oracle(W, dtype, 16, 16, blocks, X, rows=rows)
+    scale = np.abs(Yref).max()
+    bias = (np.random.default_rng(N).standard_normal(M) * 0.5 * scale).astype(np.float32)
+    want = oracle.fused(Yref, bias[rows].astype(np.float64), "clamp", -0.4 * scale, 0.7 * scale)
+    plan = _plan(kernel=6, sub_stripes=G, waves=got.waves, producers=NP)
+    for y_dtype, chosen in ((dtype, None), ("f32", plan)):              # (an fp32 Y may be another split's)
+        Y = _run_fused(W, dtype, 16, 16, blocks, X, y_dtype, bias, "clamp", -0.4 * scale, 0.7 * scale, chosen)
+        check(Y[rows], want, Yabs + np.abs(want) + np.abs(bias[rows])[:, None], dtype, y_dtype)
+        last = _run_fused(W, dtype, 16, 16, blocks, X[:, N - 64:], y_dtype, bias, "clamp", -0.4 * scale, 0.7 * scale, plan)
+        assert np.array_equal(Y[:, N - 64:], last)
 
 
 GEMM_SHAPES = [(100, 200, 328, 4, 4, 0.5), (270, 700, 520, 4, 4, 0.45), (64, 64, 200, 4, 4, 0.6), (530, 96, 1000, 4, 4, 0.5),
@@ -582,6 +611,29 @@ def test_handle_holds_only_the_layout_that_runs(name):
     ubp.spmm(p, Xd.data_ptr(), cfg.N, cfg.N, Yd.data_ptr(), cfg.N, "f32", torch.cuda.current_stream().cuda_stream, None)
     torch.cuda.synchronize()
     assert p.info(8) == after
+    p.free()
+
+
+def test_handle_that_serves_several_numbers_of_pixels():
+    """The block kernel's split follows from the number of pixels: one handle keeps a layout for each number of stripes that was
+    used, three at most, and what it has it does not build again."""
+    M, K, most = 2048, 2048, 6144
+    blocks, W, X = _layer(M, K, most, 16, 16, 0.1, "bf16", seed=12)
+    p = ubp.pack(W, "bf16", 16, 16, blocks, device=torch.cuda.current_device())
+    canonical = p.info(7)
+    Xd, Yd = to_device(X, "bf16"), torch.empty((M, most), dtype=torch.bfloat16, device="cuda")
+    held, split = [p.info(8)], {}
+    for N in (1536, 3136, most, 1536, 3136, most):
+        plan = ubp.spmm_prepare(p, Xd.data_ptr(), most, N, Yd.data_ptr(), most, "bf16")
+        assert plan.kernel == 6
+        split[N] = plan.sub_stripes
+        ubp.spmm(p, Xd.data_ptr(), most, N, Yd.data_ptr(), most, "bf16", torch.cuda.current_stream().cuda_stream, None)
+        held.append(p.info(8))
+    torch.cuda.synchronize()
+    assert len(set(split.values())) == 3, split
+    for before, after in zip(held[:3], held[1:4]):
+        assert 0 < after - before <= 2 * canonical, (held, canonical)
+    assert held[3:] == [held[3]] * 4, held
     p.free()
 
 
