@@ -90,9 +90,9 @@ bool selector_args_ok(const double *S, int64_t b, int32_t N, int64_t m, const in
     return b >= 0 && (b == 0 || S) && N >= 1 && m >= 0 && (m == 0 || I) && count;
 }
 
-// Waits for `done`, for about as long as a thread that sleeps takes to wake up.
-template <class F> void spin(F &&done) {
-    const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(50);
+// Waits for `done`, but not longer than a few times what a thread that sleeps takes to wake up.
+template <class F> void spin(int us, F &&done) {
+    const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(us);
     do {
         for (int i = 0; i < 16; ++i) {
             if (done()) return;
@@ -120,7 +120,8 @@ class Team {
         if (want > 1) threads = std::max<size_t>(1, std::min(want, cores ? cores : usable_cores()));
         start(1);
     }
-    ~Team() {
+    ~Team() { end(); }
+    void end() { // the caller goes on alone
         {
             std::lock_guard<std::mutex> hold(lock);
             over = true;
@@ -129,6 +130,7 @@ class Team {
         wake.notify_all();
         for (std::thread &t : thread) // (the ones that start others come before those)
             if (t.joinable()) t.join();
+        threads = 1;
     }
     Team(const Team &) = delete;
     Team &operator=(const Team &) = delete;
@@ -136,8 +138,8 @@ class Team {
 
     // f(part, member) for parts 0 .. parts - 1, each once, by the same thread as the last time where that one is not late: what a part
     // reads and writes is then in that core's caches (a line out of another core's takes 100 to 200 ns).  What one of them
-    // throws is thrown here, after all have ended.
-    template <class F> void share(size_t parts, F &&f) {
+    // throws is thrown here, after all have ended.  Behind the last ones the threads end by themselves (to be told costs 10 us).
+    template <class F> void share(size_t parts, F &&f, bool last = false) {
         if (threads == 1 || parts < 2) {
             for (size_t p = 0; p < parts; ++p) f(p, 0);
             return;
@@ -152,11 +154,12 @@ class Team {
                 share_of[t].end = parts * (t + 1) / size();
             }
             open = true;
+            over = last;
             ++turn;
         }
         wake.notify_all();
         work(0);
-        spin([this] { return inside == 0; });
+        spin(200, [this] { return inside == 0; });
         std::unique_lock<std::mutex> hold(lock);
         open = false; // (who wakes up only now has nothing left to do)
         done.wait(hold, [this] { return inside == 0; });
@@ -178,17 +181,18 @@ class Team {
         start(2 * me);
         start(2 * me + 1);
         for (uint64_t seen = 0;;) {
-            spin([&] { return turn != seen; });
+            spin(50, [&] { return turn != seen; });
             std::unique_lock<std::mutex> hold(lock);
             wake.wait(hold, [&] { return turn != seen; });
             seen = turn;
+            if (open) {
+                ++inside;
+                hold.unlock();
+                work(me);
+                hold.lock();
+                if (--inside == 0) done.notify_one();
+            }
             if (over) return;
-            if (!open) continue;
-            ++inside;
-            hold.unlock();
-            work(me);
-            hold.lock();
-            if (--inside == 0) done.notify_one();
         }
     }
     void work(size_t me) {
@@ -701,16 +705,21 @@ void scores_of(const void *W, ubp_dtype dtype, int64_t ldw, int32_t M, int32_t b
     }
 }
 
-size_t threads_for_scores(int32_t M, int32_t K) { return (size_t)std::min<int64_t>((int64_t)M * K / 32768, 64); } // (a weight: about 1 ns)
+int32_t score_cols(int32_t M) { return std::max(1, std::min(kScoreCols, (1 << 17) / M)); } // (at most 1 MB of norms, or one column)
+size_t score_pieces(int32_t M, int32_t K, int32_t bw) { return ((size_t)(K / bw) + (size_t)score_cols(M) - 1) / (size_t)score_cols(M); }
+size_t threads_for_scores(int32_t M, int32_t K, int32_t bw) { // (a weight: about 1 ns)
+    return std::min((size_t)std::min<int64_t>((int64_t)M * K / 32768, 64), score_pieces(M, K, bw));
+}
 
 void block_scores(const void *W, ubp_dtype dtype, int64_t ldw, int32_t M, int32_t K, int32_t bh, int32_t bw, int32_t aligned, double *S,
-                  Team &team) {
-    const int32_t groups = K / bw, cols = std::max(1, std::min(kScoreCols, (1 << 17) / M)); // (at most 1 MB of norms, or one column)
+                  Team &team, bool last) {
+    const int32_t groups = K / bw, cols = score_cols(M);
     std::vector<std::vector<double>> norms(team.size());
-    team.share((size_t)((groups + cols - 1) / cols), [&](size_t piece, size_t member) {
+    const auto score = [&](size_t piece, size_t member) {
         const int32_t j0 = (int32_t)piece * cols;
         scores_of(W, dtype, ldw, M, bh, bw, aligned, j0, std::min(cols, groups - j0), norms[member], S);
-    });
+    };
+    team.share(score_pieces(M, K, bw), score, last);
 }
 
 }  // namespace
@@ -721,8 +730,8 @@ ubp_status ubp_block_scores(const void *W, ubp_dtype dtype, int64_t ldw, int32_t
                             int32_t aligned, double *S, int64_t b) {
     if (!layer_ok(W, dtype, ldw, M, K, bh, bw) || !S || b != (int64_t)M * (K / bw)) return UBP_ERR_INVALID_ARG;
     try {
-        Team team(threads_for_scores(M, K));
-        block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S, team);
+        Team team(threads_for_scores(M, K, bw));
+        block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S, team, true);
     } catch (const std::bad_alloc &) {
         return UBP_ERR_ALLOC;
     } catch (const std::length_error &) {
@@ -833,8 +842,10 @@ ubp_status ubp_select_blocks(const void *W, ubp_dtype dtype, int64_t ldw, int32_
         S.reserve(MaxTree::padded(b));
         S.resize((size_t)b);
         std::vector<int64_t> I((size_t)std::max<int64_t>(m, 1));
-        Team team(std::max(threads_for_scores(M, K), method == 2 ? 1 : threads_for_rounds(m)));
-        block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S.data(), team);
+        const size_t for_rounds = method == 2 ? 1 : threads_for_rounds(m);
+        Team team(std::max(threads_for_scores(M, K, bw), for_rounds));
+        block_scores(W, dtype, ldw, M, K, bh, bw, aligned, S.data(), team, for_rounds == 1);
+        if (for_rounds == 1) team.end();
         ubp_status rc = UBP_OK;
         int64_t got = 0;
         if (method == 2) {
