@@ -112,8 +112,9 @@ int blk_auto_G(const ubp_packed *p) { // 5 stripes per wavefront where that save
 // not one after the other, each is through sooner with fewer steps per wavefront and with more producers.  4096 x 4096 at 10 %, by
 // stripes / producers: 1024 pixels 5/2 34.8, 4/2 31.9, 2/2 27.8, 2/4 25.1 us, 8192 pixels 77, 94, 130, 131; 2048 x 4096 at 5 % with 4096 pixels
 // 30.5, 28.5, 45.0 and by 4/4 26.1.
-// Coefficients fitted to 600 layers of 512 to 4096 rows, 1152 to 4096 columns and 128 to 8192 pixels at 3 to 20 %, even and skewed: mean
-// error 4 to 7 %; the split of the smallest estimate takes 0.5 % longer than the fastest of the six, 17 % at most.
+// Coefficients fitted to 600 layers of 512 to 4096 rows, 1152 to 4096 columns and 128 to 8192 pixels at 5 to 20 %, even and skewed: mean
+// error 4 to 7 %; on 400 others what is chosen, by this estimate or for another kernel, takes as long as the fastest of the six and the direct kernel
+// on average, 5 % longer at the 95th percentile, 17 % at most.
 struct BlkSplit {
     int G, NP;
     double fixed, per_stage, per_step, per_y;
@@ -291,10 +292,10 @@ void choose(const ubp_packed *p, int N, int64_t ldx_bytes, bool vec_ok, size_t y
         s.kernel = 4;
     }
     if (blk_eligible(p) && p->bh == kStripe && p->bw >= 16 && p->K > ring_rows(4) && vec_ok && N >= 64) {
-        // (A margin of its mean error, but not against the direct kernel, whose estimate knows nothing of stripes that hold
-        // more than the others: with it there too 2800 x 3904 at 10 % with 1472 pixels stays at 45 us and 1024 x 2864 at 5 %,
-        // skewed, with 6144 at 47.3, which take 33.7 and 23.3 here; without any 2048 x 1488 at 20 % with 2624 takes 29.9
-        // instead of 26.7.)
+        // (A margin in the range of its mean error against the dense tiles, whose estimate is the finer one: it decides 16 of 1998 drawn
+        // layers, which by the dense tiles take 0.89 to 1.10 of this kernel's time, 1.02 on average.  None against the direct kernel, whose estimate
+        // knows nothing of stripes that hold more than the others: it would decide 31 of 3000 layers, which the direct kernel takes 1.05 of this
+        // one's time for on average, 0.91 to 1.20; 1024 x 2864 at 5 %, skewed, with 6144 pixels takes 42.3 us there and 21.5 here.)
         const BlkSplit *split = nullptr;
         const double t = estimate_blk(p, N, ysz, split);
         if ((s.kernel == 8 ? t : 1.06 * t) < best) {

@@ -57,8 +57,9 @@ constexpr int stripe_max_waves(int G, int CT) { return stripe_max_threads(G, CT)
 // Wavefronts of a workgroup of the block kernel.
 constexpr int kBlkConsumers = 14; // of them multiplying, at most
 // Whether the last N % 64 pixels go to the gather kernel.  Not where N is a multiple of 8: the last tile then overlaps the one
-// before it, its pieces of rows still aligned, for at most a tile's work (16 x 16 blocks, by this kernel: 4096 x 4096 at 10 % with
-// 1000 pixels 196.7 -> 35.1 us, 2048 x 4096 at 5 % with 4040 191 -> 30.1; by the kernel chosen before, which was the direct one, 40.2 and 65.1).
+// before it, its pieces of rows still aligned, for at most a tile's work (16 x 16 blocks, wavefronts of 5 stripes and 2 producers: 4096 x 4096 at 10 %
+// with 1000 pixels 196.7 -> 35.1 us, 2048 x 4096 at 5 % with 4040 191 -> 30.1; with the splits that are chosen there now 26.1 and 27.5, by the
+// direct kernel 43.1 and 42.4).
 constexpr bool blk_leaves_tail(int N) { return N % 8 != 0; }
 constexpr int blk_max_waves(int G) { return (G == 2 || G == 4 || G == 5) ? 16 : 0; }
 
