@@ -116,10 +116,13 @@ const void *ubp_packed_values(const ubp_packed *p, int64_t *len_elems);
  *           result is overwritten, rows no block touches with +0.  X and Y must not alias.
  *   hip_stream : a hipStream_t (NULL = the default stream).  The call only enqueues
  *           kernels on that stream and never synchronises.
- * Allocation: the FIRST call for a given kernel choice (which depends on N and on the
+ * Allocation: the FIRST call for a given kernel choice (which depends on N, on Y's type and on the
  * alignment of the pointers and pitches) builds and uploads that kernel's re-layout of W - it
  * allocates host and device memory and copies synchronously - and raises the kernel's LDS limit.
- * Every later call with the same choice does neither.  Call ubp_spmm_prepare with the same
+ * Every later call with the same choice does neither.  A handle keeps every re-layout that it has
+ * used until it is freed: one for the kernels 4, 5, 7 and 9, one for 8, one for each shape of 2 and one for
+ * each number of stripes of 6 (three at most, each 1.2 to 1.8 times the canonical arrays of a large layer), whichever
+ * its calls at several N come to; what runs does not depend on which are there.  Call ubp_spmm_prepare with the same
  * arguments beforehand (for instance before capturing the stream into a graph) to have all of
  * that done up front.
  * N == 0 is a no-op.  Errors: UBP_ERR_INVALID_ARG (null pointer, N < 0, pitch < N,

@@ -215,6 +215,7 @@ static int cores() {
         Team team(8);
         bad += team.size() != n || threads_for_rounds(50000) != 1 || pick(greedy, S.data(), 100000, 1, 50000, nullptr, team).size() != 1;
     }
+    bad += threads_for_scores(888, 124, 4) != 1 || threads_for_scores(512, 512, 1) != 8; // pieces of 64 columns
     return bad + (sched_setaffinity(0, sizeof had, &had) != 0);
 }
 
